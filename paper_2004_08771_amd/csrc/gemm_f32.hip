@@ -2,18 +2,15 @@
 // (Section 3 of the paper: forward Eq. (1), backward Eq. (2); on a batch the
 // matrix-vector products become matrix-matrix products, the dominant cost).
 //
-// gfx950 design: 256-thread workgroups (4 wavefronts of 64), v_mfma_f32_32x32x2_f32
-// blocks, operands staged global -> registers -> LDS with a double-buffered LDS tile:
-// global loads run two k-tiles ahead, the next tile is written to the idle LDS stage
-// early in the current tile, fragments are read one MFMA step ahead, one barrier per tile.
-// K-major operands are read from LDS as 16-byte vectors along k (the k index is permuted
-// identically for both operands, which leaves the contraction unchanged); M-major
-// operands are read one float per lane with the 32 rows of a block on consecutive
-// addresses.  Epilogues fuse bias + activation (forward), the activation derivative
-// (backward-data) and the bias-gradient column sums (weight gradient); interior tiles take
-// a form without guards that requests everything it reads in one batch.  Products with few
-// output tiles (small batches) run a second kernel family further down: 32 x 32 tiles with
-// the contraction split over the four wavefronts of a workgroup.
+// This file: the plan (which kernel, tile shape and split a product gets) and the kernels for
+// products with few output tiles (small batches), on fp32 MFMAs: 32 x 32 tiles, 256-thread
+// workgroups (4 wavefronts of 64), the contraction split over the four wavefronts,
+// v_mfma_f32_32x32x2_f32 blocks, operands staged global -> registers -> LDS with a double-buffered
+// LDS tile.  K-major operands are read from LDS as 16-byte vectors along k (the k index is permuted
+// identically for both operands, which leaves the contraction unchanged); M-major operands are
+// read one float per lane with the 32 rows of a block on consecutive addresses.  Epilogues fuse
+// bias + activation (forward), the activation derivative (backward-data) and the bias-gradient
+// column sums (weight gradient).  The large products are in gemm_split.hip.
 #include "hb_internal.h"
 
 #include <stdlib.h>
@@ -180,352 +177,10 @@ __device__ __forceinline__ int xcd_tile_order(int b, int T)
     return ((T & 7) == 0) ? (b & 7) * (T >> 3) + (b >> 3) : b;
 }
 
-// One output tile (index id in n-fastest order) of one K-slice (split) of C = A . B^T.
-template <int BM, int BN, int BK, int WAVES_M, bool A_KMAJ, bool B_KMAJ, int KIND>
-__device__ __forceinline__ void gemm_f32_tile(const GemmArgs &a, float *smem, int id, int split)
-{
-    constexpr int WAVES_N = 4 / WAVES_M;
-    constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
-    constexpr int TM = WM / 32, TN = WN / 32;
-    static_assert(TM >= 1 && TN >= 1 && WM % 32 == 0 && WN % 32 == 0, "wave tile");
-    using TA = Tile<BM, BK, A_KMAJ>;
-    using TB = Tile<BN, BK, B_KMAJ>;
-    constexpr int STAGE = TA::FLOATS + TB::FLOATS;
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int r = lane & 31, h = lane >> 5;
-    const int wm = wave % WAVES_M, wn = wave / WAVES_M;
-
-    const int tile_m = id / a.tiles_n, tile_n = id - tile_m * a.tiles_n;
-    const int m0 = tile_m * BM, n0 = tile_n * BN;
-    const int kbeg = split * a.k_chunk;
-    const int kend = min(a.K, kbeg + a.k_chunk);
-    const int nk = (kend - kbeg + BK - 1) / BK;
-
-    const float *__restrict__ A = static_cast<const float *>(a.A);
-    const float *__restrict__ Bm = static_cast<const float *>(a.B);
-
-    // With a single 32 x 32 block per wavefront every MFMA would depend on the one before
-    // it; two accumulators per block, fed by alternating k-groups, give two independent chains.
-    constexpr int CHAINS = (TM * TN == 1) ? 2 : 1;
-    v16f acc[TM][TN][CHAINS];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int c = 0; c < CHAINS; ++c)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[i][j][c][v] = 0.f;
-
-    // tiles that lie inside the matrix are loaded without guards (uniform per workgroup)
-    const bool a_in = (m0 + BM <= a.M), b_in = (n0 + BN <= a.N);
-
-    // DW only: column sums of the A tile (the bias gradient), by the blocks of the first tile
-    // column.  All threads share the work: thread (crow, cpart) adds every CP-th k of row crow,
-    // the CP partial sums meet in LDS after the loop (one wavefront alone did 32 LDS reads per
-    // k-tile in front of its MFMAs, and its workgroup waited for it at every barrier: the paired
-    // launch at B = 4096 42.4 -> 42.0 us).
-    constexpr int CP = NT / BM;
-    const int crow = tid % BM, cpart = tid / BM;
-    float colsum = 0.f;
-    const bool do_colsum = (KIND == GEMM_DW) && a.colsum != nullptr && tile_n == 0;
-
-    // forward: the lane's bias values are requested now, not after the main loop
-    float bias_pre[TN];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const int n = n0 + wn * WN + j * 32 + r;
-        bias_pre[j] = (KIND == GEMM_FWD && a.bias != nullptr && n < a.N) ? a.bias[n] : 0.f;
-    }
-
-    // Software pipeline, three levels deep:
-    //   global -> registers : the loads of tile kt+2 are issued at the top of iteration kt
-    //   registers -> LDS    : just before that, tile kt+1 (loaded during iteration kt-1) is
-    //                         written to the idle LDS stage, long before anyone needs it
-    //   LDS -> fragments    : the fragments of k-group g+1 are read while the MFMAs of group g
-    //                         run; the first group of tile kt+1 is read right after the
-    //                         barrier, under the last MFMAs of tile kt.
-    // One barrier per k-tile; nothing but the barrier itself sits between two MFMA groups.
-    constexpr int G = BK / 8;
-    static_assert(G % 2 == 0, "fragment slots alternate with the k-group parity");
-    v4f ra[TA::VPT], rb[TB::VPT];
-    auto load_tile = [&](int t) {
-        const int k0 = kbeg + t * BK;
-        const bool kfull = (k0 + BK <= kend);
-        if (a_in && kfull) TA::load_fast(ra, A, a.lda, m0, k0, a.a_vec != 0, tid);
-        else TA::load(ra, A, a.lda, m0, a.M, k0, kend, a.a_vec != 0, tid);
-        if (b_in && kfull) TB::load_fast(rb, Bm, a.ldb, n0, k0, a.b_vec != 0, tid);
-        else TB::load(rb, Bm, a.ldb, n0, a.N, k0, kend, a.b_vec != 0, tid);
-    };
-    v4f fa[2][TM], fb[2][TN];
-    auto read_frags = [&](int slot, const float *As, const float *Bs, int g) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i) fa[slot][i] = TA::frag(As, wm * WM + i * 32 + r, g, h);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) fb[slot][j] = TB::frag(Bs, wn * WN + j * 32 + r, g, h);
-    };
-    auto mfma_group = [&](int slot, int chain) {
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j][chain % CHAINS] = __builtin_amdgcn_mfma_f32_32x32x2f32(
-                        fa[slot][i][s], fb[slot][j][s], acc[i][j][chain % CHAINS], 0, 0, 0);
-    };
-
-    // Interior tiles with 16-byte aligned rows and a whole number of k-tiles take a loop without
-    // any guard, in which every memory operation has a fixed place between the MFMAs of a
-    // group (a wavefront can issue other instructions while its MFMA executes): the fragment
-    // reads of the next group after the group's first MFMA, the LDS write of tile kt+1 in
-    // group 0, the global loads of tile kt+2 in group 1.  The explicit lgkmcnt(0) at the head
-    // of a group tells the compiler that the reads of the previous group have arrived; left
-    // to itself it places the reads next to their first use and waits for them there.
-    // (a last, partial k-tile is loaded through the guarded path, which pads it with zeros)
-    const bool fast = (G == 4) && a_in && b_in && a.a_vec != 0 && a.b_vec != 0 && nk > 0 && !a.no_fast_loop;
-    const int nk_full = (kend - kbeg) / BK;  // tiles [0, nk_full) are whole
-    if (fast) {
-        auto group = [&](int slot, int chain, auto &&extra) {
-            bool first = true;
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) {
-                        acc[i][j][chain % CHAINS] = __builtin_amdgcn_mfma_f32_32x32x2f32(
-                            fa[slot][i][s], fb[slot][j][s], acc[i][j][chain % CHAINS], 0, 0, 0);
-                        if (first) {
-                            first = false;
-                            __builtin_amdgcn_sched_barrier(0);
-                            extra();
-                            __builtin_amdgcn_sched_barrier(0);
-                        }
-                    }
-        };
-        auto load_any = [&](int t) {
-            if (t < nk_full) {
-                TA::load_fast(ra, A, a.lda, m0, kbeg + t * BK, true, tid);
-                TB::load_fast(rb, Bm, a.ldb, n0, kbeg + t * BK, true, tid);
-            } else {
-                TA::load(ra, A, a.lda, m0, a.M, kbeg + t * BK, kend, true, tid);
-                TB::load(rb, Bm, a.ldb, n0, a.N, kbeg + t * BK, kend, true, tid);
-            }
-        };
-        load_any(0);
-        TA::store(smem, ra, tid);
-        TB::store(smem + TA::FLOATS, rb, tid);
-        if (nk > 1) load_any(1);
-        __syncthreads();
-        read_frags(0, smem, smem + TA::FLOATS, 0);
-        for (int kt = 0; kt < nk; ++kt) {
-            const float *As = smem + (kt & 1) * STAGE;
-            const float *Bs = As + TA::FLOATS;
-            float *An = smem + ((kt + 1) & 1) * STAGE;
-            const bool next = (kt + 1 < nk), next2 = (kt + 2 < nk);
-            if (KIND == GEMM_DW && !A_KMAJ) {
-                if (do_colsum) {
-#pragma unroll
-                    for (int k = 0; k < BK / CP; ++k) colsum += As[(cpart + k * CP) * TA::LD + crow];
-                }
-            }
-            __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
-            group(0, 0, [&]() {
-                read_frags(1, As, Bs, 1);
-                if (next) {  // tile kt+1 -> the stage nobody reads during this iteration
-                    TA::store(An, ra, tid);
-                    TB::store(An + TA::FLOATS, rb, tid);
-                }
-            });
-            __builtin_amdgcn_s_waitcnt(0xc07f);
-            group(1, 1, [&]() {
-                read_frags(0, As, Bs, 2);
-                if (next2) load_any(kt + 2);
-            });
-            __builtin_amdgcn_s_waitcnt(0xc07f);
-            group(0, 2, [&]() { read_frags(1, As, Bs, 3); });
-            __syncthreads();  // tile kt fully read by everyone, tile kt+1 fully written
-            __builtin_amdgcn_s_waitcnt(0xc07f);
-            group(1, 3, [&]() {
-                if (next) read_frags(0, An, An + TA::FLOATS, 0);
-            });
-        }
-    } else {
-    if (nk > 0) {
-        load_tile(0);
-        TA::store(smem, ra, tid);
-        TB::store(smem + TA::FLOATS, rb, tid);
-        if (nk > 1) load_tile(1);
-    }
-    __syncthreads();
-    if (nk > 0) read_frags(0, smem, smem + TA::FLOATS, 0);
-
-    for (int kt = 0; kt < nk; ++kt) {
-        const float *As = smem + (kt & 1) * STAGE;
-        const float *Bs = As + TA::FLOATS;
-        float *An = smem + ((kt + 1) & 1) * STAGE;
-        if (kt + 1 < nk) {  // tile kt+1 -> the stage nobody reads during this iteration
-            TA::store(An, ra, tid);
-            TB::store(An + TA::FLOATS, rb, tid);
-        }
-        if (kt + 2 < nk) load_tile(kt + 2);
-        if (KIND == GEMM_DW && !A_KMAJ) {
-            if (do_colsum) {
-#pragma unroll
-                for (int k = 0; k < BK / CP; ++k) colsum += As[(cpart + k * CP) * TA::LD + crow];
-            }
-        }
-#pragma unroll
-        for (int g = 0; g + 1 < G; ++g) {
-            read_frags((g + 1) & 1, As, Bs, g + 1);
-            mfma_group(g & 1, g);
-        }
-        __syncthreads();  // tile kt fully read by everyone, tile kt+1 fully written
-        if (kt + 1 < nk) read_frags(0, An, An + TA::FLOATS, 0);
-        mfma_group((G - 1) & 1, G - 1);
-    }
-    }
-
-    if (KIND == GEMM_DW) {
-        if (do_colsum) {  // uniform per workgroup; after the loop's last barrier nobody reads a stage
-            smem[cpart * BM + crow] = colsum;
-            __syncthreads();
-            if (tid < BM && m0 + tid < a.M) {
-                float s = smem[tid];
-#pragma unroll
-                for (int q = 1; q < CP; ++q) s += smem[q * BM + tid];
-                a.colsum[(size_t)split * a.M + m0 + tid] = s;
-            }
-        }
-    }
-
-    // ---- epilogue.  acc[i][j][v] is C(row, col) with
-    //      row = 8 (v / 4) + 4 h + (v % 4), col = r   inside its 32 x 32 block.
-    // The activation enters as a constant: tested per value at run time it was three scalar
-    // branches in front of every one of the lane's outputs.
-    float *__restrict__ C = static_cast<float *>(a.C) + (size_t)split * a.c_split_stride;
-    auto epilogue = [&](auto act_c) {
-    constexpr int ACT = decltype(act_c)::value;
-    if (a_in && b_in) {
-        // Interior tile: no guards.  The backward-data product requests the 16 activation
-        // values a lane needs for the derivative together; behind a bounds check per element
-        // each load waited for the one before it (16 round trips to memory per block).
-        // Every address is a wavefront-uniform base (block row, block column, row inside the
-        // block: scalar arithmetic) plus one per-lane offset that is the same for all 16 values,
-        // instead of a 64-bit multiply-add per value and lane.
-        const float *__restrict__ aux = static_cast<const float *>(a.aux);
-        const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-        const int wm_u = wave_u % WAVES_M, wn_u = wave_u / WAVES_M;
-        const unsigned lo_c = (unsigned)(4 * h * a.ldc + r), lo_x = (unsigned)(4 * h * a.ldaux + r);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int nb = n0 + wn_u * WN + j * 32;  // uniform
-            const float bias = bias_pre[j];
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                const int mbu = m0 + wm_u * WM + i * 32;  // uniform; the lane's rows are mbu + 8 (v / 4) + 4 h + v % 4
-                float o[16];
-                if (KIND == GEMM_DA) {
-#pragma unroll
-                    for (int v = 0; v < 16; ++v)
-                        o[v] = (aux + ((size_t)(mbu + 8 * (v >> 2) + (v & 3)) * a.ldaux + nb))[lo_x];
-                }
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    float x = acc[i][j][0][v];
-                    if (CHAINS == 2) x += acc[i][j][CHAINS - 1][v];
-                    if (KIND == GEMM_FWD) {
-                        x += bias;
-                        if (ACT == ACT_SIGMOID) x = sigmoidf_fast(x);
-                        else if (ACT == ACT_RELU) x = fmaxf(x, 0.f);
-                    } else if (KIND == GEMM_DA) {
-                        if (ACT == ACT_SIGMOID) x *= o[v] * (1.f - o[v]);
-                        else if (ACT == ACT_RELU) x = (o[v] > 0.f) ? x : 0.f;
-                    }
-                    (C + ((size_t)(mbu + 8 * (v >> 2) + (v & 3)) * a.ldc + nb))[lo_c] = x;
-                }
-            }
-        }
-        return;
-    }
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const int n = n0 + wn * WN + j * 32 + r;
-        const bool n_ok = n < a.N;
-        const float bias = bias_pre[j];
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int m = m0 + wm * WM + i * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-                if (m < a.M && n_ok) {
-                    float x = acc[i][j][0][v];
-                    if (CHAINS == 2) x += acc[i][j][CHAINS - 1][v];
-                    if (KIND == GEMM_FWD) {
-                        x += bias;
-                        if (ACT == ACT_SIGMOID) x = sigmoidf_fast(x);
-                        else if (ACT == ACT_RELU) x = fmaxf(x, 0.f);
-                    } else if (KIND == GEMM_DA) {
-                        const float o = static_cast<const float *>(a.aux)[(size_t)m * a.ldaux + n];
-                        if (ACT == ACT_SIGMOID) x *= o * (1.f - o);
-                        else if (ACT == ACT_RELU) x = (o > 0.f) ? x : 0.f;
-                    }
-                    C[(size_t)m * a.ldc + n] = x;
-                }
-            }
-        }
-    }
-    };
-    with_activation(KIND == GEMM_DW ? (int)ACT_NONE : a.act, epilogue);
-}
-
-template <int BM, int BN, int BK, int WAVES_M, bool A_KMAJ, bool B_KMAJ, int KIND>
-__global__ __launch_bounds__(NT) void gemm_f32_kernel(GemmArgs a)
-{
-    __shared__ __attribute__((aligned(16))) float smem[lds_floats<BM, BN, BK, A_KMAJ, B_KMAJ>()];
-    gemm_f32_tile<BM, BN, BK, WAVES_M, A_KMAJ, B_KMAJ, KIND>(a, smem, xcd_tile_order(blockIdx.x, gridDim.x),
-                                                             blockIdx.y);
-}
-
-// Backward of one hidden layer in ONE launch: the backward-data product D_{l-1} = (D_l W_l) f'
-// (64 x 64 x 32 tiles) and the weight-gradient product dW_l = D_l^T A_{l-1} (DW_BM x 64 x 32
-// tiles x K-slices, DW_BM = 128 or 64).  Both only read D_l, so they are independent; sharing
-// a launch lets the prologue / epilogue of one hide under the main loop of the other and pays
-// the per-launch latencies once.
-template <int DW_BM>
-__global__ __launch_bounds__(NT) void gemm_f32_bwd_pair_kernel(GemmArgs da, GemmArgs dw, int n_dw)
-{
-    constexpr int LDS_DA = lds_floats<64, 64, 32, true, false>();
-    constexpr int LDS_DW = lds_floats<DW_BM, 64, 32, false, false>();
-    __shared__ __attribute__((aligned(16))) float smem[LDS_DA > LDS_DW ? LDS_DA : LDS_DW];
-    const int b = blockIdx.x;
-    if (b < n_dw) {  // the weight-gradient blocks are the longer ones: they are dispatched first
-        const int tiles = dw.tiles_m * dw.tiles_n;
-        if ((dw.splits & 7) == 0) {
-            // Workgroup ids go round-robin over the 8 XCDs, each with an L2 of its own.  Slice s of
-            // the batch is given to XCD s % 8, all of its output tiles: the XCD then reads only its
-            // slices' rows of D_l and A_{l-1}, once.  (Dealt out tile by tile, every XCD read every
-            // row of A_{l-1}: 8 x 8.4 MB at B = 4096 for 8.4 MB of activations.)  The backward-data
-            // blocks below give XCD x a contiguous run of row tiles -- at the usual sizes the very
-            // rows of slice x -- so both products find D_l and A_{l-1} in the same L2.
-            const int q = b >> 3;
-            gemm_f32_tile<DW_BM, 64, 32, 2, false, false, GEMM_DW>(dw, smem, q % tiles, (b & 7) + 8 * (q / tiles));
-        } else {
-            gemm_f32_tile<DW_BM, 64, 32, 2, false, false, GEMM_DW>(dw, smem, xcd_tile_order(b % tiles, tiles), b / tiles);
-        }
-    } else {
-        const int n_da = gridDim.x - n_dw;
-        gemm_f32_tile<64, 64, 32, 2, true, false, GEMM_DA>(da, smem, xcd_tile_order(b - n_dw, n_da), 0);
-    }
-}
-
 // ---- small products: one 32 x 32 output block per workgroup, the contraction split over
 // the four wavefronts.
 //
-// With few output tiles (a small batch) the 64 x 64 kernel leaves most compute units idle
+// With few output tiles (a small batch) a 64 x 64 tile leaves most compute units idle
 // while each wavefront walks the whole contraction alone: K / 2 dependent-issue MFMAs of 64
 // cycles each are the run time, whatever the batch.  Here every workgroup owns one 32 x 32
 // block and its wavefront w takes the k-groups {w, w + 4, ...} of every k-tile, so the MFMA
@@ -687,7 +342,7 @@ __global__ __launch_bounds__(NT) void gemm_f32_small_kernel(GemmArgs a)
                                                        blockIdx.y);
 }
 
-// The backward pair of one hidden layer (see gemm_f32_bwd_pair_kernel) for small batches.
+// The backward pair of one hidden layer (see launch_gemm_f32_bwd_pair) for small batches.
 __global__ __launch_bounds__(NT) void gemm_f32_small_pair_kernel(GemmArgs da, GemmArgs dw, int n_dw)
 {
     constexpr int LDS_DA = lds_floats<32, 32, SMALL_BK, true, false>();
@@ -709,66 +364,57 @@ int env_int(const char *name, int dflt)
     return (s && *s) ? atoi(s) : dflt;
 }
 
-// Workgroups wanted per launch: two per compute unit on a 256-CU device.
-int target_wgs()
-{
-    static const int v = env_int("HB_GEMM_WGS", 512);  // tuning aid
-    return v;
-}
-
+// ---- plan of the split-plane kernels (gemm_split.hip).
 struct Shape {
-    int bm, bn, bk;
+    int bm, bn;
 };
+constexpr Shape SHAPES[] = {{64, 64}, {128, 64}, {128, 128}};  // by the number launch_gemm_split takes
+constexpr int CUS = 256;
+constexpr int K_CHUNK_ALIGN = 32;  // slices of a split contraction are multiples of the k-tile
 
-// Tile shapes that are instantiated.  HB_GEMM_TILE = 1..5 forces one (tuning aid).
-constexpr Shape SHAPES[] = {{64, 64, 16}, {64, 64, 32}, {128, 64, 16}, {128, 64, 32}, {128, 128, 16}};
-constexpr int K_CHUNK_ALIGN = 32;  // split-K slices are multiples of every BK above
-
-Shape pick_shape(GemmKind kind, int M, int N)
+long long tiles_of(int sh, int M, int N)
 {
-    static const int forced = env_int("HB_GEMM_TILE", 0);
-    if (forced >= 1 && forced <= 5) return SHAPES[forced - 1];
-    // measured on 4096 x 512 x 512 (MI355X): forward / backward-data are fastest with
-    // 64 x 64 x 32 tiles (two workgroups per CU), the split-K weight gradient with 128 x 64 x 32
-    (void)N;
-    if (kind == GEMM_DW && M >= 128) return SHAPES[3];
-    return SHAPES[1];
+    return (long long)((M + SHAPES[sh].bm - 1) / SHAPES[sh].bm) * ((N + SHAPES[sh].bn - 1) / SHAPES[sh].bn);
 }
 
-template <int BM, int BN, int BK, int WAVES_M>
-hipError_t launch_shape(GemmKind kind, const GemmArgs &a, dim3 grid, hipStream_t stream,
-                        const LaunchEvents &ev)
+// Clocks per k-tile of a workgroup, in hundreds, from time stamps around the main loop (MI355X,
+// K = 512): 64 x 64 9 alone on its compute unit and 15 for two that share one, 128 x 64 12.5,
+// 128 x 128 20 (one per compute unit).  The shape with the shortest sequence of rounds wins:
+// 4096 x 512 outputs 14.6 us as 128 x 64 (256 workgroups), 16.8 as 64 x 64, 20 as 128 x 128;
+// 8192 x 512 27 / 31 / 25.8; 2048 x 512 12.0 / 11.2 / 19.
+double rounds_cost(int sh, long long blocks)
 {
-    switch (kind) {
-    case GEMM_FWD:
-        return launch_kernel(gemm_f32_kernel<BM, BN, BK, WAVES_M, true, true, GEMM_FWD>, grid,
-                             dim3(NT), stream, ev, a);
-    case GEMM_DA:
-        return launch_kernel(gemm_f32_kernel<BM, BN, BK, WAVES_M, true, false, GEMM_DA>, grid,
-                             dim3(NT), stream, ev, a);
-    case GEMM_DW:
-        return launch_kernel(gemm_f32_kernel<BM, BN, BK, WAVES_M, false, false, GEMM_DW>, grid,
-                             dim3(NT), stream, ev, a);
-    }
-    return hipErrorInvalidValue;
+    const long long r = (blocks + CUS - 1) / CUS;
+    if (sh == 2) return 20.0 * r;
+    if (sh == 1) return 12.5 * r;
+    return blocks <= CUS ? 9.0 : 15.0 * ((r + 1) / 2);
+}
+int pick_shape(int M, int N)
+{
+    int best = 0;
+    for (int sh = 1; sh < 3; ++sh)
+        if (rounds_cost(sh, tiles_of(sh, M, N)) <= rounds_cost(best, tiles_of(best, M, N))) best = sh;
+    return best;
 }
 
 struct SplitPlan {
     int splits, chunk;
 };
-
-// Split-K plan for the weight-gradient product (its contraction runs over the batch):
-// enough slices to fill the device, each a multiple of BK long, none empty.
-SplitPlan plan_splits(int tiles, int K, int max_splits, int wgs = 0)
+SplitPlan slices(int K, int s)
 {
-    if (wgs <= 0) wgs = target_wgs();
-    int s = (wgs + tiles - 1) / tiles;
-    const int by_k = (K + 4 * K_CHUNK_ALIGN - 1) / (4 * K_CHUNK_ALIGN);  // slices of >= 128
+    const int chunk = ((K + s - 1) / s + K_CHUNK_ALIGN - 1) / K_CHUNK_ALIGN * K_CHUNK_ALIGN;
+    return {(K + chunk - 1) / chunk, chunk};
+}
+// Slices of a weight gradient (its contraction runs over the batch) of `tiles` output tiles for
+// `wgs` workgroups in all, each slice at least 128 long.
+SplitPlan plan_splits(long long tiles, int K, int max_splits, long long wgs)
+{
+    long long s = (wgs + tiles - 1) / tiles;
+    const int by_k = (K + 4 * K_CHUNK_ALIGN - 1) / (4 * K_CHUNK_ALIGN);
     if (s > by_k) s = by_k;
     if (s > max_splits) s = max_splits;
     if (s < 1) s = 1;
-    const int chunk = ((K + s - 1) / s + K_CHUNK_ALIGN - 1) / K_CHUNK_ALIGN * K_CHUNK_ALIGN;
-    return {(K + chunk - 1) / chunk, chunk};
+    return slices(K, (int)s);
 }
 
 // Products with fewer 64 x 64 output tiles than this (forward / backward-data), or a
@@ -787,19 +433,17 @@ int small_k_max()
 }
 bool small_out(int M, int N, int K)
 {
-    static const int forced = env_int("HB_GEMM_TILE", 0);
-    return forced == 0 && K >= 64 && (long long)((M + 63) / 64) * ((N + 63) / 64) < small_tiles_max();
+    return K >= 64 && (long long)((M + 63) / 64) * ((N + 63) / 64) < small_tiles_max();
 }
 bool small_dw(int K)
 {
-    static const int forced = env_int("HB_GEMM_TILE", 0);
-    return forced == 0 && K >= 64 && K < small_k_max();
+    return K >= 64 && K < small_k_max();
 }
 // A weight gradient launched on its own (not paired with a backward-data product) whose output
 // is only a few tiles -- the first layer of a narrow input, 512 x 54 -- stays with the small
 // kernel up to four times that contraction length: with so few tiles the 64-wide kernel needs
 // tens of K-slices to fill the chip, and every slice is a partial the update has to read
-// (B = 4096, 512 x 54: 12.4 -> 11.0 us, and the update 7.7 -> 7.2 us).
+// (B = 4096, 512 x 54: 12.4 -> 11.0 us, and the update 7.7 -> 7.2 us, against fp32 MFMA tiles).
 long long small_dw_alone_kmax(int M, int N)  // contractions below this go to the small kernel
 {
     const bool few_tiles = (long long)((M + 63) / 64) * ((N + 63) / 64) <= 16;
@@ -807,8 +451,7 @@ long long small_dw_alone_kmax(int M, int N)  // contractions below this go to th
 }
 bool small_dw_alone(int M, int N, int K)
 {
-    static const int forced = env_int("HB_GEMM_TILE", 0);
-    return forced == 0 && K >= 64 && K < small_dw_alone_kmax(M, N);
+    return K >= 64 && K < small_dw_alone_kmax(M, N);
 }
 // K-slices of the small weight-gradient kernel: at most 512 long (multiples of its k-tile)
 SplitPlan plan_small_splits(int K, int max_splits)
@@ -824,9 +467,11 @@ SplitPlan plan_small_splits(int K, int max_splits)
 
 int gemm_f32_dw_splits(int M, int N, int K, int max_splits)
 {
-    const Shape sh = pick_shape(GEMM_DW, M, N);
-    const int tiles = ((M + sh.bm - 1) / sh.bm) * ((N + sh.bn - 1) / sh.bn);
-    const int big = plan_splits(tiles, K, max_splits).splits;
+    int big = 1;
+    for (int sh = 0; sh < 3; ++sh) {
+        const int n = plan_splits(tiles_of(sh, M, N), K, max_splits, CUS).splits;
+        if (n > big) big = n;
+    }
     // longest contraction the small kernel can be given for any batch up to K
     const long long kmax = small_dw_alone_kmax(M, N);
     const int ks = K < kmax ? K : (int)(kmax - 1);
@@ -859,30 +504,26 @@ hipError_t launch_gemm_f32(GemmKind kind, GemmArgs a, int max_splits, int *split
         }
         return hipErrorInvalidValue;
     }
-    const Shape sh = pick_shape(kind, a.M, a.N);
-    static const int no_fast = env_int("HB_GEMM_NOFAST", 0);
-    a.no_fast_loop = no_fast;
-    a.tiles_m = (a.M + sh.bm - 1) / sh.bm;
-    a.tiles_n = (a.N + sh.bn - 1) / sh.bn;
+    int sh = pick_shape(a.M, a.N);
+    SplitPlan sp = {1, (a.K + K_CHUNK_ALIGN - 1) / K_CHUNK_ALIGN * K_CHUNK_ALIGN};
+    if (kind == GEMM_DW) {
+        sh = (a.M >= 128) ? (a.N >= 128 ? 2 : 1) : 0;
+        sp = plan_splits(tiles_of(sh, a.M, a.N), a.K, max_splits, CUS);
+    }
+    a.tiles_m = (a.M + SHAPES[sh].bm - 1) / SHAPES[sh].bm;
+    a.tiles_n = (a.N + SHAPES[sh].bn - 1) / SHAPES[sh].bn;
     const long long tiles = (long long)a.tiles_m * a.tiles_n;
     if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
-    SplitPlan sp = {1, (a.K + K_CHUNK_ALIGN - 1) / K_CHUNK_ALIGN * K_CHUNK_ALIGN};
-    if (kind == GEMM_DW) sp = plan_splits((int)tiles, a.K, max_splits);
     a.splits = sp.splits;
     a.k_chunk = sp.chunk;
     if (splits_out) *splits_out = sp.splits;
-    const dim3 grid((unsigned)tiles, (unsigned)sp.splits, 1);
-    if (sh.bm == 64 && sh.bk == 16) return launch_shape<64, 64, 16, 2>(kind, a, grid, stream, ev);
-    if (sh.bm == 64 && sh.bk == 32) return launch_shape<64, 64, 32, 2>(kind, a, grid, stream, ev);
-    if (sh.bn == 64 && sh.bk == 16) return launch_shape<128, 64, 16, 2>(kind, a, grid, stream, ev);
-    if (sh.bn == 64 && sh.bk == 32) return launch_shape<128, 64, 32, 2>(kind, a, grid, stream, ev);
-    return launch_shape<128, 128, 16, 2>(kind, a, grid, stream, ev);
+    return launch_gemm_split(kind, a, sh, dim3((unsigned)tiles, (unsigned)sp.splits, 1), stream, ev);
 }
 
-
-// dA_l and dW_l of one hidden layer in one launch (see gemm_f32_bwd_pair_kernel).  Only for
-// shapes the fixed tile shapes of that kernel suit; the caller falls back to two launches
-// when this returns false from gemm_f32_pair_ok.
+// dA_l and dW_l of one hidden layer in one launch: both only read D_l, so they are independent, and
+// sharing a launch lets the prologue / epilogue of one hide under the main loop of the other and pays
+// the per-launch latencies once.  Only for shapes the tiles suit; the caller makes two launches
+// when gemm_f32_pair_ok returns false.
 bool gemm_f32_pair_ok(const GemmArgs &da, const GemmArgs &dw)
 {
     static const int off = env_int("HB_NO_PAIR", 0);
@@ -892,9 +533,6 @@ bool gemm_f32_pair_ok(const GemmArgs &da, const GemmArgs &dw)
 hipError_t launch_gemm_f32_bwd_pair(GemmArgs da, GemmArgs dw, int max_splits, int *splits_out,
                                     hipStream_t stream, const LaunchEvents &ev)
 {
-    static const int pair_wgs = env_int("HB_PAIR_WGS", 256);  // weight-gradient blocks wanted (tuning aid)
-    static const int no_fast = env_int("HB_GEMM_NOFAST", 0);
-    da.no_fast_loop = dw.no_fast_loop = no_fast;
     if (small_out(da.M, da.N, da.K) && small_dw(dw.K)) {
         da.tiles_m = (da.M + 31) / 32;
         da.tiles_n = (da.N + 31) / 32;
@@ -913,32 +551,31 @@ hipError_t launch_gemm_f32_bwd_pair(GemmArgs da, GemmArgs dw, int max_splits, in
         return launch_kernel(gemm_f32_small_pair_kernel, dim3((unsigned)blocks), dim3(NT), stream, ev, da, dw,
                              (int)(t_dw * sp.splits));
     }
-    da.tiles_m = (da.M + 63) / 64;
-    da.tiles_n = (da.N + 63) / 64;
+    // The larger shapes read and convert fewer operand bytes per flop; they need a workgroup for (nearly)
+    // every compute unit from the two products together.  Slices of the weight gradient: as many
+    // workgroups as the backward-data product has (at most one per compute unit), which makes them about
+    // equally long (4096 x 512 x 512: 128 + 128 workgroups of 128 x 128 x 512, 41.5 -> 26.8 us).
+    int sh = 0;
+    SplitPlan sp = {1, 0};
+    for (sh = 2; sh >= 0; --sh) {
+        const long long n = tiles_of(sh, da.M, da.N), t = tiles_of(sh, dw.M, dw.N);
+        if (n > 0x3fffffffLL || t > 0x3fffffffLL) return hipErrorInvalidValue;
+        sp = plan_splits(t, dw.K, max_splits, n < CUS ? n : CUS);
+        if (sh == 0 || n + t * sp.splits >= CUS - CUS / 8) break;
+    }
+    for (GemmArgs *g : {&da, &dw}) {
+        g->tiles_m = (g->M + SHAPES[sh].bm - 1) / SHAPES[sh].bm;
+        g->tiles_n = (g->N + SHAPES[sh].bn - 1) / SHAPES[sh].bn;
+    }
     da.splits = 1;
     da.k_chunk = (da.K + K_CHUNK_ALIGN - 1) / K_CHUNK_ALIGN * K_CHUNK_ALIGN;
-    const long long n_da = (long long)da.tiles_m * da.tiles_n;
-    // While everything fits the device at once (four 64 x 64 workgroups per CU by LDS), the
-    // weight gradient takes 64 x 64 tiles too: 2 x pair_wgs blocks as long as the backward-data
-    // ones, so no compute unit ends on a lone long block (measured at B = 2048 and 4096:
-    // 45 instead of 47 us; with more backward-data blocks than that the 128-row tile wins).
-    static const int dw64_env = env_int("HB_PAIR_DW64", -1);  // tuning aid: 0 / 1 force
-    const bool dw64 = dw64_env >= 0 ? dw64_env != 0 : (n_da + 2 * pair_wgs <= 4 * 256);
-    dw.tiles_m = dw64 ? (dw.M + 63) / 64 : (dw.M + 127) / 128;
-    dw.tiles_n = (dw.N + 63) / 64;
-    const long long t_dw = (long long)dw.tiles_m * dw.tiles_n;
-    if (n_da > 0x3fffffffLL || t_dw > 0x3fffffffLL) return hipErrorInvalidValue;
-    const SplitPlan sp = plan_splits((int)t_dw, dw.K, max_splits, dw64 ? 2 * pair_wgs : pair_wgs);
     dw.splits = sp.splits;
     dw.k_chunk = sp.chunk;
     if (splits_out) *splits_out = sp.splits;
-    const long long blocks = n_da + t_dw * sp.splits;
+    const long long n_dw = (long long)dw.tiles_m * dw.tiles_n * sp.splits;
+    const long long blocks = (long long)da.tiles_m * da.tiles_n + n_dw;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    if (dw64)
-        return launch_kernel(gemm_f32_bwd_pair_kernel<64>, dim3((unsigned)blocks), dim3(NT), stream, ev, da, dw,
-                             (int)(t_dw * sp.splits));
-    return launch_kernel(gemm_f32_bwd_pair_kernel<128>, dim3((unsigned)blocks), dim3(NT), stream, ev, da, dw,
-                         (int)(t_dw * sp.splits));
+    return launch_gemm_split_pair(da, dw, sh, (unsigned)blocks, (int)n_dw, stream, ev);
 }
 
 }  // namespace hb

@@ -53,7 +53,6 @@ struct GemmArgs {
     float *colsum;             // DW: column sums of A (= bias gradient partials) [splits][M], may be null
     int act;                   // ACT_*
     int tiles_m, tiles_n;
-    int no_fast_loop;          // tuning aid (HB_GEMM_NOFAST): always take the guarded main loop
 };
 
 // Chooses the tile shape for (kind, M, N, K), fills tiles/splits (splits <= max_splits)
@@ -67,6 +66,11 @@ hipError_t launch_gemm_f32(GemmKind kind, GemmArgs a, int max_splits, int *split
 bool gemm_f32_pair_ok(const GemmArgs &da, const GemmArgs &dw);
 hipError_t launch_gemm_f32_bwd_pair(GemmArgs da, GemmArgs dw, int max_splits, int *splits_out,
                                     hipStream_t stream, const LaunchEvents &ev = LaunchEvents());
+
+hipError_t launch_gemm_split(GemmKind kind, const GemmArgs &a, int shape, dim3 grid, hipStream_t stream,
+                             const LaunchEvents &ev);
+hipError_t launch_gemm_split_pair(const GemmArgs &da, const GemmArgs &dw, int shape, unsigned blocks, int n_dw,
+                                  hipStream_t stream, const LaunchEvents &ev);
 
 // Number of split-K slices launch_gemm_f32 will use for a DW product of this shape
 // (so that the caller can size the partial buffers).

@@ -1096,3 +1096,35 @@ def test_step_can_be_captured_in_a_graph_and_replays_like_eager_steps(bf16):
     eager.destroy()
     graphed.destroy()
 
+
+
+# ---------------------------------------------------------------- fp32 products as bf16 planes
+@pytest.mark.parametrize("dims,act,B", [
+    ((31, 40, 33, 20), hi.ACT_SIGMOID, 17),        # contractions of a single partial k-tile (17, 31, 20, 33 = 32 + 1)
+    ((32, 64, 64, 17), hi.ACT_RELU, 31),           # whole k-tiles forward, a lone partial one over the batch
+    ((100, 130, 65, 20), hi.ACT_SIGMOID, 2561),    # 64 x 64 tiles, both operands cut, rows not 16-byte aligned
+    ((97, 257, 129, 33), hi.ACT_RELU, 4099),       # 128 x 64
+    ((129, 520, 514, 40), hi.ACT_SIGMOID, 8200),   # 128 x 128, two values short of a 16-byte row
+])
+def test_split_plane_products_at_tile_edges(dims, act, B):
+    """Each tile shape of the large fp32 products with rows, columns and k-tiles cut by the end of
+    the matrix, rows of every alignment."""
+    params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=B)
+    check_case(dims, act, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=B < 100)
+
+
+def test_split_plane_products_of_values_without_finite_planes():
+    """An infinite or nearly largest fp32 input has no finite leading bf16 part, yet the product is
+    what fp32 arithmetic gives: a saturated unit, not a NaN."""
+    dims, B = (64, 128, 128, 30), 2560
+    params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=5)
+    X[3, 7], X[1300, 40], X[2559, 63] = np.inf, -np.inf, 3.4e38
+    torch = _torch()
+    m = make_model(dims, hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, B, params)
+    got = m.batch_loss(torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda(), B)
+    acts = gpu_hidden_activations(m, dims, B)
+    m.destroy()
+    with np.errstate(over="ignore"):
+        ref = oracle.batch_loss(dims, hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, params, X.astype(np.float64), y)
+    assert np.isfinite(ref) and abs(got - ref) <= TOL_F32 * abs(ref)
+    assert set(np.unique(acts[1][3])) <= {0.0, 1.0} and set(np.unique(acts[1][1300])) <= {0.0, 1.0}

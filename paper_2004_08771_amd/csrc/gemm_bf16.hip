@@ -9,17 +9,18 @@
 // The weights exist as two bf16 copies (W_l and W_l^T), rewritten by the weight-gradient
 // epilogue, which also applies the SGD update (Eq. (3)) to the fp32 master weights.  The
 // weight gradient reads D_l and A_{l-1} as they are, batch-major, through the transposing LDS
-// read of gfx950 (LDS-direct kernel, BMAJ form); only where it cannot (rows that are not
-// 16-byte aligned, products too small for 256 x 256 tiles) do the epilogues that produce a
-// tensor also write its transposed copy, and the product runs K-major like the other two.
-// Two kernel families: gemm_bf16_nt_kernel (256-thread workgroups, 256 x 128 x 32 or
-// 128 x 128 tiles, four wavefronts, operands global -> registers -> LDS, double-buffered,
-// 16-byte accesses throughout) for small or unaligned products, gemm_bf16_dma_kernel
-// (256 x 256 x 64, LDS-direct loads) for the large ones.
+// read of gfx950 (LDS-direct kernel) or transposed in registers (small tiles); only where it cannot
+// (rows that are not 4-byte aligned, or not 16-byte aligned in a large product) do the epilogues
+// that produce a tensor also write its transposed copy, and the product runs K-major like the
+// other two.
+// Two kernel families: gemm_bf16_dma_kernel (256 x 256 x 64 tiles, LDS-direct loads) for the large
+// products, gemm_bf16_mid_kernel (64 x 64 x 64, operands global -> registers -> LDS) for all others.
 #include "hb_internal.h"
 
 #include <mutex>
 #include <stdlib.h>
+
+#include <type_traits>
 
 namespace hb {
 namespace {
@@ -44,14 +45,11 @@ __device__ __forceinline__ unsigned int pack2bf(float lo, float hi)
 }
 __device__ __forceinline__ float bf2f(bf16_t b) { return __uint_as_float((unsigned int)b << 16); }
 
-// One operand tile: ROWS x BK bf16, K-major, LDS rows padded by 8 elements (16 bytes) so that
-// the 16-byte fragment reads of 8 consecutive lanes fall into disjoint bank groups.
-template <int ROWS, int BK>
+// Guarded loads of one operand tile, ROWS x BK bf16, K-major.
+template <int ROWS, int BK, int THREADS = NT>
 struct TileB {
-    static constexpr int LD = BK + 8;
-    static constexpr int ELEMS = ROWS * LD;
-    static constexpr int VPT = ROWS * BK / 8 / NT;  // 16-byte vectors per thread
-    static_assert(ROWS * BK / 8 % NT == 0, "tile must split evenly over the workgroup");
+    static constexpr int VPT = ROWS * BK / 8 / THREADS;  // 16-byte vectors per thread
+    static_assert(ROWS * BK / 8 % THREADS == 0, "tile must split evenly over the workgroup");
 
     // guarded: anything outside [0, nrows) x [.., kend) reads as zero
     static __device__ __forceinline__ void load(uint4 (&reg)[VPT], const bf16_t *__restrict__ P, long long ld,
@@ -59,7 +57,7 @@ struct TileB {
     {
 #pragma unroll
         for (int v = 0; v < VPT; ++v) {
-            const int idx = tid + v * NT;
+            const int idx = tid + v * THREADS;
             const int kq = idx % (BK / 8), r = idx / (BK / 8);
             const int row = row0 + r, k = k0 + kq * 8;
             uint4 x = {0u, 0u, 0u, 0u};
@@ -76,26 +74,6 @@ struct TileB {
                 }
             }
             reg[v] = x;
-        }
-    }
-    // no guards: the tile lies inside the matrix, rows are 16-byte aligned
-    static __device__ __forceinline__ void load_fast(uint4 (&reg)[VPT], const bf16_t *__restrict__ P,
-                                                     long long ld, int row0, int k0, int tid)
-    {
-#pragma unroll
-        for (int v = 0; v < VPT; ++v) {
-            const int idx = tid + v * NT;
-            const int kq = idx % (BK / 8), r = idx / (BK / 8);
-            reg[v] = *reinterpret_cast<const uint4 *>(P + (size_t)(row0 + r) * ld + k0 + kq * 8);
-        }
-    }
-    static __device__ __forceinline__ void store(bf16_t *S, const uint4 (&reg)[VPT], int tid)
-    {
-#pragma unroll
-        for (int v = 0; v < VPT; ++v) {
-            const int idx = tid + v * NT;
-            const int kq = idx % (BK / 8), r = idx / (BK / 8);
-            *reinterpret_cast<uint4 *>(&S[r * LD + kq * 8]) = reg[v];
         }
     }
 };
@@ -149,12 +127,6 @@ __device__ __forceinline__ float relu_keep(float val, unsigned word, int q, int 
 {
     const int m = (int)(word << (31 - relu_bit_pos(q, e))) >> 31;  // 0 or -1 (one v_bfe_i32)
     return __uint_as_float(__float_as_uint(val) & (unsigned)m);
-}
-
-template <int BM, int BN, int BK>
-constexpr size_t lds_bytes_bf16()
-{
-    return 2 * (size_t)(TileB<BM, BK>::ELEMS + TileB<BN, BK>::ELEMS) * sizeof(bf16_t);
 }
 
 // Epilogue shared by both kernels.  acc[i][j][v] = C(row, col) of the wavefront's block (i, j):
@@ -321,101 +293,261 @@ __device__ __forceinline__ void epilogue_bf16(const GemmBf16Args &a, v16f (&acc)
     });
 }
 
-// Workgroup tile BM x BN, four wavefronts as 2 x 2, each (BM/2) x (BN/2) = TM x TN blocks of
-// 32 x 32.  Same three-level software pipeline as the fp32 kernel: global loads two k-tiles
-// ahead, LDS double-buffered and written early, fragments of the next k-step read under the
-// MFMAs of the current one, one barrier per k-tile.
-template <int BM, int BN, int BK, int KIND>
-__global__ __launch_bounds__(NT, 2) void gemm_bf16_nt_kernel(GemmBf16Args a)  // two workgroups per CU
-{
-    constexpr int WM = BM / 2, WN = BN / 2;
-    constexpr int TM = WM / 32, TN = WN / 32;
-    constexpr int G = BK / 16;  // MFMA k-steps per tile
-    static_assert(G % 2 == 0, "fragment slots alternate with the k-step parity");
-    using TA = TileB<BM, BK>;
-    using TB = TileB<BN, BK>;
-    constexpr int STAGE = TA::ELEMS + TB::ELEMS;
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    bf16_t *smem = reinterpret_cast<bf16_t *>(smem_raw);
+// ---- products with too few 256 x 256 tiles: 64 x 64 or 128 x 128 tiles -----------------------
+// What bounds a product of this size is latency: a k-tile of 64 is only four MFMAs per block and
+// wavefront, and an L2 round trip under load takes about 550 cycles.  So four register sets keep
+// four k-tiles in flight per workgroup, and small tiles (32 or 48 KB of LDS, at most 128
+// registers) let several workgroups share a compute unit.  (2047 x 1024 x 1024 forward 33.7 us with
+// 128 x 128 x 64 tiles and two k-tiles in flight, 13.0 now; its weight gradient, with the passes that
+// transposed both operands and added the bias gradient up, 48 + 14 -> 19 us.)
+// LDS rows are 128 bytes, their eight 16-byte chunks exchanged by the row pair, which keeps the
+// writes (8 lanes per row) and the fragment reads (32 rows at one chunk) free of bank conflicts.
+// VEC: rows are 4-byte aligned; 16-byte buffer loads need no more.  Otherwise, and for a partial
+// k-tile (taken first), the guarded element loads of TileB.
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+constexpr int MID_BK = 64, MID_SETS = 4;
 
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
+template <int ROWS, int THREADS>
+struct MidOp {
+    using T = TileB<ROWS, MID_BK, THREADS>;  // thread tid holds chunk tid % 8 of rows tid / 8 + R1 v
+    static constexpr int R1 = THREADS / 8;
+    static constexpr int VPT = T::VPT;
+    uint4 x[MID_SETS][VPT];
+    unsigned off[VPT];
+
+    static __device__ __forceinline__ int slot(int row, int c)
+    {
+        return row * 128 + ((c ^ (((row >> 1) ^ ((row >> 5) << 2)) & 7)) << 4);
+    }
+    static __device__ __forceinline__ int frag(int row, int c) { return slot(row, c); }
+    __device__ __forceinline__ void init(long long ld, int last_row, int tid)
+    {
+#pragma unroll
+        for (int v = 0; v < VPT; ++v)
+            off[v] = (unsigned)(min((tid >> 3) + R1 * v, last_row) - min(R1 * v, last_row)) * (unsigned)ld * 2u +
+                     (tid & 7) * 16u;
+    }
+    __device__ __forceinline__ void load(int set, const bf16_t *__restrict__ tile, long long ld, int last_row)
+    {
+#pragma unroll
+        for (int v = 0; v < VPT; ++v) {
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<bf16_t *>(tile + (size_t)min(R1 * v, last_row) * ld), (short)0, -1, 0x00027000);
+            const v4u t = __builtin_amdgcn_raw_buffer_load_b128(rs, off[v], 0, 0);
+            x[set][v] = make_uint4(t[0], t[1], t[2], t[3]);
+        }
+    }
+    __device__ __forceinline__ void store(int set, unsigned char *S, int tid) const
+    {
+#pragma unroll
+        for (int v = 0; v < VPT; ++v) *reinterpret_cast<uint4 *>(S + slot((tid >> 3) + R1 * v, tid & 7)) = x[set][v];
+    }
+};
+
+// The same for an operand whose rows are the contraction (weight gradient: D_l and A_{l-1} as the
+// other products leave them, batch-major), transposed on the way to LDS: thread tid holds the eight k
+// 8 (tid / 32) + q of the two columns 2 (tid % 32) + e as eight 4-byte loads, packs each column's
+// eight k and writes column 2 i + e to LDS row i + 32 e, so that the lanes write consecutive rows.
+template <int ROWS>
+struct MidOpT {
+    static_assert(ROWS == 64, "32 column pairs");
+    unsigned x[MID_SETS][8];
+    unsigned off;
+
+    static __device__ __forceinline__ int frag(int row, int c) { return MidOp<ROWS, NT>::slot((row >> 1) + 32 * (row & 1), c); }
+    // a pair that starts inside the matrix ends inside its row (rows have an even pitch)
+    __device__ __forceinline__ void init(long long ld, int last_row, int tid)
+    {
+        off = (unsigned)(8 * (tid >> 5)) * (unsigned)ld * 2u + 4u * (unsigned)(min(2 * (tid & 31), last_row) >> 1);
+    }
+    __device__ __forceinline__ void load(int set, const bf16_t *__restrict__ tile, long long ld)
+    {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<bf16_t *>(tile + (size_t)q * ld), (short)0, -1, 0x00027000);
+            x[set][q] = __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0);
+        }
+    }
+    // a partial k-tile: k rows from k0, zero from kend on
+    __device__ __forceinline__ void load_tail(int set, const bf16_t *__restrict__ P, long long ld, int row0, int last_row,
+                                              int k0, int kend, int tid)
+    {
+        const int c = min(2 * (tid & 31), last_row) & ~1;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int k = k0 + 8 * (tid >> 5) + q;
+            x[set][q] = (k < kend) ? *reinterpret_cast<const unsigned *>(P + (size_t)k * ld + row0 + c) : 0u;
+        }
+    }
+    __device__ __forceinline__ void store(int set, unsigned char *S, int tid) const
+    {
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            unsigned w[4];
+#pragma unroll
+            for (int p = 0; p < 4; ++p)
+                w[p] = __builtin_amdgcn_perm(x[set][2 * p + 1], x[set][2 * p], e ? 0x07060302u : 0x05040100u);
+            *reinterpret_cast<uint4 *>(S + MidOp<ROWS, NT>::slot((tid & 31) + 32 * e, tid >> 5)) =
+                make_uint4(w[0], w[1], w[2], w[3]);
+        }
+    }
+};
+
+// KG: groups of four wavefronts that share the contraction of one tile (group g takes the k-tiles
+// g, g + KG, ..); their sums meet in LDS, in group order, and group 0 runs the epilogue.
+// BMAJ: weight gradient with both operands batch-major; the workgroups of the first tile column also
+// add up the columns of D_l, the bias gradient.
+// TILE: 64 (four wavefronts of 32 x 32) or 128 (one group of eight wavefronts of 64 x 32).
+template <int TILE, int KG, int KIND, bool VEC, bool BMAJ>
+__global__ __launch_bounds__((TILE == 64 ? NT : 2 * NT) * KG, TILE == 64 ? (KG == 1 ? 3 : 2) : 1)
+void gemm_bf16_mid_kernel(GemmBf16Args a)
+{
+    constexpr int BM = TILE, BN = TILE, GT = (TILE == 64) ? NT : 2 * NT, TM = TILE / 64;  // GT: threads of a group
+    static_assert(!BMAJ || (VEC && KIND == GEMM_DW && TILE == 64), "batch-major operands");
+    static_assert(TILE == 64 || KG == 1, "a group of eight wavefronts does not share");
+    using OA = std::conditional_t<BMAJ, MidOpT<64>, MidOp<BM, GT>>;
+    using OB = std::conditional_t<BMAJ, MidOpT<64>, MidOp<BN, GT>>;
+    constexpr int A_BYTES = 128 * BM, STAGE = 128 * (BM + BN);
+    __shared__ __attribute__((aligned(16))) unsigned char smem[KG * 2 * STAGE];
+
+    const int lane = threadIdx.x & 63, wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tid = threadIdx.x & (GT - 1), g = wave_all / (GT / 64), wave = wave_all % (GT / 64);
     const int r = lane & 31, h = lane >> 5;
     const int wm = wave & 1, wn = wave >> 1;
+    unsigned char *const stages = smem + g * 2 * STAGE;
 
     int id = blockIdx.x;
     const int T = gridDim.x;
     if ((T & 7) == 0) id = (id & 7) * (T >> 3) + (id >> 3);  // XCD-aware tile order
     const int tile_m = id / a.tiles_n, tile_n = id - tile_m * a.tiles_n;
     const int m0 = tile_m * BM, n0 = tile_n * BN;
-    const int nk = (a.K + BK - 1) / BK;
+    const int nk_full = a.K / MID_BK, tail = (a.K % MID_BK) ? 1 : 0, nk = nk_full + tail;
+    const int rounds = (nk + KG - 1) / KG;               // k-tiles of group 0
+    const int mine = (nk - g + KG - 1) / KG;             // k-tiles of this group: rounds or one less
+    const int a_last = a.M - 1 - m0, b_last = a.N - 1 - n0;
 
     const bf16_t *__restrict__ A = static_cast<const bf16_t *>(a.A);
     const bf16_t *__restrict__ Bm = static_cast<const bf16_t *>(a.B);
-    const bool a_fast = a.a_vec && (m0 + BM <= a.M), b_fast = a.b_vec && (n0 + BN <= a.N);
 
-    v16f acc[TM][TN];
+    v16f acc[TM][1];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+        for (int v = 0; v < 16; ++v) acc[i][0][v] = 0.f;
 
-    uint4 ra[TA::VPT], rb[TB::VPT];
-    auto load_tile = [&](int t) {
-        const int k0 = t * BK;
-        const bool kfull = (k0 + BK <= a.K);
-        if (a_fast && kfull) TA::load_fast(ra, A, a.lda, m0, k0, tid);
-        else TA::load(ra, A, a.lda, m0, a.M, k0, a.K, a.a_vec != 0, tid);
-        if (b_fast && kfull) TB::load_fast(rb, Bm, a.ldb, n0, k0, tid);
-        else TB::load(rb, Bm, a.ldb, n0, a.N, k0, a.K, a.b_vec != 0, tid);
+    OA oa;
+    OB ob;
+    oa.init(a.lda, a_last, tid);
+    ob.init(a.ldb, b_last, tid);
+    auto load_guarded = [&](int set, int k0) {
+        if constexpr (BMAJ) {
+            oa.load_tail(set, A, a.lda, m0, a_last, k0, a.K, tid);
+            ob.load_tail(set, Bm, a.ldb, n0, b_last, k0, a.K, tid);
+        } else {
+            OA::T::load(oa.x[set], A, a.lda, m0, a.M, k0, a.K, a.a_vec != 0, tid);
+            OB::T::load(ob.x[set], Bm, a.ldb, n0, a.N, k0, a.K, a.b_vec != 0, tid);
+        }
     };
-    v8bf fa[2][TM], fb[2][TN];
-    auto read_frags = [&](int slot, const bf16_t *As, const bf16_t *Bs, int kk) {
+    // the group's i-th k-tile; k-tile 0 is the partial one if there is one; past the end: the last
+    // one again (not used)
+    auto load_tile = [&](int set, int i) {
+        const int f = max(g + min(i, mine - 1) * KG - tail, 0);
+        if constexpr (BMAJ) {
+            oa.load(set, A + (size_t)f * MID_BK * a.lda + m0, a.lda);
+            ob.load(set, Bm + (size_t)f * MID_BK * a.ldb + n0, a.ldb);
+        } else if (VEC) {
+            oa.load(set, A + (size_t)m0 * a.lda + f * MID_BK, a.lda, a_last);
+            ob.load(set, Bm + (size_t)n0 * a.ldb + f * MID_BK, a.ldb, b_last);
+        } else {
+            load_guarded(set, f * MID_BK);
+        }
+    };
+    const bool do_bias = BMAJ && a.bias_out != nullptr && tile_n == 0;
+    float csum[2] = {0.f, 0.f};
+    auto store_tile = [&](int set, unsigned char *S) {
+        if constexpr (BMAJ) {
+            if (do_bias) {
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    csum[0] += __uint_as_float(oa.x[set][q] << 16);
+                    csum[1] += __uint_as_float(oa.x[set][q] & 0xffff0000u);
+                }
+            }
+        }
+        oa.store(set, S, tid);
+        ob.store(set, S + A_BYTES, tid);
+    };
+    v8bf fa[4][TM], fb[4];
+    auto read_frags = [&](const unsigned char *S, int step) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
-            fa[slot][i] = *reinterpret_cast<const v8bf *>(&As[(wm * WM + i * 32 + r) * TA::LD + kk * 16 + h * 8]);
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-            fb[slot][j] = *reinterpret_cast<const v8bf *>(&Bs[(wn * WN + j * 32 + r) * TB::LD + kk * 16 + h * 8]);
-    };
-    auto mfma_step = [&](int slot) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[slot][i], fb[slot][j], acc[i][j], 0, 0, 0);
+            fa[step][i] = *reinterpret_cast<const v8bf *>(S + OA::frag(wm * (TILE / 2) + i * 32 + r, 2 * step + h));
+        fb[step] = *reinterpret_cast<const v8bf *>(S + A_BYTES + OB::frag(wn * 32 + r, 2 * step + h));
     };
 
-    load_tile(0);
-    TA::store(smem, ra, tid);
-    TB::store(smem + TA::ELEMS, rb, tid);
-    if (nk > 1) load_tile(1);
-    __syncthreads();
-    read_frags(0, smem, smem + TA::ELEMS, 0);
-
-    for (int kt = 0; kt < nk; ++kt) {
-        const bf16_t *As = smem + (kt & 1) * STAGE;
-        const bf16_t *Bs = As + TA::ELEMS;
-        bf16_t *An = smem + ((kt + 1) & 1) * STAGE;
-        if (kt + 1 < nk) {  // tile kt+1 -> the stage nobody reads during this iteration
-            TA::store(An, ra, tid);
-            TB::store(An + TA::ELEMS, rb, tid);
-        }
-        if (kt + 2 < nk) load_tile(kt + 2);
-#pragma unroll
-        for (int kk = 0; kk + 1 < G; ++kk) {
-            read_frags((kk + 1) & 1, As, Bs, kk + 1);
-            mfma_step(kk & 1);
-        }
-        __syncthreads();  // tile kt fully read by everyone, tile kt+1 fully written
-        if (kt + 1 < nk) read_frags(0, An, An + TA::ELEMS, 0);
-        mfma_step((G - 1) & 1);
+    if (mine > 0) {
+        if (tail && g == 0) load_guarded(0, nk_full * MID_BK);
+        else load_tile(0, 0);
     }
-
-    epilogue_bf16<KIND, TM, TN>(a, acc, __builtin_amdgcn_readfirstlane(m0 + wm * WM),
-                                __builtin_amdgcn_readfirstlane(n0 + wn * WN), r, h);
+    if (mine > 1) {  // then the group has a whole k-tile
+#pragma unroll
+        for (int t = 1; t < MID_SETS; ++t) load_tile(t, t);
+    }
+    if (mine > 0) store_tile(0, stages);
+    if (mine > 1) load_tile(0, MID_SETS);
+    __syncthreads();
+    for (int i = 0; i < rounds;) {
+#pragma unroll
+        for (int c = 0; c < MID_SETS; ++c) {
+            const unsigned char *S = stages + (c & 1) * STAGE;
+            if (i < mine) {
+#pragma unroll
+                for (int step = 0; step < 4; ++step) read_frags(S, step);
+                if (i + 1 < mine) {
+                    store_tile((c + 1) % MID_SETS, stages + ((c + 1) & 1) * STAGE);
+                    load_tile((c + 1) % MID_SETS, i + 1 + MID_SETS);
+                }
+#pragma unroll
+                for (int step = 0; step < 4; ++step)
+#pragma unroll
+                    for (int t = 0; t < TM; ++t)
+                        acc[t][0] =
+                            __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[step][t], fb[step], acc[t][0], 0, 0, 0);
+            }
+            if (++i >= rounds) break;
+            __syncthreads();  // tile i - 1 read and tile i written by everyone
+        }
+    }
+    if (BMAJ && do_bias) {  // uniform per workgroup: 8 KG sums of each column, added in order
+        float *red = reinterpret_cast<float *>(smem);
+        __syncthreads();  // the stages have been read
+        red[(8 * g + (tid >> 5)) * BM + 2 * (tid & 31)] = csum[0];
+        red[(8 * g + (tid >> 5)) * BM + 2 * (tid & 31) + 1] = csum[1];
+        __syncthreads();
+        if (g == 0 && tid < BM && m0 + tid < a.M) {
+            float t = red[tid];
+#pragma unroll
+            for (int q = 1; q < 8 * KG; ++q) t += red[q * BM + tid];
+            if (a.write_grad) a.bias_out[m0 + tid] = t;
+            else a.bias_out[m0 + tid] -= a.lr * t;
+        }
+    }
+    if (KG > 1) {
+        float *red = reinterpret_cast<float *>(smem);
+        __syncthreads();  // the stages (the column sums) have been read
+        if (g > 0) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) red[(((g - 1) * 4 + wave) * 16 + v) * 64 + lane] = acc[0][0][v];
+        }
+        __syncthreads();
+        if (g > 0) return;
+#pragma unroll
+        for (int q = 0; q < KG - 1; ++q)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[0][0][v] += red[((q * 4 + wave) * 16 + v) * 64 + lane];
+    }
+    epilogue_bf16<KIND, TM, 1>(a, acc, m0 + wm * (TILE / 2), n0 + wn * 32, r, h);
 }
 
 // ---- 256 x 256 x 64 kernel with LDS-direct loads ------------------------------------------
@@ -1227,34 +1359,37 @@ __global__ __launch_bounds__(256) void colsum_bias_finalize_kernel(const float *
     }
 }
 
-template <int BM, int BN, int BK>
-hipError_t launch_shape_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, const LaunchEvents &ev)
+template <int TILE, int KG, bool VEC>
+hipError_t launch_mid_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, const LaunchEvents &ev)
 {
-    constexpr size_t LDS = lds_bytes_bf16<BM, BN, BK>();
-    void (*k)(GemmBf16Args) = kind == GEMM_FWD  ? gemm_bf16_nt_kernel<BM, BN, BK, GEMM_FWD>
-                              : kind == GEMM_DA ? gemm_bf16_nt_kernel<BM, BN, BK, GEMM_DA>
-                                                : gemm_bf16_nt_kernel<BM, BN, BK, GEMM_DW>;
-    static std::mutex attr_mu;  // handles on different host threads launch concurrently
-    static bool attr_set[3] = {false, false, false};  // per instantiation (BM, BN, BK) and kind
-    if (LDS > 48 * 1024) {
-        std::lock_guard<std::mutex> lk(attr_mu);
-        if (!attr_set[kind]) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
-            if (e != hipSuccess) return e;
-            attr_set[kind] = true;
-        }
-    }
-    a.tiles_m = (a.M + BM - 1) / BM;
-    a.tiles_n = (a.N + BN - 1) / BN;
+    a.tiles_m = (a.M + TILE - 1) / TILE;
+    a.tiles_n = (a.N + TILE - 1) / TILE;
     const long long tiles = (long long)a.tiles_m * a.tiles_n;
     if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)tiles), block(NT);
-    if (ev.start)
-        hipExtLaunchKernelGGL(k, grid, block, (unsigned)LDS, stream, ev.start, ev.stop, 0, a);
-    else
-        hipLaunchKernelGGL(k, grid, block, LDS, stream, a);
-    return hipGetLastError();
+    const dim3 grid((unsigned)tiles), block((TILE == 64 ? NT : 2 * NT) * KG);
+    if constexpr (VEC && TILE == 64)
+        if (a.bmaj) return launch_kernel(gemm_bf16_mid_kernel<TILE, KG, GEMM_DW, true, true>, grid, block, stream, ev, a);
+    switch (kind) {
+    case GEMM_FWD: return launch_kernel(gemm_bf16_mid_kernel<TILE, KG, GEMM_FWD, VEC, false>, grid, block, stream, ev, a);
+    case GEMM_DA: return launch_kernel(gemm_bf16_mid_kernel<TILE, KG, GEMM_DA, VEC, false>, grid, block, stream, ev, a);
+    case GEMM_DW: return launch_kernel(gemm_bf16_mid_kernel<TILE, KG, GEMM_DW, VEC, false>, grid, block, stream, ev, a);
+    }
+    return hipErrorInvalidValue;
+}
+
+// 128 x 128 tiles where they (nearly) fill the compute units: half the operand bytes per flop
+// (1000 x 4096 x 4096, 256 tiles: 83 -> 55 us; 7001 x 1024 x 1024, 440 tiles: 31.2 -> 29.9).
+// Else 64 x 64, with two groups of wavefronts per tile while the tiles do not fill the compute units twice and there are
+// k-tiles to share (1023 x 1024 x 1024: 12.6 -> 10.1 us, 1024 x 1024 x 2047 as a weight gradient 20.2 ->
+// 17.7 us); with more tiles the compute units are shared by workgroups anyway (7001 x 1024 x 1024:
+// 28.8 us with one group, 35.3 with two).
+hipError_t launch_mid(GemmKind kind, const GemmBf16Args &a, hipStream_t stream, const LaunchEvents &ev)
+{
+    const long long tiles = (long long)((a.M + 63) / 64) * ((a.N + 63) / 64);
+    const long long big = (long long)((a.M + 127) / 128) * ((a.N + 127) / 128);
+    if (!a.bmaj && big >= 200) return launch_mid_bf16<128, 1, true>(kind, a, stream, ev);
+    return (tiles <= 256 && a.K >= 8 * MID_BK) ? launch_mid_bf16<64, 2, true>(kind, a, stream, ev)
+                                               : launch_mid_bf16<64, 1, true>(kind, a, stream, ev);
 }
 
 int env_int_bf16(const char *name, int dflt)
@@ -1307,11 +1442,9 @@ hipError_t launch_gemm_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, c
     if (colsum_slices_out) *colsum_slices_out = 0;
     if (a.M <= 0 || a.N <= 0 || a.K <= 0) return hipErrorInvalidValue;
     // The 256 x 256 LDS-direct kernel when both operands allow it and its tiles cover at least
-    // half of the CUs; else 256 x 128 tiles when they give two workgroups per CU, else 128 x 128.
-    // HB_BF16_TILE = 1 / 2 / 3 / 4 forces a kernel (tuning aid; 4 = 256 x 128, 1 = LDS-direct).
+    // half of the CUs, else 64 x 64 tiles.  HB_BF16_TILE = 1 forces the LDS-direct kernel (tuning aid).
     static const int forced = env_int_bf16("HB_BF16_TILE", 0);
     const long long dma_tiles = (long long)((a.M + DMA_BM - 1) / DMA_BM) * ((a.N + DMA_BN - 1) / DMA_BN);
-    const long long big_tiles = (long long)((a.M + 255) / 256) * ((a.N + 127) / 128);
     // the LDS-direct kernel addresses each operand with 32-bit byte offsets from its base
     // (batch-major operands: rows are batch rows, and only the first k-tile is addressed that way)
     const bool dma_ok = a.a_vec && a.b_vec &&
@@ -1320,7 +1453,11 @@ hipError_t launch_gemm_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, c
                                    a.lda >= a.M && a.ldb >= a.N)
                                 : ((unsigned long long)a.M * (unsigned long long)a.lda * 2 < (1ull << 32) &&
                                    (unsigned long long)a.N * (unsigned long long)a.ldb * 2 < (1ull << 32)));
-    if (a.bmaj) {  // batch-major operands: weight gradient through the LDS-direct kernel only
+    if (a.bmaj == BF16_DW_BMAJ_MID) {
+        if (kind != GEMM_DW || a.k_chunk > 0) return hipErrorInvalidValue;
+        return launch_mid(kind, a, stream, ev);
+    }
+    if (a.bmaj) {  // batch-major operands through the LDS-direct kernel
         if (kind != GEMM_DW || !dma_ok || (a.k_chunk > 0 && (!a.write_grad || a.C_bf16 || a.Ct_bf16 ||
                                                               (a.k_chunk % DMA_BK) != 0)))
             return hipErrorInvalidValue;
@@ -1339,21 +1476,28 @@ hipError_t launch_gemm_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, c
         return launch_dma_bf16(kind, a, stream, ev);
     }
     a.colsum_partial = nullptr;  // the other kernels do not produce them
-    if (forced == 4 || (forced == 0 && big_tiles >= 512)) return launch_shape_bf16<256, 128, 32>(kind, a, stream, ev);
-    if (forced == 3) return launch_shape_bf16<128, 128, 32>(kind, a, stream, ev);
-    return launch_shape_bf16<128, 128, 64>(kind, a, stream, ev);
+    const bool vec = ((a.lda | a.ldb) & 1) == 0 &&
+                     ((reinterpret_cast<size_t>(a.A) | reinterpret_cast<size_t>(a.B)) & 3) == 0 &&
+                     a.lda < (1ll << 25) && a.ldb < (1ll << 25);  // 32-bit byte offsets over 32 rows
+    return vec ? launch_mid(kind, a, stream, ev) : launch_mid_bf16<64, 1, false>(kind, a, stream, ev);
 }
 
-bool gemm_bf16_dw_bmaj_ok(int M, int N, int K, long long lda, long long ldb, const void *A, const void *B)
+int gemm_bf16_dw_form(int M, int N, int K, long long lda, long long ldb, const void *A, const void *B)
 {
-    // what launch_gemm_bf16 asks of batch-major operands, and a product the LDS-direct kernel
-    // is chosen for anyway (split over the batch, or at least 128 tiles)
-    if ((lda & 7) || (ldb & 7) || ((reinterpret_cast<size_t>(A) | reinterpret_cast<size_t>(B)) & 15) || lda < M ||
-        ldb < N || (unsigned long long)DMA_BK * (unsigned long long)lda * 2 >= (1ull << 32) ||
-        (unsigned long long)DMA_BK * (unsigned long long)ldb * 2 >= (1ull << 32))
-        return false;
+    const size_t base = reinterpret_cast<size_t>(A) | reinterpret_cast<size_t>(B);
+    // 32-bit byte offsets over the k-rows of a tile, and whole column pairs in every row
+    if (((lda | ldb) & 1) || (base & 3) || lda < M + (M & 1) || ldb < N + (N & 1) || lda >= (1ll << 24) ||
+        ldb >= (1ll << 24))
+        return BF16_DW_KMAJ;
+    // the LDS-direct kernel: 16-byte rows, and a product it is chosen for (split over the batch,
+    // or at least 128 tiles)
     const long long tiles = (long long)((M + DMA_BM - 1) / DMA_BM) * ((N + DMA_BN - 1) / DMA_BN);
-    return tiles >= 128 || gemm_bf16_dw_splits_cap(M, N, K) > 1;
+    static const int forced = env_int_bf16("HB_BF16_TILE", 0);
+    if (tiles >= 128 || forced == 1 || gemm_bf16_dw_splits_cap(M, N, K) > 1)
+        return ((lda | ldb) & 7) || (base & 15) || (forced == 1 && tiles < 128 && gemm_bf16_dw_splits_cap(M, N, K) < 2)
+                   ? BF16_DW_KMAJ
+                   : BF16_DW_BMAJ;
+    return BF16_DW_BMAJ_MID;
 }
 
 int gemm_bf16_dw_splits_cap(int M, int N, int K)
@@ -1363,7 +1507,10 @@ int gemm_bf16_dw_splits_cap(int M, int N, int K)
     long long s = 256 / tiles;  // fill the chip once
     if (s > 8) s = 8;
     if (s > K / 1024) s = K / 1024;  // at least 16 k-tiles per slice
-    return s < 2 ? 1 : (int)s;
+    // With fewer workgroups than half of the compute units, the kernel of small tiles is faster on
+    // the whole contraction until it gets long: 1024 x 1024 x 2048 19 us against 31 + 11 us (2 x 16
+    // workgroups, then the passes over their sums), 1024 x 1024 x 7001 47 us against 35 + 11 us.
+    return (s < 2 || (tiles * s < 128 && K < 6000)) ? 1 : (int)s;
 }
 
 int gemm_bf16_dw_splits(int M, int N, int K, long long lda, long long ldb)

@@ -611,16 +611,16 @@ int run_step_bf16(hb_model *m, const void *X, const int32_t *y, int64_t B, float
     hipStream_t st = m->stream;
     const bool back = (mode != MODE_LOSS);
 
-    // bmaj[l]: the weight gradient of layer l reads the row-major D_l and A_{l-1} themselves
-    // (batch-major operands); then neither D_l^T nor A_{l-1}^T is needed for it.  Transposed
+    // bmaj[l] (BF16_DW_*): the weight gradient of layer l reads the row-major D_l and A_{l-1}
+    // themselves (batch-major operands); then neither D_l^T nor A_{l-1}^T is needed for it.  Transposed
     // activations are still written for a sigmoid layer, whose backward-data epilogue reads them.
     std::vector<char> bmaj((size_t)L + 2, 0);
     static const bool bmaj_off = getenv("HB_BF16_BMAJ") && atoi(getenv("HB_BF16_BMAJ")) == 0;  // tuning aid
     if (back && !bmaj_off)
         for (int l = 1; l <= L; ++l)
-            bmaj[l] = gemm_bf16_dw_bmaj_ok(m->dims[l], m->dims[l - 1], Bi, m->ld8[l],
-                                           (l == 1) ? (long long)m->dims[0] : (long long)m->ld8[l - 1],
-                                           m->delta_bf[l & 1], (l == 1) ? X : m->act_bf[l - 1]);
+            bmaj[l] = (char)gemm_bf16_dw_form(m->dims[l], m->dims[l - 1], Bi, m->ld8[l],
+                                              (l == 1) ? (long long)m->dims[0] : (long long)m->ld8[l - 1],
+                                              m->delta_bf[l & 1], (l == 1) ? X : m->act_bf[l - 1]);
     if (back && !bmaj[1])  // X^T for dW_1 = D_1^T X
         HB_HIP(launch_transpose_bf16(X, m->dims[0], m->act_t[0], ldB, Bi, m->dims[0], st,
                                      prof_begin(m, HB_K_OTHER, 1, 0, 0, 0, 0.0, 4.0 * B * m->dims[0])));
@@ -719,7 +719,9 @@ int run_step_bf16(hb_model *m, const void *X, const int32_t *y, int64_t B, float
         }
         GemmBf16Args g = {};
         if (bmaj[l]) {
-            g.bmaj = 1;
+            g.bmaj = bmaj[l];
+            if (bmaj[l] == BF16_DW_BMAJ_MID)
+                g.bias_out = grad_mode ? d_grad_flat + m->b_off[l] : m->d_params + m->b_off[l];
             g.A = m->delta_bf[l & 1];
             g.lda = m->ld8[l];
             g.B = (l == 1) ? X : m->act_bf[l - 1];
@@ -748,7 +750,7 @@ int run_step_bf16(hb_model *m, const void *X, const int32_t *y, int64_t B, float
             g.Ct_bf16 = m->shadow_t[l];
             g.ldct = m->ld8[l];
         }
-        int sp = m->dw_partial ? (g.bmaj ? gemm_bf16_dw_splits_cap(g.M, g.N, g.K)
+        int sp = (m->dw_partial && bmaj[l] != BF16_DW_BMAJ_MID) ? (g.bmaj ? gemm_bf16_dw_splits_cap(g.M, g.N, g.K)
                                          : gemm_bf16_dw_splits(g.M, g.N, g.K, g.lda, g.ldb))
                                : 1;
         // never more slices than the buffer allocated at configure time holds
@@ -782,6 +784,7 @@ int run_step_bf16(hb_model *m, const void *X, const int32_t *y, int64_t B, float
                                                2.0 * ((double)g.M * g.K + (double)g.N * g.K) +
                                                    (grad_mode ? 4.0 : 12.0) * g.M * g.N)));
         }
+        if (bmaj[l] == BF16_DW_BMAJ_MID) continue;  // the bias gradient came with the weight gradient
         if (colsum_slices[l] > 0)  // the backward-data epilogue that wrote D_l left its column sums
             HB_HIP(launch_colsum_bias_finalize(m->bias_partial[l & 1], colsum_slices[l], m->dims[l],
                                                m->d_params + m->b_off[l],

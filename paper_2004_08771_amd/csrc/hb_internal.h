@@ -120,8 +120,9 @@ struct GemmBf16Args {
     int write_grad;
     float lr;
     // weight gradient with batch-major operands: A[k * lda + m], B[k * ldb + n] (the row-major
-    // deltas and activations themselves; LDS-direct kernel only, see gemm_bf16_dw_bmaj_ok)
+    // deltas and activations themselves): BF16_DW_*, see gemm_bf16_dw_form
     int bmaj;
+    float *bias_out;       // BF16_DW_BMAJ_MID: the bias (updated), or its gradient (write_grad), of length M
     int tiles_m, tiles_n;
     // weight gradient split over the contraction (the batch): slice s covers k in
     // [s k_chunk, (s+1) k_chunk) and writes its plain fp32 partial product at
@@ -136,8 +137,10 @@ hipError_t launch_gemm_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream,
 // gemm_bf16_dw_splits returns for any K <= max_K and any leading dimensions (it is
 // non-decreasing in K): the figure to size the slice buffer with.
 int gemm_bf16_dw_splits(int M, int N, int K, long long lda, long long ldb);
-// The weight gradient M x N over K batch rows can take its operands batch-major (bmaj).
-bool gemm_bf16_dw_bmaj_ok(int M, int N, int K, long long lda, long long ldb, const void *A, const void *B);
+// How the weight gradient M x N over K batch rows takes its operands (GemmBf16Args::bmaj): transposed
+// copies, or batch-major through the LDS-direct kernel or the kernel of 64 x 64 tiles.
+enum { BF16_DW_KMAJ = 0, BF16_DW_BMAJ = 1, BF16_DW_BMAJ_MID = 2 };
+int gemm_bf16_dw_form(int M, int N, int K, long long lda, long long ldb, const void *A, const void *B);
 int gemm_bf16_dw_splits_cap(int M, int N, int K);
 // out[i] = sum_s partial[s * stride + i]  (grad != null: written there)  or  master[i] -= lr * sum
 hipError_t launch_dw_reduce(const float *partial, int splits, long long stride, long long count, float *master,

@@ -1128,3 +1128,17 @@ def test_split_plane_products_of_values_without_finite_planes():
         ref = oracle.batch_loss(dims, hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, params, X.astype(np.float64), y)
     assert np.isfinite(ref) and abs(got - ref) <= TOL_F32 * abs(ref)
     assert set(np.unique(acts[1][3])) <= {0.0, 1.0} and set(np.unique(acts[1][1300])) <= {0.0, 1.0}
+
+
+# ---------------------------------------------------------------- bf16 products of small tiles
+@pytest.mark.parametrize("dims,act,B", [
+    ((66, 65, 130, 3), hi.ACT_SIGMOID, 63),      # one partial k-tile over the batch, column pairs cut in the middle
+    ((65, 70, 5), hi.ACT_SIGMOID, 130),          # odd rows of X: element loads, transposed copies for dW_1
+    ((66, 129, 65, 2), hi.ACT_RELU, 577),        # contraction over the batch shared by two groups: 9 k-tiles and one row
+    ((514, 575, 33), hi.ACT_SIGMOID, 200),       # the same forward (575) and backward-data
+    ((300, 1030, 2), hi.ACT_RELU, 1025),         # one wavefront group each (more than 256 tiles)
+    ((70, 2100, 2060, 9), hi.ACT_RELU, 1600),    # 13 x 17 tiles of 128 x 128, cut in both directions
+])
+def test_bf16_small_tile_products_at_tile_edges(dims, act, B):
+    params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=300 + B, bias_scale=0.1)
+    check_bf16_case(dims, act, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=False)

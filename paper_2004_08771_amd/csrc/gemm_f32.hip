@@ -368,7 +368,9 @@ int env_int(const char *name, int dflt)
 struct Shape {
     int bm, bn;
 };
-constexpr Shape SHAPES[] = {{64, 64}, {128, 64}, {128, 128}};  // by the number launch_gemm_split takes
+constexpr Shape SHAPES[] = {{64, 64}, {128, 64}, {128, 128}, {64, 64}};  // by the number launch_gemm_split takes
+constexpr int SHARED = 3;  // 64 x 64, the contraction shared by two groups of wavefronts ...
+constexpr int SHARED_K = 256;  // ... of at least this length (32-deep: 4.6 us alone, 4.8 shared)
 constexpr int CUS = 256;
 constexpr int K_CHUNK_ALIGN = 32;  // slices of a split contraction are multiples of the k-tile
 
@@ -378,21 +380,23 @@ long long tiles_of(int sh, int M, int N)
 }
 
 // Clocks per k-tile of a workgroup, in hundreds, from time stamps around the main loop (MI355X,
-// K = 512): 64 x 64 9 alone on its compute unit and 15 for two that share one, 128 x 64 12.5,
+// K = 512): 64 x 64 9 alone on its compute unit (6 with two groups of wavefronts, which fill its LDS)
+// and 15 for two that share one, 128 x 64 12.5,
 // 128 x 128 20 (one per compute unit).  The shape with the shortest sequence of rounds wins:
 // 4096 x 512 outputs 14.6 us as 128 x 64 (256 workgroups), 16.8 as 64 x 64, 20 as 128 x 128;
-// 8192 x 512 27 / 31 / 25.8; 2048 x 512 12.0 / 11.2 / 19.
+// 8192 x 512 27 / 31 / 25.8; 2048 x 512 12.0 / 11.2 / 19, with two groups 10.6 (12.7 without, in a step).
 double rounds_cost(int sh, long long blocks)
 {
     const long long r = (blocks + CUS - 1) / CUS;
     if (sh == 2) return 20.0 * r;
     if (sh == 1) return 12.5 * r;
+    if (sh == SHARED) return 6.0 * r;
     return blocks <= CUS ? 9.0 : 15.0 * ((r + 1) / 2);
 }
-int pick_shape(int M, int N)
+int pick_shape(int M, int N, int K)
 {
     int best = 0;
-    for (int sh = 1; sh < 3; ++sh)
+    for (int sh = 1; sh < (K >= SHARED_K ? 4 : 3); ++sh)
         if (rounds_cost(sh, tiles_of(sh, M, N)) <= rounds_cost(best, tiles_of(best, M, N))) best = sh;
     return best;
 }
@@ -434,10 +438,6 @@ int small_k_max()
 bool small_out(int M, int N, int K)
 {
     return K >= 64 && (long long)((M + 63) / 64) * ((N + 63) / 64) < small_tiles_max();
-}
-bool small_dw(int K)
-{
-    return K >= 64 && K < small_k_max();
 }
 // A weight gradient launched on its own (not paired with a backward-data product) whose output
 // is only a few tiles -- the first layer of a narrow input, 512 x 54 -- stays with the small
@@ -504,11 +504,12 @@ hipError_t launch_gemm_f32(GemmKind kind, GemmArgs a, int max_splits, int *split
         }
         return hipErrorInvalidValue;
     }
-    int sh = pick_shape(a.M, a.N);
+    int sh = pick_shape(a.M, a.N, a.K);
     SplitPlan sp = {1, (a.K + K_CHUNK_ALIGN - 1) / K_CHUNK_ALIGN * K_CHUNK_ALIGN};
     if (kind == GEMM_DW) {
         sh = (a.M >= 128) ? (a.N >= 128 ? 2 : 1) : 0;
         sp = plan_splits(tiles_of(sh, a.M, a.N), a.K, max_splits, CUS);
+        if (sh == 0 && sp.chunk >= SHARED_K && tiles_of(sh, a.M, a.N) * sp.splits <= CUS) sh = SHARED;
     }
     a.tiles_m = (a.M + SHAPES[sh].bm - 1) / SHAPES[sh].bm;
     a.tiles_n = (a.N + SHAPES[sh].bn - 1) / SHAPES[sh].bn;
@@ -522,18 +523,20 @@ hipError_t launch_gemm_f32(GemmKind kind, GemmArgs a, int max_splits, int *split
 
 // dA_l and dW_l of one hidden layer in one launch: both only read D_l, so they are independent, and
 // sharing a launch lets the prologue / epilogue of one hide under the main loop of the other and pays
-// the per-launch latencies once.  Only for shapes the tiles suit; the caller makes two launches
-// when gemm_f32_pair_ok returns false.
-bool gemm_f32_pair_ok(const GemmArgs &da, const GemmArgs &dw)
+// the per-launch latencies once (B = 16, 512-wide layers: 9.7 + 7.8 -> 8.7 us; B = 128, 32-wide:
+// 4.8 + 4.5 -> 7.4).  HB_NO_PAIR = 1 (tuning aid): two launches.
+bool gemm_f32_pair_ok()
 {
     static const int off = env_int("HB_NO_PAIR", 0);
-    return !off && da.M >= 64 && da.N >= 64 && da.K >= 32 && dw.M >= 128 && dw.N >= 64 && dw.K >= 32;
+    return !off;
 }
 
 hipError_t launch_gemm_f32_bwd_pair(GemmArgs da, GemmArgs dw, int max_splits, int *splits_out,
                                     hipStream_t stream, const LaunchEvents &ev)
 {
-    if (small_out(da.M, da.N, da.K) && small_dw(dw.K)) {
+    // Against the tiles below, 512-wide layers: B = 256 (32 tiles of 64 x 64) 9.7 us, B = 640 (80 tiles)
+    // 14.4 / 11.5 us, B = 1021 17.7 / 12.0 us.
+    if (da.K >= 64 && tiles_of(0, da.M, da.N) < 64 && dw.K < small_k_max()) {
         da.tiles_m = (da.M + 31) / 32;
         da.tiles_n = (da.N + 31) / 32;
         da.splits = 1;
@@ -563,6 +566,9 @@ hipError_t launch_gemm_f32_bwd_pair(GemmArgs da, GemmArgs dw, int max_splits, in
         sp = plan_splits(t, dw.K, max_splits, n < CUS ? n : CUS);
         if (sh == 0 || n + t * sp.splits >= CUS - CUS / 8) break;
     }
+    if (sh == 0 && (da.K >= SHARED_K || sp.chunk >= SHARED_K) &&
+        tiles_of(0, da.M, da.N) + tiles_of(0, dw.M, dw.N) * sp.splits <= CUS)
+        sh = SHARED;
     for (GemmArgs *g : {&da, &dw}) {
         g->tiles_m = (g->M + SHAPES[sh].bm - 1) / SHAPES[sh].bm;
         g->tiles_n = (g->N + SHAPES[sh].bn - 1) / SHAPES[sh].bn;

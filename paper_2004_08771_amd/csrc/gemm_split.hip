@@ -211,7 +211,9 @@ constexpr int lds_bytes()
 }
 
 // One output tile (index id in n-fastest order) of one K-slice (split) of C = A . B^T.
-template <int NT, int BM, int BN, int WAVES_M, bool A_KMAJ, bool B_KMAJ, int KIND>
+// KG: groups of NT threads that share the contraction (group g takes the k-tiles g, g + KG, .. from LDS
+// stages of its own); their sums meet in LDS, in group order, and group 0 finishes the tile.
+template <int NT, int KG, int BM, int BN, int WAVES_M, bool A_KMAJ, bool B_KMAJ, int KIND>
 __device__ __forceinline__ void split_tile(const GemmArgs &a, char *smem, int id, int split)
 {
     constexpr int WAVES_N = NT / 64 / WAVES_M;
@@ -221,16 +223,19 @@ __device__ __forceinline__ void split_tile(const GemmArgs &a, char *smem, int id
     using OB = Op<NT, BN, B_KMAJ>;
     constexpr int STAGE = OA::BYTES + OB::BYTES;
 
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tid = threadIdx.x % NT;
+    const int lane = tid & 63, wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int g = wave_all / (NT / 64), wave = wave_all % (NT / 64);
     const int r = lane & 31, h = lane >> 5;
     const int wm = wave % WAVES_M, wn = wave / WAVES_M;
+    char *const smem_all = smem;
+    smem += g * 2 * STAGE;
 
     const int tile_m = id / a.tiles_n, tile_n = id - tile_m * a.tiles_n;
     const int m0 = tile_m * BM, n0 = tile_n * BN;
     const int kbeg = split * a.k_chunk;
     const int kend = min(a.K, kbeg + a.k_chunk);
-    const int nk = (kend - kbeg + BK - 1) / BK;
+    const int nk_all = (kend - kbeg + BK - 1) / BK;
 
     const float *__restrict__ A = static_cast<const float *>(a.A);
     const float *__restrict__ Bm = static_cast<const float *>(a.B);
@@ -302,7 +307,8 @@ __device__ __forceinline__ void split_tile(const GemmArgs &a, char *smem, int id
         }
     };
     // A partial last k-tile goes first (tile 0 of the loop below); all others are whole.
-    const int nk_full = (kend - kbeg) / BK, tail = nk - nk_full;
+    const int nk_full = (kend - kbeg) / BK, tail = nk_all - nk_full;
+    const int rounds = (nk_all + KG - 1) / KG, nk = (nk_all - g + KG - 1) / KG;  // k-tiles of group 0, of this group
     auto main_loop = [&](auto a_vec, auto b_vec) {
         constexpr bool AV = decltype(a_vec)::value != 0, BV = decltype(b_vec)::value != 0;
         const int a_last = a.M - 1 - m0, b_last = a.N - 1 - n0;
@@ -313,7 +319,7 @@ __device__ __forceinline__ void split_tile(const GemmArgs &a, char *smem, int id
         const size_t a_step = A_KMAJ ? (size_t)BK : (size_t)BK * a.lda, b_step = B_KMAJ ? (size_t)BK : (size_t)BK * a.ldb;
         constexpr int LOADS = OA::LOADS + OB::LOADS;
         auto load_piece = [&](int set, int t, int v) {  // past the end: the last tile again (not used)
-            const int f = max(min(t, nk - 1) - tail, 0);
+            const int f = max(g + min(t, nk - 1) * KG - tail, 0);
             if (v < OA::LOADS) oa.template load<AV>(set, v, At + f * a_step, a.lda, a_last);
             else ob.template load<BV>(set, v - OA::LOADS, Bt + f * b_step, a.ldb, b_last);
         };
@@ -321,7 +327,7 @@ __device__ __forceinline__ void split_tile(const GemmArgs &a, char *smem, int id
 #pragma unroll
             for (int v = 0; v < LOADS; ++v) load_piece(set, t, v);
         };
-        if (tail) {
+        if (tail && g == 0) {
             oa.load_tail(0, A, a.lda, m0, a.M, kbeg + nk_full * BK, kend, tid);
             ob.load_tail(0, Bm, a.ldb, n0, a.N, kbeg + nk_full * BK, kend, tid);
         } else {
@@ -396,33 +402,53 @@ __device__ __forceinline__ void split_tile(const GemmArgs &a, char *smem, int id
         if ((A_KMAJ || a_in) && (B_KMAJ || b_in)) main_loop(IntC<1>(), IntC<1>());
         else main_loop(IntC<A_KMAJ>(), IntC<B_KMAJ>());
     }
+    // a group with one k-tile less has passed one barrier less
+    if (KG > 1 && nk < rounds) __syncthreads();
 
     if (KIND == GEMM_DW) {
         if (do_colsum) {  // uniform per workgroup
             __syncthreads();  // the last tile's fragments have been read
-            float *red = reinterpret_cast<float *>(smem);
+            float *red = reinterpret_cast<float *>(smem_all);
 #pragma unroll
-            for (int e = 0; e < OA::MV; ++e) red[(tid / OA::R1) * BM + (tid % OA::R1) * OA::MV + e] = csum[e];
+            for (int e = 0; e < OA::MV; ++e) red[(8 * g + tid / OA::R1) * BM + (tid % OA::R1) * OA::MV + e] = csum[e];
             __syncthreads();
-            if (tid < BM && m0 + tid < a.M) {
+            if (g == 0 && tid < BM && m0 + tid < a.M) {
                 float s = red[tid];
 #pragma unroll
-                for (int q = 1; q < 8; ++q) s += red[q * BM + tid];
+                for (int q = 1; q < 8 * KG; ++q) s += red[q * BM + tid];
                 a.colsum[(size_t)split * a.M + m0 + tid] = s;
             }
         }
     }
 
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) hi[i][j][v] += lo[i][j][v];
+    if constexpr (KG > 1) {
+        static_assert(TM == 1 && TN == 1, "one block per wavefront");
+        float *red = reinterpret_cast<float *>(smem_all);
+        __syncthreads();  // the stages (the column sums) have been read
+        if (g > 0) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) red[(((g - 1) * (NT / 64) + wave) * 16 + v) * 64 + lane] = hi[0][0][v];
+        }
+        __syncthreads();
+        if (g > 0) return;
+#pragma unroll
+        for (int q = 0; q < KG - 1; ++q)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) hi[0][0][v] += red[((q * (NT / 64) + wave) * 16 + v) * 64 + lane];
+    }
     float bad = 0.f;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                hi[i][j][v] += lo[i][j][v];
-                bad = fmaf(hi[i][j][v], 0.f, bad);
-            }
+            for (int v = 0; v < 16; ++v) bad = fmaf(hi[i][j][v], 0.f, bad);
     if (__any(bad != 0.f)) {  // NaN: some result of this wavefront is not finite
         for (int i = 0; i < TM; ++i)
             for (int j = 0; j < TN; ++j) {
@@ -502,18 +528,18 @@ __device__ __forceinline__ void split_tile(const GemmArgs &a, char *smem, int id
     with_activation(KIND == GEMM_DW ? (int)ACT_NONE : a.act, epilogue);
 }
 
-template <int NT, int BM, int BN, int WM, int WGS, bool A_KMAJ, bool B_KMAJ, int KIND>
-__global__ __launch_bounds__(NT, WGS) void gemm_split_kernel(GemmArgs a)
+template <int NT, int KG, int BM, int BN, int WM, int WGS, bool A_KMAJ, bool B_KMAJ, int KIND>
+__global__ __launch_bounds__(NT *KG, WGS) void gemm_split_kernel(GemmArgs a)
 {
-    __shared__ __attribute__((aligned(16))) char smem[lds_bytes<BM, BN>()];
-    split_tile<NT, BM, BN, WM, A_KMAJ, B_KMAJ, KIND>(a, smem, xcd_tile_order(blockIdx.x, gridDim.x), blockIdx.y);
+    __shared__ __attribute__((aligned(16))) char smem[KG * lds_bytes<BM, BN>()];
+    split_tile<NT, KG, BM, BN, WM, A_KMAJ, B_KMAJ, KIND>(a, smem, xcd_tile_order(blockIdx.x, gridDim.x), blockIdx.y);
 }
 
 // Backward of one hidden layer in one launch (see launch_gemm_f32_bwd_pair).
-template <int NT, int BM, int BN, int WM, int WGS>
-__global__ __launch_bounds__(NT, WGS) void gemm_split_pair_kernel(GemmArgs da, GemmArgs dw, int n_dw)
+template <int NT, int KG, int BM, int BN, int WM, int WGS>
+__global__ __launch_bounds__(NT *KG, WGS) void gemm_split_pair_kernel(GemmArgs da, GemmArgs dw, int n_dw)
 {
-    __shared__ __attribute__((aligned(16))) char smem[lds_bytes<BM, BN>()];
+    __shared__ __attribute__((aligned(16))) char smem[KG * lds_bytes<BM, BN>()];
     const int b = blockIdx.x;
     if (b < n_dw) {
         const int tiles = dw.tiles_m * dw.tiles_n;
@@ -522,39 +548,40 @@ __global__ __launch_bounds__(NT, WGS) void gemm_split_pair_kernel(GemmArgs da, G
             // batch is given to XCD s % 8, all of its output tiles, so that the XCD reads only its slices'
             // rows of D_l and A_{l-1}, once; the backward-data blocks below give it the same rows.
             const int q = b >> 3;
-            split_tile<NT, BM, BN, WM, false, false, GEMM_DW>(dw, smem, q % tiles, (b & 7) + 8 * (q / tiles));
+            split_tile<NT, KG, BM, BN, WM, false, false, GEMM_DW>(dw, smem, q % tiles, (b & 7) + 8 * (q / tiles));
         } else {
-            split_tile<NT, BM, BN, WM, false, false, GEMM_DW>(dw, smem, xcd_tile_order(b % tiles, tiles), b / tiles);
+            split_tile<NT, KG, BM, BN, WM, false, false, GEMM_DW>(dw, smem, xcd_tile_order(b % tiles, tiles), b / tiles);
         }
     } else {
-        split_tile<NT, BM, BN, WM, true, false, GEMM_DA>(da, smem, xcd_tile_order(b - n_dw, (int)gridDim.x - n_dw), 0);
+        split_tile<NT, KG, BM, BN, WM, true, false, GEMM_DA>(da, smem, xcd_tile_order(b - n_dw, (int)gridDim.x - n_dw), 0);
     }
 }
 
-template <int NT, int BM, int BN, int WM, int WGS>
+template <int NT, int KG, int BM, int BN, int WM, int WGS>
 hipError_t launch_kind(GemmKind kind, const GemmArgs &a, dim3 grid, hipStream_t stream, const LaunchEvents &ev)
 {
     switch (kind) {
     case GEMM_FWD:
-        return launch_kernel(gemm_split_kernel<NT, BM, BN, WM, WGS, true, true, GEMM_FWD>, grid, dim3(NT), stream, ev, a);
+        return launch_kernel(gemm_split_kernel<NT, KG, BM, BN, WM, WGS, true, true, GEMM_FWD>, grid, dim3(NT *KG), stream, ev, a);
     case GEMM_DA:
-        return launch_kernel(gemm_split_kernel<NT, BM, BN, WM, WGS, true, false, GEMM_DA>, grid, dim3(NT), stream, ev, a);
+        return launch_kernel(gemm_split_kernel<NT, KG, BM, BN, WM, WGS, true, false, GEMM_DA>, grid, dim3(NT *KG), stream, ev, a);
     case GEMM_DW:
-        return launch_kernel(gemm_split_kernel<NT, BM, BN, WM, WGS, false, false, GEMM_DW>, grid, dim3(NT), stream, ev, a);
+        return launch_kernel(gemm_split_kernel<NT, KG, BM, BN, WM, WGS, false, false, GEMM_DW>, grid, dim3(NT *KG), stream, ev, a);
     }
     return hipErrorInvalidValue;
 }
 
 }  // namespace
 
-// shape: 0 64 x 64, 1 128 x 64, 2 128 x 128
+// shape: 0 64 x 64, 1 128 x 64, 2 128 x 128, 3 64 x 64 with two groups
 hipError_t launch_gemm_split(GemmKind kind, const GemmArgs &a, int shape, dim3 grid, hipStream_t stream,
                              const LaunchEvents &ev)
 {
     switch (shape) {
-    case 0: return launch_kind<256, 64, 64, 2, 2>(kind, a, grid, stream, ev);
-    case 1: return launch_kind<512, 128, 64, 4, 1>(kind, a, grid, stream, ev);
-    default: return launch_kind<512, 128, 128, 2, 1>(kind, a, grid, stream, ev);
+    case 0: return launch_kind<256, 1, 64, 64, 2, 2>(kind, a, grid, stream, ev);
+    case 1: return launch_kind<512, 1, 128, 64, 4, 1>(kind, a, grid, stream, ev);
+    case 2: return launch_kind<512, 1, 128, 128, 2, 1>(kind, a, grid, stream, ev);
+    default: return launch_kind<256, 2, 64, 64, 2, 1>(kind, a, grid, stream, ev);
     }
 }
 
@@ -562,9 +589,10 @@ hipError_t launch_gemm_split_pair(const GemmArgs &da, const GemmArgs &dw, int sh
                                   hipStream_t stream, const LaunchEvents &ev)
 {
     switch (shape) {
-    case 0: return launch_kernel(gemm_split_pair_kernel<256, 64, 64, 2, 2>, dim3(blocks), dim3(256), stream, ev, da, dw, n_dw);
-    case 1: return launch_kernel(gemm_split_pair_kernel<512, 128, 64, 4, 1>, dim3(blocks), dim3(512), stream, ev, da, dw, n_dw);
-    default: return launch_kernel(gemm_split_pair_kernel<512, 128, 128, 2, 1>, dim3(blocks), dim3(512), stream, ev, da, dw, n_dw);
+    case 0: return launch_kernel(gemm_split_pair_kernel<256, 1, 64, 64, 2, 2>, dim3(blocks), dim3(256), stream, ev, da, dw, n_dw);
+    case 1: return launch_kernel(gemm_split_pair_kernel<512, 1, 128, 64, 4, 1>, dim3(blocks), dim3(512), stream, ev, da, dw, n_dw);
+    case 3: return launch_kernel(gemm_split_pair_kernel<256, 2, 64, 64, 2, 1>, dim3(blocks), dim3(512), stream, ev, da, dw, n_dw);
+    default: return launch_kernel(gemm_split_pair_kernel<512, 1, 128, 128, 2, 1>, dim3(blocks), dim3(512), stream, ev, da, dw, n_dw);
     }
 }
 

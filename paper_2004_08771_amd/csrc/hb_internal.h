@@ -61,9 +61,8 @@ hipError_t launch_gemm_f32(GemmKind kind, GemmArgs a, int max_splits, int *split
                            hipStream_t stream, const LaunchEvents &ev = LaunchEvents());
 
 // The backward-data and the weight-gradient product of one hidden layer in a single launch
-// (both read the same D_l and are independent).  gemm_f32_pair_ok: the shapes suit the fixed
-// tile shapes of that kernel; otherwise launch the two products separately.
-bool gemm_f32_pair_ok(const GemmArgs &da, const GemmArgs &dw);
+// (both read the same D_l and are independent), unless gemm_f32_pair_ok says to launch them apart.
+bool gemm_f32_pair_ok();
 hipError_t launch_gemm_f32_bwd_pair(GemmArgs da, GemmArgs dw, int max_splits, int *splits_out,
                                     hipStream_t stream, const LaunchEvents &ev = LaunchEvents());
 

@@ -1105,6 +1105,8 @@ def test_step_can_be_captured_in_a_graph_and_replays_like_eager_steps(bf16):
     ((100, 130, 65, 20), hi.ACT_SIGMOID, 2561),    # 64 x 64 tiles, both operands cut, rows not 16-byte aligned
     ((97, 257, 129, 33), hi.ACT_RELU, 4099),       # 128 x 64
     ((129, 520, 514, 40), hi.ACT_SIGMOID, 8200),   # 128 x 128, two values short of a 16-byte row
+    ((265, 258, 257, 40), hi.ACT_SIGMOID, 1030),   # 64 x 64 by two groups: nine k-tiles, the partial one first
+    ((300, 290, 270, 12), hi.ACT_RELU, 2100),      # ten k-tiles, rows and columns cut
 ])
 def test_split_plane_products_at_tile_edges(dims, act, B):
     """Each tile shape of the large fp32 products with rows, columns and k-tiles cut by the end of

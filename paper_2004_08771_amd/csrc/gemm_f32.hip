@@ -421,6 +421,73 @@ SplitPlan plan_splits(long long tiles, int K, int max_splits, long long wgs)
     return slices(K, (int)s);
 }
 
+// Shape and batch slices of a paired backward launch: the pair with the shortest estimated time, from
+// the workgroups' lengths (clocks per k-tile as above, plus 60 hundred for prologue and epilogue)
+// dealt out as the hardware does, weight-gradient workgroups first, and the slices' partial sums
+// written and read again at 3 TB/s.  Against one workgroup of the weight gradient per workgroup of
+// the backward-data product in the largest shape that fills the device: 3001 x 1024 x 1024 84.4 ->
+// 74.2 us, 3001 x 512 x 512 31.1 -> 24.5, 1500 x 512 x 512 20.3 -> 16.0, 4096 x 512 x 512 26.8 -> 26.2 (the
+// same plan; a contiguous eighth of the pieces per XCD).
+struct PairPlan {
+    int shape;
+    SplitPlan split;
+};
+// end of n1 pieces of length a followed by n2 of length b on `slots` servers, each piece on the first free one
+double makespan(long long n1, double a, long long n2, double b, long long slots)
+{
+    const long long q = n1 / slots, rem = n1 % slots;
+    double t0 = q * a, t1 = t0 + a;           // slots - rem servers are free at t0, rem at t1
+    long long c0 = slots - rem, c1 = rem;
+    const long long rounds = n2 / slots;      // whole rounds shift both groups alike
+    if (rounds > 0) {
+        t0 += rounds * b;
+        t1 += rounds * b;
+        n2 -= rounds * slots;
+    }
+    double end = rem ? t1 : t0;
+    while (n2 > 0) {
+        if (c1 > 0 && t1 < t0) {
+            const double t = t0;
+            const long long c = c0;
+            t0 = t1; c0 = c1; t1 = t; c1 = c;
+        }
+        const long long k = n2 < c0 ? n2 : c0;
+        if (t0 + b > end) end = t0 + b;
+        t0 += b;
+        n2 -= k;
+    }
+    return end;
+}
+PairPlan plan_pair(const GemmArgs &da, const GemmArgs &dw, int max_splits)
+{
+    // with the whole chip busy (its clock is lower then); the weight gradient's M-major tiles cost more
+    constexpr double DA_K[4] = {15.0, 13.0, 20.0, 7.5}, DW_K[4] = {16.0, 15.0, 21.0, 8.0};
+    constexpr int SLOTS[4] = {2 * CUS, CUS, CUS, CUS};
+    const int by_k = (dw.K + 4 * K_CHUNK_ALIGN - 1) / (4 * K_CHUNK_ALIGN);  // slices of at least 128
+    int most = max_splits < by_k ? max_splits : by_k;
+    if (most > 16) most = 16;
+    if (most < 1) most = 1;
+    PairPlan best = {0, slices(dw.K, 1)};
+    double best_t = -1.0;
+    for (int sh = 0; sh < 4; ++sh) {
+        if (sh == SHARED && da.K < SHARED_K && dw.K < SHARED_K) continue;
+        const long long n = tiles_of(sh, da.M, da.N), t = tiles_of(sh, dw.M, dw.N);
+        const double len_da = 60.0 + DA_K[sh] * ((da.K + 31) / 32);
+        for (int s = 1; s <= most; ++s) {
+            const SplitPlan sp = slices(dw.K, s);
+            if (sp.splits != s) continue;
+            const double len_dw = 60.0 + DW_K[sh] * (sp.chunk / 32);
+            const double sums = s * (double)dw.M * dw.N * 8.0 / 3.0e12 * 22.0e6;
+            const double e = makespan(t * s, len_dw, n, len_da, SLOTS[sh]) + sums;
+            if (best_t < 0.0 || e < best_t) {
+                best_t = e;
+                best = {sh, sp};
+            }
+        }
+    }
+    return best;
+}
+
 // Products with fewer 64 x 64 output tiles than this (forward / backward-data), or a
 // contraction shorter than small_k_max() (weight gradient, whose contraction is the batch),
 // go to the 32 x 32 split-wavefront kernel.  HB_GEMM_SMALL_TILES / HB_GEMM_SMALL_K: tuning aids
@@ -554,21 +621,10 @@ hipError_t launch_gemm_f32_bwd_pair(GemmArgs da, GemmArgs dw, int max_splits, in
         return launch_kernel(gemm_f32_small_pair_kernel, dim3((unsigned)blocks), dim3(NT), stream, ev, da, dw,
                              (int)(t_dw * sp.splits));
     }
-    // The larger shapes read and convert fewer operand bytes per flop; they need a workgroup for (nearly)
-    // every compute unit from the two products together.  Slices of the weight gradient: as many
-    // workgroups as the backward-data product has (at most one per compute unit), which makes them about
-    // equally long (4096 x 512 x 512: 128 + 128 workgroups of 128 x 128 x 512, 41.5 -> 26.8 us).
-    int sh = 0;
-    SplitPlan sp = {1, 0};
-    for (sh = 2; sh >= 0; --sh) {
-        const long long n = tiles_of(sh, da.M, da.N), t = tiles_of(sh, dw.M, dw.N);
-        if (n > 0x3fffffffLL || t > 0x3fffffffLL) return hipErrorInvalidValue;
-        sp = plan_splits(t, dw.K, max_splits, n < CUS ? n : CUS);
-        if (sh == 0 || n + t * sp.splits >= CUS - CUS / 8) break;
-    }
-    if (sh == 0 && (da.K >= SHARED_K || sp.chunk >= SHARED_K) &&
-        tiles_of(0, da.M, da.N) + tiles_of(0, dw.M, dw.N) * sp.splits <= CUS)
-        sh = SHARED;
+    const PairPlan pp = plan_pair(da, dw, max_splits);
+    const int sh = pp.shape;
+    const SplitPlan sp = pp.split;
+    if (tiles_of(sh, da.M, da.N) > 0x3fffffffLL || tiles_of(sh, dw.M, dw.N) > 0x3fffffffLL) return hipErrorInvalidValue;
     for (GemmArgs *g : {&da, &dw}) {
         g->tiles_m = (g->M + SHAPES[sh].bm - 1) / SHAPES[sh].bm;
         g->tiles_n = (g->N + SHAPES[sh].bn - 1) / SHAPES[sh].bn;

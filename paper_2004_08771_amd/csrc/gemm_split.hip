@@ -542,16 +542,11 @@ __global__ __launch_bounds__(NT *KG, WGS) void gemm_split_pair_kernel(GemmArgs d
     __shared__ __attribute__((aligned(16))) char smem[KG * lds_bytes<BM, BN>()];
     const int b = blockIdx.x;
     if (b < n_dw) {
-        const int tiles = dw.tiles_m * dw.tiles_n;
-        if ((dw.splits & 7) == 0) {
-            // Workgroup ids go round-robin over the 8 XCDs, each with an L2 of its own: slice s of the
-            // batch is given to XCD s % 8, all of its output tiles, so that the XCD reads only its slices'
-            // rows of D_l and A_{l-1}, once; the backward-data blocks below give it the same rows.
-            const int q = b >> 3;
-            split_tile<NT, KG, BM, BN, WM, false, false, GEMM_DW>(dw, smem, q % tiles, (b & 7) + 8 * (q / tiles));
-        } else {
-            split_tile<NT, KG, BM, BN, WM, false, false, GEMM_DW>(dw, smem, xcd_tile_order(b % tiles, tiles), b / tiles);
-        }
+        // Workgroup ids go round-robin over the 8 XCDs, each with an L2 of its own: an XCD gets a contiguous
+        // eighth of the (slice, tile) pairs, so that it reads only its slices' rows of D_l and A_{l-1}, once;
+        // the backward-data blocks below give it (nearly) the same rows.
+        const int tiles = dw.tiles_m * dw.tiles_n, w = xcd_tile_order(b, n_dw);
+        split_tile<NT, KG, BM, BN, WM, false, false, GEMM_DW>(dw, smem, w % tiles, w / tiles);
     } else {
         split_tile<NT, KG, BM, BN, WM, true, false, GEMM_DA>(da, smem, xcd_tile_order(b - n_dw, (int)gridDim.x - n_dw), 0);
     }

@@ -11,10 +11,13 @@
 // them are added per rounding, and the group of the small terms does not round at the size of
 // the large one.  Against 64 bits (relative 2-norm, one 512-deep / 4096-deep contraction of normal
 // values): fp32 MFMA 4.1e-7 / 1.1e-6, this 1.3e-7 / 4.0e-7, all six in one accumulator 3.4e-7 / 1.0e-6,
-// three terms only 4.4e-6.  Values below 2^-110 lose low bits (bf16 has fp32's exponent range, and its
-// denormals are kept), which is an absolute 2^-134 per value.  A value without a finite x0 -- infinite,
-// NaN, or within half a bf16 unit of the largest -- makes the planes NaN: a wavefront that finds
-// a non-finite result computes its tile again with fp32 MFMAs from the operands in memory.
+// three terms only 4.4e-6.  bf16 has fp32's exponent range but only 8 significand bits, so the last part of
+// a value below 2^-110 would fall under its smallest denormal: every value is multiplied by 2^24
+// first, which makes the split exact for all fp32 values down to the denormals (operands of 2^-118:
+// error 8.8e-6 -> 4.9e-8; one instruction per value, 4096 x 512 forward + backward steps 167 -> 171 us), and the sum
+// by 2^-48 at the end.  A value without a finite x0 -- infinite, NaN, or of 2^104 and more -- makes the
+// planes NaN: a wavefront that finds a non-finite result (also a sum of 2^80 and more) computes its tile
+// again with fp32 MFMAs from the operands in memory.
 //
 // What bounds it: power, then the instruction stream.  With nothing but the MFMAs of
 // 4096 x 1024 x 1024 in the loop the launch takes 33 us (clock 2.05 GHz); the whole kernel takes 45 us at
@@ -42,6 +45,7 @@ typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 
 constexpr int BK = 32;   // contraction per tile
 constexpr int SETS = 2;  // register sets of loaded tiles
+constexpr float SCALE = 16777216.f;  // on every operand value: 2^-149, the last bit of any, becomes a bf16 value
 
 __device__ __forceinline__ unsigned cvt_pk_bf16(float a, float b)
 {
@@ -160,6 +164,12 @@ struct Op {
         auto &x0 = x[set][KMAJ ? 4 * u : u], &x1 = x[set][KMAJ ? 4 * u + 1 : MV + u],
              &x2 = x[set][KMAJ ? 4 * u + 2 : 2 * MV + u], &x3 = x[set][KMAJ ? 4 * u + 3 : 3 * MV + u];
         const int kq = KMAJ ? tid & 7 : tid / R1, p = (KMAJ ? tid >> 3 : tid % R1) + R1 * u;
+        if (pl == 0) {
+            x0 *= SCALE;
+            x1 *= SCALE;
+            x2 *= SCALE;
+            x3 *= SCALE;
+        }
         uint2 w;
         w.x = cvt_pk_bf16(x0, x1);
         w.y = cvt_pk_bf16(x2, x3);
@@ -426,7 +436,7 @@ __device__ __forceinline__ void split_tile(const GemmArgs &a, char *smem, int id
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) hi[i][j][v] += lo[i][j][v];
+            for (int v = 0; v < 16; ++v) hi[i][j][v] = (hi[i][j][v] + lo[i][j][v]) * (1.f / SCALE / SCALE);
     if constexpr (KG > 1) {
         static_assert(TM == 1 && TN == 1, "one block per wavefront");
         float *red = reinterpret_cast<float *>(smem_all);

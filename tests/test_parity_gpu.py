@@ -1115,6 +1115,57 @@ def test_split_plane_products_at_tile_edges(dims, act, B):
     check_case(dims, act, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=B < 100)
 
 
+def _relu_gradient_in_64_bits(dims, params, X, y, on):
+    """Gradient and hidden activations of a ReLU network with the softmax loss; `on` = {layer: mask}."""
+    P, off = [], 0
+    for a, b in zip(dims[:-1], dims[1:]):
+        P.append(params[off:off + a * b].astype(np.float64).reshape(b, a))
+        off += a * b
+        P.append(params[off:off + b].astype(np.float64))
+        off += b
+    L = len(dims) - 1
+    acts = [X.astype(np.float64)]
+    for l in range(1, L + 1):
+        z = acts[-1] @ P[2 * l - 2].T + P[2 * l - 1]
+        acts.append(np.where(on[l], z, 0.0) if l < L else z)
+    p = np.exp(acts[L] - acts[L].max(1, keepdims=True))
+    p /= p.sum(1, keepdims=True)
+    p[np.arange(y.size), y] -= 1.0
+    d, grads = p / y.size, []
+    for l in range(L, 0, -1):
+        grads += [d.sum(0), (d.T @ acts[l - 1]).ravel()]
+        if l > 1:
+            d = np.where(on[l - 1], d @ P[2 * l - 2], 0.0)
+    return np.concatenate(grads[::-1]), acts
+
+
+def test_split_plane_products_of_tiny_operands():
+    """Operands down to 2^-126 keep all their bits in the three planes: weights of 2^-116 against inputs of 2^100
+    (forward), activations of 2^-116 (forward and weight gradient), deltas of 2^-117 (weight gradient of layer 1, read
+    M-major).  Without a scale the planes of 2^-116 hold about 18 bits (relative error 2e-6)."""
+    dims, B = (300, 300, 290, 40), 2560      # 200 tiles of 64 x 64 and 2560 rows: none goes to the kernel of small products
+    rng = np.random.default_rng(11)
+    W = [rng.standard_normal((300, 300)) * 2.0 ** -116, rng.standard_normal((290, 300)) * 2.0 ** -108,
+         rng.standard_normal((40, 290)) * 0.1]
+    params = np.concatenate([np.concatenate([w.ravel(), np.zeros(w.shape[0])]) for w in W])
+    params[-40:] = rng.standard_normal(40)
+    params = params.astype(np.float32)
+    X = (rng.standard_normal((B, 300)) * 2.0 ** 100).astype(np.float32)
+    y = rng.integers(0, 40, size=B).astype(np.int32)
+    _, g, _, _, _, acts = gpu_grad_and_step(dims, hi.ACT_RELU, hi.LOSS_SOFTMAX_CE, params, X, y, 0.0, want_acts=True)
+    ref, ref_acts = _relu_gradient_in_64_bits(dims, params, X, y, {l: acts[l] > 0 for l in (1, 2)})
+    for l in (1, 2):
+        err = np.linalg.norm(acts[l] - ref_acts[l]) / np.linalg.norm(ref_acts[l])
+        assert err <= 4e-7, f"activations of layer {l}: {err:.1e}"   # fp32 sums of 300 terms: 2.2e-7 (1.3e-7 measured)
+    off = 0
+    for l, (a, b) in enumerate(zip(dims[:-1], dims[1:]), 1):
+        for name, n in (("dW", a * b), ("db", b)):
+            r = ref[off:off + n]
+            err = np.linalg.norm(g[off:off + n] - r) / np.linalg.norm(r)
+            assert err <= 1e-6, f"{name}_{l}: {err:.1e}"   # the same and the fast exp of the loss: about 3e-7
+            off += n
+
+
 def test_split_plane_products_of_values_without_finite_planes():
     """An infinite or nearly largest fp32 input has no finite leading bf16 part, yet the product is
     what fp32 arithmetic gives: a saturated unit, not a NaN."""

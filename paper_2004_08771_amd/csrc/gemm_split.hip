@@ -5,13 +5,17 @@
 // x = x0 + x1 + x2 (leading part rounded to nearest, then the leading part of the exact remainder,
 // then the rest, which fits: 3 x 8 significand bits), and the product becomes six bf16 MFMAs
 //     x0 y0  +  (x0 y1 + x1 y0 + x1 y1 + x0 y2 + x2 y0)
-// whose two groups have accumulators of their own and meet after the loop; the terms left out are
-// below 2^-26 of |x y|.  The bf16 MFMA does 16 times the flop of the fp32 one per clock, so six of
-// them are 2.7 times as fast, and they are more exact: bf16 products are exact in fp32, 16 of
+// whose two groups have accumulators of their own and meet after the loop.  The terms left out,
+// x1 y2 + x2 y1, reach 2^-24 of |x y| (significands just above 1: |x1| up to 2^-8, |x2| up to 2^-17) and are
+// 2^-28 in the mean square.  The bf16 MFMA does 16 times the flop of the fp32 one per clock, so six of
+// them are 2.7 times as fast, and their sums are more exact: bf16 products are exact in fp32, 16 of
 // them are added per rounding, and the group of the small terms does not round at the size of
-// the large one.  Against 64 bits (relative 2-norm, one 512-deep / 4096-deep contraction of normal
-// values): fp32 MFMA 4.1e-7 / 1.1e-6, this 1.3e-7 / 4.0e-7, all six in one accumulator 3.4e-7 / 1.0e-6,
-// three terms only 4.4e-6.  bf16 has fp32's exponent range but only 8 significand bits, so the last part of
+// the large one.  Against 64 bits (relative 2-norm of contractions of normal values, 8 / 54 / 512 / 4096
+// deep): fp32 MFMA 5.4e-8 / 9.9e-8 / 2.9e-7 / 8.1e-7, this 2.9e-8 / 4.7e-8 / 1.3e-7 / 4.0e-7, all six in one
+// accumulator 3.4e-7 at 512, three terms only 4.4e-6.  Where a sum is a single product the roundings
+// that this saves do not exist and the left out terms show (largest error 1.0e-7 against 6.0e-8, rms 2.60e-8
+// against 2.53e-8): a contraction of one k-tile gets them too (8 MFMAs, 6.0e-8; its launch is bound by
+// latency).  In all contractions they would cost 4096 x 512 steps 171 -> 190 us.  bf16 has fp32's exponent range but only 8 significand bits, so the last part of
 // a value below 2^-110 would fall under its smallest denormal: every value is multiplied by 2^24
 // first, which makes the split exact for all fp32 values down to the denormals (operands of 2^-118:
 // error 8.8e-6 -> 4.9e-8; one instruction per value, 4096 x 512 forward + backward steps 167 -> 171 us), and the sum
@@ -298,7 +302,7 @@ __device__ __forceinline__ void split_tile(const GemmArgs &a, char *smem, int id
         for (int i = 0; i < READS; ++i) read_frag(slot, S, step, i);
     };
     auto mfma = [&](int slot, int i) {
-        constexpr int PA[6] = {0, 0, 1, 1, 0, 2}, PB[6] = {0, 1, 0, 1, 2, 0};
+        constexpr int PA[8] = {0, 0, 1, 1, 0, 2, 1, 2}, PB[8] = {0, 1, 0, 1, 2, 0, 2, 1};
         const int q = i / MF, bi = (i % MF) / TN, bj = (i % MF) % TN;
         v16f &acc = (q == 0) ? hi[bi][bj] : lo[bi][bj];
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[slot][bi][PA[q]], fb[slot][bj][PB[q]], acc, 0, 0, 0);
@@ -407,6 +411,10 @@ __device__ __forceinline__ void split_tile(const GemmArgs &a, char *smem, int id
         read_frags(1, smem + (kt & 1) * STAGE, 1);
 #pragma unroll
         for (int i = 0; i < 2 * NM; ++i) mfma(i / NM, i % NM);
+        if (nk_all == 1) {  // the terms left out
+#pragma unroll
+            for (int i = 0; i < 4 * MF; ++i) mfma(i / (2 * MF), NM + i % (2 * MF));
+        }
     };
     if (nk > 0) {
         if ((A_KMAJ || a_in) && (B_KMAJ || b_in)) main_loop(IntC<1>(), IntC<1>());

@@ -1166,6 +1166,27 @@ def test_split_plane_products_of_tiny_operands():
             off += n
 
 
+@pytest.mark.parametrize("K", [1, 2, 31, 32])
+def test_split_plane_products_of_one_k_tile_are_exact_before_the_rounding(K):
+    """A contraction of one k-tile has all eight products of planes that fp32 can tell from nothing: a sum of one product
+    is the fp32 product (half a unit in the last place, 2^-24, and 2^-34 of it for x2 y2).  The six of longer contractions
+    miss up to 2^-24 more, most for significands just above 1."""
+    dims, B = (K, 330, 20), 2600
+    rng = np.random.default_rng(K)
+    W = (1.0 + 0.0039 * rng.random((330, K))).astype(np.float32)
+    X = np.zeros((B, K), dtype=np.float32)
+    X[np.arange(B), rng.integers(0, K, size=B)] = 1.0 + 0.0039 * rng.random(B)
+    params = np.concatenate([W.ravel(), np.zeros(330 + 20 * 330 + 20, dtype=np.float32)])
+    torch = _torch()
+    m = make_model(dims, hi.ACT_RELU, hi.LOSS_SOFTMAX_CE, B, params)
+    m.batch_loss(torch.from_numpy(X).cuda(), torch.zeros(B, dtype=torch.int32, device="cuda"), B)
+    got = gpu_hidden_activations(m, dims, B)[1]
+    m.destroy()
+    ref = X.astype(np.float64) @ W.T.astype(np.float64)
+    err = float(np.max(np.abs(got - ref) / ref))
+    assert err <= 2.0 ** -24 * 1.01, f"{err:.2e}"
+
+
 def test_split_plane_products_of_values_without_finite_planes():
     """An infinite or nearly largest fp32 input has no finite leading bf16 part, yet the product is
     what fp32 arithmetic gives: a saturated unit, not a NaN."""

@@ -21,7 +21,10 @@
 // error 8.8e-6 -> 4.9e-8; one instruction per value, 4096 x 512 forward + backward steps 167 -> 171 us), and the sum
 // by 2^-48 at the end.  A value without a finite x0 -- infinite, NaN, or of 2^104 and more -- makes the
 // planes NaN: a wavefront that finds a non-finite result (also a sum of 2^80 and more) computes its tile
-// again with fp32 MFMAs from the operands in memory.
+// again with fp32 MFMAs from the operands in memory, unless a NaN among the first values of its
+// operands' rows explains it.  (54-512x4-7, B = 4096: step with all weights NaN 162 us, as with finite ones,
+// and 869 when every block was computed again behind loads that nothing covered; gradient with all of W_2
+// infinite 257 us, 421 before, 262 on fp32 MFMAs alone.)
 //
 // What bounds it: power, then the instruction stream.  With nothing but the MFMAs of
 // 4096 x 1024 x 1024 in the loop the launch takes 33 us (clock 2.05 GHz); the whole kernel takes 45 us at
@@ -216,6 +219,93 @@ __device__ __forceinline__ void with_activation(int act, F &&f)
 __device__ __forceinline__ int xcd_tile_order(int b, int T)
 {
     return ((T & 7) == 0) ? (b & 7) * (T >> 3) + (b >> 3) : b;
+}
+
+// One 32 x 32 block on fp32 MFMAs from the operands in memory, for one wavefront: lane (r, h) reads the values
+// k = 8 q + 4 h + c of its two rows, the k-tile ahead while the MFMAs of the present one run.  Rare: sums
+// that are infinite or beyond 2^80.
+template <bool KMAJ>
+struct Fp32Rows {  // the 32 rows from `first` on (wavefront-uniform), those past `last` read as that one
+    const float *base;
+    int ld, h;
+    unsigned off;  // bytes from the lane's h = 0 value of row `first`
+    __device__ __forceinline__ Fp32Rows(const float *P, int ld_, int first, int last, int r, int h_) : ld(ld_), h(h_)
+    {
+        first = min(first, last);
+        const unsigned row = (unsigned)min(r, last - first);
+        base = KMAJ ? P + (size_t)first * ld : P + first;
+        off = 4u * (KMAJ ? row * (unsigned)ld + 4u * h : row + 4u * h * (unsigned)ld);
+    }
+    template <bool WHOLE>
+    __device__ __forceinline__ void load(float *x, int k0, int kend) const
+    {
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float *>(KMAJ ? base + k0 : base + (size_t)k0 * ld), (short)0, -1, 0x00027000);
+#pragma unroll
+        for (int q = 0; q < BK / 8; ++q) {
+            if (KMAJ && WHOLE) {
+                const v4u t = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 32 * q, 0);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) x[4 * q + c] = __uint_as_float(t[c]);
+            } else {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    x[4 * q + c] = 0.f;
+                    if (WHOLE || k0 + 8 * q + 4 * h + c < kend)
+                        x[4 * q + c] = __uint_as_float(
+                            __builtin_amdgcn_raw_buffer_load_b32(rs, off, 4 * (8 * q + c) * (KMAJ ? 1 : ld), 0));
+                }
+            }
+        }
+    }
+};
+template <typename RA, typename RB>
+__device__ __forceinline__ v16f fp32_block(const RA &ra, const RB &rb, int kbeg, int kend)
+{
+    v16f acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    float xa[2][BK / 2], xb[2][BK / 2];
+    auto load = [&](int set, int k0) {
+        ra.template load<true>(xa[set], k0, kend);
+        rb.template load<true>(xb[set], k0, kend);
+    };
+    auto mfma = [&](int set) {
+#pragma unroll
+        for (int q = 0; q < BK / 2; ++q)
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[set][q], xb[set][q], acc, 0, 0, 0);
+    };
+    const int whole = (kend - kbeg) / BK;  // k-tiles
+    if (whole > 0) load(0, kbeg);
+#pragma unroll 1
+    for (int t = 0; t < whole; t += 2) {
+        if (t + 1 < whole) load(1, kbeg + (t + 1) * BK);
+        mfma(0);
+        if (t + 1 < whole) {
+            if (t + 2 < whole) load(0, kbeg + (t + 2) * BK);
+            mfma(1);
+        }
+    }
+    if (kbeg + whole * BK < kend) {
+        ra.template load<false>(xa[0], kbeg + whole * BK, kend);
+        rb.template load<false>(xb[0], kbeg + whole * BK, kend);
+        mfma(0);
+    }
+    return acc;
+}
+// bit m: one of the first eight values of row m of a block is NaN (row: the lane's, m = lane % 32)
+template <bool KMAJ>
+__device__ __forceinline__ unsigned nan_rows(const float *__restrict__ P, int ld, int row, int kbeg, int kend, int h)
+{
+    bool nan = false;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const int k = min(kbeg + 4 * h + c, kend - 1);
+        const float x = KMAJ ? P[(size_t)row * ld + k] : P[(size_t)k * ld + row];
+        nan |= x != x;
+    }
+    const unsigned long long w = __ballot(nan);
+    return (unsigned)(w | (w >> 32));
 }
 
 template <int BM, int BN>
@@ -467,27 +557,40 @@ __device__ __forceinline__ void split_tile(const GemmArgs &a, char *smem, int id
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) bad = fmaf(hi[i][j][v], 0.f, bad);
-    if (__any(bad != 0.f)) {  // NaN: some result of this wavefront is not finite
+    if (__any(bad != 0.f) && kbeg < kend) {  // NaN: some result of this wavefront is not finite
+        // A row whose first values hold a NaN (all of them, once the weights of a run are NaN) has a NaN in
+        // every result in either arithmetic: only the other results that are not finite ask for the second one.
+        auto row_a = [&](int i) { return min(m0 + wm * WM + i * 32 + r, a.M - 1); };
+        auto row_b = [&](int j) { return min(n0 + wn * WN + j * 32 + r, a.N - 1); };
+        unsigned nan_a[TM], nan_b[TN], again = 0;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) nan_a[i] = nan_rows<A_KMAJ>(A, a.lda, row_a(i), kbeg, kend, h);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) nan_b[j] = nan_rows<B_KMAJ>(Bm, a.ldb, row_b(j), kbeg, kend, h);
+#pragma unroll
         for (int i = 0; i < TM; ++i)
+#pragma unroll
             for (int j = 0; j < TN; ++j) {
-                const int m = min(m0 + wm * WM + i * 32 + r, a.M - 1), n = min(n0 + wn * WN + j * 32 + r, a.N - 1);
-                const float *pa = A_KMAJ ? A + (size_t)m * a.lda : A + m;
-                const float *pb = B_KMAJ ? Bm + (size_t)n * a.ldb : Bm + n;
-                v16f acc;
+                unsigned open = 0;
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-                for (int k = kbeg + h; k - h < kend; k += 2) {
-                    const bool in = k < kend;
-                    const float xa = in ? (A_KMAJ ? pa[k] : pa[(size_t)k * a.lda]) : 0.f;
-                    const float xb = in ? (B_KMAJ ? pb[k] : pb[(size_t)k * a.ldb]) : 0.f;
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(xa, xb, acc, 0, 0, 0);
+                for (int v = 0; v < 16; ++v) {
+                    const int row = 8 * (v >> 2) + 4 * h + (v & 3);
+                    open |= (hi[i][j][v] * 0.f != 0.f) ? ~(nan_a[i] >> row) & 1u : 0u;
                 }
-#pragma unroll
-                for (int ii = 0; ii < TM; ++ii)
-#pragma unroll
-                    for (int jj = 0; jj < TN; ++jj)
-                        if (ii == i && jj == j) hi[ii][jj] = acc;
+                if (__any(open & ~(nan_b[j] >> r) & 1u)) again |= 1u << (i * TN + j);
             }
+#pragma unroll 1
+        for (int b = 0; b < TM * TN; ++b) {
+            if (!((again >> b) & 1u)) continue;  // uniform per wavefront
+            const Fp32Rows<A_KMAJ> ra(A, a.lda, m0 + wm * WM + (b / TN) * 32, a.M - 1, r, h);
+            const Fp32Rows<B_KMAJ> rb(Bm, a.ldb, n0 + wn * WN + (b % TN) * 32, a.N - 1, r, h);
+            const v16f acc = fp32_block(ra, rb, kbeg, kend);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    if (i * TN + j == b) hi[i][j] = acc;
+        }
     }
 
     // ---- epilogue.  hi[i][j][v] is C(row, col) with row = 8 (v / 4) + 4 h + (v % 4), col = r inside

@@ -1187,21 +1187,93 @@ def test_split_plane_products_of_one_k_tile_are_exact_before_the_rounding(K):
     assert err <= 2.0 ** -24 * 1.01, f"{err:.2e}"
 
 
-def test_split_plane_products_of_values_without_finite_planes():
+# rows, columns and k-tiles cut; forward products of layer 1 in 64 x 64 (two groups: 300 deep; one: 100 deep), 128 x 64
+# and 128 x 128 tiles
+SPLIT_SIZES = [((300, 330, 290, 40), 2561), ((100, 330, 290, 40), 2561), ((130, 257, 250, 40), 4099),
+               ((100, 500, 500, 40), 8150)]
+
+
+@pytest.mark.parametrize("dims,B", SPLIT_SIZES)
+def test_split_plane_products_of_huge_operands(dims, B):
+    """Operands of 2^104 and more have no finite planes and sums beyond 2^80 do not fit the scaled accumulators: those
+    blocks are computed again with fp32 MFMAs.  Inputs of 2^105, weights of layer 2 of 2^106 and activations of
+    2^99 send every product but the last layer's forward one there, with results that fp32 holds."""
+    rng = np.random.default_rng(B)
+    scales = [2.0 ** -120, 2.0 ** 106, 2.0 ** -104]
+    W = [rng.standard_normal((b, a)) * s for a, b, s in zip(dims[:-1], dims[1:], scales)]
+    params = np.concatenate([np.concatenate([w.ravel(), np.zeros(w.shape[0])]) for w in W]).astype(np.float32)
+    X = (rng.standard_normal((B, dims[0])) * 2.0 ** 105).astype(np.float32)
+    y = rng.integers(0, dims[-1], size=B).astype(np.int32)
+    _, g, _, _, _, acts = gpu_grad_and_step(dims, hi.ACT_RELU, hi.LOSS_SOFTMAX_CE, params, X, y, 0.0, want_acts=True)
+    ref, ref_acts = _relu_gradient_in_64_bits(dims, params, X, y, {l: acts[l] > 0 for l in (1, 2)})
+    for l in (1, 2):
+        err = np.linalg.norm(acts[l].astype(np.float64) - ref_acts[l]) / np.linalg.norm(ref_acts[l])
+        assert err <= 6e-7, f"activations of layer {l}: {err:.1e}"   # fp32 MFMAs: 2.9e-7 for 512 terms; two layers
+    off = 0
+    for l, (a, b) in enumerate(zip(dims[:-1], dims[1:]), 1):
+        for name, n in (("dW", a * b), ("db", b)):
+            r = ref[off:off + n]
+            err = np.linalg.norm(g[off:off + n].astype(np.float64) - r) / np.linalg.norm(r)
+            # the scores are sums of about 2^0 .. 2^3 whose rounding the softmax passes on; sums over the batch
+            assert err <= 5e-6, f"{name}_{l}: {err:.1e}"
+            off += n
+
+
+@pytest.mark.parametrize("dims,B", SPLIT_SIZES)
+def test_split_plane_products_of_values_without_finite_planes(dims, B):
     """An infinite or nearly largest fp32 input has no finite leading bf16 part, yet the product is
-    what fp32 arithmetic gives: a saturated unit, not a NaN."""
-    dims, B = (64, 128, 128, 30), 2560
+    what fp32 arithmetic gives: a saturated unit, not a NaN.  In the first and the last row tile (cut) and in the
+    partial k-tile."""
     params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=5)
-    X[3, 7], X[1300, 40], X[2559, 63] = np.inf, -np.inf, 3.4e38
+    X[3, 7], X[B - 1, dims[0] - 1], X[B - 2, dims[0] - 2] = np.inf, -np.inf, 3.4e38
     torch = _torch()
     m = make_model(dims, hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, B, params)
     got = m.batch_loss(torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda(), B)
     acts = gpu_hidden_activations(m, dims, B)
     m.destroy()
     with np.errstate(over="ignore"):
-        ref = oracle.batch_loss(dims, hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, params, X.astype(np.float64), y)
+        ref = mf.batch_grad(dims, hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, params, X.astype(np.float64), y)[0]
     assert np.isfinite(ref) and abs(got - ref) <= TOL_F32 * abs(ref)
-    assert set(np.unique(acts[1][3])) <= {0.0, 1.0} and set(np.unique(acts[1][1300])) <= {0.0, 1.0}
+    for row in (3, B - 1, B - 2):
+        assert set(np.unique(acts[1][row])) <= {0.0, 1.0}
+
+
+def test_nan_operands_stay_nan_and_cost_no_second_product():
+    """A NaN reaches exactly the results that depend on it (here one row of X, through two layers), and a run whose
+    weights have become NaN is about as quick as any other: its products are not computed twice."""
+    import paper_2004_08771_amd as hb
+    torch = _torch()
+    dims, B = (300, 512, 512, 512, 40), 4096
+    params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=6)
+    dX, dy = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
+    bad = dX.clone()
+    bad[1234, 17] = float("nan")
+    m = make_model(dims, hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, B, params)
+    m.batch_loss_async(dX, dy, B)
+    clean = gpu_hidden_activations(m, dims, B)
+    m.batch_loss_async(bad, dy, B)
+    acts = gpu_hidden_activations(m, dims, B)
+    m.destroy()
+    for l in (1, 2, 3):
+        assert np.isnan(acts[l][1234]).all()
+        rest = np.arange(B) != 1234
+        assert np.allclose(acts[l][rest], clean[l][rest], rtol=1e-5, atol=0)   # fp32 or split products of the same values
+    us = {}
+    for name, p in (("finite", params), ("nan", np.full_like(params, np.nan))):
+        m = hb.Model(dims, hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE).configure(hb.HB_F32, B, False,
+                                                                        torch.cuda.current_stream().cuda_stream)
+        m.set_params(p)
+        times = []
+        for i in range(40):
+            ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            ev[0].record()
+            m.batch_step_async(dX, dy, B, 0.0)
+            ev[1].record()
+            times.append(ev)
+        torch.cuda.synchronize()
+        us[name] = sorted(a.elapsed_time(b) for a, b in times[20:])[5] * 1e3
+        m.destroy()
+    assert us["nan"] <= 2.0 * us["finite"], us    # 1.0 measured; 5 when every product was computed again
 
 
 # ---------------------------------------------------------------- bf16 products of small tiles

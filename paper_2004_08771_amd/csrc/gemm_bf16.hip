@@ -302,39 +302,77 @@ __device__ __forceinline__ void epilogue_bf16(const GemmBf16Args &a, v16f (&acc)
 // transposed both operands and added the bias gradient up, 48 + 14 -> 19 us.)
 // LDS rows are 128 bytes, their eight 16-byte chunks exchanged by the row pair, which keeps the
 // writes (8 lanes per row) and the fragment reads (32 rows at one chunk) free of bank conflicts.
-// VEC: rows are 4-byte aligned; 16-byte buffer loads need no more.  Otherwise, and for a partial
-// k-tile (taken first), the guarded element loads of TileB.
+// 16-byte buffer loads need rows that are 4-byte aligned.  SHIFT: the rows of A are not (the caller's X with
+// an odd d_0, or at an odd address): a lane reads the five dwords that hold its eight values and shifts them
+// down as it writes them to LDS.  (Element loads instead: 5999 x 2050 x 301 forward 141 us, with this
+// 57; 1021 x 512 x 1001 41 -> 12; 16384 x 4096 x 301 558 -> 198.)  A partial k-tile is taken first, through the guarded loads of TileB; with
+// SHIFT every contraction ends in one, so that no wide load reads past the end of a row.
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 constexpr int MID_BK = 64, MID_SETS = 4;
 
-template <int ROWS, int THREADS>
+template <int ROWS, int THREADS, bool SHIFT = false>
 struct MidOp {
     using T = TileB<ROWS, MID_BK, THREADS>;  // thread tid holds chunk tid % 8 of rows tid / 8 + R1 v
     static constexpr int R1 = THREADS / 8;
     static constexpr int VPT = T::VPT;
     uint4 x[MID_SETS][VPT];
     unsigned off[VPT];
+    // SHIFT: the fifth dword (its own offset: of a row that is aligned after all, the fourth again) and the bytes to shift by
+    unsigned x4[SHIFT ? MID_SETS : 1][VPT], off4[VPT], sh[VPT];
 
     static __device__ __forceinline__ int slot(int row, int c)
     {
         return row * 128 + ((c ^ (((row >> 1) ^ ((row >> 5) << 2)) & 7)) << 4);
     }
     static __device__ __forceinline__ int frag(int row, int c) { return slot(row, c); }
-    __device__ __forceinline__ void init(long long ld, int last_row, int tid)
+    // tile: the first value of the tile's first row
+    __device__ __forceinline__ void init(const bf16_t *tile, long long ld, int last_row, int tid)
     {
 #pragma unroll
-        for (int v = 0; v < VPT; ++v)
-            off[v] = (unsigned)(min((tid >> 3) + R1 * v, last_row) - min(R1 * v, last_row)) * (unsigned)ld * 2u +
-                     (tid & 7) * 16u;
+        for (int v = 0; v < VPT; ++v) {
+            unsigned row = (unsigned)(min((tid >> 3) + R1 * v, last_row) - min(R1 * v, last_row)) * (unsigned)ld * 2u;
+            if (SHIFT) {
+                row += (unsigned)(reinterpret_cast<size_t>(tile + (size_t)min(R1 * v, last_row) * ld) & 3);
+                sh[v] = row & 2u;
+                row &= ~3u;
+            }
+            off[v] = row + (tid & 7) * 16u;
+            if (SHIFT) off4[v] = off[v] + (sh[v] ? 16u : 12u);
+        }
     }
     __device__ __forceinline__ void load(int set, const bf16_t *__restrict__ tile, long long ld, int last_row)
     {
 #pragma unroll
         for (int v = 0; v < VPT; ++v) {
-            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-                const_cast<bf16_t *>(tile + (size_t)min(R1 * v, last_row) * ld), (short)0, -1, 0x00027000);
+            size_t base = reinterpret_cast<size_t>(tile + (size_t)min(R1 * v, last_row) * ld);
+            if (SHIFT) base &= ~(size_t)3;
+            const __amdgpu_buffer_rsrc_t rs =
+                __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(base), (short)0, -1, 0x00027000);
             const v4u t = __builtin_amdgcn_raw_buffer_load_b128(rs, off[v], 0, 0);
             x[set][v] = make_uint4(t[0], t[1], t[2], t[3]);
+            if (SHIFT) x4[set][v] = __builtin_amdgcn_raw_buffer_load_b32(rs, off4[v], 0, 0);
+        }
+    }
+    // SHIFT: drops the half dword below each of the eight values that were read
+    __device__ __forceinline__ void align(int set)
+    {
+#pragma unroll
+        for (int v = 0; v < VPT; ++v) {
+            const uint4 t = x[set][v];
+            x[set][v] = make_uint4(
+                __builtin_amdgcn_alignbyte(t.y, t.x, sh[v]), __builtin_amdgcn_alignbyte(t.z, t.y, sh[v]),
+                __builtin_amdgcn_alignbyte(t.w, t.z, sh[v]), __builtin_amdgcn_alignbyte(x4[set][v], t.w, sh[v]));
+        }
+    }
+    // a partial k-tile (aligned at once): wide loads where another value follows in the row
+    __device__ __forceinline__ void load_tail(int set, const bf16_t *__restrict__ P, long long ld, int row0, int nrows,
+                                              int k0, int kend, bool vec, int tid)
+    {
+        if (SHIFT && k0 + 8 * (tid & 7) + 8 < kend) {
+            load(set, P + (size_t)row0 * ld + k0, ld, nrows - 1 - row0);
+            align(set);
+        } else {
+            T::load(x[set], P, ld, row0, nrows, k0, kend, vec, tid);
         }
     }
     __device__ __forceinline__ void store(int set, unsigned char *S, int tid) const
@@ -399,14 +437,14 @@ struct MidOpT {
 // BMAJ: weight gradient with both operands batch-major; the workgroups of the first tile column also
 // add up the columns of D_l, the bias gradient.
 // TILE: 64 (four wavefronts of 32 x 32) or 128 (one group of eight wavefronts of 64 x 32).
-template <int TILE, int KG, int KIND, bool VEC, bool BMAJ>
+template <int TILE, int KG, int KIND, bool SHIFT, bool BMAJ>
 __global__ __launch_bounds__((TILE == 64 ? NT : 2 * NT) * KG, TILE == 64 ? (KG == 1 ? 3 : 2) : 1)
 void gemm_bf16_mid_kernel(GemmBf16Args a)
 {
     constexpr int BM = TILE, BN = TILE, GT = (TILE == 64) ? NT : 2 * NT, TM = TILE / 64;  // GT: threads of a group
-    static_assert(!BMAJ || (VEC && KIND == GEMM_DW && TILE == 64), "batch-major operands");
+    static_assert(!BMAJ || (!SHIFT && KIND == GEMM_DW && TILE == 64), "batch-major operands");
     static_assert(TILE == 64 || KG == 1, "a group of eight wavefronts does not share");
-    using OA = std::conditional_t<BMAJ, MidOpT<64>, MidOp<BM, GT>>;
+    using OA = std::conditional_t<BMAJ, MidOpT<64>, MidOp<BM, GT, SHIFT>>;
     using OB = std::conditional_t<BMAJ, MidOpT<64>, MidOp<BN, GT>>;
     constexpr int A_BYTES = 128 * BM, STAGE = 128 * (BM + BN);
     __shared__ __attribute__((aligned(16))) unsigned char smem[KG * 2 * STAGE];
@@ -422,7 +460,7 @@ void gemm_bf16_mid_kernel(GemmBf16Args a)
     if ((T & 7) == 0) id = (id & 7) * (T >> 3) + (id >> 3);  // XCD-aware tile order
     const int tile_m = id / a.tiles_n, tile_n = id - tile_m * a.tiles_n;
     const int m0 = tile_m * BM, n0 = tile_n * BN;
-    const int nk_full = a.K / MID_BK, tail = (a.K % MID_BK) ? 1 : 0, nk = nk_full + tail;
+    const int nk_full = (SHIFT ? a.K - 1 : a.K) / MID_BK, tail = (nk_full * MID_BK < a.K) ? 1 : 0, nk = nk_full + tail;
     const int rounds = (nk + KG - 1) / KG;               // k-tiles of group 0
     const int mine = (nk - g + KG - 1) / KG;             // k-tiles of this group: rounds or one less
     const int a_last = a.M - 1 - m0, b_last = a.N - 1 - n0;
@@ -438,15 +476,20 @@ void gemm_bf16_mid_kernel(GemmBf16Args a)
 
     OA oa;
     OB ob;
-    oa.init(a.lda, a_last, tid);
-    ob.init(a.ldb, b_last, tid);
+    if constexpr (BMAJ) {
+        oa.init(a.lda, a_last, tid);
+        ob.init(a.ldb, b_last, tid);
+    } else {
+        oa.init(A + (size_t)m0 * a.lda, a.lda, a_last, tid);
+        ob.init(Bm + (size_t)n0 * a.ldb, a.ldb, b_last, tid);
+    }
     auto load_guarded = [&](int set, int k0) {
         if constexpr (BMAJ) {
             oa.load_tail(set, A, a.lda, m0, a_last, k0, a.K, tid);
             ob.load_tail(set, Bm, a.ldb, n0, b_last, k0, a.K, tid);
         } else {
-            OA::T::load(oa.x[set], A, a.lda, m0, a.M, k0, a.K, a.a_vec != 0, tid);
-            OB::T::load(ob.x[set], Bm, a.ldb, n0, a.N, k0, a.K, a.b_vec != 0, tid);
+            oa.load_tail(set, A, a.lda, m0, a.M, k0, a.K, a.a_vec != 0, tid);
+            ob.load_tail(set, Bm, a.ldb, n0, a.N, k0, a.K, a.b_vec != 0, tid);
         }
     };
     // the group's i-th k-tile; k-tile 0 is the partial one if there is one; past the end: the last
@@ -456,16 +499,14 @@ void gemm_bf16_mid_kernel(GemmBf16Args a)
         if constexpr (BMAJ) {
             oa.load(set, A + (size_t)f * MID_BK * a.lda + m0, a.lda);
             ob.load(set, Bm + (size_t)f * MID_BK * a.ldb + n0, a.ldb);
-        } else if (VEC) {
+        } else {
             oa.load(set, A + (size_t)m0 * a.lda + f * MID_BK, a.lda, a_last);
             ob.load(set, Bm + (size_t)n0 * a.ldb + f * MID_BK, a.ldb, b_last);
-        } else {
-            load_guarded(set, f * MID_BK);
         }
     };
     const bool do_bias = BMAJ && a.bias_out != nullptr && tile_n == 0;
     float csum[2] = {0.f, 0.f};
-    auto store_tile = [&](int set, unsigned char *S) {
+    auto store_tile = [&](int set, unsigned char *S, bool aligned) {
         if constexpr (BMAJ) {
             if (do_bias) {
 #pragma unroll
@@ -475,6 +516,8 @@ void gemm_bf16_mid_kernel(GemmBf16Args a)
                 }
             }
         }
+        if constexpr (SHIFT)
+            if (!aligned) oa.align(set);
         oa.store(set, S, tid);
         ob.store(set, S + A_BYTES, tid);
     };
@@ -494,7 +537,7 @@ void gemm_bf16_mid_kernel(GemmBf16Args a)
 #pragma unroll
         for (int t = 1; t < MID_SETS; ++t) load_tile(t, t);
     }
-    if (mine > 0) store_tile(0, stages);
+    if (mine > 0) store_tile(0, stages, tail && g == 0);
     if (mine > 1) load_tile(0, MID_SETS);
     __syncthreads();
     for (int i = 0; i < rounds;) {
@@ -505,7 +548,7 @@ void gemm_bf16_mid_kernel(GemmBf16Args a)
 #pragma unroll
                 for (int step = 0; step < 4; ++step) read_frags(S, step);
                 if (i + 1 < mine) {
-                    store_tile((c + 1) % MID_SETS, stages + ((c + 1) & 1) * STAGE);
+                    store_tile((c + 1) % MID_SETS, stages + ((c + 1) & 1) * STAGE, false);
                     load_tile((c + 1) % MID_SETS, i + 1 + MID_SETS);
                 }
 #pragma unroll
@@ -1359,7 +1402,7 @@ __global__ __launch_bounds__(256) void colsum_bias_finalize_kernel(const float *
     }
 }
 
-template <int TILE, int KG, bool VEC>
+template <int TILE, int KG, bool SHIFT>
 hipError_t launch_mid_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, const LaunchEvents &ev)
 {
     a.tiles_m = (a.M + TILE - 1) / TILE;
@@ -1367,14 +1410,18 @@ hipError_t launch_mid_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, co
     const long long tiles = (long long)a.tiles_m * a.tiles_n;
     if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid((unsigned)tiles), block((TILE == 64 ? NT : 2 * NT) * KG);
-    if constexpr (VEC && TILE == 64)
-        if (a.bmaj) return launch_kernel(gemm_bf16_mid_kernel<TILE, KG, GEMM_DW, true, true>, grid, block, stream, ev, a);
-    switch (kind) {
-    case GEMM_FWD: return launch_kernel(gemm_bf16_mid_kernel<TILE, KG, GEMM_FWD, VEC, false>, grid, block, stream, ev, a);
-    case GEMM_DA: return launch_kernel(gemm_bf16_mid_kernel<TILE, KG, GEMM_DA, VEC, false>, grid, block, stream, ev, a);
-    case GEMM_DW: return launch_kernel(gemm_bf16_mid_kernel<TILE, KG, GEMM_DW, VEC, false>, grid, block, stream, ev, a);
+    if constexpr (SHIFT) {
+        return launch_kernel(gemm_bf16_mid_kernel<TILE, KG, GEMM_FWD, true, false>, grid, block, stream, ev, a);
+    } else {
+        if constexpr (TILE == 64)
+            if (a.bmaj) return launch_kernel(gemm_bf16_mid_kernel<TILE, KG, GEMM_DW, false, true>, grid, block, stream, ev, a);
+        switch (kind) {
+        case GEMM_FWD: return launch_kernel(gemm_bf16_mid_kernel<TILE, KG, GEMM_FWD, false, false>, grid, block, stream, ev, a);
+        case GEMM_DA: return launch_kernel(gemm_bf16_mid_kernel<TILE, KG, GEMM_DA, false, false>, grid, block, stream, ev, a);
+        case GEMM_DW: return launch_kernel(gemm_bf16_mid_kernel<TILE, KG, GEMM_DW, false, false>, grid, block, stream, ev, a);
+        }
+        return hipErrorInvalidValue;
     }
-    return hipErrorInvalidValue;
 }
 
 // 128 x 128 tiles where they (nearly) fill the compute units: half the operand bytes per flop
@@ -1383,13 +1430,14 @@ hipError_t launch_mid_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, co
 // k-tiles to share (1023 x 1024 x 1024: 12.6 -> 10.1 us, 1024 x 1024 x 2047 as a weight gradient 20.2 ->
 // 17.7 us); with more tiles the compute units are shared by workgroups anyway (7001 x 1024 x 1024:
 // 28.8 us with one group, 35.3 with two).
+template <bool SHIFT>
 hipError_t launch_mid(GemmKind kind, const GemmBf16Args &a, hipStream_t stream, const LaunchEvents &ev)
 {
     const long long tiles = (long long)((a.M + 63) / 64) * ((a.N + 63) / 64);
     const long long big = (long long)((a.M + 127) / 128) * ((a.N + 127) / 128);
-    if (!a.bmaj && big >= 200) return launch_mid_bf16<128, 1, true>(kind, a, stream, ev);
-    return (tiles <= 256 && a.K >= 8 * MID_BK) ? launch_mid_bf16<64, 2, true>(kind, a, stream, ev)
-                                               : launch_mid_bf16<64, 1, true>(kind, a, stream, ev);
+    if (!a.bmaj && big >= 200) return launch_mid_bf16<128, 1, SHIFT>(kind, a, stream, ev);
+    return (tiles <= 256 && a.K >= 8 * MID_BK) ? launch_mid_bf16<64, 2, SHIFT>(kind, a, stream, ev)
+                                               : launch_mid_bf16<64, 1, SHIFT>(kind, a, stream, ev);
 }
 
 int env_int_bf16(const char *name, int dflt)
@@ -1455,7 +1503,7 @@ hipError_t launch_gemm_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, c
                                    (unsigned long long)a.N * (unsigned long long)a.ldb * 2 < (1ull << 32)));
     if (a.bmaj == BF16_DW_BMAJ_MID) {
         if (kind != GEMM_DW || a.k_chunk > 0) return hipErrorInvalidValue;
-        return launch_mid(kind, a, stream, ev);
+        return launch_mid<false>(kind, a, stream, ev);
     }
     if (a.bmaj) {  // batch-major operands through the LDS-direct kernel
         if (kind != GEMM_DW || !dma_ok || (a.k_chunk > 0 && (!a.write_grad || a.C_bf16 || a.Ct_bf16 ||
@@ -1476,10 +1524,11 @@ hipError_t launch_gemm_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, c
         return launch_dma_bf16(kind, a, stream, ev);
     }
     a.colsum_partial = nullptr;  // the other kernels do not produce them
-    const bool vec = ((a.lda | a.ldb) & 1) == 0 &&
-                     ((reinterpret_cast<size_t>(a.A) | reinterpret_cast<size_t>(a.B)) & 3) == 0 &&
-                     a.lda < (1ll << 25) && a.ldb < (1ll << 25);  // 32-bit byte offsets over 32 rows
-    return vec ? launch_mid(kind, a, stream, ev) : launch_mid_bf16<64, 1, false>(kind, a, stream, ev);
+    // rows of the weight copies, activations and deltas have a pitch of 8; only the caller's X can be off
+    auto aligned4 = [](const void *p, long long ld) { return (ld & 1) == 0 && (reinterpret_cast<size_t>(p) & 3) == 0; };
+    if (a.lda >= (1ll << 25) || a.ldb >= (1ll << 25) || !aligned4(a.B, a.ldb)) return hipErrorInvalidValue;  // 32-bit byte offsets over 64 rows
+    if (aligned4(a.A, a.lda)) return launch_mid<false>(kind, a, stream, ev);
+    return (kind == GEMM_FWD) ? launch_mid<true>(kind, a, stream, ev) : hipErrorInvalidValue;
 }
 
 int gemm_bf16_dw_form(int M, int N, int K, long long lda, long long ldb, const void *A, const void *B)

@@ -1288,3 +1288,37 @@ def test_nan_operands_stay_nan_and_cost_no_second_product():
 def test_bf16_small_tile_products_at_tile_edges(dims, act, B):
     params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=300 + B, bias_scale=0.1)
     check_bf16_case(dims, act, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=False)
+
+
+@pytest.mark.parametrize("dims,B,at", [
+    ((63, 70, 5), 130, 0),        # one k-tile, element loads at its end
+    ((65, 129, 3), 200, 0),       # a whole k-tile and one value
+    ((65, 129, 3), 200, 1),       # the same from an odd address: other rows are the aligned ones
+    ((64, 66, 3), 67, 1),         # even rows from an odd address, whole k-tiles: the last one is taken as a partial one
+    ((577, 300, 2), 513, 0),      # two groups of wavefronts share ten k-tiles
+    ((201, 1030, 2), 1921, 1),    # 64 x 64 tiles, one group
+    ((201, 2060, 2), 1601, 0),    # 128 x 128 tiles, cut in both directions
+])
+def test_bf16_rows_of_X_that_are_not_4_byte_aligned(dims, B, at):
+    """The forward product of layer 1 reads such rows as aligned dwords and shifts them: the activations
+    are those of the same X in rows of even pitch (the layer's other operand and the sums are the same, the order of
+    the k-tiles may not be: fp32 sums, then rounded to bf16)."""
+    import paper_2004_08771_amd as hb
+    torch = _torch()
+    params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=B + at)
+    flat = torch.zeros(X.size + 1, dtype=torch.bfloat16, device="cuda")
+    dX = flat[at:at + X.size].view(X.shape)
+    dX.copy_(torch.from_numpy(X))
+    dy = torch.from_numpy(y).cuda()
+    W = torch.from_numpy(params[:dims[0] * dims[1]].reshape(dims[1], dims[0])).to(torch.bfloat16).double()
+    b = params[dims[0] * dims[1]:dims[0] * dims[1] + dims[1]].astype(np.float64)
+    z = dX.cpu().double().numpy() @ W.numpy().T + b
+    m = hb.Model(dims, hi.ACT_RELU, hi.LOSS_SOFTMAX_CE).configure(hb.HB_BF16_F32MASTER, B)
+    m.set_params(params)
+    m.batch_loss(dX, dy, B)
+    got = gpu_hidden_activations(m, dims, B)[1]
+    m.destroy()
+    # half a bf16 unit in the last place: 2^-8 of a value with eight significand bits; fp32 rounding of sums of K terms
+    # of about 1 / sqrt(K) each: far below 1e-5
+    off = float(np.max(np.abs(got - np.maximum(z, 0)) - 2.0 ** -8 * np.abs(z)))
+    assert off <= 1e-5, off

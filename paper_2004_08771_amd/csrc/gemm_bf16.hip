@@ -302,29 +302,33 @@ __device__ __forceinline__ void epilogue_bf16(const GemmBf16Args &a, v16f (&acc)
 // transposed both operands and added the bias gradient up, 48 + 14 -> 19 us.)
 // LDS rows are 128 bytes, their eight 16-byte chunks exchanged by the row pair, which keeps the
 // writes (8 lanes per row) and the fragment reads (32 rows at one chunk) free of bank conflicts.
+// A long contraction has four k-tiles in flight; what bounds one of one or two k-tiles with many outputs is its
+// epilogue (16384 x 4096 x 54 forward: 110 us with one workgroup per compute unit, 85 with two; x 33 102 -> 83).
 // 16-byte buffer loads need rows that are 4-byte aligned.  SHIFT: the rows of A are not (the caller's X with
 // an odd d_0, or at an odd address): a lane reads the five dwords that hold its eight values and shifts them
 // down as it writes them to LDS.  (Element loads instead: 5999 x 2050 x 301 forward 141 us, with this
 // 57; 1021 x 512 x 1001 41 -> 12; 16384 x 4096 x 301 558 -> 198.)  A partial k-tile is taken first, through the guarded loads of TileB; with
 // SHIFT every contraction ends in one, so that no wide load reads past the end of a row.
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
-constexpr int MID_BK = 64, MID_SETS = 4;
+constexpr int MID_BK = 64;
 
-template <int ROWS, int THREADS, bool SHIFT = false>
+// byte offset of chunk c of an LDS row
+__device__ __forceinline__ int mid_slot(int row, int c)
+{
+    return row * 128 + ((c ^ (((row >> 1) ^ ((row >> 5) << 2)) & 7)) << 4);
+}
+
+template <int ROWS, int THREADS, int SETS, bool SHIFT = false>
 struct MidOp {
     using T = TileB<ROWS, MID_BK, THREADS>;  // thread tid holds chunk tid % 8 of rows tid / 8 + R1 v
     static constexpr int R1 = THREADS / 8;
     static constexpr int VPT = T::VPT;
-    uint4 x[MID_SETS][VPT];
+    uint4 x[SETS][VPT];
     unsigned off[VPT];
     // SHIFT: the fifth dword (its own offset: of a row that is aligned after all, the fourth again) and the bytes to shift by
-    unsigned x4[SHIFT ? MID_SETS : 1][VPT], off4[VPT], sh[VPT];
+    unsigned x4[SHIFT ? SETS : 1][VPT], off4[VPT], sh[VPT];
 
-    static __device__ __forceinline__ int slot(int row, int c)
-    {
-        return row * 128 + ((c ^ (((row >> 1) ^ ((row >> 5) << 2)) & 7)) << 4);
-    }
-    static __device__ __forceinline__ int frag(int row, int c) { return slot(row, c); }
+    static __device__ __forceinline__ int frag(int row, int c) { return mid_slot(row, c); }
     // tile: the first value of the tile's first row
     __device__ __forceinline__ void init(const bf16_t *tile, long long ld, int last_row, int tid)
     {
@@ -378,7 +382,7 @@ struct MidOp {
     __device__ __forceinline__ void store(int set, unsigned char *S, int tid) const
     {
 #pragma unroll
-        for (int v = 0; v < VPT; ++v) *reinterpret_cast<uint4 *>(S + slot((tid >> 3) + R1 * v, tid & 7)) = x[set][v];
+        for (int v = 0; v < VPT; ++v) *reinterpret_cast<uint4 *>(S + mid_slot((tid >> 3) + R1 * v, tid & 7)) = x[set][v];
     }
 };
 
@@ -386,13 +390,13 @@ struct MidOp {
 // other products leave them, batch-major), transposed on the way to LDS: thread tid holds the eight k
 // 8 (tid / 32) + q of the two columns 2 (tid % 32) + e as eight 4-byte loads, packs each column's
 // eight k and writes column 2 i + e to LDS row i + 32 e, so that the lanes write consecutive rows.
-template <int ROWS>
+template <int ROWS, int SETS>
 struct MidOpT {
     static_assert(ROWS == 64, "32 column pairs");
-    unsigned x[MID_SETS][8];
+    unsigned x[SETS][8];
     unsigned off;
 
-    static __device__ __forceinline__ int frag(int row, int c) { return MidOp<ROWS, NT>::slot((row >> 1) + 32 * (row & 1), c); }
+    static __device__ __forceinline__ int frag(int row, int c) { return mid_slot((row >> 1) + 32 * (row & 1), c); }
     // a pair that starts inside the matrix ends inside its row (rows have an even pitch)
     __device__ __forceinline__ void init(long long ld, int last_row, int tid)
     {
@@ -426,7 +430,7 @@ struct MidOpT {
 #pragma unroll
             for (int p = 0; p < 4; ++p)
                 w[p] = __builtin_amdgcn_perm(x[set][2 * p + 1], x[set][2 * p], e ? 0x07060302u : 0x05040100u);
-            *reinterpret_cast<uint4 *>(S + MidOp<ROWS, NT>::slot((tid & 31) + 32 * e, tid >> 5)) =
+            *reinterpret_cast<uint4 *>(S + mid_slot((tid & 31) + 32 * e, tid >> 5)) =
                 make_uint4(w[0], w[1], w[2], w[3]);
         }
     }
@@ -437,15 +441,18 @@ struct MidOpT {
 // BMAJ: weight gradient with both operands batch-major; the workgroups of the first tile column also
 // add up the columns of D_l, the bias gradient.
 // TILE: 64 (four wavefronts of 32 x 32) or 128 (one group of eight wavefronts of 64 x 32).
-template <int TILE, int KG, int KIND, bool SHIFT, bool BMAJ>
-__global__ __launch_bounds__((TILE == 64 ? NT : 2 * NT) * KG, TILE == 64 ? (KG == 1 ? 3 : 2) : 1)
+// SETS: k-tiles in flight.  Two for contractions of up to two k-tiles, which fit 128 registers: two workgroups of 128 x 128
+// tiles share a compute unit, and the epilogue of one runs beside the loads of the other.
+template <int TILE, int KG, int KIND, bool SHIFT, bool BMAJ, int SETS>
+__global__ __launch_bounds__((TILE == 64 ? NT : 2 * NT) * KG, TILE == 64 ? (KG == 1 ? 3 : 2) : SETS == 2 ? 4 : 1)
 void gemm_bf16_mid_kernel(GemmBf16Args a)
 {
     constexpr int BM = TILE, BN = TILE, GT = (TILE == 64) ? NT : 2 * NT, TM = TILE / 64;  // GT: threads of a group
     static_assert(!BMAJ || (!SHIFT && KIND == GEMM_DW && TILE == 64), "batch-major operands");
     static_assert(TILE == 64 || KG == 1, "a group of eight wavefronts does not share");
-    using OA = std::conditional_t<BMAJ, MidOpT<64>, MidOp<BM, GT, SHIFT>>;
-    using OB = std::conditional_t<BMAJ, MidOpT<64>, MidOp<BN, GT>>;
+    static_assert(SETS % 2 == 0, "a register set's parity is its LDS stage's");
+    using OA = std::conditional_t<BMAJ, MidOpT<64, SETS>, MidOp<BM, GT, SETS, SHIFT>>;
+    using OB = std::conditional_t<BMAJ, MidOpT<64, SETS>, MidOp<BN, GT, SETS>>;
     constexpr int A_BYTES = 128 * BM, STAGE = 128 * (BM + BN);
     __shared__ __attribute__((aligned(16))) unsigned char smem[KG * 2 * STAGE];
 
@@ -535,21 +542,21 @@ void gemm_bf16_mid_kernel(GemmBf16Args a)
     }
     if (mine > 1) {  // then the group has a whole k-tile
 #pragma unroll
-        for (int t = 1; t < MID_SETS; ++t) load_tile(t, t);
+        for (int t = 1; t < SETS; ++t) load_tile(t, t);
     }
     if (mine > 0) store_tile(0, stages, tail && g == 0);
-    if (mine > 1) load_tile(0, MID_SETS);
+    if (mine > 1) load_tile(0, SETS);
     __syncthreads();
     for (int i = 0; i < rounds;) {
 #pragma unroll
-        for (int c = 0; c < MID_SETS; ++c) {
+        for (int c = 0; c < SETS; ++c) {
             const unsigned char *S = stages + (c & 1) * STAGE;
             if (i < mine) {
 #pragma unroll
                 for (int step = 0; step < 4; ++step) read_frags(S, step);
                 if (i + 1 < mine) {
-                    store_tile((c + 1) % MID_SETS, stages + ((c + 1) & 1) * STAGE, false);
-                    load_tile((c + 1) % MID_SETS, i + 1 + MID_SETS);
+                    store_tile((c + 1) % SETS, stages + ((c + 1) & 1) * STAGE, false);
+                    load_tile((c + 1) % SETS, i + 1 + SETS);
                 }
 #pragma unroll
                 for (int step = 0; step < 4; ++step)
@@ -1402,7 +1409,7 @@ __global__ __launch_bounds__(256) void colsum_bias_finalize_kernel(const float *
     }
 }
 
-template <int TILE, int KG, bool SHIFT>
+template <int TILE, int KG, bool SHIFT, int SETS = 4>
 hipError_t launch_mid_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, const LaunchEvents &ev)
 {
     a.tiles_m = (a.M + TILE - 1) / TILE;
@@ -1410,22 +1417,24 @@ hipError_t launch_mid_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, co
     const long long tiles = (long long)a.tiles_m * a.tiles_n;
     if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid((unsigned)tiles), block((TILE == 64 ? NT : 2 * NT) * KG);
-    if constexpr (SHIFT) {
-        return launch_kernel(gemm_bf16_mid_kernel<TILE, KG, GEMM_FWD, true, false>, grid, block, stream, ev, a);
-    } else {
-        if constexpr (TILE == 64)
-            if (a.bmaj) return launch_kernel(gemm_bf16_mid_kernel<TILE, KG, GEMM_DW, false, true>, grid, block, stream, ev, a);
-        switch (kind) {
-        case GEMM_FWD: return launch_kernel(gemm_bf16_mid_kernel<TILE, KG, GEMM_FWD, false, false>, grid, block, stream, ev, a);
-        case GEMM_DA: return launch_kernel(gemm_bf16_mid_kernel<TILE, KG, GEMM_DA, false, false>, grid, block, stream, ev, a);
-        case GEMM_DW: return launch_kernel(gemm_bf16_mid_kernel<TILE, KG, GEMM_DW, false, false>, grid, block, stream, ev, a);
-        }
-        return hipErrorInvalidValue;
+    if constexpr (TILE == 64 && !SHIFT)
+        if (a.bmaj) return launch_kernel(gemm_bf16_mid_kernel<TILE, KG, GEMM_DW, false, true, SETS>, grid, block, stream, ev, a);
+    if (kind == GEMM_FWD)
+        return launch_kernel(gemm_bf16_mid_kernel<TILE, KG, GEMM_FWD, SHIFT, false, SETS>, grid, block, stream, ev, a);
+    if constexpr (!SHIFT) {
+        if (kind == GEMM_DA)
+            return launch_kernel(gemm_bf16_mid_kernel<TILE, KG, GEMM_DA, false, false, SETS>, grid, block, stream, ev, a);
+        if constexpr (SETS == 4)
+            return launch_kernel(gemm_bf16_mid_kernel<TILE, KG, GEMM_DW, false, false, SETS>, grid, block, stream, ev, a);
     }
+    return hipErrorInvalidValue;
 }
 
 // 128 x 128 tiles where they (nearly) fill the compute units: half the operand bytes per flop
-// (1000 x 4096 x 4096, 256 tiles: 83 -> 55 us; 7001 x 1024 x 1024, 440 tiles: 31.2 -> 29.9).
+// (1000 x 4096 x 4096, 256 tiles: 83 -> 55 us; 7001 x 1024 x 1024, 440 tiles: 31.2 -> 29.9).  Two of them
+// on a compute unit for contractions of one k-tile with more than 256 tiles, and of two with more than 512
+// (4096 x 2048 x 54, 512 tiles: 17.5 -> 15.2 us; 16384 x 4096 x 100: 134 -> 123; but 8192 x 512 x 128, 256 tiles:
+// 9.4 -> 13.4, and 8192 x 1000 x 100, 512 tiles: 23.2 -> 25.3).
 // Else 64 x 64, with two groups of wavefronts per tile while the tiles do not fill the compute units twice and there are
 // k-tiles to share (1023 x 1024 x 1024: 12.6 -> 10.1 us, 1024 x 1024 x 2047 as a weight gradient 20.2 ->
 // 17.7 us); with more tiles the compute units are shared by workgroups anyway (7001 x 1024 x 1024:
@@ -1435,7 +1444,11 @@ hipError_t launch_mid(GemmKind kind, const GemmBf16Args &a, hipStream_t stream, 
 {
     const long long tiles = (long long)((a.M + 63) / 64) * ((a.N + 63) / 64);
     const long long big = (long long)((a.M + 127) / 128) * ((a.N + 127) / 128);
-    if (!a.bmaj && big >= 200) return launch_mid_bf16<128, 1, SHIFT>(kind, a, stream, ev);
+    if (!a.bmaj && big >= 200) {
+        const bool epilogue_bound = kind != GEMM_DW && (a.K <= MID_BK ? big > 256 : a.K <= 2 * MID_BK && big > 512);
+        return epilogue_bound ? launch_mid_bf16<128, 1, SHIFT, 2>(kind, a, stream, ev)
+                              : launch_mid_bf16<128, 1, SHIFT>(kind, a, stream, ev);
+    }
     return (tiles <= 256 && a.K >= 8 * MID_BK) ? launch_mid_bf16<64, 2, SHIFT>(kind, a, stream, ev)
                                                : launch_mid_bf16<64, 1, SHIFT>(kind, a, stream, ev);
 }

@@ -1290,6 +1290,19 @@ def test_bf16_small_tile_products_at_tile_edges(dims, act, B):
     check_bf16_case(dims, act, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=False)
 
 
+@pytest.mark.parametrize("dims,act,B", [
+    ((54, 2060, 40, 3), hi.ACT_RELU, 2100),     # 17 x 17 tiles, one k-tile: forward, and backward-data of layer 2 (K = 40)
+    ((63, 2060, 40, 3), hi.ACT_SIGMOID, 2100),  # the same from odd rows
+    ((100, 2900, 3), hi.ACT_SIGMOID, 2900),     # 23 x 23 tiles, two k-tiles
+    ((127, 2900, 3), hi.ACT_RELU, 2900),        # the same from odd rows, the partial one of 63
+])
+def test_bf16_short_contractions_with_many_tiles(dims, act, B):
+    """Products of one or two k-tiles with more 128 x 128 tiles than compute units (and twice as many) run two
+    workgroups per compute unit with two register sets."""
+    params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=700 + dims[0], bias_scale=0.1)
+    check_bf16_case(dims, act, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=False)
+
+
 @pytest.mark.parametrize("dims,B,at", [
     ((63, 70, 5), 130, 0),        # one k-tile, element loads at its end
     ((65, 129, 3), 200, 0),       # a whole k-tile and one value

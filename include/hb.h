@@ -262,6 +262,20 @@ int hb_profile_read(hb_model *m, hb_kernel_stat *out, int32_t cap, int32_t *n_ou
  */
 int32_t hb_plan_bf16_dw_slices(int32_t d_out, int32_t d_in, int64_t B, int32_t capacity);
 
+/*
+ * Planning aids, host only: the kernel that a product of a d_out x d_in layer takes at batch size B.
+ * product: 0 forward, 1 backward-data (fp32 mode: with the weight gradient of the layer, one launch),
+ * 2 weight gradient (fp32 mode: on its own, as the first layer's).
+ * fp32 mode, model configured for max_B: 0 tiles of 32 x 32 (small products), 1 64 x 64, 2 128 x 64, 3 128 x 128,
+ * 4 64 x 64 with two groups of wavefronts; *slices (may be NULL): slices of the weight gradient's batch.
+ * bf16 mode: 1 256 x 256 (LDS-direct), 2 128 x 128, 3 128 x 128 with two workgroups per compute unit, 4 64 x 64,
+ * 5 64 x 64 with two groups; + 16: rows of X that are not 4-byte aligned (16-byte aligned dX assumed), + 32: weight
+ * gradient from the batch-major tensors.  layer: 1 for the first layer, 2 for the last, 3 for both, else 0.
+ * Products of the fused output layer and of a CSR first layer run other kernels.  -1 on invalid arguments.
+ */
+int32_t hb_plan_f32_kernel(int32_t product, int32_t d_out, int32_t d_in, int64_t B, int64_t max_B, int32_t *slices);
+int32_t hb_plan_bf16_kernel(int32_t product, int32_t d_out, int32_t d_in, int64_t B, int32_t layer);
+
 /* Library version string, e.g. for logs. */
 const char *hb_version(void);
 

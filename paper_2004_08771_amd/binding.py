@@ -38,6 +38,8 @@ SIGNATURES = {
     "hb_last_error": (ctypes.c_char_p, []),
     "hb_version": (ctypes.c_char_p, []),
     "hb_plan_bf16_dw_slices": (_i32, [_i32, _i32, _i64, _i32]),
+    "hb_plan_f32_kernel": (_i32, [_i32, _i32, _i32, _i64, _i64, _i32p]),
+    "hb_plan_bf16_kernel": (_i32, [_i32, _i32, _i32, _i64, _i32]),
 }
 
 HB_K_NAMES = {0: "fwd_gemm", 1: "da_gemm", 2: "dw_gemm", 3: "loss", 4: "update", 5: "spmm_fwd",

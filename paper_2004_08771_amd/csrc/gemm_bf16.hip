@@ -1439,18 +1439,25 @@ hipError_t launch_mid_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, co
 // k-tiles to share (1023 x 1024 x 1024: 12.6 -> 10.1 us, 1024 x 1024 x 2047 as a weight gradient 20.2 ->
 // 17.7 us); with more tiles the compute units are shared by workgroups anyway (7001 x 1024 x 1024:
 // 28.8 us with one group, 35.3 with two).
-template <bool SHIFT>
-hipError_t launch_mid(GemmKind kind, const GemmBf16Args &a, hipStream_t stream, const LaunchEvents &ev)
+int mid_kernel_of(GemmKind kind, const GemmBf16Args &a)
 {
     const long long tiles = (long long)((a.M + 63) / 64) * ((a.N + 63) / 64);
     const long long big = (long long)((a.M + 127) / 128) * ((a.N + 127) / 128);
     if (!a.bmaj && big >= 200) {
         const bool epilogue_bound = kind != GEMM_DW && (a.K <= MID_BK ? big > 256 : a.K <= 2 * MID_BK && big > 512);
-        return epilogue_bound ? launch_mid_bf16<128, 1, SHIFT, 2>(kind, a, stream, ev)
-                              : launch_mid_bf16<128, 1, SHIFT>(kind, a, stream, ev);
+        return epilogue_bound ? BF16_K_128_SHORT : BF16_K_128;
     }
-    return (tiles <= 256 && a.K >= 8 * MID_BK) ? launch_mid_bf16<64, 2, SHIFT>(kind, a, stream, ev)
-                                               : launch_mid_bf16<64, 1, SHIFT>(kind, a, stream, ev);
+    return (tiles <= 256 && a.K >= 8 * MID_BK) ? BF16_K_64_SHARED : BF16_K_64;
+}
+template <bool SHIFT>
+hipError_t launch_mid(GemmKind kind, const GemmBf16Args &a, hipStream_t stream, const LaunchEvents &ev)
+{
+    switch (mid_kernel_of(kind, a)) {
+    case BF16_K_128_SHORT: return launch_mid_bf16<128, 1, SHIFT, 2>(kind, a, stream, ev);
+    case BF16_K_128: return launch_mid_bf16<128, 1, SHIFT>(kind, a, stream, ev);
+    case BF16_K_64_SHARED: return launch_mid_bf16<64, 2, SHIFT>(kind, a, stream, ev);
+    default: return launch_mid_bf16<64, 1, SHIFT>(kind, a, stream, ev);
+    }
 }
 
 int env_int_bf16(const char *name, int dflt)
@@ -1497,13 +1504,15 @@ hipError_t launch_dma_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, co
 
 }  // namespace
 
-hipError_t launch_gemm_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, const LaunchEvents &ev,
-                            int *colsum_slices_out)
+namespace {
+bool aligned4(const void *p, long long ld) { return (ld & 1) == 0 && (reinterpret_cast<size_t>(p) & 3) == 0; }
+}  // namespace
+
+int gemm_bf16_kernel(GemmKind kind, const GemmBf16Args &a)
 {
-    if (colsum_slices_out) *colsum_slices_out = 0;
-    if (a.M <= 0 || a.N <= 0 || a.K <= 0) return hipErrorInvalidValue;
+    if (a.M <= 0 || a.N <= 0 || a.K <= 0) return 0;
     // The 256 x 256 LDS-direct kernel when both operands allow it and its tiles cover at least
-    // half of the CUs, else 64 x 64 tiles.  HB_BF16_TILE = 1 forces the LDS-direct kernel (tuning aid).
+    // half of the CUs, else the smaller tiles.  HB_BF16_TILE = 1 forces the LDS-direct kernel (tuning aid).
     static const int forced = env_int_bf16("HB_BF16_TILE", 0);
     const long long dma_tiles = (long long)((a.M + DMA_BM - 1) / DMA_BM) * ((a.N + DMA_BN - 1) / DMA_BN);
     // the LDS-direct kernel addresses each operand with 32-bit byte offsets from its base
@@ -1514,22 +1523,26 @@ hipError_t launch_gemm_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, c
                                    a.lda >= a.M && a.ldb >= a.N)
                                 : ((unsigned long long)a.M * (unsigned long long)a.lda * 2 < (1ull << 32) &&
                                    (unsigned long long)a.N * (unsigned long long)a.ldb * 2 < (1ull << 32)));
-    if (a.bmaj == BF16_DW_BMAJ_MID) {
-        if (kind != GEMM_DW || a.k_chunk > 0) return hipErrorInvalidValue;
-        return launch_mid<false>(kind, a, stream, ev);
+    if (a.bmaj && kind != GEMM_DW) return 0;
+    if (a.bmaj == BF16_DW_BMAJ_MID) return (a.k_chunk > 0) ? 0 : mid_kernel_of(kind, a);
+    if (a.bmaj || a.k_chunk > 0) {  // batch-major operands, or split over the batch: the LDS-direct kernel only
+        const bool slices_ok = a.k_chunk == 0 || (a.write_grad && !a.C_bf16 && !a.Ct_bf16 && (a.k_chunk % DMA_BK) == 0);
+        return (kind == GEMM_DW && dma_ok && slices_ok) ? BF16_K_DMA : 0;
     }
-    if (a.bmaj) {  // batch-major operands through the LDS-direct kernel
-        if (kind != GEMM_DW || !dma_ok || (a.k_chunk > 0 && (!a.write_grad || a.C_bf16 || a.Ct_bf16 ||
-                                                              (a.k_chunk % DMA_BK) != 0)))
-            return hipErrorInvalidValue;
-        return launch_dma_bf16(kind, a, stream, ev);
-    }
-    if (a.k_chunk > 0) {  // split weight gradient: only the LDS-direct kernel implements it
-        if (kind != GEMM_DW || !dma_ok || !a.write_grad || a.C_bf16 || a.Ct_bf16 || (a.k_chunk % DMA_BK) != 0)
-            return hipErrorInvalidValue;
-        return launch_dma_bf16(kind, a, stream, ev);
-    }
-    if (dma_ok && (forced == 1 || (forced == 0 && dma_tiles >= 128))) {
+    if (dma_ok && (forced == 1 || (forced == 0 && dma_tiles >= 128))) return BF16_K_DMA;
+    // 32-bit byte offsets over 64 rows.  Rows of the weight copies, activations and deltas have a pitch of 8; only the
+    // caller's X can be off.
+    if (a.lda >= (1ll << 25) || a.ldb >= (1ll << 25) || !aligned4(a.B, a.ldb)) return 0;
+    return (aligned4(a.A, a.lda) || kind == GEMM_FWD) ? mid_kernel_of(kind, a) : 0;
+}
+
+hipError_t launch_gemm_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, const LaunchEvents &ev,
+                            int *colsum_slices_out)
+{
+    if (colsum_slices_out) *colsum_slices_out = 0;
+    const int kernel = gemm_bf16_kernel(kind, a);
+    if (kernel == 0) return hipErrorInvalidValue;
+    if (kernel == BF16_K_DMA) {
         // column sums of a backward-data result: two slices per tile row, if the caller has room
         const int slices = 2 * ((a.M + DMA_BM - 1) / DMA_BM);
         if (kind != GEMM_DA || a.colsum_partial == nullptr || slices > a.colsum_cap) a.colsum_partial = nullptr;
@@ -1537,11 +1550,7 @@ hipError_t launch_gemm_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, c
         return launch_dma_bf16(kind, a, stream, ev);
     }
     a.colsum_partial = nullptr;  // the other kernels do not produce them
-    // rows of the weight copies, activations and deltas have a pitch of 8; only the caller's X can be off
-    auto aligned4 = [](const void *p, long long ld) { return (ld & 1) == 0 && (reinterpret_cast<size_t>(p) & 3) == 0; };
-    if (a.lda >= (1ll << 25) || a.ldb >= (1ll << 25) || !aligned4(a.B, a.ldb)) return hipErrorInvalidValue;  // 32-bit byte offsets over 64 rows
-    if (aligned4(a.A, a.lda)) return launch_mid<false>(kind, a, stream, ev);
-    return (kind == GEMM_FWD) ? launch_mid<true>(kind, a, stream, ev) : hipErrorInvalidValue;
+    return (a.bmaj || aligned4(a.A, a.lda)) ? launch_mid<false>(kind, a, stream, ev) : launch_mid<true>(kind, a, stream, ev);
 }
 
 int gemm_bf16_dw_form(int M, int N, int K, long long lda, long long ldb, const void *A, const void *B)

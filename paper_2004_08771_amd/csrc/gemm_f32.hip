@@ -546,46 +546,80 @@ int gemm_f32_dw_splits(int M, int N, int K, int max_splits)
     return big > small ? big : small;
 }
 
+namespace {
+
+// shape < 0: the kernel of small products (tiles of 32 x 32), else the one launch_gemm_split takes
+struct F32Plan {
+    int shape;
+    SplitPlan split;
+};
+F32Plan plan_f32(GemmKind kind, int M, int N, int K, int max_splits)
+{
+    if (kind == GEMM_DW ? small_dw_alone(M, N, K) : small_out(M, N, K)) {
+        if (kind == GEMM_DW) return {-1, plan_small_splits(K, max_splits)};
+        return {-1, {1, (K + SMALL_BK - 1) / SMALL_BK * SMALL_BK}};
+    }
+    if (kind != GEMM_DW)
+        return {pick_shape(M, N, K), {1, (K + K_CHUNK_ALIGN - 1) / K_CHUNK_ALIGN * K_CHUNK_ALIGN}};
+    int sh = (M >= 128) ? (N >= 128 ? 2 : 1) : 0;
+    const SplitPlan sp = plan_splits(tiles_of(sh, M, N), K, max_splits, CUS);
+    if (sh == 0 && sp.chunk >= SHARED_K && tiles_of(sh, M, N) * sp.splits <= CUS) sh = SHARED;
+    return {sh, sp};
+}
+// da M x N over K and dw M x N over K of one layer.  Against the split-plane tiles, 512-wide layers: B = 256
+// (32 tiles of 64 x 64) 9.7 us, B = 640 (80 tiles) 14.4 / 11.5 us, B = 1021 17.7 / 12.0 us.
+F32Plan plan_f32_pair(const GemmArgs &da, const GemmArgs &dw, int max_splits)
+{
+    const int most = small_tiles_max() < 64 ? small_tiles_max() : 64;
+    if (da.K >= 64 && tiles_of(0, da.M, da.N) < most && dw.K < small_k_max())
+        return {-1, plan_small_splits(dw.K, max_splits)};
+    const PairPlan pp = plan_pair(da, dw, max_splits);
+    return {pp.shape, pp.split};
+}
+
+}  // namespace
+
+int gemm_f32_plan(int product, int B, int d_out, int d_in, int max_splits, int *splits)
+{
+    F32Plan p;
+    if (product == 0) {
+        p = plan_f32(GEMM_FWD, B, d_out, d_in, 1);
+    } else if (product == 1) {
+        GemmArgs da = {}, dw = {};
+        da.M = B, da.N = d_in, da.K = d_out;
+        dw.M = d_out, dw.N = d_in, dw.K = B;
+        p = plan_f32_pair(da, dw, max_splits);
+    } else {
+        p = plan_f32(GEMM_DW, d_out, d_in, B, max_splits);
+    }
+    *splits = p.split.splits;
+    return p.shape;
+}
+
 hipError_t launch_gemm_f32(GemmKind kind, GemmArgs a, int max_splits, int *splits_out,
                            hipStream_t stream, const LaunchEvents &ev)
 {
     if (a.M <= 0 || a.N <= 0 || a.K <= 0) return hipErrorInvalidValue;
-    if (kind == GEMM_DW ? small_dw_alone(a.M, a.N, a.K) : small_out(a.M, a.N, a.K)) {
-        a.tiles_m = (a.M + 31) / 32;
-        a.tiles_n = (a.N + 31) / 32;
-        const long long tiles = (long long)a.tiles_m * a.tiles_n;
-        if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
-        SplitPlan sp = {1, (a.K + SMALL_BK - 1) / SMALL_BK * SMALL_BK};
-        if (kind == GEMM_DW) sp = plan_small_splits(a.K, max_splits);
-        a.splits = sp.splits;
-        a.k_chunk = sp.chunk;
-        if (splits_out) *splits_out = sp.splits;
-        const dim3 grid((unsigned)tiles, (unsigned)sp.splits, 1);
-        switch (kind) {
-        case GEMM_FWD:
-            return launch_kernel(gemm_f32_small_kernel<true, true, GEMM_FWD>, grid, dim3(NT), stream, ev, a);
-        case GEMM_DA:
-            return launch_kernel(gemm_f32_small_kernel<true, false, GEMM_DA>, grid, dim3(NT), stream, ev, a);
-        case GEMM_DW:
-            return launch_kernel(gemm_f32_small_kernel<false, false, GEMM_DW>, grid, dim3(NT), stream, ev, a);
-        }
-        return hipErrorInvalidValue;
-    }
-    int sh = pick_shape(a.M, a.N, a.K);
-    SplitPlan sp = {1, (a.K + K_CHUNK_ALIGN - 1) / K_CHUNK_ALIGN * K_CHUNK_ALIGN};
-    if (kind == GEMM_DW) {
-        sh = (a.M >= 128) ? (a.N >= 128 ? 2 : 1) : 0;
-        sp = plan_splits(tiles_of(sh, a.M, a.N), a.K, max_splits, CUS);
-        if (sh == 0 && sp.chunk >= SHARED_K && tiles_of(sh, a.M, a.N) * sp.splits <= CUS) sh = SHARED;
-    }
-    a.tiles_m = (a.M + SHAPES[sh].bm - 1) / SHAPES[sh].bm;
-    a.tiles_n = (a.N + SHAPES[sh].bn - 1) / SHAPES[sh].bn;
+    const F32Plan p = plan_f32(kind, a.M, a.N, a.K, max_splits);
+    const int bm = p.shape < 0 ? 32 : SHAPES[p.shape].bm, bn = p.shape < 0 ? 32 : SHAPES[p.shape].bn;
+    a.tiles_m = (a.M + bm - 1) / bm;
+    a.tiles_n = (a.N + bn - 1) / bn;
     const long long tiles = (long long)a.tiles_m * a.tiles_n;
     if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
-    a.splits = sp.splits;
-    a.k_chunk = sp.chunk;
-    if (splits_out) *splits_out = sp.splits;
-    return launch_gemm_split(kind, a, sh, dim3((unsigned)tiles, (unsigned)sp.splits, 1), stream, ev);
+    a.splits = p.split.splits;
+    a.k_chunk = p.split.chunk;
+    if (splits_out) *splits_out = p.split.splits;
+    const dim3 grid((unsigned)tiles, (unsigned)p.split.splits, 1);
+    if (p.shape >= 0) return launch_gemm_split(kind, a, p.shape, grid, stream, ev);
+    switch (kind) {
+    case GEMM_FWD:
+        return launch_kernel(gemm_f32_small_kernel<true, true, GEMM_FWD>, grid, dim3(NT), stream, ev, a);
+    case GEMM_DA:
+        return launch_kernel(gemm_f32_small_kernel<true, false, GEMM_DA>, grid, dim3(NT), stream, ev, a);
+    case GEMM_DW:
+        return launch_kernel(gemm_f32_small_kernel<false, false, GEMM_DW>, grid, dim3(NT), stream, ev, a);
+    }
+    return hipErrorInvalidValue;
 }
 
 // dA_l and dW_l of one hidden layer in one launch: both only read D_l, so they are independent, and
@@ -601,43 +635,23 @@ bool gemm_f32_pair_ok()
 hipError_t launch_gemm_f32_bwd_pair(GemmArgs da, GemmArgs dw, int max_splits, int *splits_out,
                                     hipStream_t stream, const LaunchEvents &ev)
 {
-    // Against the tiles below, 512-wide layers: B = 256 (32 tiles of 64 x 64) 9.7 us, B = 640 (80 tiles)
-    // 14.4 / 11.5 us, B = 1021 17.7 / 12.0 us.
-    if (da.K >= 64 && tiles_of(0, da.M, da.N) < 64 && dw.K < small_k_max()) {
-        da.tiles_m = (da.M + 31) / 32;
-        da.tiles_n = (da.N + 31) / 32;
-        da.splits = 1;
-        da.k_chunk = (da.K + SMALL_BK - 1) / SMALL_BK * SMALL_BK;
-        dw.tiles_m = (dw.M + 31) / 32;
-        dw.tiles_n = (dw.N + 31) / 32;
-        const long long n_da = (long long)da.tiles_m * da.tiles_n;
-        const long long t_dw = (long long)dw.tiles_m * dw.tiles_n;
-        const SplitPlan sp = plan_small_splits(dw.K, max_splits);
-        dw.splits = sp.splits;
-        dw.k_chunk = sp.chunk;
-        if (splits_out) *splits_out = sp.splits;
-        const long long blocks = n_da + t_dw * sp.splits;
-        if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-        return launch_kernel(gemm_f32_small_pair_kernel, dim3((unsigned)blocks), dim3(NT), stream, ev, da, dw,
-                             (int)(t_dw * sp.splits));
-    }
-    const PairPlan pp = plan_pair(da, dw, max_splits);
-    const int sh = pp.shape;
-    const SplitPlan sp = pp.split;
-    if (tiles_of(sh, da.M, da.N) > 0x3fffffffLL || tiles_of(sh, dw.M, dw.N) > 0x3fffffffLL) return hipErrorInvalidValue;
+    const F32Plan p = plan_f32_pair(da, dw, max_splits);
+    const int bm = p.shape < 0 ? 32 : SHAPES[p.shape].bm, bn = p.shape < 0 ? 32 : SHAPES[p.shape].bn;
     for (GemmArgs *g : {&da, &dw}) {
-        g->tiles_m = (g->M + SHAPES[sh].bm - 1) / SHAPES[sh].bm;
-        g->tiles_n = (g->N + SHAPES[sh].bn - 1) / SHAPES[sh].bn;
+        g->tiles_m = (g->M + bm - 1) / bm;
+        g->tiles_n = (g->N + bn - 1) / bn;
     }
+    const int align = p.shape < 0 ? SMALL_BK : K_CHUNK_ALIGN;
     da.splits = 1;
-    da.k_chunk = (da.K + K_CHUNK_ALIGN - 1) / K_CHUNK_ALIGN * K_CHUNK_ALIGN;
-    dw.splits = sp.splits;
-    dw.k_chunk = sp.chunk;
-    if (splits_out) *splits_out = sp.splits;
-    const long long n_dw = (long long)dw.tiles_m * dw.tiles_n * sp.splits;
+    da.k_chunk = (da.K + align - 1) / align * align;
+    dw.splits = p.split.splits;
+    dw.k_chunk = p.split.chunk;
+    if (splits_out) *splits_out = p.split.splits;
+    const long long n_dw = (long long)dw.tiles_m * dw.tiles_n * p.split.splits;
     const long long blocks = (long long)da.tiles_m * da.tiles_n + n_dw;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    return launch_gemm_split_pair(da, dw, sh, (unsigned)blocks, (int)n_dw, stream, ev);
+    if (p.shape >= 0) return launch_gemm_split_pair(da, dw, p.shape, (unsigned)blocks, (int)n_dw, stream, ev);
+    return launch_kernel(gemm_f32_small_pair_kernel, dim3((unsigned)blocks), dim3(NT), stream, ev, da, dw, (int)n_dw);
 }
 
 }  // namespace hb

@@ -61,6 +61,11 @@ constexpr int64_t MAX_BATCH = 1 << 22;
 constexpr int64_t MAX_DIM = 1 << 24;
 
 int round_up(int x, int m) { return (x + m - 1) / m * m; }
+// pitch of the bf16 mode's rows of a layer: 8 elements (16 bytes); the output layer's rows are padded to a
+// whole k-tile of 64 when that adds less than half a tile: its delta is the left operand of the last
+// layer's backward-data product, which then needs no masked tail (the padding is zero on both sides:
+// the loss kernel writes it, the weight copies keep it)
+int bf16_pitch(int d, bool last) { return (last && d % 64 >= 32) ? round_up(d, 64) : round_up(d, 8); }
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 enum StepMode { MODE_STEP = 0, MODE_GRAD = 1, MODE_LOSS = 2 };
@@ -991,6 +996,51 @@ int32_t hb_plan_bf16_dw_slices(int32_t d_out, int32_t d_in, int64_t B, int32_t c
     return gemm_bf16_dw_splits(d_out, d_in, (int)B, ldB, ldB);
 }
 
+int32_t hb_plan_f32_kernel(int32_t product, int32_t d_out, int32_t d_in, int64_t B, int64_t max_B, int32_t *slices)
+{
+    if (product < 0 || product > 2 || d_out < 1 || d_in < 1 || d_out > MAX_DIM || d_in > MAX_DIM || B < 1 || B > max_B ||
+        max_B > MAX_BATCH)
+        return -1;
+    int n = 1;
+    const int shape = gemm_f32_plan(product, (int)B, d_out, d_in, gemm_f32_dw_splits(d_out, d_in, (int)max_B, MAX_SPLITS), &n);
+    if (slices) *slices = n;
+    return shape + 1;
+}
+
+int32_t hb_plan_bf16_kernel(int32_t product, int32_t d_out, int32_t d_in, int64_t B, int32_t layer)
+{
+    if (product < 0 || product > 2 || d_out < 1 || d_in < 1 || d_out > MAX_DIM || d_in > MAX_DIM || B < 1 || B > MAX_BATCH)
+        return -1;
+    const bool first = (layer & 1) != 0, last = (layer & 2) != 0;
+    const int Bi = (int)B, pitch_in = first ? d_in : round_up(d_in, 8), pitch_out = bf16_pitch(d_out, last);
+    GemmBf16Args g = {};
+    g.b_vec = 1;
+    if (product == 0) {
+        g.M = Bi, g.N = d_out, g.K = d_in;
+        g.lda = pitch_in, g.ldb = round_up(d_in, 8);
+        g.a_vec = (g.lda % 8 == 0);
+        return gemm_bf16_kernel(GEMM_FWD, g) + ((g.lda & 1) ? 16 : 0);
+    }
+    g.a_vec = 1;
+    if (product == 1) {
+        g.M = Bi, g.N = d_in, g.K = last ? pitch_out : d_out;
+        g.lda = g.ldb = pitch_out;
+        return gemm_bf16_kernel(GEMM_DA, g);
+    }
+    g.M = d_out, g.N = d_in, g.K = Bi;
+    g.bmaj = gemm_bf16_dw_form(d_out, d_in, Bi, pitch_out, pitch_in, nullptr, nullptr);
+    g.lda = g.bmaj ? pitch_out : round_up(Bi, 8);
+    g.ldb = g.bmaj ? pitch_in : round_up(Bi, 8);
+    const int sp = g.bmaj == BF16_DW_BMAJ_MID ? 1
+                   : g.bmaj                   ? gemm_bf16_dw_splits_cap(g.M, g.N, g.K)
+                                              : gemm_bf16_dw_splits(g.M, g.N, g.K, g.lda, g.ldb);
+    if (sp > 1) {
+        g.write_grad = 1;
+        g.k_chunk = (int)round_up((Bi + sp - 1) / sp, 64);
+    }
+    return gemm_bf16_kernel(GEMM_DW, g) + (g.bmaj ? 32 : 0);
+}
+
 hb_model *hb_mlp_create(const int32_t *layer_dims, int32_t n_dims, int activation, int loss)
 {
     if (!layer_dims) { fail(HB_ERR_INVALID, "layer_dims is NULL"); return nullptr; }
@@ -1112,11 +1162,7 @@ int hb_mlp_configure(hb_model *m, int dtype, int64_t max_B, int sparse_first_lay
         m->relu_mask.assign(L + 1, nullptr);
         int max_ld8 = 8, max_d = 1;
         for (int l = 0; l <= L; ++l) {
-            // rows of 8 elements (16 bytes); the output layer's rows are padded to a whole k-tile
-            // of 64 when that adds less than half a tile: its delta is the left operand of the
-            // last layer's backward-data product, which then needs no masked tail (the padding
-            // is zero on both sides: the loss kernel writes it, the weight copies keep it)
-            m->ld8[l] = (l == L && m->dims[l] % 64 >= 32) ? round_up(m->dims[l], 64) : round_up(m->dims[l], 8);
+            m->ld8[l] = bf16_pitch(m->dims[l], l == L);
             if (l >= 1 && m->ld8[l] > max_ld8) max_ld8 = m->ld8[l];
             if (l >= 1 && m->dims[l] > max_d) max_d = m->dims[l];
         }

@@ -71,6 +71,10 @@ hipError_t launch_gemm_split(GemmKind kind, const GemmArgs &a, int shape, dim3 g
 hipError_t launch_gemm_split_pair(const GemmArgs &da, const GemmArgs &dw, int shape, unsigned blocks, int n_dw,
                                   hipStream_t stream, const LaunchEvents &ev);
 
+// The kernel and the batch slices of a layer's product (0 forward, 1 backward pair, 2 weight gradient alone): -1 the
+// kernel of small products, else the shape launch_gemm_split takes.
+int gemm_f32_plan(int product, int B, int d_out, int d_in, int max_splits, int *splits);
+
 // Number of split-K slices launch_gemm_f32 will use for a DW product of this shape
 // (so that the caller can size the partial buffers).
 int gemm_f32_dw_splits(int M, int N, int K, int max_splits);
@@ -141,6 +145,9 @@ int gemm_bf16_dw_splits(int M, int N, int K, long long lda, long long ldb);
 enum { BF16_DW_KMAJ = 0, BF16_DW_BMAJ = 1, BF16_DW_BMAJ_MID = 2 };
 int gemm_bf16_dw_form(int M, int N, int K, long long lda, long long ldb, const void *A, const void *B);
 int gemm_bf16_dw_splits_cap(int M, int N, int K);
+// The kernel launch_gemm_bf16 takes for a product (BF16_K_*), or 0 for arguments that it refuses.
+enum { BF16_K_DMA = 1, BF16_K_128 = 2, BF16_K_128_SHORT = 3, BF16_K_64 = 4, BF16_K_64_SHARED = 5 };
+int gemm_bf16_kernel(GemmKind kind, const GemmBf16Args &a);
 // out[i] = sum_s partial[s * stride + i]  (grad != null: written there)  or  master[i] -= lr * sum
 hipError_t launch_dw_reduce(const float *partial, int splits, long long stride, long long count, float *master,
                             float *grad, float lr, hipStream_t stream, const LaunchEvents &ev = LaunchEvents());

@@ -160,6 +160,33 @@ def _problem(dims, loss, B, seed, bias_scale=0.3):
     return params, X, y
 
 
+F32_KERNELS = ["small", "64", "128x64", "128", "64s"]        # hb_plan_f32_kernel
+BF16_KERNELS = ["refused", "dma", "128", "128s", "64", "64s"]  # hb_plan_bf16_kernel; S: shifted rows of X, B: batch-major
+
+
+def f32_plan(dims, B):
+    """"forward ...; backward pairs of layers 2 ...; weight gradient of layer 1" of a dense fp32 network."""
+    from paper_2004_08771_amd import lib
+    name = lambda product, l: F32_KERNELS[lib().hb_plan_f32_kernel(product, dims[l], dims[l - 1], B, B, None)]
+    L = len(dims) - 1
+    return "; ".join([" ".join(name(0, l) for l in range(1, L + 1)), " ".join(name(1, l) for l in range(2, L + 1)),
+                      name(2, 1)])
+
+
+def bf16_plan(dims, B):
+    """"forward ...; backward-data of layers 2 ...; weight gradients" of a bf16 network, 16-byte aligned X."""
+    from paper_2004_08771_amd import lib
+    L = len(dims) - 1
+
+    def name(product, l):
+        v = lib().hb_plan_bf16_kernel(product, dims[l], dims[l - 1], B, (l == 1) + 2 * (l == L))
+        slices = lib().hb_plan_bf16_dw_slices(dims[l], dims[l - 1], B, 0) if product == 2 else 1
+        return (BF16_KERNELS[v & 15] + ("S" if v & 16 else "") + ("B" if v & 32 else "") +
+                (f"/{slices}" if slices > 1 else ""))
+
+    return "; ".join(" ".join(name(q, l) for l in range(2 if q == 1 else 1, L + 1)) for q in range(3))
+
+
 # ---------------------------------------------------------------- small shapes, every mode
 SMALL = [
     # dims, act, loss, B   (ragged everything: odd widths, B not a tile multiple)
@@ -880,20 +907,24 @@ def test_bf16_overshooting_step_on_one_row():
     check_bf16_case(dims, hi.ACT_RELU, loss, params, X, y, lr=0.05)
 
 
-@pytest.mark.parametrize("dims,act,loss,B", [
-    # every product of the two 2050-wide layers takes the LDS-direct 256 x 256 x 64 kernel (at least
-    # 128 tiles: 15 x 9) with a steady-state k loop: forward K = 520 and 2050 (8 and 32 k-tiles +
-    # tails), backward-data K = 2050 and 10 (tail only), weight gradients K = B = 3700 (split over
-    # the batch, operands batch-major: the row-major deltas and activations, a ragged last k-tile
-    # in every slice); ragged edges in every dimension
-    ((520, 2050, 2050, 10), hi.ACT_RELU, hi.LOSS_SOFTMAX_CE, 3700),
-    ((520, 2050, 2050, 10), hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, 3700),
+BF16_WIDE = [
+    # the forward and backward-data products of the two 2050-wide layers take the LDS-direct 256 x 256 x 64
+    # kernel (at least 128 tiles: 15 x 9) with a steady-state k loop: forward K = 520 and 2050 (8 and 32
+    # k-tiles + tails), backward-data K = 2050 and 10 (tail only); the weight gradient of layer 2, K = B = 3700,
+    # is split over the batch (operands batch-major: the row-major deltas and activations, a ragged last
+    # k-tile in every slice); ragged edges in every dimension
+    ((520, 2050, 2050, 10), hi.ACT_RELU, hi.LOSS_SOFTMAX_CE, 3700, "dma dma 64s; dma dma; 64B dmaB/3 64sB"),
+    ((520, 2050, 2050, 10), hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, 3700, "dma dma 64s; dma dma; 64B dmaB/3 64sB"),
     # rows of X that are not 16-byte aligned (d_0 = 516): the first layer's weight gradient cannot
     # read X itself and takes the transposed copies of X and of D_1 (written by the transpose
-    # kernel and by the backward-data epilogue of layer 2), the other layers the row-major tensors
-    ((516, 2050, 2050, 10), hi.ACT_RELU, hi.LOSS_SOFTMAX_CE, 3700),
-])
-def test_bf16_wide_layers_with_many_k_tiles(dims, act, loss, B):
+    # kernel and by the backward-data epilogue of layer 2), split over the batch; layer 2 the row-major tensors
+    ((516, 2050, 2050, 10), hi.ACT_RELU, hi.LOSS_SOFTMAX_CE, 5200, "128 dma 64s; dma dma; dma/5 dmaB/3 64sB"),
+]
+
+
+@pytest.mark.parametrize("dims,act,loss,B,plan", BF16_WIDE)
+def test_bf16_wide_layers_with_many_k_tiles(dims, act, loss, B, plan):
+    assert bf16_plan(dims, B) == plan
     params, X, y = _problem(dims, loss, B, seed=600 + B + len(dims), bias_scale=0.1)
     stats = check_bf16_case(dims, act, loss, params, X, y, lr=0.1, condition_relu=False)
     if act == hi.ACT_RELU:
@@ -937,16 +968,17 @@ def test_bf16_relu_batch_edges_of_the_backward_data_epilogue(B):
 @pytest.mark.parametrize("act", [hi.ACT_RELU, hi.ACT_SIGMOID])
 def test_bf16_one_replica_through_changing_batch_sizes(act):
     """What Adaptive Hogbatch does to the GPU worker: ONE replica, configured for the largest batch,
-    takes steps on batches of changing size.  The sizes move the weight gradients between their
-    two forms from step to step (below 2048 rows the transposed copies and K-major operands, from
-    2048 rows on the row-major tensors themselves, split over the batch) and the other products
-    between the 128 x 128 and the LDS-direct kernel, so every step finds the buffers as another
-    form left them.  Each step is compared with an oracle step from the replica's parameters
+    takes steps on batches of changing size.  The sizes move the weight gradients between the kernel of
+    small tiles (one or two groups of wavefronts) and, at 6100 rows, the LDS-direct one split over the batch,
+    and the other products between 64 x 64, 128 x 128 and LDS-direct tiles, so every step finds the buffers as
+    another form left them.  Each step is compared with an oracle step from the replica's parameters
     before it (read back), so errors do not add up over the ladder."""
     import paper_2004_08771_amd as hb
     torch = _torch()
     dims, loss, lr = (264, 2050, 520, 5), hi.LOSS_SOFTMAX_CE, 0.1
-    sizes = [300, 2500, 64, 4096, 1000, 2049, 1]
+    sizes = [300, 2500, 64, 6100, 1000, 4096, 2049, 1]
+    plans = [bf16_plan(dims, B) for B in sizes]
+    assert "dmaB/5" in plans[3] and "dma" in plans[5] and plans[1].startswith("128 64 ") and len(set(plans)) >= 5
     rng = np.random.default_rng(4242 + act)
     params = hi.xavier_uniform_params(dims, rng, bias_scale=0.1)
     m = hb.Model(dims, act, loss).configure(hb.HB_BF16_F32MASTER, max(sizes))
@@ -1099,18 +1131,37 @@ def test_step_can_be_captured_in_a_graph_and_replays_like_eager_steps(bf16):
 
 
 # ---------------------------------------------------------------- fp32 products as bf16 planes
-@pytest.mark.parametrize("dims,act,B", [
-    ((31, 40, 33, 20), hi.ACT_SIGMOID, 17),        # contractions of a single partial k-tile (17, 31, 20, 33 = 32 + 1)
-    ((32, 64, 64, 17), hi.ACT_RELU, 31),           # whole k-tiles forward, a lone partial one over the batch
-    ((100, 130, 65, 20), hi.ACT_SIGMOID, 2561),    # 64 x 64 tiles, both operands cut, rows not 16-byte aligned
-    ((97, 257, 129, 33), hi.ACT_RELU, 4099),       # 128 x 64
-    ((129, 520, 514, 40), hi.ACT_SIGMOID, 8200),   # 128 x 128, two values short of a 16-byte row
-    ((265, 258, 257, 40), hi.ACT_SIGMOID, 1030),   # 64 x 64 by two groups: nine k-tiles, the partial one first
-    ((300, 290, 270, 12), hi.ACT_RELU, 2100),      # ten k-tiles, rows and columns cut
-])
-def test_split_plane_products_at_tile_edges(dims, act, B):
+F32_EDGES = [
+    # contractions of a single partial k-tile (17, 31, 20, 33 = 32 + 1)
+    ((31, 40, 33, 20), hi.ACT_SIGMOID, 17, "64 64 64; 128x64 128x64; 64"),
+    # whole k-tiles forward, a lone partial one over the batch
+    ((32, 64, 64, 17), hi.ACT_RELU, 31, "64 small small; small 128x64; 64"),
+    # 64 x 64 by two groups backward, both operands cut, rows not 16-byte aligned
+    ((100, 130, 65, 20), hi.ACT_SIGMOID, 2561, "small small small; 64s 64s; small"),
+    # 64 x 64 by one group forward, four k-tiles, the partial one first
+    ((100, 330, 290, 40), hi.ACT_SIGMOID, 2561, "64 64s small; 128x64 64s; small"),
+    # the same backward; 128 x 64 forward
+    ((97, 257, 129, 33), hi.ACT_RELU, 4099, "128x64 64s small; 64 64s; small"),
+    # 128 x 128 backward, two values short of a 16-byte row
+    ((129, 520, 514, 40), hi.ACT_SIGMOID, 8200, "128x64 64s small; 128 128x64; 128"),
+    # 128 x 128 forward, rows and columns cut
+    ((100, 500, 500, 40), hi.ACT_RELU, 8150, "128 128 small; 128 128x64; small"),
+    # 64 x 64 by two groups: nine k-tiles, the partial one first
+    ((265, 258, 257, 40), hi.ACT_SIGMOID, 1030, "small small small; 64s 64s; small"),
+    # ten k-tiles, rows and columns cut
+    ((300, 290, 270, 12), hi.ACT_RELU, 2100, "64s 64s small; 128x64 64s; 128"),
+    # weight gradients on their own: 64 x 64, by two groups, 128 x 64
+    ((1100, 100, 40), hi.ACT_SIGMOID, 2101, "small small; 64s; 64"),
+    ((1020, 63, 40), hi.ACT_SIGMOID, 8201, "small 64; 64s; 64s"),
+    ((100, 130, 40), hi.ACT_SIGMOID, 8201, "128x64 small; 64s; 128x64"),
+]
+
+
+@pytest.mark.parametrize("dims,act,B,plan", F32_EDGES)
+def test_split_plane_products_at_tile_edges(dims, act, B, plan):
     """Each tile shape of the large fp32 products with rows, columns and k-tiles cut by the end of
     the matrix, rows of every alignment."""
+    assert f32_plan(dims, B) == plan
     params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=B)
     check_case(dims, act, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=B < 100)
 
@@ -1143,7 +1194,8 @@ def test_split_plane_products_of_tiny_operands():
     """Operands down to 2^-126 keep all their bits in the three planes: weights of 2^-116 against inputs of 2^100
     (forward), activations of 2^-116 (forward and weight gradient), deltas of 2^-117 (weight gradient of layer 1, read
     M-major).  Without a scale the planes of 2^-116 hold about 18 bits (relative error 2e-6)."""
-    dims, B = (300, 300, 290, 40), 2560      # 200 tiles of 64 x 64 and 2560 rows: none goes to the kernel of small products
+    dims, B = (300, 300, 290, 40), 2560
+    assert f32_plan(dims, B) == "64s 64s small; 128x64 64s; 128"
     rng = np.random.default_rng(11)
     W = [rng.standard_normal((300, 300)) * 2.0 ** -116, rng.standard_normal((290, 300)) * 2.0 ** -108,
          rng.standard_normal((40, 290)) * 0.1]
@@ -1172,6 +1224,7 @@ def test_split_plane_products_of_one_k_tile_are_exact_before_the_rounding(K):
     is the fp32 product (half a unit in the last place, 2^-24, and 2^-34 of it for x2 y2).  The six of longer contractions
     miss up to 2^-24 more, most for significands just above 1."""
     dims, B = (K, 330, 20), 2600
+    assert f32_plan(dims, B).startswith("64 ")
     rng = np.random.default_rng(K)
     W = (1.0 + 0.0039 * rng.random((330, K))).astype(np.float32)
     X = np.zeros((B, K), dtype=np.float32)
@@ -1187,17 +1240,42 @@ def test_split_plane_products_of_one_k_tile_are_exact_before_the_rounding(K):
     assert err <= 2.0 ** -24 * 1.01, f"{err:.2e}"
 
 
-# rows, columns and k-tiles cut; forward products of layer 1 in 64 x 64 (two groups: 300 deep; one: 100 deep), 128 x 64
-# and 128 x 128 tiles
-SPLIT_SIZES = [((300, 330, 290, 40), 2561), ((100, 330, 290, 40), 2561), ((130, 257, 250, 40), 4099),
-               ((100, 500, 500, 40), 8150)]
+# every shape of the split-plane kernels, forward and backward; rows, columns and k-tiles cut
+SPLIT_SIZES = [
+    ((300, 330, 290, 40), 2561, "64s 64s small; 128x64 64s; 128"),
+    ((100, 330, 290, 40), 2561, "64 64s small; 128x64 64s; small"),
+    ((130, 257, 250, 40), 4099, "128x64 128x64 small; 128 128x64; small"),
+    ((97, 257, 129, 33), 4099, "128x64 64s small; 64 64s; small"),
+    ((100, 500, 500, 40), 8150, "128 128 small; 128 128x64; small"),
+]
 
 
-@pytest.mark.parametrize("dims,B", SPLIT_SIZES)
-def test_split_plane_products_of_huge_operands(dims, B):
+@pytest.mark.parametrize("dims,B,plan", SPLIT_SIZES)
+def test_split_plane_products_are_as_close_to_64_bits_as_fp32_ones(dims, B, plan):
+    """Sums of up to 512 products: fp32 MFMAs are within 3e-7 (relative 2-norm), the planes within 1.3e-7; with the three
+    largest of the six products of planes alone it would be 4.4e-6."""
+    assert f32_plan(dims, B) == plan
+    params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=B + 1)
+    _, g, _, _, _, acts = gpu_grad_and_step(dims, hi.ACT_RELU, hi.LOSS_SOFTMAX_CE, params, X, y, 0.0, want_acts=True)
+    ref, ref_acts = _relu_gradient_in_64_bits(dims, params, X, y, {l: acts[l] > 0 for l in (1, 2)})
+    for l in (1, 2):
+        err = np.linalg.norm(acts[l] - ref_acts[l]) / np.linalg.norm(ref_acts[l])
+        assert err <= 3e-7 * l, f"activations of layer {l}: {err:.1e}"
+    off = 0
+    for l, (a, b) in enumerate(zip(dims[:-1], dims[1:]), 1):
+        r = ref[off:off + a * b]
+        err = np.linalg.norm(g[off:off + a * b] - r) / np.linalg.norm(r)
+        # up to three products forward and three backward, the loss's fast exponential and sums over the batch
+        assert err <= 1.5e-6, f"dW_{l}: {err:.1e}"
+        off += a * b + b
+
+
+@pytest.mark.parametrize("dims,B,plan", SPLIT_SIZES)
+def test_split_plane_products_of_huge_operands(dims, B, plan):
     """Operands of 2^104 and more have no finite planes and sums beyond 2^80 do not fit the scaled accumulators: those
     blocks are computed again with fp32 MFMAs.  Inputs of 2^105, weights of layer 2 of 2^106 and activations of
     2^99 send every product but the last layer's forward one there, with results that fp32 holds."""
+    assert f32_plan(dims, B) == plan
     rng = np.random.default_rng(B)
     scales = [2.0 ** -120, 2.0 ** 106, 2.0 ** -104]
     W = [rng.standard_normal((b, a)) * s for a, b, s in zip(dims[:-1], dims[1:], scales)]
@@ -1219,11 +1297,12 @@ def test_split_plane_products_of_huge_operands(dims, B):
             off += n
 
 
-@pytest.mark.parametrize("dims,B", SPLIT_SIZES)
-def test_split_plane_products_of_values_without_finite_planes(dims, B):
+@pytest.mark.parametrize("dims,B,plan", SPLIT_SIZES)
+def test_split_plane_products_of_values_without_finite_planes(dims, B, plan):
     """An infinite or nearly largest fp32 input has no finite leading bf16 part, yet the product is
     what fp32 arithmetic gives: a saturated unit, not a NaN.  In the first and the last row tile (cut) and in the
     partial k-tile."""
+    assert f32_plan(dims, B) == plan
     params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=5)
     X[3, 7], X[B - 1, dims[0] - 1], X[B - 2, dims[0] - 2] = np.inf, -np.inf, 3.4e38
     torch = _torch()
@@ -1277,46 +1356,72 @@ def test_nan_operands_stay_nan_and_cost_no_second_product():
 
 
 # ---------------------------------------------------------------- bf16 products of small tiles
-@pytest.mark.parametrize("dims,act,B", [
-    ((66, 65, 130, 3), hi.ACT_SIGMOID, 63),      # one partial k-tile over the batch, column pairs cut in the middle
-    ((65, 70, 5), hi.ACT_SIGMOID, 130),          # odd rows of X: element loads, transposed copies for dW_1
-    ((66, 129, 65, 2), hi.ACT_RELU, 577),        # contraction over the batch shared by two groups: 9 k-tiles and one row
-    ((514, 575, 33), hi.ACT_SIGMOID, 200),       # the same forward (575) and backward-data
-    ((300, 1030, 2), hi.ACT_RELU, 1025),         # one wavefront group each (more than 256 tiles)
-    ((70, 2100, 2060, 9), hi.ACT_RELU, 1600),    # 13 x 17 tiles of 128 x 128, cut in both directions
-])
-def test_bf16_small_tile_products_at_tile_edges(dims, act, B):
+BF16_SMALL_TILES = [
+    # one partial k-tile over the batch, column pairs cut in the middle
+    ((66, 65, 130, 3), hi.ACT_SIGMOID, 63, "64 64 64; 64 64; 64B 64B 64B"),
+    # odd rows of X: shifted loads, transposed copies for dW_1
+    ((65, 70, 5), hi.ACT_SIGMOID, 130, "64S 64; 64; 64 64B"),
+    # contraction over the batch shared by two groups: 9 k-tiles and one row
+    ((66, 129, 65, 2), hi.ACT_RELU, 577, "64 64 64; 64 64; 64sB 64sB 64sB"),
+    # the same forward (514, 575) ...
+    ((514, 575, 33), hi.ACT_SIGMOID, 200, "64s 64s; 64; 64B 64B"),
+    # ... and backward-data (575)
+    ((66, 300, 575, 33), hi.ACT_RELU, 200, "64 64 64s; 64s 64; 64B 64B 64B"),
+    # one wavefront group each (more than 256 tiles) forward
+    ((300, 1030, 2), hi.ACT_RELU, 1025, "64 64s; 64; 64sB 64sB"),
+    # 13 x 17 tiles of 128 x 128, cut in both directions
+    ((70, 2100, 2060, 9), hi.ACT_RELU, 1600, "128 128 64s; 128 128; 64sB 64B 64sB"),
+    # the same for a weight gradient from the transposed copies (odd rows of X)
+    ((1101, 3000, 2), hi.ACT_SIGMOID, 300, "64sS 64s; 64; 128 64B"),
+]
+
+
+@pytest.mark.parametrize("dims,act,B,plan", BF16_SMALL_TILES)
+def test_bf16_small_tile_products_at_tile_edges(dims, act, B, plan):
+    assert bf16_plan(dims, B) == plan
     params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=300 + B, bias_scale=0.1)
     check_bf16_case(dims, act, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=False)
 
 
-@pytest.mark.parametrize("dims,act,B", [
-    ((54, 2060, 40, 3), hi.ACT_RELU, 2100),     # 17 x 17 tiles, one k-tile: forward, and backward-data of layer 2 (K = 40)
-    ((63, 2060, 40, 3), hi.ACT_SIGMOID, 2100),  # the same from odd rows
-    ((100, 2900, 3), hi.ACT_SIGMOID, 2900),     # 23 x 23 tiles, two k-tiles
-    ((127, 2900, 3), hi.ACT_RELU, 2900),        # the same from odd rows, the partial one of 63
-])
-def test_bf16_short_contractions_with_many_tiles(dims, act, B):
+BF16_SHORT = [
+    # 17 x 17 tiles, one k-tile: forward, and backward-data of layer 2 (K = 40)
+    ((54, 2060, 40, 3), hi.ACT_RELU, 2100, "128s 64s 64; 128s 64; 64sB 64sB 64sB"),
+    # the same from odd rows
+    ((63, 2060, 40, 3), hi.ACT_SIGMOID, 2100, "128sS 64s 64; 128s 64; 64s 64sB 64sB"),
+    # 23 x 23 tiles, two k-tiles
+    ((100, 2900, 3), hi.ACT_SIGMOID, 2900, "128s 64s; dma; 64sB 64sB"),
+    # the same from odd rows, the partial one of 63
+    ((127, 2900, 3), hi.ACT_RELU, 2900, "128sS 64s; dma; 64s 64sB"),
+]
+
+
+@pytest.mark.parametrize("dims,act,B,plan", BF16_SHORT)
+def test_bf16_short_contractions_with_many_tiles(dims, act, B, plan):
     """Products of one or two k-tiles with more 128 x 128 tiles than compute units (and twice as many) run two
     workgroups per compute unit with two register sets."""
+    assert bf16_plan(dims, B) == plan
     params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=700 + dims[0], bias_scale=0.1)
     check_bf16_case(dims, act, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=False)
 
 
-@pytest.mark.parametrize("dims,B,at", [
-    ((63, 70, 5), 130, 0),        # one k-tile, element loads at its end
-    ((65, 129, 3), 200, 0),       # a whole k-tile and one value
-    ((65, 129, 3), 200, 1),       # the same from an odd address: other rows are the aligned ones
-    ((64, 66, 3), 67, 1),         # even rows from an odd address, whole k-tiles: the last one is taken as a partial one
-    ((577, 300, 2), 513, 0),      # two groups of wavefronts share ten k-tiles
-    ((201, 1030, 2), 1921, 1),    # 64 x 64 tiles, one group
-    ((201, 2060, 2), 1601, 0),    # 128 x 128 tiles, cut in both directions
-])
-def test_bf16_rows_of_X_that_are_not_4_byte_aligned(dims, B, at):
+BF16_SHIFTED = [
+    ((63, 70, 5), 130, 0, "64S"),        # one k-tile, element loads at its end
+    ((65, 129, 3), 200, 0, "64S"),       # a whole k-tile and one value
+    ((65, 129, 3), 200, 1, "64S"),       # the same from an odd address: other rows are the aligned ones
+    ((64, 66, 3), 67, 1, "64"),          # even rows from an odd address, whole k-tiles: the last one is taken as a partial one
+    ((577, 300, 2), 513, 0, "64sS"),     # two groups of wavefronts share ten k-tiles
+    ((201, 1030, 2), 1921, 1, "64S"),    # 64 x 64 tiles, one group
+    ((201, 2060, 2), 1601, 0, "128S"),   # 128 x 128 tiles, cut in both directions
+]
+
+
+@pytest.mark.parametrize("dims,B,at,first", BF16_SHIFTED)
+def test_bf16_rows_of_X_that_are_not_4_byte_aligned(dims, B, at, first):
     """The forward product of layer 1 reads such rows as aligned dwords and shifts them: the activations
     are those of the same X in rows of even pitch (the layer's other operand and the sums are the same, the order of
     the k-tiles may not be: fp32 sums, then rounded to bf16)."""
     import paper_2004_08771_amd as hb
+    assert bf16_plan(dims, B).split()[0] == first
     torch = _torch()
     params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=B + at)
     flat = torch.zeros(X.size + 1, dtype=torch.bfloat16, device="cuda")

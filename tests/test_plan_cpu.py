@@ -1,0 +1,31 @@
+"""The sizes of the parity tests reach the kernels that their comments name (the plans are host code)."""
+import pytest
+
+import test_parity_gpu as t
+
+
+@pytest.mark.parametrize("dims,B,plan", [(r[0], r[-2], r[-1]) for r in t.F32_EDGES] + t.SPLIT_SIZES)
+def test_f32_cases_run_the_kernels_they_name(dims, B, plan):
+    assert t.f32_plan(dims, B) == plan
+
+
+@pytest.mark.parametrize("dims,B,plan", [(r[0], r[-2], r[-1]) for r in t.BF16_WIDE + t.BF16_SMALL_TILES + t.BF16_SHORT])
+def test_bf16_cases_run_the_kernels_they_name(dims, B, plan):
+    assert t.bf16_plan(dims, B) == plan
+
+
+def test_the_cases_reach_every_kernel():
+    forward, pairs, alone = ({k for r in t.F32_EDGES for k in r[-1].split("; ")[q].split()} for q in range(3))
+    assert forward == set(t.F32_KERNELS) and pairs == set(t.F32_KERNELS) and alone == set(t.F32_KERNELS)
+    bf16 = [r[-1].split("; ") for r in t.BF16_WIDE + t.BF16_SMALL_TILES + t.BF16_SHORT]
+    forward, da, dw = ({k.split("/")[0] for r in bf16 for k in r[q].split()} for q in range(3))
+    assert forward | {r[-1] for r in t.BF16_SHIFTED} == {"dma", "128", "128s", "64", "64s", "64S", "64sS", "128S", "128sS"}
+    assert da == {"dma", "128", "128s", "64", "64s"}
+    assert dw == {"dma", "dmaB", "128", "64", "64B", "64s", "64sB"}
+
+
+def test_plans_refuse_invalid_arguments():
+    from paper_2004_08771_amd import lib
+    f, b = lib().hb_plan_f32_kernel, lib().hb_plan_bf16_kernel
+    assert f(0, 0, 5, 5, 5, None) == -1 and f(3, 5, 5, 5, 5, None) == -1 and f(0, 5, 5, 6, 5, None) == -1
+    assert b(0, 5, 0, 5, 0) == -1 and b(-1, 5, 5, 5, 0) == -1 and b(0, 5, (1 << 24) + 1, 5, 0) == -1

@@ -1556,9 +1556,10 @@ hipError_t launch_gemm_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, c
 int gemm_bf16_dw_form(int M, int N, int K, long long lda, long long ldb, const void *A, const void *B)
 {
     const size_t base = reinterpret_cast<size_t>(A) | reinterpret_cast<size_t>(B);
-    // 32-bit byte offsets over the k-rows of a tile, and whole column pairs in every row
-    if (((lda | ldb) & 1) || (base & 3) || lda < M + (M & 1) || ldb < N + (N & 1) || lda >= (1ll << 24) ||
-        ldb >= (1ll << 24))
+    // 32-bit byte offsets over the k-rows of a tile (64 rows of up to 2^24 values, the widest layer there is), and whole
+    // column pairs in every row
+    if (((lda | ldb) & 1) || (base & 3) || lda < M + (M & 1) || ldb < N + (N & 1) || lda > (1ll << 24) ||
+        ldb > (1ll << 24))
         return BF16_DW_KMAJ;
     // the LDS-direct kernel: 16-byte rows, and a product it is chosen for (split over the batch,
     // or at least 128 tiles)

@@ -24,6 +24,13 @@ def test_the_cases_reach_every_kernel():
     assert dw == {"dma", "dmaB", "128", "64", "64B", "64s", "64sB"}
 
 
+def test_the_widest_input_keeps_its_batch_major_weight_gradient():
+    """Rows of 2^24 values, the largest d_0, fit the kernels' 32-bit offsets: no transposed copy of X (32 MB a row)."""
+    from paper_2004_08771_amd import lib
+    for d_in in ((1 << 24) - 8, 1 << 24):
+        assert lib().hb_plan_bf16_kernel(2, 64, d_in, 300, 1) & 32, d_in
+
+
 def test_plans_refuse_invalid_arguments():
     from paper_2004_08771_amd import lib
     f, b = lib().hb_plan_f32_kernel, lib().hb_plan_bf16_kernel

@@ -264,7 +264,8 @@ int32_t hb_plan_bf16_dw_slices(int32_t d_out, int32_t d_in, int64_t B, int32_t c
 
 /*
  * Planning aids, host only: the kernel that a product of a d_out x d_in layer takes at batch size B.
- * product: 0 forward, 1 backward-data (fp32 mode: with the weight gradient of the layer, one launch),
+ * product: 0 forward, 1 backward-data (fp32 mode: with the weight gradient of the layer in one launch, but for
+ * batches under 64 of a layer of more than 2^24 weights),
  * 2 weight gradient (fp32 mode: on its own, as the first layer's).
  * fp32 mode, model configured for max_B: 0 tiles of 32 x 32 (small products), 1 64 x 64, 2 128 x 64, 3 128 x 128,
  * 4 64 x 64 with two groups of wavefronts; *slices (may be NULL): slices of the weight gradient's batch.

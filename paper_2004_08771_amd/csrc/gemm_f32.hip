@@ -342,19 +342,22 @@ __global__ __launch_bounds__(NT) void gemm_f32_small_kernel(GemmArgs a)
                                                        blockIdx.y);
 }
 
-// The backward pair of one hidden layer (see launch_gemm_f32_bwd_pair) for small batches.
+// The backward pair of one hidden layer (see launch_gemm_f32_bwd_pair) for small batches.  The product whose
+// workgroups walk the longer contraction goes first: of a wide layer the backward-data product, whose few workgroups
+// take most of the launch, while the many short ones of the weight gradient fill the other compute units (16 rows,
+// 2048 wide: 35.2 us with the weight gradient first, 27 so; 4096 wide 99 -> 60).
 __global__ __launch_bounds__(NT) void gemm_f32_small_pair_kernel(GemmArgs da, GemmArgs dw, int n_dw)
 {
     constexpr int LDS_DA = lds_floats<32, 32, SMALL_BK, true, false>();
     constexpr int LDS_DW = lds_floats<32, 32, SMALL_BK, false, false>();
     __shared__ __attribute__((aligned(16))) float smem[LDS_DA > LDS_DW ? LDS_DA : LDS_DW];
-    const int b = blockIdx.x;
-    if (b < n_dw) {
+    const int n_da = (int)gridDim.x - n_dw, dw_from = (da.K > dw.k_chunk) ? n_da : 0;
+    const int b = (int)blockIdx.x - dw_from;  // of the weight gradient if in [0, n_dw)
+    if (b >= 0 && b < n_dw) {
         const int tiles = dw.tiles_m * dw.tiles_n;
         gemm_f32_small_tile<SMALL_BK, false, false, GEMM_DW>(dw, smem, xcd_tile_order(b % tiles, tiles), b / tiles);
     } else {
-        const int n_da = gridDim.x - n_dw;
-        gemm_f32_small_tile<SMALL_BK, true, false, GEMM_DA>(da, smem, xcd_tile_order(b - n_dw, n_da), 0);
+        gemm_f32_small_tile<SMALL_BK, true, false, GEMM_DA>(da, smem, xcd_tile_order(dw_from ? (int)blockIdx.x : b - n_dw, n_da), 0);
     }
 }
 
@@ -566,12 +569,15 @@ F32Plan plan_f32(GemmKind kind, int M, int N, int K, int max_splits)
     if (sh == 0 && sp.chunk >= SHARED_K && tiles_of(sh, M, N) * sp.splits <= CUS) sh = SHARED;
     return {sh, sp};
 }
-// da M x N over K and dw M x N over K of one layer.  Against the split-plane tiles, 512-wide layers: B = 256
-// (32 tiles of 64 x 64) 9.7 us, B = 640 (80 tiles) 14.4 / 11.5 us, B = 1021 17.7 / 12.0 us.
+// da M x N over K and dw M x N over K of one layer.  Small tiles / split-plane tiles, 512-wide layers: B = 512 (64 tiles
+// of 64 x 64) 14.2 / 12.8 us, B = 640 16.3 / 12.3, B = 1024 18.3 / 13.2.  A long contraction favours the small ones
+// while each has a compute unit of its own: B = 256, 1024 wide (256 of 32 x 32) 22.7 / 24.2 us, B = 128, 2048 wide
+// 44.4 / 48.0; but B = 384, 1536 wide (576) 55 / 42.
 F32Plan plan_f32_pair(const GemmArgs &da, const GemmArgs &dw, int max_splits)
 {
     const int most = small_tiles_max() < 64 ? small_tiles_max() : 64;
-    if (da.K >= 64 && tiles_of(0, da.M, da.N) < most && dw.K < small_k_max())
+    const bool one_each = da.K >= 1024 && (long long)((da.M + 31) / 32) * ((da.N + 31) / 32) <= CUS;
+    if (da.K >= 64 && (tiles_of(0, da.M, da.N) < most || (one_each && most > 0)) && dw.K < small_k_max())
         return {-1, plan_small_splits(dw.K, max_splits)};
     const PairPlan pp = plan_pair(da, dw, max_splits);
     return {pp.shape, pp.split};
@@ -584,6 +590,9 @@ int gemm_f32_plan(int product, int B, int d_out, int d_in, int max_splits, int *
     F32Plan p;
     if (product == 0) {
         p = plan_f32(GEMM_FWD, B, d_out, d_in, 1);
+    } else if (product == 1 && !gemm_f32_pair_ok(B, d_out, d_in)) {
+        p = plan_f32(GEMM_DA, B, d_in, d_out, 1);
+        p.split.splits = plan_f32(GEMM_DW, d_out, d_in, B, max_splits).split.splits;
     } else if (product == 1) {
         GemmArgs da = {}, dw = {};
         da.M = B, da.N = d_in, da.K = d_out;
@@ -625,11 +634,13 @@ hipError_t launch_gemm_f32(GemmKind kind, GemmArgs a, int max_splits, int *split
 // dA_l and dW_l of one hidden layer in one launch: both only read D_l, so they are independent, and
 // sharing a launch lets the prologue / epilogue of one hide under the main loop of the other and pays
 // the per-launch latencies once (B = 16, 512-wide layers: 9.7 + 7.8 -> 8.7 us; B = 128, 32-wide:
-// 4.8 + 4.5 -> 7.4).  HB_NO_PAIR = 1 (tuning aid): two launches.
-bool gemm_f32_pair_ok()
+// 4.8 + 4.5 -> 7.4).  Apart only with fewer rows than a k-tile and a weight gradient of more than 2^24 values: its
+// 32 x 32 tiles then outlast the backward-data product (16 rows, 8192 wide: 158 us apart, 244 together; 4096 wide 66 / 62).
+// HB_NO_PAIR = 1 (tuning aid): two launches.
+bool gemm_f32_pair_ok(int B, int d_out, int d_in)
 {
     static const int off = env_int("HB_NO_PAIR", 0);
-    return !off;
+    return !off && (B >= SMALL_BK || (long long)d_out * d_in <= (1ll << 24));
 }
 
 hipError_t launch_gemm_f32_bwd_pair(GemmArgs da, GemmArgs dw, int max_splits, int *splits_out,

@@ -506,7 +506,7 @@ int run_step(hb_model *m, const Input &in, const int32_t *y, int64_t B, float lr
         const bool dense_dw = !(l == 1 && m->sparse);
         int splits = 1;
         bool dw_done = false;
-        if (l > 1 && dense_dw && gemm_f32_pair_ok()) {
+        if (l > 1 && dense_dw && gemm_f32_pair_ok(Bi, m->dims[l], m->dims[l - 1])) {
             HB_HIP(launch_gemm_f32_bwd_pair(
                 gda, gdw, m->cap_splits[l], &splits, st,
                 prof_begin(m, HB_K_BWD_PAIR, l, gda.M, gda.N, gda.K,

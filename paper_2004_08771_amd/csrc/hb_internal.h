@@ -62,7 +62,7 @@ hipError_t launch_gemm_f32(GemmKind kind, GemmArgs a, int max_splits, int *split
 
 // The backward-data and the weight-gradient product of one hidden layer in a single launch
 // (both read the same D_l and are independent), unless gemm_f32_pair_ok says to launch them apart.
-bool gemm_f32_pair_ok();
+bool gemm_f32_pair_ok(int B, int d_out, int d_in);
 hipError_t launch_gemm_f32_bwd_pair(GemmArgs da, GemmArgs dw, int max_splits, int *splits_out,
                                     hipStream_t stream, const LaunchEvents &ev = LaunchEvents());
 

@@ -1157,6 +1157,26 @@ F32_EDGES = [
 ]
 
 
+F32_FEW_ROWS = [
+    # the backward-data product's workgroups first (contraction 1100 against 17 rows) ...
+    ((20, 1100, 1100, 3), hi.ACT_SIGMOID, 17, "64 small small; small 128x64; 128x64"),
+    # ... also with 64 tiles of 64 x 64 (256 of 32 x 32); rows and columns cut
+    ((20, 1020, 1100, 3), hi.ACT_RELU, 225, "64 small small; small 128x64; small"),
+    # the weight gradient's first: as long a contraction
+    ((20, 200, 300, 3), hi.ACT_SIGMOID, 301, "64 small small; small 64s; small"),
+    # more than 2^24 weights and fewer than 64 rows: two launches
+    ((3, 4100, 4100, 2), hi.ACT_SIGMOID, 5, "64 small small; small 128x64; 128x64"),
+]
+
+
+@pytest.mark.parametrize("dims,act,B,plan", F32_FEW_ROWS)
+def test_backward_of_few_rows(dims, act, B, plan):
+    """Both orders of the workgroups in the paired launch of small tiles, and the launch of the two products apart."""
+    assert f32_plan(dims, B) == plan
+    params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=40 + B)
+    check_case(dims, act, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=False)
+
+
 @pytest.mark.parametrize("dims,act,B,plan", F32_EDGES)
 def test_split_plane_products_at_tile_edges(dims, act, B, plan):
     """Each tile shape of the large fp32 products with rows, columns and k-tiles cut by the end of

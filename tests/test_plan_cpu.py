@@ -4,7 +4,7 @@ import pytest
 import test_parity_gpu as t
 
 
-@pytest.mark.parametrize("dims,B,plan", [(r[0], r[-2], r[-1]) for r in t.F32_EDGES] + t.SPLIT_SIZES)
+@pytest.mark.parametrize("dims,B,plan", [(r[0], r[-2], r[-1]) for r in t.F32_EDGES + t.F32_FEW_ROWS] + t.SPLIT_SIZES)
 def test_f32_cases_run_the_kernels_they_name(dims, B, plan):
     assert t.f32_plan(dims, B) == plan
 

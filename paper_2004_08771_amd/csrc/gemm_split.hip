@@ -498,12 +498,22 @@ __device__ __forceinline__ void split_tile(const GemmArgs &a, char *smem, int id
                 if (!more) break;
             }
         }
-        read_frags(1, smem + (kt & 1) * STAGE, 1);
+        const bool lone = nk_all == 1, half = lone && kend - kbeg <= BK / 2;  // half: the second 16-deep step is zero
+        // (8192 x 8192 weight gradient over 16 rows: 78 -> 70 us)
+        if (!half) read_frags(1, smem + (kt & 1) * STAGE, 1);
 #pragma unroll
-        for (int i = 0; i < 2 * NM; ++i) mfma(i / NM, i % NM);
-        if (nk_all == 1) {  // the terms left out
+        for (int i = 0; i < NM; ++i) mfma(0, i);
+        if (lone) {  // the terms left out
 #pragma unroll
-            for (int i = 0; i < 4 * MF; ++i) mfma(i / (2 * MF), NM + i % (2 * MF));
+            for (int i = NM; i < NM + 2 * MF; ++i) mfma(0, i);
+        }
+        if (!half) {
+#pragma unroll
+            for (int i = 0; i < NM; ++i) mfma(1, i);
+            if (lone) {
+#pragma unroll
+                for (int i = NM; i < NM + 2 * MF; ++i) mfma(1, i);
+            }
         }
     };
     if (nk > 0) {

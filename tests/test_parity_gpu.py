@@ -1238,7 +1238,7 @@ def test_split_plane_products_of_tiny_operands():
             off += n
 
 
-@pytest.mark.parametrize("K", [1, 2, 31, 32])
+@pytest.mark.parametrize("K", [1, 2, 16, 17, 31, 32])
 def test_split_plane_products_of_one_k_tile_are_exact_before_the_rounding(K):
     """A contraction of one k-tile has all eight products of planes that fp32 can tell from nothing: a sum of one product
     is the fp32 product (half a unit in the last place, 2^-24, and 2^-34 of it for x2 y2).  The six of longer contractions

@@ -14,8 +14,8 @@
 // that produce a tensor also write its transposed copy, and the product runs K-major like the
 // other two.
 // Two kernel families: gemm_bf16_dma_kernel (256 x 256 x 64 tiles, LDS-direct loads) for the large
-// products, gemm_bf16_mid_kernel (64 x 64 x 64, operands global -> registers -> LDS) for all others.
-#include "hb_internal.h"
+// products, gemm_bf16_mid_kernel (64 x 64 x 64 or 128 x 128 x 64, operands global -> registers -> LDS) for all others.
+#include "gemm_device.h"
 
 #include <mutex>
 #include <stdlib.h>
@@ -84,14 +84,10 @@ struct TileB {
 template <int ACT>
 __device__ __forceinline__ float act_fwd(float z)
 {
-    if (ACT == ACT_SIGMOID) return __builtin_amdgcn_rcpf(1.0f + __expf(-z));
+    if (ACT == ACT_SIGMOID) return sigmoidf_fast(z);
     if (ACT == ACT_RELU) return fmaxf(z, 0.f);
     return z;
 }
-template <int V>
-struct IntC {
-    static constexpr int value = V;
-};
 // calls f(IntC<activation>, IntC<mask ? 1 : 0>) with the run-time activation as a constant
 template <typename F>
 __device__ __forceinline__ void with_activation(int act, bool mask, F &&f)
@@ -296,8 +292,8 @@ __device__ __forceinline__ void epilogue_bf16(const GemmBf16Args &a, v16f (&acc)
 // ---- products with too few 256 x 256 tiles: 64 x 64 or 128 x 128 tiles -----------------------
 // What bounds a product of this size is latency: a k-tile of 64 is only four MFMAs per block and
 // wavefront, and an L2 round trip under load takes about 550 cycles.  So four register sets keep
-// four k-tiles in flight per workgroup, and small tiles (32 or 48 KB of LDS, at most 128
-// registers) let several workgroups share a compute unit.  (2047 x 1024 x 1024 forward 33.7 us with
+// four k-tiles in flight per workgroup, and the 64 x 64 tiles (32 KB of LDS, 64 with two groups of
+// wavefronts; 129 to 150 registers) let several workgroups share a compute unit.  (2047 x 1024 x 1024 forward 33.7 us with
 // 128 x 128 x 64 tiles and two k-tiles in flight, 13.0 now; its weight gradient, with the passes that
 // transposed both operands and added the bias gradient up, 48 + 14 -> 19 us.)
 // LDS rows are 128 bytes, their eight 16-byte chunks exchanged by the row pair, which keeps the
@@ -1431,14 +1427,15 @@ hipError_t launch_mid_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, co
 }
 
 // 128 x 128 tiles where they (nearly) fill the compute units: half the operand bytes per flop
-// (1000 x 4096 x 4096, 256 tiles: 83 -> 55 us; 7001 x 1024 x 1024, 440 tiles: 31.2 -> 29.9).  Two of them
+// (against 64 x 64, both in turn: 1600 x 2050 x 2050, 221 tiles: 59.1 -> 32.8 us; 3300 x 1024 x 1024, 208: 21.6 -> 18.6;
+// 7001 x 1024 x 1024, 440: 34.2 -> 31.5; one and a half rounds lose a little, 3001 x 2048 x 1024, 384: 31.4 -> 32.6).  Two of them
 // on a compute unit for contractions of one k-tile with more than 256 tiles, and of two with more than 512
 // (4096 x 2048 x 54, 512 tiles: 17.5 -> 15.2 us; 16384 x 4096 x 100: 134 -> 123; but 8192 x 512 x 128, 256 tiles:
 // 9.4 -> 13.4, and 8192 x 1000 x 100, 512 tiles: 23.2 -> 25.3).
-// Else 64 x 64, with two groups of wavefronts per tile while the tiles do not fill the compute units twice and there are
+// Else 64 x 64, with two groups of wavefronts per tile while there are no more tiles than compute units and there are
 // k-tiles to share (1023 x 1024 x 1024: 12.6 -> 10.1 us, 1024 x 1024 x 2047 as a weight gradient 20.2 ->
-// 17.7 us); with more tiles the compute units are shared by workgroups anyway (7001 x 1024 x 1024:
-// 28.8 us with one group, 35.3 with two).
+// 17.7 us); with more tiles the compute units are shared by workgroups anyway (7001 x 1024 x 1024 in such tiles: two
+// groups take a fifth longer than one).
 int mid_kernel_of(GemmKind kind, const GemmBf16Args &a)
 {
     const long long tiles = (long long)((a.M + 63) / 64) * ((a.N + 63) / 64);

@@ -11,7 +11,7 @@
 // read one float per lane with the 32 rows of a block on consecutive addresses.  Epilogues fuse
 // bias + activation (forward), the activation derivative (backward-data) and the bias-gradient
 // column sums (weight gradient).  The large products are in gemm_split.hip.
-#include "hb_internal.h"
+#include "gemm_device.h"
 
 #include <stdlib.h>
 
@@ -145,36 +145,11 @@ struct Tile {
     }
 };
 
-__device__ __forceinline__ float sigmoidf_fast(float z)
-{
-    return __builtin_amdgcn_rcpf(1.0f + __expf(-z));  // v_rcp_f32: 1 ulp, no division sequence
-}
-
-template <int V>
-struct IntC {
-    static constexpr int value = V;
-};
-// calls f(IntC<activation>) with the run-time activation as a constant
-template <typename F>
-__device__ __forceinline__ void with_activation(int act, F &&f)
-{
-    if (act == ACT_SIGMOID) f(IntC<ACT_SIGMOID>());
-    else if (act == ACT_RELU) f(IntC<ACT_RELU>());
-    else f(IntC<ACT_NONE>());
-}
-
 // LDS floats one workgroup of this shape needs (two stages of an A and a B tile)
 template <int BM, int BN, int BK, bool A_KMAJ, bool B_KMAJ>
 constexpr int lds_floats()
 {
     return 2 * (Tile<BM, BK, A_KMAJ>::FLOATS + Tile<BN, BK, B_KMAJ>::FLOATS);
-}
-
-// XCD-aware tile order: consecutive hardware workgroup ids go round-robin over the 8 XCDs,
-// so give each XCD a contiguous run of the T tiles (they share an A row panel in its L2).
-__device__ __forceinline__ int xcd_tile_order(int b, int T)
-{
-    return ((T & 7) == 0) ? (b & 7) * (T >> 3) + (b >> 3) : b;
 }
 
 // ---- small products: one 32 x 32 output block per workgroup, the contraction split over
@@ -491,13 +466,14 @@ PairPlan plan_pair(const GemmArgs &da, const GemmArgs &dw, int max_splits)
     return best;
 }
 
-// Products with fewer 64 x 64 output tiles than this (forward / backward-data), or a
-// contraction shorter than small_k_max() (weight gradient, whose contraction is the batch),
-// go to the 32 x 32 split-wavefront kernel.  HB_GEMM_SMALL_TILES / HB_GEMM_SMALL_K: tuning aids
-// (0 switches the small kernels off).
+// Products with fewer 64 x 64 output tiles than this (forward / backward-data; plan_f32_pair has a line of its own),
+// or a contraction shorter than small_k_max() (weight gradient, whose contraction is the batch),
+// go to the 32 x 32 split-wavefront kernel.  Both lines were measured against 64 x 64 tiles on fp32 MFMAs.
+// HB_GEMM_SMALL_TILES / HB_GEMM_SMALL_K: tuning aids (0: no small kernel for outputs / for weight gradients; either
+// one for the paired launch).
 int small_tiles_max()
 {
-    static const int v = env_int("HB_GEMM_SMALL_TILES", 160);  // measured crossover: B = 1280 for 512-wide layers
+    static const int v = env_int("HB_GEMM_SMALL_TILES", 160);  // B = 1280 for 512-wide layers
     return v;
 }
 int small_k_max()

@@ -35,7 +35,7 @@
 // four wavefronts of 64 x 64 takes 49 us), fp32 in memory (planes written by the producer would be
 // 6 bytes per value through an L1 path of 64 B/clk that is already a third busy), no dot2 for the
 // remainders (one instruction instead of two, but it does not run beside an MFMA).
-#include "hb_internal.h"
+#include "gemm_device.h"
 
 #include <stdlib.h>
 
@@ -195,31 +195,6 @@ struct Op {
         return p * 64 + ((h ^ swz(p)) << 4);
     }
 };
-
-__device__ __forceinline__ float sigmoidf_fast(float z)
-{
-    return __builtin_amdgcn_rcpf(1.0f + __expf(-z));  // v_rcp_f32: 1 ulp, no division sequence
-}
-
-template <int V>
-struct IntC {
-    static constexpr int value = V;
-};
-// calls f(IntC<activation>) with the run-time activation as a constant
-template <typename F>
-__device__ __forceinline__ void with_activation(int act, F &&f)
-{
-    if (act == ACT_SIGMOID) f(IntC<ACT_SIGMOID>());
-    else if (act == ACT_RELU) f(IntC<ACT_RELU>());
-    else f(IntC<ACT_NONE>());
-}
-
-// XCD-aware tile order: consecutive hardware workgroup ids go round-robin over the 8 XCDs,
-// so give each XCD a contiguous run of the T tiles (they share an A row panel in its L2).
-__device__ __forceinline__ int xcd_tile_order(int b, int T)
-{
-    return ((T & 7) == 0) ? (b & 7) * (T >> 3) + (b >> 3) : b;
-}
 
 // One 32 x 32 block on fp32 MFMAs from the operands in memory, for one wavefront: lane (r, h) reads the values
 // k = 8 q + 4 h + c of its two rows, the k-tile ahead while the MFMAs of the present one run.  Rare: sums

@@ -24,12 +24,26 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-# MI355X dense MFMA peaks.  The fp32 products run as six bf16 MFMAs each (csrc/gemm_split.hip), so what
-# the matrix cores can give them is a sixth of the bf16 peak; fp32 MFMAs would give 157.3.
+# MI355X dense MFMA peaks.  The large fp32 products run as six bf16 MFMAs each (csrc/gemm_split.hip), so what
+# the matrix cores can give them is a sixth of the bf16 peak; small fp32 products run on fp32 MFMAs.
 PEAK_TFLOPS = {"f32": 2500.0 / 6, "bf16": 2500.0}
+PEAK_F32_MFMA_TFLOPS = 157.3
+
+
 PEAK_HBM_GBS = 8000.0
 WARM_SECONDS = 0.5     # untimed steps before the timed regions, at least
 REPEATS = 5            # timed regions of --steps steps each; the median is reported
+
+
+def mfma_peak(dtype_name, kernel, M, N, K, max_B):
+    """Peak of the MFMAs that a kernel of the profile runs on."""
+    if dtype_name != "f32":
+        return PEAK_TFLOPS[dtype_name]
+    import paper_2004_08771_amd as hb
+    product, d_out, d_in, B = {"fwd_gemm": (0, N, K, M), "bwd_pair": (1, K, N, M), "da_gemm": (1, K, N, M),
+                               "dw_gemm": (2, M, N, K)}.get(kernel, (None, 0, 0, 0))
+    split = product is not None and hb.lib().hb_plan_f32_kernel(product, d_out, d_in, B, max_B, None) > 0
+    return PEAK_TFLOPS["f32"] if split else PEAK_F32_MFMA_TFLOPS
 
 
 def parse_args():
@@ -235,12 +249,13 @@ def main():
             g["n"] += k["launches"]
         (name, M, N, K), g = max(groups.items(), key=lambda kv: kv[1]["ms"])
         avg_s = 1e-3 * g["ms"] / g["n"]
-        mfma_time = g["flops"] / (PEAK_TFLOPS[dtype_name] * 1e12)
+        peak = mfma_peak(dtype_name, name, M, N, K, B)
+        mfma_time = g["flops"] / (peak * 1e12)
         hbm_time = g["bytes"] / (PEAK_HBM_GBS * 1e9)
         if mfma_time >= hbm_time and g["flops"] > 0:
             ach = g["flops"] / avg_s / 1e12
-            roofline = {"bound": "mfma", "achieved": round(ach, 3), "peak": round(PEAK_TFLOPS[dtype_name], 1),
-                        "unit": "TFLOP/s", "frac": round(ach / PEAK_TFLOPS[dtype_name], 4)}
+            roofline = {"bound": "mfma", "achieved": round(ach, 3), "peak": round(peak, 1),
+                        "unit": "TFLOP/s", "frac": round(ach / peak, 4)}
         else:
             ach = g["bytes"] / avg_s / 1e9
             roofline = {"bound": "hbm", "achieved": round(ach, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",

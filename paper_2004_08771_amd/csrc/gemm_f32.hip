@@ -358,7 +358,7 @@ long long tiles_of(int sh, int M, int N)
 }
 
 // Clocks per k-tile of a workgroup, in hundreds, from time stamps around the main loop (MI355X,
-// K = 512): 64 x 64 9 alone on its compute unit (6 with two groups of wavefronts, which fill its LDS)
+// K = 512; taken, as the times below and plan_pair's, before the operands were scaled, which adds 2 to 4 % to all shapes): 64 x 64 9 alone on its compute unit (6 with two groups of wavefronts, which fill its LDS)
 // and 15 for two that share one, 128 x 64 12.5,
 // 128 x 128 20 (one per compute unit).  The shape with the shortest sequence of rounds wins:
 // 4096 x 512 outputs 14.6 us as 128 x 64 (256 workgroups), 16.8 as 64 x 64, 20 as 128 x 128;

@@ -27,7 +27,7 @@
 // infinite 257 us, 421 before, 262 on fp32 MFMAs alone.)
 //
 // What bounds it: power, then the instruction stream.  With nothing but the MFMAs of
-// 4096 x 1024 x 1024 in the loop the launch takes 33 us (clock 2.05 GHz); the whole kernel takes 45 us at
+// 4096 x 1024 x 1024 in the loop the launch takes 33 us (clock 2.05 GHz); the whole kernel takes 47 us (45 without the scale) at
 // 1.7 GHz and 2000 clocks per k-tile of a 128 x 128 tile, against 1536 of MFMA (fp32 MFMA kernel: 73 us).
 // Hence: the largest tile that still gives every compute unit a workgroup (fewer operand bytes
 // loaded, converted and read back per flop), eight wavefronts (one wavefront on a SIMD issues

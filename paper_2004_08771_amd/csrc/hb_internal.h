@@ -223,6 +223,45 @@ int out_layer_rows_for_batch(int d, int K, long long B);
 int out_layer_min_rows();
 hipError_t launch_out_layer(OutLayerArgs a, hipStream_t stream, const LaunchEvents &ev = LaunchEvents());
 
+// ---------------------------------------------------------------- small networks
+constexpr int SMALL_NET_LAYERS = 16, SMALL_NET_BLOCKS = 128;  // workgroups at most
+// What the kernel has to know of layer l (0: the input), in device memory: the arguments of a launch are read from the
+// host's memory, a line at a time, so a launch has few of them.
+struct SmallNetLayer {
+    int d, ld;            // width, pitch in LDS
+    int nt, inv_nt;       // blocks of 16, and 2^16 / nt
+    int cum;              // pitches of the layers before
+    int lds_w, lds_b;     // W_l and b_l in LDS (floats), [1 .. L]
+    int w_off, b_off;     // the same in the flat parameters
+    int act_ld;
+    float *act;           // [1 .. L - 1]: the hidden activations, B x act_ld
+    float *partial_w, *partial_b;  // several workgroups: sums over the rows of each, [block][d_l x d_(l-1)] and [block][d_l]
+};
+struct SmallNetArgs {
+    const SmallNetLayer *net;  // device
+    const int *place;          // device: every flat parameter's place in LDS
+    const float *params;
+    const float *X;            // B x d_0
+    const int32_t *y;
+    long long B;
+    int L, P, R;               // R: rows per workgroup, small_net_rows
+    int loss, act;             // HB_LOSS_*, ACT_*
+    int backward;              // 0: loss only
+    // one workgroup: the whole gradient goes to `grad` (flat), or with `update` the new parameters do (grad = params),
+    // and the mean loss to loss_out and loss_out2 (the second may be null)
+    float *grad;
+    int update;
+    float lr;
+    float *loss_out, *loss_out2;
+    float *block_partials;     // several: the loss of each block's rows
+    int lds_act, lds_delta[2], lds_red, lds_floats;  // set by the launcher
+};
+// Rows per workgroup for a batch of B rows, 0: the network goes through the kernels of its single layers.
+int small_net_rows(const int *dims, int L, long long B);
+// fills net[0 .. L] but for its pointers and act_ld, and place[0 .. P)
+void small_net_layers(const int *dims, int L, SmallNetLayer *net, int *place);
+hipError_t launch_small_net(const int *dims, SmallNetArgs a, hipStream_t stream, const LaunchEvents &ev = LaunchEvents());
+
 // ---------------------------------------------------------------- update
 // One segment = one parameter tensor: value[i] -= lr * sum_s partial[s*stride + i]   (STEP)
 //                                 or  grad[i]  =       sum_s partial[s*stride + i]   (GRAD)

@@ -221,6 +221,40 @@ def test_small_shapes_match_oracle(dims, act, loss, B):
     check_case(dims, act, loss, params, X, y, lr=0.1)
 
 
+@pytest.mark.parametrize("dims,act,loss,B", [
+    # one workgroup: row blocks of 16, 32 and 64 rows, full and cut; widths of one block of 16 and one value more or less
+    ((16, 15, 17, 16), hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, 16),
+    ((1, 33, 1), hi.ACT_SIGMOID, hi.LOSS_LOGISTIC, 17),
+    ((63, 48, 31, 2), hi.ACT_RELU, hi.LOSS_LOGISTIC, 32),
+    ((54, 32, 7), hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, 33),
+    ((65, 47, 3), hi.ACT_RELU, hi.LOSS_SOFTMAX_CE, 64),
+    # several: the last with one row; the most of them, and the first size with blocks of 32 and 64 rows
+    ((54, 32, 7), hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, 65),
+    ((20, 24, 24, 1), hi.ACT_SIGMOID, hi.LOSS_LOGISTIC, 2048),
+    ((33, 40, 12, 5), hi.ACT_RELU, hi.LOSS_SOFTMAX_CE, 2049),
+    ((9, 17, 16), hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, 4097),
+    # the most layers; nearly the most parameters of two layers
+    ((8,) + (10,) * 15 + (4,), hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, 50),
+    ((80, 100, 4), hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, 100),
+])
+def test_networks_that_fit_a_workgroup(dims, act, loss, B):
+    params, X, y = _problem(dims, loss, B, seed=200 + B + len(dims))
+    check_case(dims, act, loss, params, X, y, lr=0.1)
+    # a smaller batch on the same handle, and rows of X at an odd address: as a handle of its own
+    torch, n = _torch(), B // 2 + 1
+    buf = torch.zeros(n * dims[0] + 1, device="cuda")
+    buf[1:] = torch.from_numpy(X[:n].ravel().copy()).cuda()
+    yd, out = torch.from_numpy(y[:n].copy()).cuda(), []
+    for max_B, Xd in ((B, buf[1:]), (n, buf[1:].clone())):
+        m = make_model(dims, act, loss, max_B, params)
+        g = torch.empty(params.size, device="cuda")
+        l = m.batch_grad(Xd, yd, n, g)
+        out.append((l, g.cpu().numpy()))
+        m.destroy()
+    assert out[0][0] == out[1][0]
+    np.testing.assert_array_equal(out[0][1], out[1][1])
+
+
 WIDTHS = [1, 2, 3, 5, 7, 8, 13, 16, 17, 31, 32, 33, 54, 63, 64, 65, 96, 100, 127, 128, 129, 200, 256, 300, 512, 520]
 BATCHES = [1, 2, 3, 7, 16, 31, 32, 33, 63, 64, 65, 100, 127, 128, 129, 200, 255, 256, 257, 500, 769, 1000,
            1025, 1500, 2047, 2048, 2049]

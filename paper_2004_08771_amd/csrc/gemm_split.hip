@@ -394,52 +394,55 @@ __device__ __forceinline__ void split_tile(const GemmArgs &a, char *smem, int id
         __syncthreads();
         read_frags(0, smem, 0);
         int kt = 0;
-        for (bool more = nk > 1; more;) {
+        auto round = [&](int c, bool more) {  // more: a tile kt + 2 is prepared (past the end: the last one again, not used)
+            // Tile kt is in stage c % 2.  First half: the second half of tile kt + 1 goes to the other
+            // stage.  Second half, behind the barrier, when the fragments of tile kt have all been
+            // read: the first half of tile kt + 2 goes to stage c.  Every memory operation and
+            // every piece of the conversion has its place behind an MFMA.
+            const int s1 = (c + 1) % SETS, s2 = (c + 2) % SETS;  // register sets of tiles kt + 1, kt + 2
+            char *S = smem + (c & 1) * STAGE, *N = smem + ((c + 1) & 1) * STAGE;
 #pragma unroll
-            for (int c = 0; c < SETS; ++c) {
-                // Tile kt is in stage c % 2.  First half: the second half of tile kt + 1 goes to the other
-                // stage.  Second half, behind the barrier, when the fragments of tile kt have all been
-                // read: the first half of tile kt + 2 goes to stage c.  Every memory operation and
-                // every piece of the conversion has its place behind an MFMA.
-                const int s1 = (c + 1) % SETS, s2 = (c + 2) % SETS;  // register sets of tiles kt + 1, kt + 2
-                char *S = smem + (c & 1) * STAGE, *N = smem + ((c + 1) & 1) * STAGE;
+            for (int i = 0; i < NM; ++i) {
+                mfma(0, i);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int i = 0; i < NM; ++i) {
-                    mfma(0, i);
-                    __builtin_amdgcn_sched_barrier(0);
+                for (int f = 0; f < READS; ++f)
+                    if (f * (2 * NM / 3) / READS == i) read_frag(1, S, 1, f);
 #pragma unroll
-                    for (int f = 0; f < READS; ++f)
-                        if (f * (2 * NM / 3) / READS == i) read_frag(1, S, 1, f);
+                for (int p = PIECES / 2; p < PIECES; ++p)
+                    if ((p - PIECES / 2) * NM / (PIECES - PIECES / 2) == i) split_piece(s1, N, p, true);
 #pragma unroll
-                    for (int p = PIECES / 2; p < PIECES; ++p)
-                        if ((p - PIECES / 2) * NM / (PIECES - PIECES / 2) == i) split_piece(s1, N, p, true);
-#pragma unroll
-                    for (int v = 0; v < OA::LOADS; ++v)
-                        if (NM / 3 + v * (2 * NM / 3) / OA::LOADS == i) load_piece(s1, kt + 1 + SETS, v);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                __syncthreads();
-                const bool two = kt + 2 < nk;
-#pragma unroll
-                for (int i = 0; i < NM; ++i) {
-                    mfma(1, i);
-                    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int f = 0; f < READS; ++f)
-                        if (f * (2 * NM / 3) / READS == i) read_frag(0, N, 0, f);
-#pragma unroll
-                    for (int p = 0; p < PIECES / 2; ++p)
-                        if (p * NM / (PIECES / 2) == i) split_piece(s2, S, p, two);
-#pragma unroll
-                    for (int v = 0; v < OB::LOADS; ++v)
-                        if (v * NM / OB::LOADS == i) load_piece(s1, kt + 1 + SETS, OA::LOADS + v);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                ++kt;
-                more = kt + 1 < nk;
-                if (!more) break;
+                for (int v = 0; v < OA::LOADS; ++v)
+                    if (more && NM / 3 + v * (2 * NM / 3) / OA::LOADS == i) load_piece(s1, kt + 1 + SETS, v);
+                __builtin_amdgcn_sched_barrier(0);
             }
+            __syncthreads();
+            const bool two = kt + 2 < nk;
+#pragma unroll
+            for (int i = 0; i < NM; ++i) {
+                mfma(1, i);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int f = 0; f < READS; ++f)
+                    if (f * (2 * NM / 3) / READS == i) read_frag(0, N, 0, f);
+#pragma unroll
+                for (int p = 0; p < PIECES / 2; ++p)
+                    if (more && p * NM / (PIECES / 2) == i) split_piece(s2, S, p, two);
+#pragma unroll
+                for (int v = 0; v < OB::LOADS; ++v)
+                    if (more && v * NM / OB::LOADS == i) load_piece(s1, kt + 1 + SETS, OA::LOADS + v);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            ++kt;
+        };
+        // Whole turns of the register sets: where a way out in between reaches the head of the loop as well, the compiler
+        // cannot tell how many loads are in flight there and waits for all of them in every second k-tile (3001 x 1024 x 1024
+        // forward 40.8 -> 37.9 us, backward 78.0 -> 75.7; 3000 x 700 x 700 31.3 -> 28.7, 46.7 -> 45.9).
+        while (kt + 2 < nk) {
+            round(0, true);
+            round(1, true);
         }
+        if (kt + 1 < nk) round(0, false);
         const bool lone = nk_all == 1, half = lone && kend - kbeg <= BK / 2;  // half: the second 16-deep step is zero
         // (8192 x 8192 weight gradient over 16 rows: 78 -> 70 us)
         if (!half) read_frags(1, smem + (kt & 1) * STAGE, 1);

@@ -6,7 +6,7 @@
 // shuffles for the row reductions, no atomics.  The loss kernel leaves one partial sum per
 // block; the kernel that runs next in the stream anyway (the update, or a one-block
 // finalise kernel in loss-only / gradient-only calls) adds them up in index order.
-#include "hb_internal.h"
+#include "gemm_device.h"
 
 namespace hb {
 namespace {
@@ -158,26 +158,6 @@ __global__ __launch_bounds__(LOSS_NT) void loss_kernel(LossArgs a)
         __syncthreads();
     }
     if (tid == 0) a.block_partials[blockIdx.x] = red[0];
-}
-
-// mean loss = (sum of the block partials, in index order per thread then a fixed tree) / B
-__device__ __forceinline__ void loss_finalize(const LossFinalize &f, double *dred /* 256 */)
-{
-    const int tid = threadIdx.x;
-    double s = 0.0;
-    for (int i = tid; i < f.n; i += 256) s += (double)f.partials[i];
-    dred[tid] = s;
-    __syncthreads();
-#pragma unroll
-    for (int st = 128; st > 0; st >>= 1) {
-        if (tid < st) dred[tid] += dred[tid + st];
-        __syncthreads();
-    }
-    if (tid == 0) {
-        const float mean = (float)(dred[0] / (double)f.B);
-        f.out[0] = mean;
-        if (f.out2) f.out2[0] = mean;
-    }
 }
 
 __global__ __launch_bounds__(256) void loss_finalize_kernel(LossFinalize f)

@@ -92,6 +92,28 @@ __device__ __forceinline__ void load_rows(const RA &ra, const RB &rb, float *xa,
     }
 }
 
+// mean loss = (sum of the block partials, in index order per thread then a fixed tree) / B, by the first 256 threads
+__device__ __forceinline__ void loss_finalize(const LossFinalize &f, double *dred /* 256 */)
+{
+    const int tid = threadIdx.x;
+    if (tid < 256) {
+        double s = 0.0;
+        for (int i = tid; i < f.n; i += 256) s += (double)f.partials[i];
+        dred[tid] = s;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int st = 128; st > 0; st >>= 1) {
+        if (tid < st) dred[tid] += dred[tid + st];
+        __syncthreads();
+    }
+    if (tid == 0) {
+        const float mean = (float)(dred[0] / (double)f.B);
+        f.out[0] = mean;
+        if (f.out2) f.out2[0] = mean;
+    }
+}
+
 // XCD-aware tile order: consecutive hardware workgroup ids go round-robin over the 8 XCDs,
 // so give each XCD a contiguous run of the T tiles (they share an A row panel in its L2).
 __device__ __forceinline__ int xcd_tile_order(int b, int T)

@@ -737,7 +737,8 @@ int run_step_bf16(hb_model *m, const void *X, const int32_t *y, int64_t B, float
     la.block_partials = m->d_loss_partials;
     HB_HIP(launch_loss(la, st, prof_begin(m, HB_K_LOSS, 0, 0, 0, 0, 0.0, B * (4.0 * la.K + 2.0 * la.K + 4.0))));
     LossFinalize fin = {m->d_loss_partials, loss_grid_blocks(B, la.K), B, m->d_loss, d_loss_user};
-    HB_HIP(launch_loss_finalize(fin, st));
+    // the mean: with the weight gradient of the output layer where its kernel can
+    if (!back || bmaj[L] != BF16_DW_BMAJ_MID) HB_HIP(launch_loss_finalize(fin, st));
     if (!back) return HB_OK;
     if (!bmaj[L])
         HB_HIP(launch_transpose_bf16(m->delta_bf[L & 1], m->ld8[L], m->delta_t[L & 1], ldB, Bi, m->dims[L], st,
@@ -783,6 +784,7 @@ int run_step_bf16(hb_model *m, const void *X, const int32_t *y, int64_t B, float
         GemmBf16Args g = {};
         if (bmaj[l]) {
             g.bmaj = bmaj[l];
+            if (bmaj[l] == BF16_DW_BMAJ_MID && l == L) g.fin = fin;
             if (bmaj[l] == BF16_DW_BMAJ_MID)
                 g.bias_out = grad_mode ? d_grad_flat + m->b_off[l] : m->d_params + m->b_off[l];
             g.A = m->delta_bf[l & 1];

@@ -78,6 +78,15 @@ int gemm_f32_plan(int product, int B, int d_out, int d_in, int max_splits, int *
 // (so that the caller can size the partial buffers).
 int gemm_f32_dw_splits(int M, int N, int K, int max_splits);
 
+// The mean loss is finished by the next consumer on the stream: sum of n block partials / B.
+struct LossFinalize {
+    const float *partials;
+    int n;                   // 0: nothing to do
+    long long B;
+    float *out;              // 1 float: mean loss
+    float *out2;             // optional second destination (the caller's d_loss), may be null
+};
+
 // ---------------------------------------------------------------- bf16 MFMA GEMM
 // C[M x N] = sum_k A[m*lda + k] * B[n*ldb + k] (bmaj: A[k*lda + m] * B[k*ldb + n]), bf16 operands,
 // fp32 accumulation.  Outputs
@@ -126,6 +135,8 @@ struct GemmBf16Args {
     int bmaj;
     float *bias_out;       // BF16_DW_BMAJ_MID: the bias (updated), or its gradient (write_grad), of length M
     int tiles_m, tiles_n;
+    int xcd_m;             // set by the launcher of the small tiles
+    LossFinalize fin;      // BF16_DW_BMAJ_MID: n > 0 finishes the mean loss in the same launch
     // weight gradient split over the contraction (the batch): slice s covers k in
     // [s k_chunk, (s+1) k_chunk) and writes its plain fp32 partial product at
     // C_f32 + s c_split_stride (write_grad form, no bf16 outputs).  0: no split.
@@ -182,14 +193,6 @@ struct LossArgs {
     int zero_pad;            // bf16 delta: columns K .. ldd-1 of every row are written as zeros
     float *block_partials;   // one loss sum per block (>= loss_grid_blocks entries)
     int vec4;                // set by launch_loss: rows of Z and delta allow 16-byte / 8-byte accesses
-};
-// The mean loss is finished by the next consumer on the stream: sum of n block partials / B.
-struct LossFinalize {
-    const float *partials;
-    int n;                   // 0: nothing to do
-    long long B;
-    float *out;              // 1 float: mean loss
-    float *out2;             // optional second destination (the caller's d_loss), may be null
 };
 hipError_t launch_loss_finalize(const LossFinalize &f, hipStream_t stream,
                                 const LaunchEvents &ev = LaunchEvents());

@@ -1463,6 +1463,16 @@ def test_bf16_small_tile_products_at_tile_edges(dims, act, B, plan):
     check_bf16_case(dims, act, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=False)
 
 
+@pytest.mark.parametrize("d0,B", [(66, 64), (70, 65), (76, 128), (130, 129), (134, 1), (72, 640), (302, 641)])
+def test_bf16_weight_gradient_of_rows_without_padding(d0, B):
+    """The last columns of X's rows (2, 4 or 6 past a 16-byte piece) run on into the next row, the last batch row's must not:
+    batches that end with a k-tile of 64 and one row later, by one group of wavefronts and by two."""
+    dims = (d0, 70, 5)
+    assert bf16_plan(dims, B).split("; ")[2].split()[0] in ("64B", "64sB")
+    params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=500 + B + d0, bias_scale=0.1)
+    check_bf16_case(dims, hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=False)
+
+
 BF16_SHORT = [
     # 17 x 17 tiles, one k-tile: forward, and backward-data of layer 2 (K = 40)
     ((54, 2060, 40, 3), hi.ACT_RELU, 2100, "128s 64s 64; 128s 64; 64sB 64sB 64sB"),

@@ -66,11 +66,14 @@ struct TileB {
                 if (vec && k + 8 <= kend) {
                     x = *reinterpret_cast<const uint4 *>(p);
                 } else {
-                    unsigned int w[4] = {0u, 0u, 0u, 0u};
+                    // all eight are requested before the first is used (past the end: the last again); under a condition
+                    // each would wait for the one before it
+                    unsigned int b[8];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        if (k + e < kend) w[e >> 1] |= (unsigned int)p[e] << (16 * (e & 1));
-                    x = make_uint4(w[0], w[1], w[2], w[3]);
+                    for (int e = 0; e < 8; ++e) b[e] = p[min(e, kend - 1 - k)];
+#pragma unroll
+                    for (int e = 1; e < 8; ++e) b[e] = (k + e < kend) ? b[e] : 0u;
+                    x = make_uint4(b[0] | b[1] << 16, b[2] | b[3] << 16, b[4] | b[5] << 16, b[6] | b[7] << 16);
                 }
             }
             reg[v] = x;

@@ -550,7 +550,7 @@ bool small_out(int M, int N, int K)
 // is only a few tiles -- the first layer of a narrow input, 512 x 54 -- stays with the small
 // kernel up to four times that contraction length: with so few tiles the 64-wide kernel needs
 // tens of K-slices to fill the chip, and every slice is a partial the update has to read
-// (B = 4096, 512 x 54: 12.4 -> 11.0 us, and the update 7.7 -> 7.2 us, against fp32 MFMA tiles).
+// (B = 4096, 512 x 54: split-plane tiles 7.0 us and the update 7.95, small ones 5.2 and 7.2).
 long long small_dw_alone_kmax(int M, int N)  // contractions below this go to the small kernel
 {
     const bool few_tiles = (long long)((M + 63) / 64) * ((N + 63) / 64) <= 16;
@@ -624,10 +624,13 @@ F32Plan plan_f32(GemmKind kind, int M, int N, int K, int max_splits)
     if (sh == 0 && sp.chunk >= SHARED_K && tiles_of(sh, M, N) * sp.splits <= CUS) sh = SHARED;
     return {sh, sp};
 }
-// da M x N over K and dw M x N over K of one layer.  Small tiles / split-plane tiles, 512-wide layers: B = 512 (64 tiles
-// of 64 x 64) 14.2 / 12.8 us, B = 640 16.3 / 12.3, B = 1024 18.3 / 13.2.  A long contraction favours the small ones
-// while each has a compute unit of its own: B = 256, 1024 wide (256 of 32 x 32) 22.7 / 24.2 us, B = 128, 2048 wide
-// 44.4 / 48.0; but B = 384, 1536 wide (576) 55 / 42.
+// da M x N over K and dw M x N over K of one layer.  Small tiles / split-plane tiles, 512-wide layers: B = 640 (80 tiles
+// of 64 x 64) 12.4 / 10.3 us, B = 768 13.4 / 10.5, B = 1024 16.4 / 10.9; 256 wide, B = 2000 12.0 / 8.8; 1024 wide, B = 512
+// 29.8 / 25.0.  At just 64 tiles the small ones are ahead (512 wide, B = 512 9.1 / 10.1; 256 wide, B = 1024 6.9 / 7.7), but
+// their sums on fp32 MFMAs are further from 64 bits than the split-plane ones, so the line stays below 64.  A contraction
+// of 1024 and more goes to the small ones while each has a compute unit of its own (measured with the staged small kernel,
+// which was slower than the present one: B = 256, 1024 wide 22.7 / 24.2 us, B = 128, 2048 wide 44.4 / 48.0; B = 384,
+// 1536 wide, 576 tiles of 32 x 32, 55 / 42).
 F32Plan plan_f32_pair(const GemmArgs &da, const GemmArgs &dw, int max_splits)
 {
     const int most = small_tiles_max() < 64 ? small_tiles_max() : 64;
@@ -696,8 +699,8 @@ hipError_t launch_gemm_f32(GemmKind kind, GemmArgs a, int max_splits, int *split
 
 // dA_l and dW_l of one hidden layer in one launch: both only read D_l, so they are independent, and
 // sharing a launch lets the prologue / epilogue of one hide under the main loop of the other and pays
-// the per-launch latencies once (B = 16, 512-wide layers: 9.7 + 7.8 -> 8.7 us; B = 128, 32-wide:
-// 4.8 + 4.5 -> 7.4).  Apart only with fewer rows than a k-tile and a weight gradient of more than 2^24 values: its
+// the per-launch latencies once (B = 16, 512-wide layers: 4.7 + 5.1 us apart, 4.7 together; the step of
+// 54-512x4-7 70 / 55 us).  Apart only with fewer rows than a k-tile and a weight gradient of more than 2^24 values: its
 // 32 x 32 tiles then outlast the backward-data product (16 rows, 8192 wide: 158 us apart, 244 together; 4096 wide 66 / 62).
 // HB_NO_PAIR = 1 (tuning aid): two launches.
 bool gemm_f32_pair_ok(int B, int d_out, int d_in)

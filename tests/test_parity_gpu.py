@@ -255,6 +255,24 @@ def test_networks_that_fit_a_workgroup(dims, act, loss, B):
     np.testing.assert_array_equal(out[0][1], out[1][1])
 
 
+@pytest.mark.parametrize("dims,B", [((480, 16, 2), 32), ((480, 16, 2), 100), ((54, 32, 7), 64), ((40, 33, 2), 2000)])
+def test_networks_that_fit_a_workgroup_sum_in_short_chains(dims, B):
+    """A_1 of positive rows and weights.  The result's own rounding is 2.5e-8 to 3.4e-8 rms; one running fp32 sum of n such
+    terms adds 2^-24 sqrt(n) / 3 and more (n = 54: 1.1e-7 measured, 480: 2.9e-7), sums of sixteen terms that meet in a tree
+    2^-24 / 2 at most.  The kernels of the single layers: 4.8e-8 to 5.8e-8."""
+    torch, rng = _torch(), np.random.default_rng(5)
+    params = rng.random(hi.num_params(dims), dtype=np.float32)
+    X, y = rng.random((B, dims[0]), dtype=np.float32), rng.integers(0, 2, size=B).astype(np.int32)
+    m = make_model(dims, hi.ACT_RELU, hi.LOSS_SOFTMAX_CE, B, params)
+    m.batch_loss(torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda(), B)
+    got = gpu_hidden_activations(m, dims, B)[1]
+    m.destroy()
+    n = dims[0] * dims[1]
+    z = X.astype(np.float64) @ params[:n].astype(np.float64).reshape(dims[1], dims[0]).T + params[n:n + dims[1]]
+    err = np.sqrt(np.mean((got / z - 1.0) ** 2))
+    assert err <= 7.5e-8, f"{err:.2e}"
+
+
 WIDTHS = [1, 2, 3, 5, 7, 8, 13, 16, 17, 31, 32, 33, 54, 63, 64, 65, 96, 100, 127, 128, 129, 200, 256, 300, 512, 520]
 BATCHES = [1, 2, 3, 7, 16, 31, 32, 33, 63, 64, 65, 100, 127, 128, 129, 200, 255, 256, 257, 500, 769, 1000,
            1025, 1500, 2047, 2048, 2049]

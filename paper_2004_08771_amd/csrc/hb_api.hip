@@ -303,6 +303,24 @@ int ensure_csc_capacity(hb_model *m, int64_t nnz)
     return HB_OK;
 }
 
+// What the kernel of small networks reads, into d_net and m->d_net_place in stream order.
+int make_small_net_plan(hb_model *m, SmallNetLayer *d_net)
+{
+    SmallNetPlan plan = {};
+    small_net_layers(m->dims.data(), m->L, plan);
+    for (int l = 1; l <= m->L; ++l) {
+        plan.layer[l].act = m->acts[l];
+        plan.layer[l].act_ld = m->ld[l];
+        plan.layer[l].partial_w = m->partial_w[l];
+        plan.layer[l].partial_b = m->partial_b[l];
+    }
+    plan.net = d_net;
+    plan.place = m->d_net_place;
+    HB_HIP(launch_small_net_plan(plan, m->stream));
+    m->d_net = d_net;
+    return HB_OK;
+}
+
 // The whole step of a small network (see small_net_rows): one launch, two for a batch of several row blocks.
 int run_small_net(hb_model *m, const float *X, const int32_t *y, int64_t B, int rows, float lr, StepMode mode,
                   float *d_grad_flat, float *d_loss_user)
@@ -1283,33 +1301,10 @@ int hb_mlp_configure(hb_model *m, int dtype, int64_t max_B, int sparse_first_lay
                 rc = dev_alloc(m, &m->bias_partial[i], (size_t)rows * (size_t)max_d);
         }
     }
-    if (rc == HB_OK && small_net) {
-        std::vector<SmallNetLayer> net;
-        std::vector<int> place;
-        try {
-            net.resize(L + 1);
-            place.resize((size_t)m->P);
-        } catch (const std::bad_alloc &) {
-            rc = fail(HB_ERR_ALLOC, "out of host memory");
-        }
-        SmallNetLayer *d_net = nullptr;
-        if (rc == HB_OK) rc = dev_alloc(m, &d_net, net.size());
-        if (rc == HB_OK) rc = dev_alloc(m, &m->d_net_place, place.size());
-        if (rc == HB_OK) {
-            small_net_layers(m->dims.data(), L, net.data(), place.data());
-            for (int l = 1; l <= L; ++l) {
-                net[l].act = m->acts[l];
-                net[l].act_ld = m->ld[l];
-                net[l].partial_w = m->partial_w[l];
-                net[l].partial_b = m->partial_b[l];
-            }
-            if (hipMemcpy(d_net, net.data(), net.size() * sizeof(SmallNetLayer), hipMemcpyHostToDevice) != hipSuccess ||
-                hipMemcpy(m->d_net_place, place.data(), place.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess)
-                rc = fail(HB_ERR_DEVICE, "cannot copy the plan of a small network: %s", hipGetErrorString(hipGetLastError()));
-            else
-                m->d_net = d_net;
-        }
-    }
+    SmallNetLayer *d_net = nullptr;
+    if (rc == HB_OK && small_net) rc = dev_alloc(m, &d_net, (size_t)L + 1);
+    if (rc == HB_OK && small_net) rc = dev_alloc(m, &m->d_net_place, (size_t)m->P);
+    if (rc == HB_OK && small_net) rc = make_small_net_plan(m, d_net);
     if (m->sparse && rc == HB_OK) {
         const size_t d0 = (size_t)m->dims[0];
         rc = dev_alloc(m, &m->d_w1t, d0 * m->dims[1]);
@@ -1524,8 +1519,11 @@ int hb_batch_loss_static(const int32_t *layer_dims, int32_t n_dims, int activati
         const size_t ob = (size_t)((B + out_layer_min_rows() - 1) / out_layer_min_rows());
         if (ob > nblk) nblk = ob;
     }
-    // layout: [activations of layer 1 .. L, each B x ld_l floats][loss partials][mean loss], every
-    // part starting on a 256-byte boundary
+    // a small network goes through its own kernel, as on a handle
+    const int rows = small_net_rows(m->dims.data(), L, B);
+    if (rows > 0 && (size_t)((B + rows - 1) / rows) > nblk) nblk = (size_t)((B + rows - 1) / rows);
+    // layout: [activations of layer 1 .. L, each B x ld_l floats][loss partials][mean loss] and of a small network
+    // [layers][places of the parameters], every part starting on a 256-byte boundary
     auto align256 = [](size_t b) { return (b + 255) / 256 * 256; };
     size_t need = 0;
     std::vector<size_t> act_off(L + 1, 0);
@@ -1537,6 +1535,11 @@ int hb_batch_loss_static(const int32_t *layer_dims, int32_t n_dims, int activati
     need += align256(sizeof(float) * (nblk + 1));
     const size_t loss_off = need;
     need += 256;
+    // (these fit whenever the rest did: at most 8192 rows whose activations are in LDS, 64 at a time)
+    const size_t net_off = need;
+    if (rows > 0) need += align256(sizeof(SmallNetLayer) * (L + 1));
+    const size_t place_off = need;
+    if (rows > 0) need += align256(sizeof(int) * (size_t)m->P);
     if (need > STATIC_SCRATCH_BYTES)
         return fail(HB_ERR_UNSUPPORTED,
                     "hb_batch_loss_static: B = %lld rows of this network need %zu bytes of workspace, the static "
@@ -1550,6 +1553,11 @@ int hb_batch_loss_static(const int32_t *layer_dims, int32_t n_dims, int activati
     m->d_loss = reinterpret_cast<float *>(ws + loss_off);
     m->d_params = const_cast<float *>(d_params);  // MODE_LOSS only reads the parameters
     m->configured = true;
+    if (rows > 0) {
+        m->d_net_place = reinterpret_cast<int *>(ws + place_off);
+        rc = make_small_net_plan(m, reinterpret_cast<SmallNetLayer *>(ws + net_off));
+        if (rc != HB_OK) return rc;
+    }
     Input in;
     in.X = dX;
     return run_step(m, in, dy, B, 0.f, MODE_LOSS, nullptr, d_loss);

@@ -261,8 +261,16 @@ struct SmallNetArgs {
 };
 // Rows per workgroup for a batch of B rows, 0: the network goes through the kernels of its single layers.
 int small_net_rows(const int *dims, int L, long long B);
-// fills net[0 .. L] but for its pointers and act_ld, and place[0 .. P)
-void small_net_layers(const int *dims, int L, SmallNetLayer *net, int *place);
+// What the kernel reads of a network, made on the device by one launch: `layer` goes to net[0 .. L], and place[0 .. P) follows.
+struct SmallNetPlan {
+    SmallNetLayer layer[SMALL_NET_LAYERS + 1];
+    SmallNetLayer *net;
+    int *place;
+    int L, P;
+};
+// fills plan.layer but for its pointers and act_ld, and plan.L, plan.P
+void small_net_layers(const int *dims, int L, SmallNetPlan &plan);
+hipError_t launch_small_net_plan(const SmallNetPlan &plan, hipStream_t stream);
 hipError_t launch_small_net(const int *dims, SmallNetArgs a, hipStream_t stream, const LaunchEvents &ev = LaunchEvents());
 
 // ---------------------------------------------------------------- update

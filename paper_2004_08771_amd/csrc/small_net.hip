@@ -262,6 +262,18 @@ __global__ __launch_bounds__(SN_NT) void small_net_kernel(SmallNetArgs a)
     }
 }
 
+__global__ __launch_bounds__(256) void small_net_plan_kernel(SmallNetPlan p)
+{
+    if (blockIdx.x == 0 && (int)threadIdx.x <= p.L) p.net[threadIdx.x] = p.layer[threadIdx.x];
+    for (int e = blockIdx.x * 256 + threadIdx.x; e < p.P; e += gridDim.x * 256) {
+        int l = 1;
+        while (l < p.L && e >= p.layer[l + 1].w_off) ++l;
+        const SmallNetLayer &o = p.layer[l];
+        const int i = e - o.w_off, di = p.layer[l - 1].d, row = i / di;
+        p.place[e] = (e >= o.b_off) ? o.lds_b + e - o.b_off : o.lds_w + row * p.layer[l - 1].ld + i - row * di;
+    }
+}
+
 // LDS of a block of R rows in floats; the offsets of `a` and the layers' places (either may be null)
 int lds_floats(const int *dims, int L, int R, SmallNetArgs *a, SmallNetLayer *net)
 {
@@ -311,8 +323,9 @@ int small_net_rows(const int *dims, int L, long long B)
     return 0;
 }
 
-void small_net_layers(const int *dims, int L, SmallNetLayer *net, int *place)
+void small_net_layers(const int *dims, int L, SmallNetPlan &plan)
 {
+    SmallNetLayer *net = plan.layer;
     lds_floats(dims, L, 16, nullptr, net);
     int at = 0;
     for (int l = 0; l <= L; ++l) {
@@ -323,11 +336,16 @@ void small_net_layers(const int *dims, int L, SmallNetLayer *net, int *place)
         o.inv_nt = (65536 + o.nt - 1) / o.nt;  // (i inv_nt) >> 16 = i / nt for i < 4096
         if (l == 0) continue;
         o.w_off = at;
-        for (int i = 0; i < dims[l]; ++i)
-            for (int k = 0; k < dims[l - 1]; ++k) place[at++] = o.lds_w + i * pitch(dims[l - 1]) + k;
-        o.b_off = at;
-        for (int i = 0; i < dims[l]; ++i) place[at++] = o.lds_b + i;
+        o.b_off = at + dims[l] * dims[l - 1];
+        at = o.b_off + dims[l];
     }
+    plan.L = L;
+    plan.P = at;
+}
+
+hipError_t launch_small_net_plan(const SmallNetPlan &plan, hipStream_t stream)
+{
+    return launch_kernel(small_net_plan_kernel, dim3((unsigned)((plan.P + 255) / 256)), dim3(256), stream, LaunchEvents(), plan);
 }
 
 hipError_t launch_small_net(const int *dims, SmallNetArgs a, hipStream_t stream, const LaunchEvents &ev)

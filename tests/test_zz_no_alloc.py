@@ -16,6 +16,11 @@ CASES = [
     ((70, 65, 129, 67, 2), hi.ACT_RELU, hi.LOSS_LOGISTIC, 321, 33),                 # ragged widths, 2-way logistic
     ((40, 72, 100), hi.ACT_RELU, hi.LOSS_SOFTMAX_CE, 500, 77),                      # wide output: general product + loss kernel
     ((33, 1), hi.ACT_SIGMOID, hi.LOSS_LOGISTIC, 130, 1),                            # no hidden layer
+    # networks that fit a workgroup: one block of rows and several, the most layers, and more rows than that kernel takes
+    ((54, 32, 7), hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, 2000, 64),
+    ((20, 24, 24, 1), hi.ACT_RELU, hi.LOSS_LOGISTIC, 65, 16),
+    ((8,) + (10,) * 15 + (4,), hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, 4097, 33),
+    ((200, 60, 60, 10), hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, 8200, 300),
 ]
 
 
@@ -73,3 +78,30 @@ def test_static_loss_rejects_what_does_not_fit_and_bad_arguments():
         assert e.value.code == hb.HB_ERR_INVALID
     hb.batch_loss_static(dims, 0, 0, p, x, y, 16, out)     # zero weights: ln 7
     assert abs(float(out.cpu()[0]) - np.log(7.0)) < 1e-6
+
+
+def test_static_loss_of_a_small_network_can_be_captured():
+    """Kernels only: five replays with eager work of the caller's own between them, each equal to the eager result."""
+    import torch
+    import paper_2004_08771_amd as hb
+    dims, B = (54, 32, 7), 300
+    rng = np.random.default_rng(99)
+    p = torch.from_numpy(hi.xavier_uniform_params(dims, rng, bias_scale=0.2)).cuda()
+    X = torch.from_numpy(rng.standard_normal((B, dims[0]), dtype=np.float32)).cuda()
+    y = torch.from_numpy(rng.integers(0, 5, size=B).astype(np.int32)).cuda()
+    st = torch.cuda.Stream()
+    out, want = torch.zeros(1, device="cuda"), torch.zeros(1, device="cuda")
+    other = torch.ones(1 << 16, device="cuda")
+    torch.cuda.synchronize()
+    hb.batch_loss_static(dims, 0, 0, p, X, y, B, want, st.cuda_stream)
+    st.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=st):
+        hb.batch_loss_static(dims, 0, 0, p, X, y, B, out, st.cuda_stream)
+    for k in range(5):
+        out.zero_()
+        hb.batch_loss_static((33, 40, 5), 1, 0, p, X, y, 64, other)  # another network in the same workspace
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert float(out) == float(want), k

@@ -274,9 +274,12 @@ int32_t hb_plan_bf16_dw_slices(int32_t d_out, int32_t d_in, int64_t B, int32_t c
  * gradient from the batch-major tensors.  layer: 1 for the first layer, 2 for the last, 3 for both, else 0.
  * Products of the fused output layer, of a CSR first layer and of a dense fp32 network that fits a workgroup run other
  * kernels.  -1 on invalid arguments.
+ * hb_plan_small_net: whether a dense fp32 network (layer_dims and n_dims as for hb_mlp_create) fits a workgroup at batch
+ * size B: the rows each workgroup takes through the whole network (16, 32 or 64), 0 if its layers run kernels of their own.
  */
 int32_t hb_plan_f32_kernel(int32_t product, int32_t d_out, int32_t d_in, int64_t B, int64_t max_B, int32_t *slices);
 int32_t hb_plan_bf16_kernel(int32_t product, int32_t d_out, int32_t d_in, int64_t B, int32_t layer);
+int32_t hb_plan_small_net(const int32_t *layer_dims, int32_t n_dims, int64_t B);
 
 /* Library version string, e.g. for logs. */
 const char *hb_version(void);

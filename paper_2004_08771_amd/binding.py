@@ -40,6 +40,7 @@ SIGNATURES = {
     "hb_plan_bf16_dw_slices": (_i32, [_i32, _i32, _i64, _i32]),
     "hb_plan_f32_kernel": (_i32, [_i32, _i32, _i32, _i64, _i64, _i32p]),
     "hb_plan_bf16_kernel": (_i32, [_i32, _i32, _i32, _i64, _i32]),
+    "hb_plan_small_net": (_i32, [_i32p, _i32, _i64]),
 }
 
 HB_K_NAMES = {0: "fwd_gemm", 1: "da_gemm", 2: "dw_gemm", 3: "loss", 4: "update", 5: "spmm_fwd",

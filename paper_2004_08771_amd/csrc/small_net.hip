@@ -304,23 +304,30 @@ int lds_floats(const int *dims, int L, int R, SmallNetArgs *a, SmallNetLayer *ne
 
 }  // namespace
 
-// A narrow output, and everything in LDS.  Up to 64 rows in one workgroup; above, blocks of 16 rows (32, 64) for up to 128
-// workgroups, whose partial sums a second launch adds.  Launches of the single layers / so, us per step: 54-32-7 64 rows 21.1 / 10.9,
-// 2048 rows 24.0 / 13.0; 32x8-2 64 rows 86 / 31, 5000 rows 110 / 36; 64x4-5 32 rows 36.7 / 21.6, 2000 rows 45.7 / 25.3; 200-60-60-10
-// 1000 rows 38.8 / 24.7.  A chain of few layers with many parameters is as fast in launches of their own, each on more
-// compute units (100-100-100-3 100 rows 27.3 / 26.5, 3000 rows 40 / 42; 100-100-7 64 rows 18.8 / 18.5; 105-108-4 13.9 / 17.8; 500-32-2
-// 100 rows 19.2 / 21.1): hence the limit on the parameters.
+// A narrow output, and everything in LDS.  Up to 64 rows in one workgroup if so large a block fits; above, blocks of 16 rows
+// (32, 64) for up to 128 workgroups, whose partial sums a second launch adds.  Launches of the single layers / so, us per step:
+// 54-32-7 64 rows 21.1 / 11.1, 2048 rows 24.0 / 13.9; 32x8-2 64 rows 86 / 31, 5000 rows 110 / 36; 64x4-5 32 rows 36.7 / 21.3, 2000 rows
+// 45.7 / 25.7; 200-60-60-10 1000 rows 38.8 / 25.3.  A chain of few layers with many parameters is as fast in launches of their own,
+// each on more compute units (100-100-100-3 100 rows 27.3 / 26.5, 3000 rows 40 / 42; 100-100-7 64 rows 18.8 / 18.5; 105-108-4
+// 13.9 / 17.8; 500-32-2 100 rows 19.2 / 21.1): hence the limit on the parameters.  Where a block of all rows does not fit, 17 .. 64
+// rows go in blocks of 16: 64x4-5 40 rows 35.5 / 21.7, 64 rows 31.6 / 21.8; 200-60-60-10 64 rows 33.9 / 22.8; 400-20-20-3 28.4 /
+// 21.1; 100-64x5-4 32 rows 46.0 / 31.9; but two layers are faster apart (80-100-4 15.5 / 17.3; 500-16-2 15.7 / 18.3; 1000-8-2 16.1 /
+// 24.9).  More than 128 blocks cost as much to add up as the layers' launches: with blocks of 16 54-32-7 8193 rows 28.2 / 30.4,
+// 16000 rows 31.6 / 44.4; 64x4-5 4097 rows 45.2 / 44.6; 200-60-60-10 4097 rows 45.2 / 49.5; 80-100-4 24.0 / 34.6; only a chain
+// of many narrow layers would gain (32x8-2 8193 rows 128 / 75).
 int small_net_rows(const int *dims, int L, long long B)
 {
     if (L < 2 || L > SMALL_NET_LAYERS || dims[L] > 16) return 0;
     long long P = 0;
     for (int l = 1; l <= L; ++l) P += (long long)dims[l] * (dims[l - 1] + 1);
     if (P > 9000ll * (L - 1)) return 0;
+    bool fits = false;
     for (int R = 16; R <= 64; R *= 2) {
-        if (lds_floats(dims, L, R, nullptr, nullptr) > SN_LDS_FLOATS) return 0;
+        if (lds_floats(dims, L, R, nullptr, nullptr) > SN_LDS_FLOATS) break;
+        fits = true;
         if (B <= R || (B > 64 && B <= (long long)R * SMALL_NET_BLOCKS)) return R;
     }
-    return 0;
+    return (fits && B <= 64 && L > 2) ? 16 : 0;  // too many rows for one block
 }
 
 void small_net_layers(const int *dims, int L, SmallNetPlan &plan)

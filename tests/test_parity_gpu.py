@@ -181,6 +181,13 @@ def f32_plan(dims, B):
                       name(2, 1)])
 
 
+def small_net_rows(dims, B):
+    """Rows per workgroup of a dense fp32 network that fits one, 0: its layers run kernels of their own."""
+    import ctypes
+    from paper_2004_08771_amd import lib
+    return lib().hb_plan_small_net((ctypes.c_int32 * len(dims))(*dims), len(dims), B)
+
+
 def bf16_plan(dims, B):
     """"forward ...; backward-data of layers 2 ...; weight gradients" of a bf16 network, 16-byte aligned X."""
     from paper_2004_08771_amd import lib
@@ -233,6 +240,9 @@ def test_small_shapes_match_oracle(dims, act, loss, B):
     ((20, 24, 24, 1), hi.ACT_SIGMOID, hi.LOSS_LOGISTIC, 2048),
     ((33, 40, 12, 5), hi.ACT_RELU, hi.LOSS_SOFTMAX_CE, 2049),
     ((9, 17, 16), hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, 4097),
+    # up to 64 rows in several blocks of 16: one row over, all of them
+    ((64, 64, 64, 64, 5), hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, 33),
+    ((100, 64, 64, 64, 64, 64, 4), hi.ACT_RELU, hi.LOSS_SOFTMAX_CE, 64),
     # the most layers; nearly the most parameters of two layers
     ((8,) + (10,) * 15 + (4,), hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, 50),
     ((80, 100, 4), hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, 100),

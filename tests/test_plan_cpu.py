@@ -44,8 +44,26 @@ def test_bf16_weight_gradients_are_split_where_the_small_tiles_fall_behind(d_out
     assert caps == sorted(caps)
 
 
+@pytest.mark.parametrize("dims,rows", [
+    # {batch: rows per workgroup}: every block size fits
+    ((54, 32, 7), {1: 16, 16: 16, 17: 32, 33: 64, 64: 64, 65: 16, 2048: 16, 2049: 32, 4097: 64, 8192: 64, 8193: 0}),
+    # blocks of 32 rows at most, and of 16: more rows in several blocks of 16, also below 65
+    ((64, 64, 64, 64, 5), {32: 32, 33: 16, 48: 16, 64: 16, 65: 16, 4096: 32, 4097: 0}),
+    ((100, 64, 64, 64, 64, 64, 4), {16: 16, 17: 16, 33: 16, 64: 16, 65: 16, 2048: 16, 2049: 0}),
+    # two layers: apart where a block of all rows does not fit
+    ((80, 100, 4), {32: 32, 33: 0, 64: 0, 65: 16}),
+    ((100, 100, 100, 3), {16: 0, 100: 0}), ((54, 32, 17), {16: 0}), ((54, 7), {16: 0}),
+])
+def test_small_networks_take_any_batch_up_to_their_largest(dims, rows):
+    assert {B: t.small_net_rows(dims, B) for B in rows} == rows
+    if len(dims) > 3 and rows.get(16, 16):  # no gap
+        most = max(B for B in rows if rows[B])
+        assert all(t.small_net_rows(dims, B) for B in range(1, most + 1))
+
+
 def test_plans_refuse_invalid_arguments():
     from paper_2004_08771_amd import lib
     f, b = lib().hb_plan_f32_kernel, lib().hb_plan_bf16_kernel
     assert f(0, 0, 5, 5, 5, None) == -1 and f(3, 5, 5, 5, 5, None) == -1 and f(0, 5, 5, 6, 5, None) == -1
+    assert t.small_net_rows((5,), 5) == -1 and t.small_net_rows((5, 0, 5), 5) == -1 and t.small_net_rows((5, 5, 5), 0) == -1
     assert b(0, 5, 0, 5, 0) == -1 and b(-1, 5, 5, 5, 0) == -1 and b(0, 5, (1 << 24) + 1, 5, 0) == -1

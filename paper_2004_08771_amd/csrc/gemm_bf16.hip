@@ -17,7 +17,6 @@
 // products, gemm_bf16_mid_kernel (64 x 64 x 64 or 128 x 128 x 64, operands global -> registers -> LDS) for all others.
 #include "gemm_device.h"
 
-#include <mutex>
 #include <stdlib.h>
 
 #include <type_traits>
@@ -1560,17 +1559,9 @@ hipError_t launch_dma_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, co
                               : a.bmaj          ? gemm_bf16_dma_kernel<GEMM_DW, true>
                                                 : gemm_bf16_dma_kernel<GEMM_DW>;
     const int slot = (kind == GEMM_DW && a.bmaj) ? 3 : (int)kind;
-    static std::mutex attr_mu;
-    static bool attr_set[4] = {false, false, false, false};
-    {
-        std::lock_guard<std::mutex> lk(attr_mu);
-        if (!attr_set[slot]) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)DMA_LDS_BYTES);
-            if (e != hipSuccess) return e;
-            attr_set[slot] = true;
-        }
-    }
+    static LdsGrant granted[4];
+    const hipError_t e = grant_lds(granted[slot], DMA_LDS_BYTES, k);
+    if (e != hipSuccess) return e;
     a.tiles_m = (a.M + DMA_BM - 1) / DMA_BM;
     a.tiles_n = (a.N + DMA_BN - 1) / DMA_BN;
     const long long tiles = (long long)a.tiles_m * a.tiles_n;

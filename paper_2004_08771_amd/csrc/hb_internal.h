@@ -5,6 +5,8 @@
 #include <hip/hip_ext.h>
 #include <stdint.h>
 
+#include "lds_grant.h"
+
 struct hb_model;
 
 namespace hb {
@@ -25,6 +27,21 @@ inline hipError_t launch_kernel(F kernel, dim3 grid, dim3 block, hipStream_t str
     else
         hipLaunchKernelGGL(kernel, grid, block, 0, stream, args...);
     return hipGetLastError();
+}
+
+// `bytes` of dynamic LDS for the kernels on the current device
+template <typename... Kernels>
+inline hipError_t grant_lds(LdsGrant &grant, size_t bytes, Kernels... kernels)
+{
+    int device = -1;
+    const hipError_t e = hipGetDevice(&device);
+    if (e != hipSuccess) return e;
+    return grant.ensure(device, bytes, [&]() {
+        hipError_t r = hipSuccess;
+        for (const void *k : {reinterpret_cast<const void *>(kernels)...})
+            if (r == hipSuccess) r = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        return r;
+    });
 }
 
 // ---------------------------------------------------------------- fp32 MFMA GEMM

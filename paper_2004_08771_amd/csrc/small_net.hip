@@ -11,8 +11,6 @@
 // lie in host memory, the step took 17 us.)
 #include "gemm_device.h"
 
-#include <mutex>
-
 namespace hb {
 namespace {
 
@@ -360,18 +358,9 @@ hipError_t launch_small_net(const int *dims, SmallNetArgs a, hipStream_t stream,
     a.lds_floats = lds_floats(dims, a.L, a.R, &a, nullptr);
     const size_t lds = 4 * (size_t)a.lds_floats;
     if (lds > 4 * (size_t)SN_LDS_FLOATS) return hipErrorInvalidValue;
-    {
-        static std::mutex granted_mu;  // handles on different host threads launch concurrently
-        static size_t granted = 0;
-        std::lock_guard<std::mutex> lk(granted_mu);
-        if (lds > granted) {
-            for (const void *k : {reinterpret_cast<const void *>(small_net_kernel<ACT_SIGMOID>), reinterpret_cast<const void *>(small_net_kernel<ACT_RELU>)}) {
-                const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-                if (e != hipSuccess) return e;
-            }
-            granted = lds;
-        }
-    }
+    static LdsGrant granted;
+    const hipError_t e = grant_lds(granted, lds, small_net_kernel<ACT_SIGMOID>, small_net_kernel<ACT_RELU>);
+    if (e != hipSuccess) return e;
     const dim3 grid((unsigned)((a.B + a.R - 1) / a.R)), block(SN_NT);
     const auto kernel = a.act == ACT_SIGMOID ? small_net_kernel<ACT_SIGMOID> : small_net_kernel<ACT_RELU>;
     if (ev.start) hipExtLaunchKernelGGL(kernel, grid, block, (unsigned)lds, stream, ev.start, ev.stop, 0, a);

@@ -295,7 +295,7 @@ __device__ __forceinline__ void epilogue_bf16(const GemmBf16Args &a, v16f (&acc)
 // What bounds a product of this size is latency: a k-tile of 64 is only four MFMAs per block and
 // wavefront, and an L2 round trip under load takes about 550 cycles.  So four register sets keep
 // four k-tiles in flight per workgroup, and the 64 x 64 tiles (32 KB of LDS, 64 with two groups of
-// wavefronts; 110 to 133 registers) let several workgroups share a compute unit.  (2047 x 1024 x 1024 forward 33.7 us with
+// wavefronts; 144 to 168 registers) let several workgroups share a compute unit.  (2047 x 1024 x 1024 forward 33.7 us with
 // 128 x 128 x 64 tiles and two k-tiles in flight, 12.1 now; its weight gradient, with the passes that
 // transposed both operands and added the bias gradient up, 48 + 14 -> 14.7 us.)  A round of the loop still takes some 1300
 // clocks: LDS write, barrier, LDS read and the chain of four MFMAs follow each other.
@@ -580,12 +580,11 @@ void gemm_bf16_mid_kernel(GemmBf16Args a)
         if constexpr (BMAJ) {
             fa[step][0] = OA::frag(S, wm, step, lane);
             fb[step] = OB::frag(S + A_BYTES, wn, step, lane);
-            return;
         } else {
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
-            fa[step][i] = *reinterpret_cast<const v8bf *>(S + OA::frag(wm * (TILE / 2) + i * 32 + r, 2 * step + h));
-        fb[step] = *reinterpret_cast<const v8bf *>(S + A_BYTES + OB::frag(wn * 32 + r, 2 * step + h));
+            for (int i = 0; i < TM; ++i)
+                fa[step][i] = *reinterpret_cast<const v8bf *>(S + OA::frag(wm * (TILE / 2) + i * 32 + r, 2 * step + h));
+            fb[step] = *reinterpret_cast<const v8bf *>(S + A_BYTES + OB::frag(wn * 32 + r, 2 * step + h));
         }
     };
 

@@ -527,9 +527,15 @@ PairPlan plan_pair(const GemmArgs &da, const GemmArgs &dw, int max_splits)
     return best;
 }
 
-// Products with fewer 64 x 64 output tiles than this (forward / backward-data; plan_f32_pair has a line of its own),
-// or a contraction shorter than small_k_max() (weight gradient, whose contraction is the batch),
-// go to the kernels of small products.  Both lines were measured against 64 x 64 tiles on fp32 MFMAs.
+// Products with fewer 64 x 64 output tiles than small_tiles_max() (forward / backward-data; plan_f32_pair has a line of its
+// own), or a contraction shorter than small_k_max() (weight gradient, whose contraction is the batch), go to the kernels
+// of small products.  Small / split planes, us, forward products 512 wide: contraction of 128 4.4 / 5.0 with 64 tiles, 5.1 / 5.4
+// with 128, 5.9 / 5.6 with 152; of 256 4.7 / 6.4, 7.0 / 6.9, 8.2 / 7.0; of 512 7.5 / 9.2 with 64, 9.9 / 9.3 with 80, 9.8 / 9.4 with
+// 128, 11.7 / 9.4 with 152; of 1024 11.3 / 14.6, 15.8 / 14.7, 15.8 / 14.5, 19.8 / 14.8.  So the line of 160 tiles is that of
+// contractions up to 256; longer ones would be 0.5 to 5 us shorter as split planes from 80 tiles on.
+// Contractions below 64 stay with split planes, although the small kernels are quicker there (512 x 54 forward, 16 rows 5.3 us,
+// small 4.2; pair of 512 x 40, 48 rows 6.8, 4.2): over 300 drawn networks with inputs below 64 and 4 .. 63 rows their gradients
+// would be 1.035 times as far from 64 bits.
 // HB_GEMM_SMALL_TILES / HB_GEMM_SMALL_K: tuning aids (0: no small kernel for outputs / for weight gradients; either
 // one for the paired launch).
 int small_tiles_max()
@@ -550,7 +556,11 @@ bool small_out(int M, int N, int K)
 // is only a few tiles -- the first layer of a narrow input, 512 x 54 -- stays with the small
 // kernel up to four times that contraction length: with so few tiles the 64-wide kernel needs
 // tens of K-slices to fill the chip, and every slice is a partial the update has to read
-// (B = 4096, 512 x 54: split-plane tiles 7.0 us and the update 7.95, small ones 5.2 and 7.2).
+// (512 x 54, small / split planes: 1000 rows 4.8 / 6.9 us, 4096 rows 5.3 / 8.0, 8000 rows 7.8 / 8.3, 8192 rows 8.1 / 8.6,
+// 12000 rows 11.6 / 9.8; 100 x 100: 6000 rows 5.6 / 6.3, 8000 rows 6.7 / 6.6).  For other outputs: 1024 x 300, 80 tiles,
+// 1000 rows 11.3 / 12.0, 2000 rows 16.5 / 19.6 (a longer update with it), 2500 rows 21.2 / 15.5; 2048 x 600, 320 tiles,
+// 500 rows 18.2 / 18.8, 1000 rows 28.1 / 27.3, 2000 rows 52 / 44; of 1024 x 1024, 256 tiles, split planes would be ahead
+// at every batch (500 rows 14.3 / 11.4 and 1.7 us more in the update, 1000 rows 25 / 17, 2000 rows 46 / 27).
 long long small_dw_alone_kmax(int M, int N)  // contractions below this go to the small kernel
 {
     const bool few_tiles = (long long)((M + 63) / 64) * ((N + 63) / 64) <= 16;
@@ -568,8 +578,8 @@ int small_tile(int M, int N, bool pair)
 {
     return (long long)((M + 15) / 16) * ((N + 15) / 16) <= (pair ? CUS : 2 * CUS) ? 16 : 32;
 }
-// Weight gradient: a wavefront per block where the blocks alone occupy the device for as long as one of them walks the
-// batch (pairs with a workgroup per block / so: 1024 blocks, 64 rows 11.5 / 10.8 us, 128 rows 14.1 / 10.6, 220 rows 18.0 / 19.5;
+// Weight gradient: a wavefront per block for up to 32 rows, where a block takes one wavefront no longer than eight need to
+// meet, and where the blocks alone occupy the device for as long as one of them walks the batch (pairs with a workgroup per block / so: 1024 blocks, 64 rows 11.5 / 10.8 us, 128 rows 14.1 / 10.6, 220 rows 18.0 / 19.5;
 // 484 blocks, 64 rows 8.7 / 6.5, 150 rows 9.4 / 10.5; 256 blocks, 16 rows 5.1 / 4.5, 64 rows 5.4 / 5.8; 4096 blocks, 32 rows
 // 27.4 / 18.4).  Above 128 rows its registers would spill.
 int small_dw_wave(int M, int N, int K)  // 0, or the rows in units of 64
@@ -606,7 +616,7 @@ int gemm_f32_dw_splits(int M, int N, int K, int max_splits)
 
 namespace {
 
-// shape < 0: the kernel of small products (tiles of 32 x 32), else the one launch_gemm_split takes
+// shape < 0: the kernels of small products (blocks of 16 x 16 or 32 x 32), else the one launch_gemm_split takes
 struct F32Plan {
     int shape;
     SplitPlan split;
@@ -628,9 +638,10 @@ F32Plan plan_f32(GemmKind kind, int M, int N, int K, int max_splits)
 // of 64 x 64) 12.4 / 10.3 us, B = 768 13.4 / 10.5, B = 1024 16.4 / 10.9; 256 wide, B = 2000 12.0 / 8.8; 1024 wide, B = 512
 // 29.8 / 25.0.  At just 64 tiles the small ones are ahead (512 wide, B = 512 9.1 / 10.1; 256 wide, B = 1024 6.9 / 7.7), but
 // their sums on fp32 MFMAs are further from 64 bits than the split-plane ones, so the line stays below 64.  A contraction
-// of 1024 and more goes to the small ones while each has a compute unit of its own (measured with the staged small kernel,
-// which was slower than the present one: B = 256, 1024 wide 22.7 / 24.2 us, B = 128, 2048 wide 44.4 / 48.0; B = 384,
-// 1536 wide, 576 tiles of 32 x 32, 55 / 42).
+// of 1024 and more goes to the small ones while each block of 32 x 32 has a compute unit of its own: 1024 wide, B = 128
+// (128 blocks) 10.7 / 21.2 us, B = 256 (256) 18.6 / 22.2, B = 320 (320) 21.0 / 23.1, B = 512 (512) 29.6 / 25.5; 2048 wide, B = 128 (256)
+// 33.3 / 44.7, B = 192 (384) 48.9 / 48.7, B = 256 (512) 58.6 / 50.9; 1536 wide, B = 170 (288) 30.3 / 36.7, B = 256 (384) 35.6 /
+// 33.6; 4096 wide, B = 64 (256) 69 / 97, B = 128 (512) 118 / 118.
 F32Plan plan_f32_pair(const GemmArgs &da, const GemmArgs &dw, int max_splits)
 {
     const int most = small_tiles_max() < 64 ? small_tiles_max() : 64;

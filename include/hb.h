@@ -267,18 +267,22 @@ int32_t hb_plan_bf16_dw_slices(int32_t d_out, int32_t d_in, int64_t B, int32_t c
  * product: 0 forward, 1 backward-data (fp32 mode: with the weight gradient of the layer in one launch, but for
  * batches under 64 of a layer of more than 2^24 weights),
  * 2 weight gradient (fp32 mode: on its own, as the first layer's).
- * fp32 mode, model configured for max_B: 0 tiles of 32 x 32 (small products), 1 64 x 64, 2 128 x 64, 3 128 x 128,
+ * fp32 mode, model configured for max_B: 0 small products (blocks of 16 x 16 or 32 x 32), 1 64 x 64, 2 128 x 64, 3 128 x 128,
  * 4 64 x 64 with two groups of wavefronts; *slices (may be NULL): slices of the weight gradient's batch.
  * bf16 mode: 1 256 x 256 (LDS-direct), 2 128 x 128, 3 128 x 128 with two workgroups per compute unit, 4 64 x 64,
  * 5 64 x 64 with two groups; + 16: rows of X that are not 4-byte aligned (16-byte aligned dX assumed), + 32: weight
  * gradient from the batch-major tensors.  layer: 1 for the first layer, 2 for the last, 3 for both, else 0.
  * Products of the fused output layer, of a CSR first layer and of a dense fp32 network that fits a workgroup run other
  * kernels.  -1 on invalid arguments.
+ * hb_plan_f32_small_form: how a small product (hb_plan_f32_kernel: 0) runs, 0 if it is none.  The block, 16 or 32; + 64: operands
+ * through LDS (forward); + 128 or + 256: weight gradient with a wavefront to each block of 32 x 32 over up to 64 or 128 rows
+ * (product 1: that of the same launch, beside the block of the backward-data product).
  * hb_plan_small_net: whether a dense fp32 network (layer_dims and n_dims as for hb_mlp_create) fits a workgroup at batch
  * size B: the rows each workgroup takes through the whole network (16, 32 or 64), 0 if its layers run kernels of their own.
  */
 int32_t hb_plan_f32_kernel(int32_t product, int32_t d_out, int32_t d_in, int64_t B, int64_t max_B, int32_t *slices);
 int32_t hb_plan_bf16_kernel(int32_t product, int32_t d_out, int32_t d_in, int64_t B, int32_t layer);
+int32_t hb_plan_f32_small_form(int32_t product, int32_t d_out, int32_t d_in, int64_t B, int64_t max_B);
 int32_t hb_plan_small_net(const int32_t *layer_dims, int32_t n_dims, int64_t B);
 
 /* Library version string, e.g. for logs. */

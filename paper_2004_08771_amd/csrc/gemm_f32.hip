@@ -578,6 +578,11 @@ int small_tile(int M, int N, bool pair)
 {
     return (long long)((M + 15) / 16) * ((N + 15) / 16) <= (pair ? CUS : 2 * CUS) ? 16 : 32;
 }
+// Forward products of more 32 x 32 blocks than compute units pass through LDS (see gemm_f32_staged_kernel).
+bool small_staged(int M, int N)
+{
+    return (long long)((M + 31) / 32) * ((N + 31) / 32) > CUS;
+}
 // Weight gradient: a wavefront per block for up to 32 rows, where a block takes one wavefront no longer than eight need to
 // meet, and where the blocks alone occupy the device for as long as one of them walks the batch (pairs with a workgroup per block / so: 1024 blocks, 64 rows 11.5 / 10.8 us, 128 rows 14.1 / 10.6, 220 rows 18.0 / 19.5;
 // 484 blocks, 64 rows 8.7 / 6.5, 150 rows 9.4 / 10.5; 256 blocks, 16 rows 5.1 / 4.5, 64 rows 5.4 / 5.8; 4096 blocks, 32 rows
@@ -674,6 +679,20 @@ int gemm_f32_plan(int product, int B, int d_out, int d_in, int max_splits, int *
     return p.shape;
 }
 
+int gemm_f32_small_form(int product, int B, int d_out, int d_in, int max_splits)
+{
+    int splits = 1;
+    if (gemm_f32_plan(product, B, d_out, d_in, max_splits, &splits) >= 0) return 0;
+    if (product == 0) {
+        const int block = small_tile(B, d_out, false);
+        return block + (block == 32 && small_staged(B, d_out) ? 64 : 0);
+    }
+    const int wave = small_dw_wave(d_out, d_in, std::min(B, plan_small_splits(B, max_splits).chunk));
+    if (product == 2) return 32 + 128 * wave;
+    const bool pair = gemm_f32_pair_ok(B, d_out, d_in);
+    return small_tile(B, d_in, pair) + (pair ? 128 * wave : 0);
+}
+
 hipError_t launch_gemm_f32(GemmKind kind, GemmArgs a, int max_splits, int *splits_out,
                            hipStream_t stream, const LaunchEvents &ev)
 {
@@ -693,7 +712,7 @@ hipError_t launch_gemm_f32(GemmKind kind, GemmArgs a, int max_splits, int *split
     switch (kind) {
     case GEMM_FWD:
         if (small == 16) return launch_kernel(gemm_f32_small_kernel<16, true, true, GEMM_FWD>, grid, dim3(NT), stream, ev, a);
-        if (tiles > CUS) return launch_kernel(gemm_f32_staged_kernel, grid, dim3(STAGED_NT), stream, ev, a);
+        if (small_staged(a.M, a.N)) return launch_kernel(gemm_f32_staged_kernel, grid, dim3(STAGED_NT), stream, ev, a);
         return launch_kernel(gemm_f32_small_kernel<32, true, true, GEMM_FWD>, grid, dim3(NT), stream, ev, a);
     case GEMM_DA:
         if (small == 16) return launch_kernel(gemm_f32_small_kernel<16, true, false, GEMM_DA>, grid, dim3(NT), stream, ev, a);

@@ -1085,6 +1085,14 @@ int32_t hb_plan_f32_kernel(int32_t product, int32_t d_out, int32_t d_in, int64_t
     return shape + 1;
 }
 
+int32_t hb_plan_f32_small_form(int32_t product, int32_t d_out, int32_t d_in, int64_t B, int64_t max_B)
+{
+    if (product < 0 || product > 2 || d_out < 1 || d_in < 1 || d_out > MAX_DIM || d_in > MAX_DIM || B < 1 || B > max_B ||
+        max_B > MAX_BATCH)
+        return -1;
+    return gemm_f32_small_form(product, (int)B, d_out, d_in, gemm_f32_dw_splits(d_out, d_in, (int)max_B, MAX_SPLITS));
+}
+
 int32_t hb_plan_small_net(const int32_t *layer_dims, int32_t n_dims, int64_t B)
 {
     if (!layer_dims || n_dims < 2 || n_dims > MAX_LAYERS + 1 || B < 1 || B > MAX_BATCH) return -1;

@@ -90,6 +90,8 @@ hipError_t launch_gemm_split_pair(const GemmArgs &da, const GemmArgs &dw, int sh
 // The kernel and the batch slices of a layer's product (0 forward, 1 backward pair, 2 weight gradient alone): -1 the
 // kernel of small products, else the shape launch_gemm_split takes.
 int gemm_f32_plan(int product, int B, int d_out, int d_in, int max_splits, int *splits);
+// ... and how the kernels of small products run it, see hb_plan_f32_small_form
+int gemm_f32_small_form(int product, int B, int d_out, int d_in, int max_splits);
 
 // Number of split-K slices launch_gemm_f32 will use for a DW product of this shape
 // (so that the caller can size the partial buffers).

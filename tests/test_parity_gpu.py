@@ -228,7 +228,8 @@ def test_small_shapes_match_oracle(dims, act, loss, B):
     check_case(dims, act, loss, params, X, y, lr=0.1)
 
 
-@pytest.mark.parametrize("dims,act,loss,B", [
+# dense fp32 networks that fit a workgroup, with the rows of its blocks
+SMALL_NETS = [
     # one workgroup: row blocks of 16, 32 and 64 rows, full and cut; widths of one block of 16 and one value more or less
     ((16, 15, 17, 16), hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, 16),
     ((1, 33, 1), hi.ACT_SIGMOID, hi.LOSS_LOGISTIC, 17),
@@ -246,8 +247,14 @@ def test_small_shapes_match_oracle(dims, act, loss, B):
     # the most layers; nearly the most parameters of two layers
     ((8,) + (10,) * 15 + (4,), hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, 50),
     ((80, 100, 4), hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, 100),
-])
+    # the most layers over several workgroups: every segment of the update kernel
+    ((8,) + (10,) * 15 + (4,), hi.ACT_RELU, hi.LOSS_SOFTMAX_CE, 100),
+]
+
+
+@pytest.mark.parametrize("dims,act,loss,B", SMALL_NETS)
 def test_networks_that_fit_a_workgroup(dims, act, loss, B):
+    assert small_net_rows(dims, B) > 0
     params, X, y = _problem(dims, loss, B, seed=200 + B + len(dims))
     check_case(dims, act, loss, params, X, y, lr=0.1)
     # a smaller batch on the same handle, and rows of X at an odd address: as a handle of its own
@@ -281,6 +288,15 @@ def test_networks_that_fit_a_workgroup_sum_in_short_chains(dims, B):
     z = X.astype(np.float64) @ params[:n].astype(np.float64).reshape(dims[1], dims[0]).T + params[n:n + dims[1]]
     err = np.sqrt(np.mean((got / z - 1.0) ** 2))
     assert err <= 7.5e-8, f"{err:.2e}"
+
+
+@pytest.mark.parametrize("K", range(1, 17))
+def test_every_width_of_the_fused_output_layer(K):
+    """On networks that do not fit a workgroup, one block of rows and one more row."""
+    dims, B = (600, 40, K), 9
+    assert small_net_rows(dims, B) == 0
+    params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE if K > 2 else hi.LOSS_LOGISTIC, B, seed=900 + K)
+    check_case(dims, hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE if K > 2 else hi.LOSS_LOGISTIC, params, X, y, lr=0.1)
 
 
 WIDTHS = [1, 2, 3, 5, 7, 8, 13, 16, 17, 31, 32, 33, 54, 63, 64, 65, 96, 100, 127, 128, 129, 200, 256, 300, 512, 520]
@@ -451,9 +467,11 @@ def test_paper_shaped_deep_nets(dims, B):
     check_case(dims, hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1)
 
 
-def test_async_step_matches_sync_and_writes_device_loss():
+@pytest.mark.parametrize("dims", [(54, 64, 64, 7), (254, 64, 64, 7)])  # whole in a workgroup; layer by layer
+def test_async_step_matches_sync_and_writes_device_loss(dims):
     torch = _torch()
-    dims, act, loss = (54, 64, 64, 7), hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE
+    act, loss = hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE
+    assert (small_net_rows(dims, 500) > 0) == (dims[0] == 54)
     params, X, y = _problem(dims, loss, 500, seed=5)
     dX, dy = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
     a = make_model(dims, act, loss, 500, params)
@@ -1149,15 +1167,17 @@ def test_config5_bf16_full_batch_equals_mean_of_sub_batches():
                             "full-batch gradient vs mean of quarter-batch gradients", abs_floor=1e-9)
 
 
-@pytest.mark.parametrize("bf16", [False, True])
-def test_step_can_be_captured_in_a_graph_and_replays_like_eager_steps(bf16):
+@pytest.mark.parametrize("bf16,dims", [(False, (40, 96, 64, 5)), (True, (40, 96, 64, 5)),
+                                       (False, (340, 96, 64, 5))])  # whole in a workgroup; bf16; layer by layer
+def test_step_can_be_captured_in_a_graph_and_replays_like_eager_steps(bf16, dims):
     """hb_batch_step_async records kernels only (no memset or copy nodes, no allocation, no
     synchronisation), so a caller may capture it.  A captured step is replayed five times, with
     eager work and synchronisations of the caller's own in between; after every replay the
     replica equals, bit for bit, that of a second handle taking the same steps eagerly."""
     import paper_2004_08771_amd as hb
     torch = _torch()
-    dims, act, loss, B = (40, 96, 64, 5), hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, 200
+    act, loss, B = hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, 200
+    assert bf16 or (small_net_rows(dims, B) > 0) == (dims[0] == 40)
     rng = np.random.default_rng(77)
     X = rng.standard_normal((B, dims[0])).astype(np.float32)
     y = rng.integers(0, dims[-1], size=B).astype(np.int32)
@@ -1263,6 +1283,111 @@ def test_small_products_at_block_edges(dims, act, B):
     """Both block sizes of the small fp32 products and both forms of their weight gradient, rows and contractions cut."""
     params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=60 + B)
     check_case(dims, act, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=act == hi.ACT_RELU)
+
+
+def f32_small_forms(dims, B):
+    """"forward ...; backward pairs of layers 2 ...; weight gradient of layer 1": block, s: through LDS, w1 / w2: a wavefront
+    to each block of the weight gradient over up to 64 / 128 rows; -: no small product."""
+    from paper_2004_08771_amd import lib
+
+    def name(product, l):
+        v = lib().hb_plan_f32_small_form(product, dims[l], dims[l - 1], B, B)
+        return f"{v & 63}{'s' if v & 64 else ''}{['', 'w1', 'w2'][v >> 7]}" if v else "-"
+
+    L = len(dims) - 1
+    return "; ".join([" ".join(name(0, l) for l in range(1, L + 1)), " ".join(name(1, l) for l in range(2, L + 1)), name(2, 1)])
+
+
+F32_SMALL = [
+    # pairs with 16 x 16 blocks: weight gradient by workgroups, by a wavefront to each block over 33 .. 64 and 65 .. 128 rows
+    ((70, 300, 300, 40), hi.ACT_SIGMOID, 65, "16 16 16; 16 -; 32"),
+    ((70, 700, 640, 40), hi.ACT_SIGMOID, 48, "16 16 16; 16w1 -; -"),
+    ((70, 700, 640, 40), hi.ACT_RELU, 65, "16 16 16; 16w2 -; 32"),
+    ((70, 700, 640, 40), hi.ACT_SIGMOID, 73, "16 16 16; 16w2 -; 32"),
+    # the same with 32 x 32 blocks, at the most rows of each
+    ((70, 600, 600, 40), hi.ACT_RELU, 130, "16 16 16; 32 -; 32"),
+    ((70, 1040, 1040, 40), hi.ACT_SIGMOID, 64, "16 16 16; 32w1 -; 32"),
+    ((70, 1040, 1040, 40), hi.ACT_RELU, 127, "32 32 16; 32w2 -; 32"),
+    # the weight gradient of a first layer of 800 blocks on its own: 64 rows, 128 rows and one more
+    ((1000, 800, 20), hi.ACT_SIGMOID, 64, "16 16; -; 32w1"),
+    ((1000, 800, 20), hi.ACT_RELU, 128, "16 16; -; 32w2"),
+    ((1000, 800, 20), hi.ACT_SIGMOID, 129, "16 16; -; 32"),
+    # forward by 32 x 32 blocks straight from memory and through LDS
+    ((70, 500, 500, 40), hi.ACT_SIGMOID, 300, "32 32 16; 32 -; 32"),
+    ((70, 500, 500, 40), hi.ACT_RELU, 1000, "32s 32s 16; - -; 32"),
+]
+
+
+@pytest.mark.parametrize("dims,act,B,forms", F32_SMALL)
+def test_forms_of_small_products(dims, act, B, forms):
+    check_plan(f32_small_forms(dims, B), forms)
+    params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=700 + B)
+    check_case(dims, act, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=False)
+
+
+def _padded(dims, wide, params, X):
+    """The same ReLU network with zero columns of X or hidden units without weights up to `wide`."""
+    P, off = [], 0
+    for l in range(1, len(dims)):
+        W, b = np.zeros((wide[l], wide[l - 1]), np.float32), np.zeros(wide[l], np.float32)
+        n = dims[l] * dims[l - 1]
+        W[:dims[l], :dims[l - 1]] = params[off:off + n].reshape(dims[l], dims[l - 1])
+        b[:dims[l]] = params[off + n:off + n + dims[l]]
+        off += n + dims[l]
+        P += [W.ravel(), b]
+    Xw = np.zeros((X.shape[0], wide[0]), np.float32)
+    Xw[:, :dims[0]] = X
+    return np.concatenate(P), Xw
+
+
+SAME_SUMS = [
+    # the weight gradient of layer 1 by workgroups, and by a wavefront to each block over 64 and over 100 rows
+    ((512, 512, 40), (800, 512, 40), 64, "16 16; -; 32", "16 16; -; 32w1"),
+    ((512, 512, 40), (1220, 512, 40), 100, "16 16; -; 32", "16 16; -; 32w2"),
+    # 16 x 16 and 32 x 32 blocks of the backward-data product; the weight gradient of the same launch in both forms
+    ((70, 512, 512, 40), (70, 804, 512, 40), 100, "16 16 16; 16 -; 32", "16 16 16; 32 -; 32"),
+    ((70, 512, 512, 40), (70, 1300, 512, 40), 100, "16 16 16; 16 -; 32", "32 16 16; 32w2 -; 32"),
+]
+
+
+@pytest.mark.parametrize("dims,wide,B,forms,wide_forms", SAME_SUMS)
+def test_forms_of_small_products_add_the_same_sums(dims, wide, B, forms, wide_forms):
+    """Zeros added to a contraction change no sum, so both networks give the same gradient, bit for bit."""
+    torch = _torch()
+    check_plan(f32_small_forms(dims, B), forms)
+    check_plan(f32_small_forms(wide, B), wide_forms)
+    params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=800 + B)
+    out = []
+    for d, (p, x) in ((dims, (params, X)), (wide, _padded(dims, wide, params, X))):
+        m = make_model(d, hi.ACT_RELU, hi.LOSS_SOFTMAX_CE, B, p)
+        g = torch.empty(p.size, device="cuda")
+        m.batch_grad(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda(), B, g)
+        m.destroy()
+        g, off, tensors = g.cpu().numpy(), 0, []
+        for l in range(1, len(d)):
+            n = d[l] * d[l - 1]
+            tensors += [g[off:off + n].reshape(d[l], d[l - 1])[:dims[l], :dims[l - 1]], g[off + n:off + n + dims[l]]]
+            off += n + d[l]
+        out.append(tensors)
+    for i, (a, b) in enumerate(zip(*out)):
+        np.testing.assert_array_equal(a, b, err_msg=f"{'dW db'.split()[i % 2]}_{i // 2 + 1}")
+
+
+def test_forward_forms_add_the_same_sums():
+    """The first 100 rows in batches that take 16 x 16 blocks, 32 x 32 blocks and those through LDS."""
+    torch = _torch()
+    dims, forms = (70, 512, 512, 40), {100: "16", 300: "32", 1000: "32s"}
+    params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, 1000, seed=81)
+    m = make_model(dims, hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, 1000, params)
+    dX, dy, acts = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda(), []
+    for B, form in forms.items():
+        check_plan(f32_small_forms(dims, B).split()[:2], [form] * 2)
+        m.batch_loss(dX, dy, B)
+        acts.append(gpu_hidden_activations(m, dims, 100))
+    m.destroy()
+    for a in acts[1:]:
+        for l in (1, 2):
+            np.testing.assert_array_equal(a[l], acts[0][l])
 
 
 @pytest.mark.parametrize("dims,act,B,plan", F32_EDGES)
@@ -1496,7 +1621,8 @@ def test_bf16_weight_gradient_of_rows_without_padding(d0, B):
     """The last columns of X's rows (2, 4 or 6 past a 16-byte piece) run on into the next row, the last batch row's must not:
     batches that end with a k-tile of 64 and one row later, by one group of wavefronts and by two."""
     dims = (d0, 70, 5)
-    assert bf16_plan(dims, B).split("; ")[2].split()[0] in ("64B", "64sB")
+    form = bf16_plan(dims, B).split("; ")[2].split()[0]
+    check_plan(form, form if form in ("64B", "64sB") else "64B or 64sB")
     params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=500 + B + d0, bias_scale=0.1)
     check_bf16_case(dims, hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=False)
 

@@ -14,6 +14,18 @@ def test_bf16_cases_run_the_kernels_they_name(dims, B, plan):
     assert t.bf16_plan(dims, B) == plan
 
 
+def test_the_cases_reach_every_form_of_the_small_products():
+    for r in t.F32_SMALL:
+        assert t.f32_small_forms(r[0], r[2]) == r[3]
+    for r in t.SAME_SUMS:
+        assert (t.f32_small_forms(r[0], r[2]), t.f32_small_forms(r[1], r[2])) == r[3:]
+    forms = [r[3].split("; ") for r in t.F32_SMALL]
+    assert {k for f in forms for k in f[0].split()} == {"16", "32", "32s"}
+    assert {k for f in forms for k in f[1].split()} == {"-", "16", "16w1", "16w2", "32", "32w1", "32w2"}
+    assert {f[2] for f in forms} == {"-", "32", "32w1", "32w2"}
+    assert {t.small_net_rows(dims, B) for dims, _, _, B in t.SMALL_NETS} == {16, 32, 64}
+
+
 def test_the_cases_reach_every_kernel():
     forward, pairs, alone = ({k for r in t.F32_EDGES for k in r[-1].split("; ")[q].split()} for q in range(3))
     assert forward == set(t.F32_KERNELS) and pairs == set(t.F32_KERNELS) and alone == set(t.F32_KERNELS)
@@ -65,5 +77,7 @@ def test_plans_refuse_invalid_arguments():
     from paper_2004_08771_amd import lib
     f, b = lib().hb_plan_f32_kernel, lib().hb_plan_bf16_kernel
     assert f(0, 0, 5, 5, 5, None) == -1 and f(3, 5, 5, 5, 5, None) == -1 and f(0, 5, 5, 6, 5, None) == -1
+    s = lib().hb_plan_f32_small_form
+    assert s(0, 0, 5, 5, 5) == -1 and s(3, 5, 5, 5, 5) == -1 and s(0, 5, 5, 6, 5) == -1 and s(0, 512, 512, 4096, 4096) == 0
     assert t.small_net_rows((5,), 5) == -1 and t.small_net_rows((5, 0, 5), 5) == -1 and t.small_net_rows((5, 5, 5), 0) == -1
     assert b(0, 5, 0, 5, 0) == -1 and b(-1, 5, 5, 5, 0) == -1 and b(0, 5, (1 << 24) + 1, 5, 0) == -1

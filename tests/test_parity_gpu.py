@@ -170,6 +170,7 @@ def check_plan(got, want):
     """The sizes of a case reach the kernels it names -- unless a tuning aid of the environment sends them elsewhere."""
     aids = ("HB_BF16_TILE", "HB_BF16_BMAJ", "HB_GEMM_SMALL_TILES", "HB_GEMM_SMALL_K", "HB_NO_PAIR")
     assert got == want or any(a in os.environ for a in aids), (got, want)
+    return got == want
 
 
 def f32_plan(dims, B):
@@ -1354,8 +1355,8 @@ SAME_SUMS = [
 def test_forms_of_small_products_add_the_same_sums(dims, wide, B, forms, wide_forms):
     """Zeros added to a contraction change no sum, so both networks give the same gradient, bit for bit."""
     torch = _torch()
-    check_plan(f32_small_forms(dims, B), forms)
-    check_plan(f32_small_forms(wide, B), wide_forms)
+    if not (check_plan(f32_small_forms(dims, B), forms) and check_plan(f32_small_forms(wide, B), wide_forms)):
+        pytest.skip("a tuning aid sends the products to other kernels")
     params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=800 + B)
     out = []
     for d, (p, x) in ((dims, (params, X)), (wide, _padded(dims, wide, params, X))):
@@ -1381,7 +1382,8 @@ def test_forward_forms_add_the_same_sums():
     m = make_model(dims, hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, 1000, params)
     dX, dy, acts = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda(), []
     for B, form in forms.items():
-        check_plan(f32_small_forms(dims, B).split()[:2], [form] * 2)
+        if not check_plan(f32_small_forms(dims, B).split()[:2], [form] * 2):
+            pytest.skip("a tuning aid sends the products to other kernels")
         m.batch_loss(dX, dy, B)
         acts.append(gpu_hidden_activations(m, dims, 100))
     m.destroy()

@@ -470,9 +470,13 @@ struct MidOpT {
 // SETS: k-tiles in flight.  Two for contractions of up to two k-tiles, which fit 128 registers: two workgroups of 128 x 128
 // tiles share a compute unit, and the epilogue of one runs beside the loads of the other.
 // The weight gradient that follows the loss kernel also finishes the mean loss, in a workgroup of its own (a launch less).
+template <int TILE, int KG>
+constexpr int mid_lds_bytes()
+{
+    return KG * 2 * 128 * 2 * TILE;
+}
 template <int TILE, int KG, int KIND, bool SHIFT, bool BMAJ, int SETS>
-__global__ __launch_bounds__((TILE == 64 ? NT : 2 * NT) * KG, TILE == 64 ? (KG == 1 ? 3 : 2) : SETS == 2 ? 4 : 1)
-void gemm_bf16_mid_kernel(GemmBf16Args a)
+__device__ __forceinline__ void mid_tile(const GemmBf16Args &a, int id, unsigned char *smem)
 {
     constexpr int BM = TILE, BN = TILE, GT = (TILE == 64) ? NT : 2 * NT, TM = TILE / 64;  // GT: threads of a group
     static_assert(!BMAJ || (!SHIFT && KIND == GEMM_DW && TILE == 64), "batch-major operands");
@@ -481,8 +485,7 @@ void gemm_bf16_mid_kernel(GemmBf16Args a)
     using OA = std::conditional_t<BMAJ, MidOpT<SETS>, MidOp<BM, GT, SETS, SHIFT>>;
     using OB = std::conditional_t<BMAJ, MidOpT<SETS>, MidOp<BN, GT, SETS>>;
     constexpr int A_BYTES = 128 * BM, STAGE = 128 * (BM + BN);
-    __shared__ __attribute__((aligned(16))) unsigned char smem[KG * 2 * STAGE];
-
+    static_assert(KG * 2 * STAGE == mid_lds_bytes<TILE, KG>(), "LDS of a workgroup");
     const int lane = threadIdx.x & 63, wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int tid = threadIdx.x & (GT - 1), g = wave_all / (GT / 64), wave = wave_all % (GT / 64);
     const int r = lane & 31, h = lane >> 5;
@@ -490,13 +493,13 @@ void gemm_bf16_mid_kernel(GemmBf16Args a)
     unsigned char *const stages = smem + g * 2 * STAGE;
 
     if constexpr (BMAJ) {
-        if ((int)blockIdx.x == a.tiles_m * a.tiles_n) {
+        if (id == a.tiles_m * a.tiles_n) {
             loss_finalize(a.fin, reinterpret_cast<double *>(smem));
             return;
         }
     }
     // XCD-aware tile order: each XCD gets a block of the tiles (a.xcd_m such blocks along m)
-    int id = blockIdx.x, tile_m, tile_n;
+    int tile_m, tile_n;
     if (a.xcd_m > 0) {
         const int x = id & 7, j = id >> 3, rm = a.tiles_m / a.xcd_m, rn = a.tiles_n * a.xcd_m >> 3;
         tile_m = j / rn;
@@ -669,6 +672,30 @@ void gemm_bf16_mid_kernel(GemmBf16Args a)
             for (int v = 0; v < 16; ++v) acc[0][0][v] += red[((q * 4 + wave) * 16 + v) * 64 + lane];
     }
     epilogue_bf16<KIND, TM, 1>(a, acc, m0 + wm * (TILE / 2), n0 + wn * 32, r, h);
+}
+
+template <int TILE, int KG, int KIND, bool SHIFT, bool BMAJ, int SETS>
+__global__ __launch_bounds__((TILE == 64 ? NT : 2 * NT) * KG, TILE == 64 ? (KG == 1 ? 3 : 2) : SETS == 2 ? 4 : 1)
+void gemm_bf16_mid_kernel(GemmBf16Args a)
+{
+    __shared__ __attribute__((aligned(16))) unsigned char smem[mid_lds_bytes<TILE, KG>()];
+    mid_tile<TILE, KG, KIND, SHIFT, BMAJ, SETS>(a, blockIdx.x, smem);
+}
+
+// A weight gradient and the next product of the backward pass in one launch (pair_shares() below: KG).  What bounds either alone
+// is latency -- of the launch, of its first loads and of the round trip to memory that a k-tile is -- so both together
+// take little longer than one: 1024 x 1024 over 2047 rows 12.8 us + 2047 x 1024 x 1024 11.9 us apart, 22.4 in one launch, and
+// the narrow products of the output layer or of a 300-wide input vanish behind their neighbour (300-1024x3-2, 2047 rows: 133.5 ->
+// 113.1 us per step).  With two groups the register sets are two (105 registers), so that two workgroups fit a compute
+// unit; with one they are four and three workgroups do.
+template <int KG, int KIND>
+__global__ __launch_bounds__(NT *KG, KG == 1 ? 3 : 4) void gemm_bf16_mid_pair_kernel(GemmBf16Args dw, GemmBf16Args next, int n_dw)
+{
+    constexpr int SETS = KG == 1 ? 4 : 2;
+    __shared__ __attribute__((aligned(16))) unsigned char smem[mid_lds_bytes<64, KG>()];
+    const int b = blockIdx.x;
+    if (b < n_dw) mid_tile<64, KG, GEMM_DW, false, true, SETS>(dw, b, smem);
+    else mid_tile<64, KG, KIND, false, KIND == GEMM_DW, SETS>(next, b - n_dw, smem);
 }
 
 // ---- 256 x 256 x 64 kernel with LDS-direct loads ------------------------------------------
@@ -1486,15 +1513,12 @@ int env_int_bf16(const char *name, int dflt)
     return (v && *v) ? atoi(v) : dflt;
 }
 
-template <int TILE, int KG, bool SHIFT, int SETS = 4>
-hipError_t launch_mid_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, const LaunchEvents &ev)
+// Tiles of a product and the blocks of them that the 8 XCDs take: those with the fewest operand rows (4096 x 4096 x 1000:
+// forward 46.9 -> 42.5 us, backward-data 47.3 -> 41.7; 1024 x 1024 x 2047 the same either way).
+long long mid_tiles(GemmBf16Args &a, int tile)
 {
-    a.tiles_m = (a.M + TILE - 1) / TILE;
-    a.tiles_n = (a.N + TILE - 1) / TILE;
-    const long long tiles = (long long)a.tiles_m * a.tiles_n;
-    if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
-    // the blocks that the 8 XCDs take: those with the fewest operand rows (4096 x 4096 x 1000: forward 46.9 -> 42.5 us, backward-data
-    // 47.3 -> 41.7; 1024 x 1024 x 2047 the same either way)
+    a.tiles_m = (a.M + tile - 1) / tile;
+    a.tiles_n = (a.N + tile - 1) / tile;
     a.xcd_m = 0;
     for (int m = 1, best = 0; m <= 8; m *= 2) {
         if (a.tiles_m % m != 0 || a.tiles_n % (8 / m) != 0) continue;
@@ -1504,6 +1528,14 @@ hipError_t launch_mid_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, co
             best = rows;
         }
     }
+    return (long long)a.tiles_m * a.tiles_n;
+}
+
+template <int TILE, int KG, bool SHIFT, int SETS = 4>
+hipError_t launch_mid_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, const LaunchEvents &ev)
+{
+    const long long tiles = mid_tiles(a, TILE);
+    if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid((unsigned)tiles), block((TILE == 64 ? NT : 2 * NT) * KG);
     if constexpr (TILE == 64 && !SHIFT)
         if (a.bmaj)
@@ -1627,6 +1659,41 @@ hipError_t launch_gemm_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, c
     }
     a.colsum_partial = nullptr;  // the other kernels do not produce them
     return (a.bmaj || aligned4(a.A, a.lda)) ? launch_mid<false>(kind, a, stream, ev) : launch_mid<true>(kind, a, stream, ev);
+}
+
+// Two groups of wavefronts per tile for a pair of `tiles` 64 x 64 tiles whose weight gradient runs over K rows?  They halve the
+// longest chain, the weight gradient's k-tiles, and hold half as many loads each: better where there are chains to halve and
+// the workgroups have a compute unit for themselves or nearly, and for long batches always.  One group / two, us per step:
+// 300-1024x3-2 64 rows 65.3 / 66.4, 500 78.0 / 78.0, 2047 (768 tiles) 113.1 / 115.6, 4000 172.6 / 170.4, 7001 287 / 281;
+// 64-256x3-10 64 rows 43.0 / 45.3, 500 54.3 / 53.6, 2047 80.1 / 71.8, 7001 167 / 131; 1024-2048-2048-10 64 rows 68.5 / 73.0, 1000
+// (1536 tiles) 103.9 / 107.8, 2047 157.2 / 159.3, 4000 309 / 309, 7001 400 / 392.
+static bool pair_shares(long long tiles, int K) { return K >= 8 * MID_BK && (tiles <= 512 || K >= 48 * MID_BK); }
+
+// Products that the kernels of 64 x 64 tiles take (apart / in one launch, us per step: 64-128-7 64 rows 25.7 / 21.5, 7001 80.1 / 50.4;
+// 512x4-100 500 rows 83.7 / 62.9; 2048-700x3-1000 2047 rows 172 / 137, 7001 rows, which has hardly any such product, 395 / 394;
+// 1024-2048-2048-10 4000 rows 309 / 309).  HB_BF16_NO_PAIR=1 (tuning aid): apart.
+bool gemm_bf16_pair_ok(const GemmBf16Args &dw, GemmKind kind, const GemmBf16Args &next)
+{
+    static const int off = env_int_bf16("HB_BF16_NO_PAIR", 0);
+    if (off || dw.bmaj != BF16_DW_BMAJ_MID || kind == GEMM_FWD || (kind == GEMM_DW && next.bmaj != BF16_DW_BMAJ_MID)) return false;
+    for (const GemmBf16Args *a : {&dw, &next}) {
+        const int k = gemm_bf16_kernel(a == &dw ? GEMM_DW : kind, *a);
+        if (k != BF16_K_64 && k != BF16_K_64_SHARED) return false;
+    }
+    return next.bmaj || aligned4(next.A, next.lda);
+}
+
+hipError_t launch_gemm_bf16_pair(GemmBf16Args dw, GemmKind kind, GemmBf16Args next, hipStream_t stream, const LaunchEvents &ev)
+{
+    if (!gemm_bf16_pair_ok(dw, kind, next)) return hipErrorInvalidValue;
+    next.colsum_partial = nullptr;
+    const long long n_dw = mid_tiles(dw, 64) + (dw.fin.n > 0 ? 1 : 0);
+    const long long blocks = n_dw + mid_tiles(next, 64) + (kind == GEMM_DW && next.fin.n > 0 ? 1 : 0);
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    const bool two = pair_shares(blocks, dw.K);
+    const auto kernel = kind == GEMM_DA ? (two ? gemm_bf16_mid_pair_kernel<2, GEMM_DA> : gemm_bf16_mid_pair_kernel<1, GEMM_DA>)
+                                        : (two ? gemm_bf16_mid_pair_kernel<2, GEMM_DW> : gemm_bf16_mid_pair_kernel<1, GEMM_DW>);
+    return launch_kernel(kernel, dim3((unsigned)blocks), dim3(two ? 2 * NT : NT), stream, ev, dw, next, (int)n_dw);
 }
 
 int gemm_bf16_dw_form(int M, int N, int K, long long lda, long long ldb, const void *A, const void *B)

@@ -702,6 +702,12 @@ int run_step_bf16(hb_model *m, const void *X, const int32_t *y, int64_t B, float
             bmaj[l] = (char)gemm_bf16_dw_form(m->dims[l], m->dims[l - 1], Bi, m->ld8[l],
                                               (l == 1) ? (long long)m->dims[0] : (long long)m->ld8[l - 1],
                                               m->delta_bf[l & 1], (l == 1) ? X : m->act_bf[l - 1]);
+    // D_l: while its weight gradient reads it, the backward-data product beside that reads D_{l-1} and writes D_{l-2}.  The third
+    // buffer is that of the transposed copies of even layers, where none of those needs one.
+    bool three = true;
+    for (int l = 2; l <= L; l += 2) three = three && bmaj[l];
+    void *const deltas[3] = {m->delta_bf[0], m->delta_bf[1], m->delta_t[0]};
+    auto delta = [&](int l) { return deltas[three ? l % 3 : l & 1]; };
     if (back && !bmaj[1])  // X^T for dW_1 = D_1^T X
         HB_HIP(launch_transpose_bf16(X, m->dims[0], m->act_t[0], ldB, Bi, m->dims[0], st,
                                      prof_begin(m, HB_K_OTHER, 1, 0, 0, 0, 0.0, 4.0 * B * m->dims[0])));
@@ -748,7 +754,7 @@ int run_step_bf16(hb_model *m, const void *X, const int32_t *y, int64_t B, float
     la.B = B;
     la.K = m->dims[L];
     la.loss = m->loss;
-    la.delta = back ? m->delta_bf[L & 1] : nullptr;
+    la.delta = back ? delta(L) : nullptr;
     la.ldd = m->ld8[L];
     la.delta_bf16 = 1;
     la.zero_pad = 1;
@@ -759,53 +765,49 @@ int run_step_bf16(hb_model *m, const void *X, const int32_t *y, int64_t B, float
     if (!back || bmaj[L] != BF16_DW_BMAJ_MID) HB_HIP(launch_loss_finalize(fin, st));
     if (!back) return HB_OK;
     if (!bmaj[L])
-        HB_HIP(launch_transpose_bf16(m->delta_bf[L & 1], m->ld8[L], m->delta_t[L & 1], ldB, Bi, m->dims[L], st,
+        HB_HIP(launch_transpose_bf16(delta(L), m->ld8[L], m->delta_t[L & 1], ldB, Bi, m->dims[L], st,
                                      prof_begin(m, HB_K_OTHER, 2, 0, 0, 0, 0.0, 4.0 * B * m->dims[L])));
 
     const bool grad_mode = (mode == MODE_GRAD);
     std::vector<int> colsum_slices((size_t)L + 2, 0);  // [l] > 0: slices of column sums of D_l already written
-    for (int l = L; l >= 1; --l) {
-        if (l > 1) {
-            GemmBf16Args g = {};
-            g.A = m->delta_bf[l & 1];
-            g.lda = m->ld8[l];
-            g.B = m->shadow_t[l];
-            g.ldb = m->ld8[l];
-            g.M = Bi;
-            g.N = m->dims[l - 1];
-            g.K = (l == L) ? m->ld8[l] : m->dims[l];  // output layer: zero padding included (see ld8)
-            g.a_vec = 1;
-            g.b_vec = 1;
-            g.aux = m->act_bf[l - 1];
-            g.ldaux = m->ld8[l - 1];
-            g.aux_t = m->act_t[l - 1];  // written by the forward pass of layer l-1
-            g.ldauxt = ldB;
-            if (m->act == ACT_RELU) {
-                g.mask_in = m->relu_mask[l - 1];
-                g.mask_nb = (m->dims[l - 1] + 31) / 32;
-            }
-            g.act = m->act;
-            g.C_bf16 = m->delta_bf[(l - 1) & 1];
-            g.ldcb = m->ld8[l - 1];
-            if (!bmaj[l - 1]) {
-                g.Ct_bf16 = m->delta_t[(l - 1) & 1];
-                g.ldct = ldB;
-            }
-            g.colsum_partial = m->bias_partial[(l - 1) & 1];  // the bias gradient of layer l-1, if this kernel can
-            g.colsum_cap = m->bias_partial_slices;
-            const double Kd = m->dims[l];  // priced without the padding
-            HB_HIP(launch_gemm_bf16(GEMM_DA, g, st,
-                                    prof_begin(m, HB_K_DA_GEMM, l, g.M, g.N, m->dims[l], 2.0 * g.M * g.N * Kd,
-                                               2.0 * ((double)g.M * Kd + (double)g.N * Kd + 3.0 * g.M * g.N)),
-                                    &colsum_slices[l - 1]));
+    auto da_args = [&](int l) {  // D_{l-1} = (D_l W_l) * f'(A_{l-1})
+        GemmBf16Args g = {};
+        g.A = delta(l);
+        g.lda = m->ld8[l];
+        g.B = m->shadow_t[l];
+        g.ldb = m->ld8[l];
+        g.M = Bi;
+        g.N = m->dims[l - 1];
+        g.K = (l == L) ? m->ld8[l] : m->dims[l];  // output layer: zero padding included (see ld8)
+        g.a_vec = 1;
+        g.b_vec = 1;
+        g.aux = m->act_bf[l - 1];
+        g.ldaux = m->ld8[l - 1];
+        g.aux_t = m->act_t[l - 1];  // written by the forward pass of layer l-1
+        g.ldauxt = ldB;
+        if (m->act == ACT_RELU) {
+            g.mask_in = m->relu_mask[l - 1];
+            g.mask_nb = (m->dims[l - 1] + 31) / 32;
         }
+        g.act = m->act;
+        g.C_bf16 = delta(l - 1);
+        g.ldcb = m->ld8[l - 1];
+        if (!bmaj[l - 1]) {
+            g.Ct_bf16 = m->delta_t[(l - 1) & 1];
+            g.ldct = ldB;
+        }
+        g.colsum_partial = m->bias_partial[(l - 1) & 1];  // the bias gradient of layer l-1, if this kernel can
+        g.colsum_cap = m->bias_partial_slices;
+        return g;
+    };
+    auto dw_args = [&](int l) {  // dW_l = D_l^T A_{l-1}, applied to the master weights and their bf16 copies
         GemmBf16Args g = {};
         if (bmaj[l]) {
             g.bmaj = bmaj[l];
             if (bmaj[l] == BF16_DW_BMAJ_MID && l == L) g.fin = fin;
             if (bmaj[l] == BF16_DW_BMAJ_MID)
                 g.bias_out = grad_mode ? d_grad_flat + m->b_off[l] : m->d_params + m->b_off[l];
-            g.A = m->delta_bf[l & 1];
+            g.A = delta(l);
             g.lda = m->ld8[l];
             g.B = (l == 1) ? X : m->act_bf[l - 1];
             g.ldb = (l == 1) ? m->dims[0] : m->ld8[l - 1];
@@ -832,6 +834,36 @@ int run_step_bf16(hb_model *m, const void *X, const int32_t *y, int64_t B, float
             g.ldcb = m->ld8[l - 1];
             g.Ct_bf16 = m->shadow_t[l];
             g.ldct = m->ld8[l];
+        }
+        return g;
+    };
+    auto da_flops = [&](int l) { return 2.0 * B * m->dims[l - 1] * m->dims[l]; };  // priced without the padding
+    auto da_bytes = [&](int l) {
+        return 2.0 * ((double)B * m->dims[l] + (double)m->dims[l - 1] * m->dims[l] + 3.0 * B * m->dims[l - 1]);
+    };
+    auto dw_bytes = [&](const GemmBf16Args &g) {
+        return 2.0 * ((double)g.M * g.K + (double)g.N * g.K) + (grad_mode ? 4.0 : 12.0) * g.M * g.N;
+    };
+    std::vector<char> done_da((size_t)L + 2, 0), done_dw((size_t)L + 2, 0);
+    for (int l = L; l >= 1; --l) {
+        if (l > 1 && !done_da[l])
+            HB_HIP(launch_gemm_bf16(GEMM_DA, da_args(l), st,
+                                    prof_begin(m, HB_K_DA_GEMM, l, Bi, m->dims[l - 1], m->dims[l], da_flops(l), da_bytes(l)),
+                                    &colsum_slices[l - 1]));
+        if (done_dw[l]) continue;
+        const GemmBf16Args g = dw_args(l);
+        if (l > 1) {  // with what comes next, which does not need it: D_{l-2}, or dW_1
+            const GemmKind kind = l > 2 ? GEMM_DA : GEMM_DW;
+            const GemmBf16Args next = l > 2 ? da_args(l - 1) : dw_args(1);
+            if ((three || kind == GEMM_DW) && gemm_bf16_pair_ok(g, kind, next)) {
+                HB_HIP(launch_gemm_bf16_pair(
+                    g, kind, next, st,
+                    prof_begin(m, HB_K_BWD_PAIR, l, g.M, g.N, g.K,
+                               2.0 * g.M * g.N * g.K + (l > 2 ? da_flops(l - 1) : 2.0 * next.M * next.N * next.K),
+                               dw_bytes(g) + (l > 2 ? da_bytes(l - 1) : dw_bytes(next)))));
+                (l > 2 ? done_da : done_dw)[l - 1] = 1;
+                continue;  // the bias gradient came with the weight gradient
+            }
         }
         int sp = (m->dw_partial && bmaj[l] != BF16_DW_BMAJ_MID) ? (g.bmaj ? gemm_bf16_dw_splits_cap(g.M, g.N, g.K)
                                          : gemm_bf16_dw_splits(g.M, g.N, g.K, g.lda, g.ldb))
@@ -863,9 +895,7 @@ int run_step_bf16(hb_model *m, const void *X, const int32_t *y, int64_t B, float
                                      m->ld8[l - 1], m->shadow_t[l], m->ld8[l], st));
         } else {
             HB_HIP(launch_gemm_bf16(GEMM_DW, g, st,
-                                    prof_begin(m, HB_K_DW_GEMM, l, g.M, g.N, g.K, 2.0 * g.M * g.N * g.K,
-                                               2.0 * ((double)g.M * g.K + (double)g.N * g.K) +
-                                                   (grad_mode ? 4.0 : 12.0) * g.M * g.N)));
+                                    prof_begin(m, HB_K_DW_GEMM, l, g.M, g.N, g.K, 2.0 * g.M * g.N * g.K, dw_bytes(g))));
         }
         if (bmaj[l] == BF16_DW_BMAJ_MID) continue;  // the bias gradient came with the weight gradient
         if (colsum_slices[l] > 0)  // the backward-data epilogue that wrote D_l left its column sums
@@ -876,7 +906,7 @@ int run_step_bf16(hb_model *m, const void *X, const int32_t *y, int64_t B, float
                                                           (double)colsum_slices[l] * m->dims[l],
                                                           4.0 * colsum_slices[l] * m->dims[l])));
         else if (bmaj[l])
-            HB_HIP(launch_colsum_bias(m->delta_bf[l & 1], m->ld8[l], m->dims[l], B, m->bias_partial[l & 1],
+            HB_HIP(launch_colsum_bias(delta(l), m->ld8[l], m->dims[l], B, m->bias_partial[l & 1],
                                       m->d_params + m->b_off[l], grad_mode ? d_grad_flat + m->b_off[l] : nullptr,
                                       lr, st,
                                       prof_begin(m, HB_K_UPDATE, l, 0, 0, 0, (double)B * m->dims[l],
@@ -1288,9 +1318,10 @@ int hb_mlp_configure(hb_model *m, int dtype, int64_t max_B, int sparse_first_lay
         }
         for (int i = 0; i < 2 && rc == HB_OK; ++i) {
             unsigned short *p = nullptr;
-            rc = dev_alloc(m, &p, (size_t)max_B * max_ld8);
+            const size_t rows = (size_t)max_B * max_ld8, cols = (size_t)max_d * ldB;
+            rc = dev_alloc(m, &p, rows);
             m->delta_bf[i] = p;
-            if (rc == HB_OK) rc = dev_alloc(m, &p, (size_t)max_d * ldB);
+            if (rc == HB_OK) rc = dev_alloc(m, &p, rows > cols ? rows : cols);  // [0]: or a third row-major delta
             m->delta_t[i] = p;
         }
         {

@@ -1629,6 +1629,28 @@ def test_bf16_weight_gradient_of_rows_without_padding(d0, B):
     check_bf16_case(dims, hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=False)
 
 
+BF16_PAIRS = [
+    # two layers: the two weight gradients share a launch, with the mean loss; a batch cut inside its second k-tile
+    ((66, 129, 5), hi.ACT_RELU, 65),
+    # each weight gradient with the next backward-data product, one group of wavefronts; three deltas at once
+    ((66, 129, 65, 70, 3), hi.ACT_SIGMOID, 200),
+    # two groups: nine k-tiles over the batch and one row
+    ((66, 129, 65, 70, 3), hi.ACT_RELU, 577),
+    # 758 tiles over ten k-tiles: one group; the launch before it 298 tiles: two
+    ((34, 1700, 1700, 2), hi.ACT_RELU, 600),
+    # 550 tiles over 49 k-tiles: two groups
+    ((34, 700, 700, 3), hi.ACT_SIGMOID, 3100),
+    # odd rows of X: dW_1 from transposed copies, in a launch of its own
+    ((65, 70, 90, 5), hi.ACT_SIGMOID, 130),
+]
+
+
+@pytest.mark.parametrize("dims,act,B", BF16_PAIRS)
+def test_bf16_backward_products_that_share_a_launch(dims, act, B):
+    params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=700 + B, bias_scale=0.1)
+    check_bf16_case(dims, act, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=False)
+
+
 BF16_SHORT = [
     # 17 x 17 tiles, one k-tile: forward, and backward-data of layer 2 (K = 40)
     ((54, 2060, 40, 3), hi.ACT_RELU, 2100, "128s 64s 64; 128s 64; 64sB 64sB 64sB"),

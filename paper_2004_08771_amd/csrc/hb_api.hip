@@ -409,7 +409,10 @@ int run_step(hb_model *m, const Input &in, const int32_t *y, int64_t B, float lr
                                 prof_begin(m, HB_K_OTHER, 5, 0, 0, 0, 0.0, 16.0 * in.nnz)));
         return HB_OK;
     };
-    const bool csc_beside = m->sparse && mode != MODE_LOSS && m->csc_stream != nullptr;
+    // A small batch has it in one launch, on the handle's own stream: what four launches and the two records and waits of the
+    // other stream cost the host is more than what runs beside the forward pass saves.
+    const bool csc_one = m->sparse && mode != MODE_LOSS && csc_one_launch(in.nnz, B);
+    const bool csc_beside = m->sparse && mode != MODE_LOSS && !csc_one && m->csc_stream != nullptr;
     if (csc_beside) {
         // forked at the start of the step: later fork points (behind the first or second forward
         // product) measured the same
@@ -599,9 +602,10 @@ int run_step(hb_model *m, const Input &in, const int32_t *y, int64_t B, float lr
         if (l == 1 && m->sparse) {
             // db_1: column sums of delta_1; dW_1: column-segmented sums over the non-zeros,
             // applied to W1t directly (only columns that occur in the batch are touched)
-            HB_HIP(launch_colsum(delta_l, m->ld[1], B, m->dims[1], m->b1_splits, m->partial_b[1], sw_stream,
-                                 prof_begin(m, HB_K_OTHER, 1, 0, 0, 0, (double)B * m->dims[1],
-                                            4.0 * B * m->dims[1])));
+            if (!csc_one)
+                HB_HIP(launch_colsum(delta_l, m->ld[1], B, m->dims[1], m->b1_splits, m->partial_b[1], sw_stream,
+                                     prof_begin(m, HB_K_OTHER, 1, 0, 0, 0, (double)B * m->dims[1],
+                                                4.0 * B * m->dims[1])));
             UpdateSeg &sb = ua.seg[ua.n_seg++];
             sb.param = m->d_params + m->b_off[1];
             sb.grad_out = d_grad_flat ? d_grad_flat + m->b_off[1] : nullptr;
@@ -611,6 +615,10 @@ int run_step(hb_model *m, const Input &in, const int32_t *y, int64_t B, float lr
             sb.splits = m->b1_splits;
             if (csc_beside) {
                 HB_HIP(hipStreamWaitEvent(sw_stream, m->csc_join, 0));
+            } else if (csc_one) {
+                HB_HIP(launch_csc_one(in.row_ptr, in.col_idx, in.vals, in.nnz, B, m->dims[0], m->d_col_start, m->d_chunk_start,
+                                      m->d_chunk_desc, m->d_csc_ent, sw_stream,
+                                      prof_begin(m, HB_K_OTHER, 2, 0, 0, 0, 0.0, 24.0 * in.nnz)));
             } else {
                 const int rc_b = csc_build(sw_stream);
                 if (rc_b != HB_OK) return rc_b;
@@ -628,6 +636,11 @@ int run_step(hb_model *m, const Input &in, const int32_t *y, int64_t B, float lr
             sd.d1 = m->dims[1];
             sd.lr = lr;
             sd.vec = (m->dims[1] % 4 == 0);
+            if (csc_one) {
+                sd.colsum = m->partial_b[1];
+                sd.colsum_splits = m->b1_splits;
+                sd.B = B;
+            }
             if (mode == MODE_GRAD) {
                 sd.grad_out = d_grad_flat + m->w_off[1];
                 HB_HIP(hipMemsetAsync(sd.grad_out, 0, sizeof(float) * (size_t)m->dims[1] * m->dims[0], sw_stream));

@@ -409,6 +409,92 @@ __global__ __launch_bounds__(CSC_NT) void csc_place_kernel(const int32_t *__rest
     }
 }
 
+// The CSC of a small batch in one launch: a workgroup owns a range of columns and looks at all of the batch's column
+// indices once (up to ONE_U to a thread, in registers), counts the ones below its range, which give the place of its first column,
+// and lists its own in LDS; then it counts and places these, a thread to each.  (Counted and placed where they were
+// found, by whichever lanes of a wavefront had one, the launch took 30 us longer per 17,000 entries.)  It
+// leaves col_start only and, per range, the list of its columns of more than CHUNK entries (chunk_desc[first column ..],
+// chunk_start[range] of them), for sparse_dw_columns_kernel.
+constexpr int ONE_RANGES = 128;  // at most
+constexpr int ONE_U = 20;      // 20,480 entries
+constexpr int ONE_BITS = 15;   // of an entry's number in a list
+static_assert(ONE_U * CSC_NT <= 1 << ONE_BITS, "entry numbers");
+__host__ __device__ inline int one_width(int d0) { return (d0 + ONE_RANGES - 1) / ONE_RANGES; }  // columns of a range
+inline int one_ranges(int d0) { return (d0 + one_width(d0) - 1) / one_width(d0); }
+
+__global__ __launch_bounds__(CSC_NT) void csc_one_kernel(const int32_t *__restrict__ row_ptr,
+                                                         const int32_t *__restrict__ col_idx,
+                                                         const float *__restrict__ vals, int B, int d0, int cap,
+                                                         int32_t *__restrict__ col_start,
+                                                         int32_t *__restrict__ chunk_start,
+                                                         int4 *__restrict__ chunk_desc, int2 *__restrict__ csc_ent)
+{
+    extern __shared__ int32_t s_one[];  // cursors of the range's columns, row_ptr, the range's entries {column in the range, entry}
+    __shared__ int red[CSC_NT / 64], red2[CSC_NT / 64], n_heavy;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int width = one_width(d0), lo = blockIdx.x * width, n = min(width, d0 - lo);  // n <= CSC_NT
+    int32_t *s_cnt = s_one, *s_rp = s_one + width;
+    unsigned *s_ent = reinterpret_cast<unsigned *>(s_rp + B + 1);
+    for (int c = t; c < n; c += CSC_NT) s_cnt[c] = 0;
+    for (int i = t; i <= B; i += CSC_NT) s_rp[i] = row_ptr[i];
+    if (t == 0) n_heavy = 0;
+    const int beg = row_ptr[0], entries = min(row_ptr[B] - beg, cap);
+    int c[ONE_U];
+#pragma unroll
+    for (int u = 0; u < ONE_U; ++u) c[u] = (t + u * CSC_NT < entries) ? col_idx[beg + t + u * CSC_NT] - lo : 0x7fffffff;
+    int below = 0, mine = 0;
+#pragma unroll
+    for (int u = 0; u < ONE_U; ++u) {
+        below += c[u] < 0 ? 1 : 0;
+        mine += (unsigned)c[u] < (unsigned)n ? 1 : 0;
+    }
+    const int incl_m = wave_incl_scan(mine, lane);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) below += __shfl_xor(below, o, 64);
+    if (lane == 63) {
+        red[wave] = below;
+        red2[wave] = incl_m;
+    }
+    __syncthreads();
+    int first = 0, at = incl_m - mine, total = 0;
+#pragma unroll
+    for (int w = 0; w < CSC_NT / 64; ++w) {
+        first += red[w];
+        at += w < wave ? red2[w] : 0;
+        total += red2[w];
+    }
+#pragma unroll
+    for (int u = 0; u < ONE_U; ++u)
+        if ((unsigned)c[u] < (unsigned)n) s_ent[at++] = (unsigned)c[u] << ONE_BITS | (unsigned)(t + u * CSC_NT);
+    __syncthreads();
+    for (int i = t; i < total; i += CSC_NT) atomicAdd(&s_cnt[s_ent[i] >> ONE_BITS], 1);
+    __syncthreads();
+    const int cnt = t < n ? s_cnt[t] : 0, incl = wave_incl_scan(cnt, lane);
+    if (lane == 63) red[wave] = incl;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) first += red[w];
+    first += incl - cnt;
+    if (t < n) {
+        s_cnt[t] = first;
+        col_start[lo + t] = first;
+        if (lo + t == d0 - 1) col_start[d0] = first + cnt;
+        if (cnt > CHUNK) chunk_desc[lo + atomicAdd(&n_heavy, 1)] = make_int4(lo + t, first, first + cnt, 1);
+    }
+    __syncthreads();
+    if (t == 0) chunk_start[blockIdx.x] = n_heavy;
+    for (int i = t; i < total; i += CSC_NT) {
+        const unsigned en = s_ent[i];
+        const int p = beg + (int)(en & ((1u << ONE_BITS) - 1));
+        const float v = vals[p];
+        int a = 0, b = B;  // s_rp[a] <= p < s_rp[b]
+        while (b - a > 1) {
+            const int mid = (a + b) >> 1;
+            if (s_rp[mid] <= p) a = mid; else b = mid;
+        }
+        csc_ent[atomicAdd(&s_cnt[en >> ONE_BITS], 1)] = make_int2(a, __float_as_int(v));
+    }
+}
+
 // One workgroup per column that occurs in the batch:
 //   g[:] = sum_e val[e] * delta_1[row[e], :]   over the column's entries {row, val} of csc_ent
 // then W1t[c,:] -= lr * g, or in gradient mode dW_1[:, c] = g in the flat out x in layout.
@@ -811,36 +897,148 @@ __global__ __launch_bounds__(XS_NT) void sparse_dw_sliced_kernel(SparseDwArgs a,
     }
 }
 
-// partial[s][j] = sum over the s-th slice of rows of delta[i][j]   (bias gradient of layer 1)
+// partial[s][j] = sum over the s-th slice of rows of delta[i][j]   (bias gradient of layer 1).  The rows of a slice are
+// summed in four chains; a workgroup of NT threads gives each of its threads 256 / NT of them.
+template <int NT>
+__device__ __forceinline__ void colsum_slice(const float *__restrict__ delta, int ldd, long long B, int d, int rows_per_split,
+                                             float *__restrict__ partial, int col_block, int slice, float (&red)[4][64])
+{
+    constexpr int G = 256 / NT;
+    const int col = col_block * 64 + (threadIdx.x & 63);
+    const long long r0 = (long long)slice * rows_per_split;
+    const long long r1 = min(B, r0 + rows_per_split);
+    float s[G], s1[G];
+    long long i = r0 + (threadIdx.x >> 6);
+#pragma unroll
+    for (int g = 0; g < G; ++g) s[g] = s1[g] = 0.f;
+    if (col < d) {
+        // eight rows of a chain requested before the first is added: the slice is a chain of loads otherwise
+        for (; i + (4 - 4 / G) + 28 < r1; i += 32) {
+            float v[G][8];
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[g][u] = delta[(i + g * (4 / G) + 4 * u) * ldd + col];
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                s[g] += (v[g][0] + v[g][1]) + (v[g][2] + v[g][3]);
+                s1[g] += (v[g][4] + v[g][5]) + (v[g][6] + v[g][7]);
+            }
+        }
+        for (; i < r1; i += 4)
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+                if (i + g * (4 / G) < r1) s[g] += delta[(i + g * (4 / G)) * ldd + col];
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) red[(threadIdx.x >> 6) + g * (4 / G)][threadIdx.x & 63] = s[g] + s1[g];
+    __syncthreads();
+    if (threadIdx.x < 64 && col < d)
+        partial[(size_t)slice * d + col] = red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x];
+}
+
 __global__ __launch_bounds__(256) void colsum_kernel(const float *__restrict__ delta, int ldd,
                                                      long long B, int d, int rows_per_split,
                                                      float *__restrict__ partial)
 {
     __shared__ float red[4][64];
-    const int col = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int rg = threadIdx.x >> 6;
-    const long long r0 = (long long)blockIdx.y * rows_per_split;
-    const long long r1 = min(B, r0 + rows_per_split);
-    float s = 0.f;
-    if (col < d) {
-        // eight rows requested before the first is added: the slice is a chain of loads otherwise
-        long long i = r0 + rg;
-        float s1 = 0.f;
-        for (; i + 28 < r1; i += 32) {
-            float v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = delta[(i + 4 * u) * ldd + col];
-            s += (v[0] + v[1]) + (v[2] + v[3]);
-            s1 += (v[4] + v[5]) + (v[6] + v[7]);
-        }
-        for (; i < r1; i += 4) s += delta[i * ldd + col];
-        s += s1;
+    colsum_slice<256>(delta, ldd, B, d, rows_per_split, partial, blockIdx.x, blockIdx.y, red);
+}
+
+// Weight gradient of layer 1 from the CSC of csc_one_kernel, with the bias gradient's slices in the same launch (first: they are
+// the longest workgroups).  A workgroup takes ONE_COLS columns; the ones of up to LIGHT_MAX entries together, four
+// entries of each in a round, so that sixteen gathers are in flight, and their weight rows with one another: what bounds a
+// small batch is the chain offsets - entries - rows of delta - weights, four dependent trips to memory, and one column per
+// workgroup filled the device three times over with it.  Longer columns go one by one as in sparse_dw_kernel, the parts of
+// those above CHUNK to the last ONE_EXTRA workgroups of each range.
+constexpr int ONE_COLS = 4, ONE_EXTRA = 4;
+
+__global__ __launch_bounds__(SP_NT) void sparse_dw_columns_kernel(SparseDwArgs a, int n_colsum, int ranges)
+{
+    __shared__ float red[4][64];
+    int b = (int)blockIdx.x;
+    if (b < n_colsum) {
+        const int cols = (a.d1 + 63) / 64;
+        colsum_slice<SP_NT>(a.delta, a.ldd, a.B, a.d1, a.rows_per_split, a.colsum, b % cols, b / cols, red);
+        return;
     }
-    red[rg][threadIdx.x & 63] = s;
-    __syncthreads();
-    if (rg == 0 && col < d)
-        partial[(size_t)blockIdx.y * d + col] = red[0][threadIdx.x] + red[1][threadIdx.x] +
-                                                 red[2][threadIdx.x] + red[3][threadIdx.x];
+    b -= n_colsum;
+    const int n_light = (a.d0 + ONE_COLS - 1) / ONE_COLS;
+    if (b >= n_light) {
+        const int range = (b - n_light) % ranges, first = 1 + (b - n_light) / ranges, n = a.chunk_start[range];
+        for (int k = 0; k < n; ++k) {
+            const int4 desc = a.chunk_desc[range * one_width(a.d0) + k];
+            const int per = fb_part_len(desc.z - desc.y);
+            for (int part = first; desc.y + part * per < desc.z; part += ONE_EXTRA)
+                sparse_dw_part(a, desc.x, desc.y + part * per, min(desc.z, desc.y + (part + 1) * per), false);
+        }
+        return;
+    }
+    const int c0 = b * ONE_COLS;
+    int at[ONE_COLS + 1], n[ONE_COLS], most = 0;
+#pragma unroll
+    for (int k = 0; k <= ONE_COLS; ++k) at[k] = a.col_start[min(c0 + k, a.d0)];
+#pragma unroll
+    for (int k = 0; k < ONE_COLS; ++k) {
+        n[k] = at[k + 1] - at[k];
+        if (n[k] <= LIGHT_MAX && a.vec) most = max(most, n[k]);
+    }
+    if (most > 0) {
+        const int n4 = a.d1 >> 2;
+        for (int q = threadIdx.x; q < n4; q += SP_NT) {
+            float4 g[ONE_COLS];
+#pragma unroll
+            for (int k = 0; k < ONE_COLS; ++k) g[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int e = 0; e < most; e += 4) {
+                float4 d[ONE_COLS][4];
+                float v[ONE_COLS][4];
+#pragma unroll
+                for (int k = 0; k < ONE_COLS; ++k)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const bool ok = n[k] <= LIGHT_MAX && e + u < n[k];
+                        const int2 en = ok ? a.csc_ent[at[k] + e + u] : make_int2(0, 0);
+                        v[k][u] = __int_as_float(en.y);
+                        d[k][u] = ok ? reinterpret_cast<const float4 *>(a.delta + (size_t)en.x * a.ldd)[q]
+                                     : make_float4(0.f, 0.f, 0.f, 0.f);
+                    }
+#pragma unroll
+                for (int k = 0; k < ONE_COLS; ++k)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {  // added in index order
+                        g[k].x += v[k][u] * d[k][u].x; g[k].y += v[k][u] * d[k][u].y;
+                        g[k].z += v[k][u] * d[k][u].z; g[k].w += v[k][u] * d[k][u].w;
+                    }
+            }
+            auto mine = [&](int k) { return n[k] > 0 && n[k] <= LIGHT_MAX; };
+            if (a.grad_out) {
+#pragma unroll
+                for (int k = 0; k < ONE_COLS; ++k) {
+                    if (!mine(k)) continue;
+                    float *o = a.grad_out + (size_t)(4 * q) * a.d0 + c0 + k;
+                    o[0] = g[k].x; o[a.d0] = g[k].y; o[2 * (size_t)a.d0] = g[k].z; o[3 * (size_t)a.d0] = g[k].w;
+                }
+            } else {
+                float4 x[ONE_COLS];
+#pragma unroll
+                for (int k = 0; k < ONE_COLS; ++k)
+                    if (mine(k)) x[k] = reinterpret_cast<const float4 *>(a.W1t + (size_t)(c0 + k) * a.ldw)[q];
+#pragma unroll
+                for (int k = 0; k < ONE_COLS; ++k) {
+                    if (!mine(k)) continue;
+                    x[k].x -= a.lr * g[k].x; x[k].y -= a.lr * g[k].y; x[k].z -= a.lr * g[k].z; x[k].w -= a.lr * g[k].w;
+                    reinterpret_cast<float4 *>(a.W1t + (size_t)(c0 + k) * a.ldw)[q] = x[k];
+                }
+            }
+        }
+    }
+#pragma unroll 1
+    for (int k = 0; k < ONE_COLS; ++k) {
+        const int beg = a.col_start[min(c0 + k, a.d0)], end = a.col_start[min(c0 + k + 1, a.d0)];
+        if (end - beg <= (a.vec ? LIGHT_MAX : 0)) continue;
+        const int per = fb_part_len(end - beg);
+        sparse_dw_part(a, c0 + k, beg, min(end, beg + per), end - beg <= per);
+    }
 }
 
 // out[c][r] = in[r][c]  (R x C -> C x R), 32 x 32 tiles through LDS
@@ -911,6 +1109,14 @@ bool csc_supported(int d0, long long max_B)
 // cnt[d0 + 1] followed by the per-group totals of the column scan
 size_t csc_cnt_elems(int d0) { return (size_t)d0 + 1 + (1 + N_CLASS) * (size_t)((d0 + COLG - 1) / COLG); }
 
+// The line of the one-launch build and of the weight gradient that goes with it.  Against four launches on a stream of their
+// own beside the forward pass, us per step (rows, entries: four launches / one): 8003-320-64-2 16 rows, 461: 67.6 / 33.0, 300, 7559:
+// 65.0 / 44.1, 701, 17744: 71.6 / 54.0, 1100, 27769: 72.1 / 67.3; 20958-512-512-2 300, 12421: 76.8 / 62.8, 701, 28975: 81.0 / 83.2;
+// with 8 entries a row 900, 6805: 71.8 / 66.1, 1500, 11409: 71.2 / 80.5; 30000-1000-2 900, 16203: 86.4 / 82.4, 1500, 26792: 96.9 / 108.5;
+// 2003-50-10 701, 16934: 78.7 / 76.8, 900, 21652: 79.7 / 88.5; 4001-128-2 701, 31769: 65.8 / 46.9.
+constexpr long long CSC_ONE_NNZ = ONE_U * CSC_NT;
+constexpr long long CSC_ONE_ROWS = 1024;  // the batch's row_ptr lies in LDS
+
 size_t csc_hist_elems(long long max_B, int d0) { return (size_t)csc_blocks(max_B) * (size_t)d0; }
 
 
@@ -959,8 +1165,44 @@ hipError_t launch_csc_build(const int32_t *row_ptr, const int32_t *col_idx, cons
     return hipGetLastError();
 }
 
-hipError_t launch_sparse_dw(const SparseDwArgs &a, long long nnz, hipStream_t stream, const LaunchEvents &ev)
+// HB_CSC_ONE (tuning and test aid; read per call): a lower limit of non-zeros for the one-launch build, 0: never.
+bool csc_one_launch(long long nnz, long long B)
 {
+    const char *env = getenv("HB_CSC_ONE");
+    const long long most = env && *env && atoll(env) < CSC_ONE_NNZ ? atoll(env) : CSC_ONE_NNZ;
+    return nnz > 0 && nnz <= most && B <= CSC_ONE_ROWS;
+}
+
+hipError_t launch_csc_one(const int32_t *row_ptr, const int32_t *col_idx, const float *vals, long long nnz, long long B, int d0,
+                          int32_t *col_start, int32_t *chunk_start, int4 *chunk_desc, int2 *csc_ent, hipStream_t stream,
+                          const LaunchEvents &ev)
+{
+    if (one_width(d0) > CSC_NT || B > CSC_ONE_ROWS || nnz > CSC_ONE_NNZ) return hipErrorInvalidValue;
+    const int cap = (int)nnz;
+    const size_t lds = ((size_t)one_width(d0) + (size_t)B + 1 + (size_t)nnz) * sizeof(int32_t);  // 87 KB at most
+    if (lds > 32 * 1024) {
+        static LdsGrant granted;
+        const hipError_t ea = grant_lds(granted, lds, csc_one_kernel);
+        if (ea != hipSuccess) return ea;
+    }
+    if (ev.start)
+        hipExtLaunchKernelGGL(csc_one_kernel, dim3((unsigned)one_ranges(d0)), dim3(CSC_NT), (unsigned)lds, stream, ev.start, ev.stop,
+                              0, row_ptr, col_idx, vals, (int)B, d0, cap, col_start, chunk_start, chunk_desc, csc_ent);
+    else
+        hipLaunchKernelGGL(csc_one_kernel, dim3((unsigned)one_ranges(d0)), dim3(CSC_NT), lds, stream, row_ptr, col_idx, vals, (int)B,
+                           d0, cap, col_start, chunk_start, chunk_desc, csc_ent);
+    return hipGetLastError();
+}
+
+hipError_t launch_sparse_dw(const SparseDwArgs &a_in, long long nnz, hipStream_t stream, const LaunchEvents &ev)
+{
+    SparseDwArgs a = a_in;
+    if (a.colsum) {
+        a.rows_per_split = (int)((a.B + a.colsum_splits - 1) / a.colsum_splits);
+        const int n_colsum = (a.d1 + 63) / 64 * a.colsum_splits, ranges = one_ranges(a.d0);
+        const int blocks = n_colsum + (a.d0 + ONE_COLS - 1) / ONE_COLS + ONE_EXTRA * ranges;
+        return launch_kernel(sparse_dw_columns_kernel, dim3((unsigned)blocks), dim3(SP_NT), stream, ev, a, n_colsum, ranges);
+    }
     // descriptors: one per distinct column of the batch + the extra parts of the very long ones
     const long long max_cols = (nnz < a.d0 ? nnz : a.d0) + nnz / SPLIT;
     if (nnz <= 0) return hipSuccess;

@@ -785,6 +785,26 @@ def test_csr_weight_gradient_with_fewer_workgroups_than_pieces_of_work(monkeypat
     check_csr_case(dims, hi.ACT_SIGMOID, hi.LOSS_LOGISTIC, params, rp, ci, va, y, lr=0.1)
 
 
+CSR_ONE_LAUNCH = [
+    ((3, 8, 2), 5, 2),              # fewer columns than ranges of columns
+    ((129, 320, 2), 1024, 18),      # ranges of two columns, the last of one; the most rows; columns of several parts
+    ((20001, 64, 2), 300, 60),      # a wide range, columns of 1 .. 4 entries, ranges without any
+    ((700, 33, 2), 400, 50),        # rows of delta_1 that are no float4: close to the most entries (20,480)
+    ((400, 1028, 1), 130, 20),      # more than a float4 to a thread
+    ((900, 256, 2), 400, 40),       # in four launches: slices of d_1 per XCD
+]
+
+
+@pytest.mark.parametrize("one", ["", "0"])
+@pytest.mark.parametrize("dims,B,mean_nnz", CSR_ONE_LAUNCH)
+def test_csr_batches_with_the_columns_built_in_one_launch_and_in_four(monkeypatch, dims, B, mean_nnz, one):
+    monkeypatch.setenv("HB_CSC_ONE", one)
+    params, rp, ci, va, y = _csr_problem(dims, B, seed=900 + B, mean_nnz=mean_nnz)
+    assert B <= 1024 and ci.size <= 20480, ci.size
+    rp, ci, va = hi.scramble_csr_rows(rp, ci, va, np.random.default_rng(B), dup_prob=0.0)
+    check_csr_case(dims, hi.ACT_SIGMOID, hi.LOSS_LOGISTIC, params, rp, ci, va, y, lr=0.1)
+
+
 @pytest.mark.parametrize("seed", [11, 12])
 def test_random_csr_shapes_match_oracle(seed):
     """Seeded sweep over CSR batches: input widths from 10 to 30,000 columns, 1 to 50 stored entries

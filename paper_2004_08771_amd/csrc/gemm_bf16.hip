@@ -291,6 +291,29 @@ __device__ __forceinline__ void epilogue_bf16(const GemmBf16Args &a, v16f (&acc)
     });
 }
 
+// The 256 x 256 kernel multiplies in 16 x 16 blocks (v_mfma_f32_16x16x32_bf16): a block has rows 4 g + e and column c in lane 16 g + c, register e.
+// Two wavefronts of a SIMD that issue v_mfma_f32_32x32x16_bf16 in turn reach only two thirds of what the 16 x 16 form gives
+// (registers only, normal values: 1290-1340 against 2030 TFLOP/s, zeros 1604 against 2468; one wavefront alone 1807 against 2041);
+// here, where both also read and load, four steps of 2048-4096x3-1000 over 16384 rows went from 18.53 to 18.06 ms with it.
+// The epilogues want 32 x 32 blocks (rows 8 q + 4 h + e, column r in lane 32 h + r, register 4 q + e): of a pair of blocks side by
+// side, lane bit 5 (rows 8 ..) becomes a register and the column block lane bit 4, two lane exchanges for two registers.
+typedef float v4f __attribute__((ext_vector_type(4)));
+template <int TM, int TN>
+__device__ __forceinline__ void blocks_of_32(v16f (&out)[TM][TN], const v4f (&in)[2 * TM][2 * TN])
+{
+#pragma unroll
+    for (int i = 0; i < 2 * TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const auto y = __builtin_amdgcn_permlane16_swap(__float_as_uint(in[i][2 * j][e]), __float_as_uint(in[i][2 * j + 1][e]), false, false);
+                const auto z = __builtin_amdgcn_permlane32_swap(y[0], y[1], false, false);
+                out[i / 2][j][8 * (i & 1) + e] = __uint_as_float(z[0]);
+                out[i / 2][j][8 * (i & 1) + 4 + e] = __uint_as_float(z[1]);
+            }
+}
+
 // ---- products with too few 256 x 256 tiles: 64 x 64 or 128 x 128 tiles -----------------------
 // What bounds a product of this size is latency: a k-tile of 64 is only four MFMAs per block and
 // wavefront, and an L2 round trip under load takes about 550 cycles.  So four register sets keep
@@ -745,13 +768,12 @@ __device__ __forceinline__ v2i lds_read_tr16_b64(unsigned addr)
     return v;
 }
 
-// slot permutation of tile row R: bit 0 of the chunk index (the half-wavefront h of a fragment
-// read) is never mixed with the row bits that vary inside one 16-lane group
-__device__ __forceinline__ int swz(int R)
-{
-    const int q = (R >> 1) & 7;
-    return ((q & 3) << 1) | (q >> 2);
-}
+// slot permutation of tile row R: the sixteen rows that a fragment read touches at one chunk, and any of its sets of rows 0-3,
+// 12-15 at one chunk and 4-11 at the next, lie on different banks
+__device__ __forceinline__ int swz(int R) { return (R >> 1) & 7; }
+// the same for k-row k of a batch-major tile (512 bytes): the four rows of a transposing read on different 64-byte segments, the
+// rows eight on, which the next sixteen lanes read, on the other 32 bytes of each
+__device__ __forceinline__ int swz_k(int k) { return ((k & 3) << 2) ^ (((k >> 3) & 1) << 1); }
 
 constexpr int DMA_NT = 512;
 constexpr int DMA_BM = 256, DMA_BN = 256, DMA_BK = 64;
@@ -932,7 +954,7 @@ __device__ __forceinline__ void epilogue_bf16_lds(const GemmBf16Args &a, v16f (&
 // k-rows 0..3 (layout checked with an in-bounds probe).  Two such reads make one operand
 // fragment.  The four k-rows a group reads together are 512 bytes apart, i.e. on the same
 // banks: the 64-byte segments of k-row k are therefore stored at segment index s ^ (k & 3)
-// (the direct loads fetch the permuted segment, their LDS side stays contiguous).
+// (the direct loads fetch the permuted segment, their LDS side stays contiguous; the 32-byte halves: swz_k).
 template <int KIND, bool BMAJ>
 __device__ __forceinline__ void gemm_bf16_dma_tile(const GemmBf16Args &a, unsigned char *smem_raw, int id, int T,
                                                    int tid)
@@ -940,7 +962,6 @@ __device__ __forceinline__ void gemm_bf16_dma_tile(const GemmBf16Args &a, unsign
     static_assert(!BMAJ || KIND == GEMM_DW, "batch-major operands: weight gradient only");
     constexpr int BM = DMA_BM, BN = DMA_BN, BK = DMA_BK;
     constexpr int TM = 4, TN = 2;  // 32 x 32 blocks per wavefront: 128 x 64
-    constexpr int G = BK / 16;     // MFMA k-steps per tile
 
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: LDS bases of the direct loads are scalars
@@ -993,7 +1014,7 @@ __device__ __forceinline__ void gemm_bf16_dma_tile(const GemmBf16Args &a, unsign
     for (int v = 0; v < 4; ++v) {
         if (BMAJ) {
             const int k = (wave + 8 * v) * 2 + (lane >> 5);
-            const int chunk = (lane & 31) ^ ((k & 3) << 2);  // the chunk whose slot is lane % 32
+            const int chunk = (lane & 31) ^ swz_k(k);  // the chunk whose slot is lane % 32
             offA[v] = (unsigned)((size_t)k * (size_t)a.lda * 2 +
                                  (size_t)min((long long)m0 * 2 + chunk * 16, a.lda * 2 - 16));
             offB[v] = (unsigned)((size_t)k * (size_t)a.ldb * 2 +
@@ -1005,55 +1026,42 @@ __device__ __forceinline__ void gemm_bf16_dma_tile(const GemmBf16Args &a, unsign
             offB[v] = (unsigned)((size_t)min(n0 + R, a.N - 1) * (size_t)a.ldb * 2 + chunk * 16);
         }
     }
-    // loads first .. first + 1 of the wavefront's four of an A / B tile (tile t -> given stage)
-    auto issue_a = [&](int t, int stage, int first) {
-        unsigned char *st = smem_raw + stage * DMA_A_BYTES;
-#pragma unroll
-        for (int v = first; v < first + 2; ++v)
-            __builtin_amdgcn_global_load_lds((gptr_t)(Ab + (size_t)t * a_tile_step + offA[v]),
-                                             (lptr_t)(st + (wave + 8 * v) * 1024), 16, 0, 0);
+    // load v of the wavefront's four of an A / B tile (tile t -> given stage)
+    auto issue_a = [&](int t, int stage, int v) {
+        __builtin_amdgcn_global_load_lds((gptr_t)(Ab + (size_t)t * a_tile_step + offA[v]),
+                                         (lptr_t)(smem_raw + stage * DMA_A_BYTES + (wave + 8 * v) * 1024), 16, 0, 0);
     };
-    auto issue_b = [&](int t, int stage, int first) {
-        unsigned char *st = smem_raw + DMA_B_BASE + stage * DMA_B_BYTES;
-#pragma unroll
-        for (int v = first; v < first + 2; ++v)
-            __builtin_amdgcn_global_load_lds((gptr_t)(Bb + (size_t)t * b_tile_step + offB[v]),
-                                             (lptr_t)(st + (wave + 8 * v) * 1024), 16, 0, 0);
+    auto issue_b = [&](int t, int stage, int v) {
+        __builtin_amdgcn_global_load_lds((gptr_t)(Bb + (size_t)t * b_tile_step + offB[v]),
+                                         (lptr_t)(smem_raw + DMA_B_BASE + stage * DMA_B_BYTES + (wave + 8 * v) * 1024), 16, 0, 0);
     };
 
-    // ---- LDS side of the fragment reads: lane (r, h) reads chunk 2 kk + h of its row.  The
-    // block offsets i * 32 rows leave (R >> 1) & 7 unchanged, so the swizzle depends on r only.
-    // BMAJ: lane 16 g + 4 j + q addresses k-row 16 kk + 8 h + 4 t + j (t = 0, 1: the two reads of
-    // a fragment), bytes 32 (g & 1) + 8 q of the block's 64-byte segment, which is stored at
-    // segment index (true index) ^ j; the block index enters as one more XOR.
-    const int fr = swz(r);
-    const int tj = (lane & 15) >> 2;
-    const int a_off = BMAJ ? (8 * h + tj) * 512 + (((wm * 4) ^ tj) << 6) + 32 * ((lane >> 4) & 1) + 8 * (lane & 3)
-                         : (wm * 128 + r) * DMA_ROW_BYTES + ((h ^ fr) << 4);  // k-step kk: a_off ^ (kk << 5)
-    const int b_off = DMA_B_BASE + (BMAJ ? (8 * h + tj) * 512 + (((wn * 2) ^ tj) << 6) + 32 * ((lane >> 4) & 1) + 8 * (lane & 3)
-                                       : (wn * 64 + r) * DMA_ROW_BYTES + ((h ^ fr) << 4));
-    v8bf fa[2][TM], fb[2][TN];
+    // ---- LDS side of the fragment reads: lane 16 g + c reads chunk 4 kk + g of row c of its block (k-step kk: 32 deep).  The
+    // block offsets i * 16 rows leave (R >> 1) & 7 unchanged, so the swizzle depends on c only.
+    // BMAJ: lane 16 g + 4 j + q addresses k-row 32 kk + 8 g + 4 t + j (t = 0, 1: the two reads of a fragment), bytes 8 q ..
+    // of the block's 32, which are the (block % 2)-th half of segment block / 2; both indices are exchanged as swz_k
+    // says, and the block index enters as one more XOR.
+    const int c16 = lane & 15, g4 = lane >> 4;
+    const int fr = swz(c16);
+    const int tj = c16 >> 2;
+    const int a_off = BMAJ ? (8 * g4 + tj) * 512 + (((wm * 4) ^ tj) << 6) + 32 * (g4 & 1) + 8 * (lane & 3)
+                         : (wm * 128 + c16) * DMA_ROW_BYTES + ((g4 ^ fr) << 4);  // k-step kk: a_off ^ (kk << 6)
+    const int b_off = DMA_B_BASE + (BMAJ ? (8 * g4 + tj) * 512 + (((wn * 2) ^ tj) << 6) + 32 * (g4 & 1) + 8 * (lane & 3)
+                                       : (wn * 64 + c16) * DMA_ROW_BYTES + ((g4 ^ fr) << 4));
+    v8bf fa[2][TM], fb[2][2 * TN];  // half of the wavefront's rows (64) / all of its columns at one k-step
     const unsigned lds0 = (unsigned)(size_t)(lptr_t)smem_raw;  // LDS byte address of the stages
     // one operand fragment (block q of the A or B tile at p, k-step kk; kk is a KStep<> so
     // that the batch-major form can put it into the instruction's offset field)
     auto frag = [&](const unsigned char *p, int off, int q, auto kkc) -> v8bf {
         constexpr int kk = decltype(kkc)::value;
         if (BMAJ) {
-            const unsigned addr = lds0 + (unsigned)(p - smem_raw) + (unsigned)(off ^ (q << 6));
-            const v2i lo = lds_read_tr16_b64<kk * 16 * 512>(addr);
-            const v2i hi = lds_read_tr16_b64<kk * 16 * 512 + 4 * 512>(addr);
+            const unsigned addr = lds0 + (unsigned)(p - smem_raw) + (unsigned)(off ^ (q << 5));
+            const v2i lo = lds_read_tr16_b64<kk * 32 * 512>(addr);
+            const v2i hi = lds_read_tr16_b64<kk * 32 * 512 + 4 * 512>(addr);
             return __builtin_bit_cast(v8bf, __builtin_shufflevector(lo, hi, 0, 1, 2, 3));
         } else {
-            return *reinterpret_cast<const v8bf *>(p + ((off ^ (kk << 5)) + q * 32 * DMA_ROW_BYTES));
+            return *reinterpret_cast<const v8bf *>(p + ((off ^ (kk << 6)) + q * 16 * DMA_ROW_BYTES));
         }
-    };
-    auto read_frags = [&](int slot, int sa, int sb, auto kkc) {
-        const unsigned char *pa = smem_raw + sa * DMA_A_BYTES;
-        const unsigned char *pb = smem_raw + sb * DMA_B_BYTES;
-#pragma unroll
-        for (int i = 0; i < TM; ++i) fa[slot][i] = frag(pa, a_off, i, kkc);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) fb[slot][j] = frag(pb, b_off, j, kkc);
     };
     // the compiler does not know when the batch-major form's fragments have arrived
     auto frags_landed = [&]() {
@@ -1061,13 +1069,11 @@ __device__ __forceinline__ void gemm_bf16_dma_tile(const GemmBf16Args &a, unsign
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    v16f acc[TM][TN];
+    v4f acc16[2 * TM][2 * TN];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < 2 * TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+        for (int j = 0; j < 2 * TN; ++j) acc16[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
 
     // Epilogue through LDS (uniform for the workgroup): bf16 output wanted, row-major or in both
     // layouts (and, except for the fused update, nothing else), workgroup tile inside the
@@ -1097,66 +1103,64 @@ __device__ __forceinline__ void gemm_bf16_dma_tile(const GemmBf16Args &a, unsign
             for (int j = 0; j < TN; ++j) mword[i][j] = mi[((size_t)i * a.mask_nb + j) * 64];
     }
 
-    auto mfma_step = [&](int slot) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[slot][i], fb[slot][j], acc[i][j], 0, 0, 0);
-    };
-    // One MFMA group: the eight MFMAs of the k-step whose fragments are in `slot`, and in
-    // their shadow (a wavefront can issue other instructions while its MFMA executes) the
-    // requests for the next group's fragments, two after each of the first three MFMAs, and
-    // two direct loads after the fifth.  Clumped in front of the group instead, these
+    // One MFMA group: the sixteen MFMAs of one half of the wavefront's rows at one k-step (A fragments in fa[half], B fragments in
+    // fb[bs]), and in their shadow (a wavefront can issue other instructions while its MFMA executes) the
+    // requests for the next group's fragments -- the other half of the rows, or (second half) the first one of the next k-step
+    // and that step's B --, one after each of the first MFMAs, and
+    // two direct loads after the sixth and eleventh (eleventh and fifteenth).  Clumped, these
     // requests are issued by both wavefronts of a SIMD at the same time (the barrier keeps
-    // them in step) and the MFMA pipe idles meanwhile.  Only the requests are conditional,
+    // them in step) and the MFMA pipe idles meanwhile: with two fragments to an MFMA and the two loads together four steps of
+    // 2048-4096x3-1000 over 16384 rows, their readback included, take 18.06 ms, so 17.53.  Only the requests are conditional,
     // so that there is one MFMA stream.
-    auto group = [&](int slot, bool rd, int sa, int sb, auto kk, bool ld, bool is_a, int t, int stage, int first) {
+    auto group = [&](auto half_c, int bs, bool rd, int sa, int sb, auto kk, bool ld, bool is_a, int t, int stage, int first) {
+        constexpr int half = decltype(half_c)::value;
         const unsigned char *pa = smem_raw + sa * DMA_A_BYTES;
         const unsigned char *pb = smem_raw + sb * DMA_B_BYTES;
-        const int rs = slot ^ 1;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[slot][i], fb[slot][j], acc[i][j], 0, 0, 0);
-                const int b = i * TN + j;
+            for (int j = 0; j < 2 * TN; ++j) {
+                acc16[TM * half + i][j] =
+                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[half][i], fb[bs][j], acc16[TM * half + i][j], 0, 0, 0);
+                const int b = i * 2 * TN + j;
                 __builtin_amdgcn_sched_barrier(0);
-                if (b < 2) {
-                    if (rd) {
-#pragma unroll
-                        for (int q = 2 * b; q < 2 * b + 2; ++q) fa[rs][q] = frag(pa, a_off, q, kk);
-                    }
-                } else if (b == 2) {
-                    if (rd) {
-#pragma unroll
-                        for (int q = 0; q < TN; ++q) fb[rs][q] = frag(pb, b_off, q, kk);
-                    }
-                } else if (b == 4) {
-                    if (ld) {
-                        if (is_a) issue_a(t, stage, first);
-                        else issue_b(t, stage, first);
-                    }
+                if (rd) {
+                    if (b < TM) fa[half ^ 1][b] = frag(pa, a_off, b + (half ? 0 : TM), kk);
+                    else if (half && b < TM + 2 * TN) fb[bs ^ 1][b - TM] = frag(pb, b_off, b - TM, kk);
+                }
+                if (ld && (b == (half ? 10 : 5) || b == (half ? 14 : 10))) {
+                    const int v = first + (b == (half ? 14 : 10) ? 1 : 0);
+                    if (is_a) issue_a(t, stage, v);
+                    else issue_b(t, stage, v);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
     };
+    constexpr KStep<0> LO = {}, S0 = {};
+    constexpr KStep<1> HI = {}, S1 = {};
+    auto read_first = [&]() {  // the first group's fragments of the tile in stages 0
+#pragma unroll
+        for (int q = 0; q < TM; ++q) fa[0][q] = frag(smem_raw, a_off, q, S0);
+#pragma unroll
+        for (int q = 0; q < 2 * TN; ++q) fb[0][q] = frag(smem_raw, b_off, q, S0);
+    };
 
     if (nkf > 0) {
-        issue_a(0, 0, 0);
-        issue_a(0, 0, 2);
-        issue_b(0, 0, 0);
-        issue_b(0, 0, 2);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) issue_a(0, 0, v);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) issue_b(0, 0, v);
         if (nkf > 1) {
-            issue_b(1, 1, 0);
-            issue_b(1, 1, 2);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) issue_b(1, 1, v);
             issue_a(1, 1, 0);
+            issue_a(1, 1, 1);
             asm volatile("s_waitcnt vmcnt(6)\n\ts_barrier" ::: "memory");  // tile 0 landed
         } else {
             asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
         }
-        read_frags(0, 0, 0, KStep<0>());
-        static_assert(G == 4, "the load schedule below is written for four k-steps per tile");
+        read_first();
+        static_assert(BK == 64, "the load schedule below is written for two k-steps per tile");
         int b_cur = 0, b_nxt = 1, b_ld = 2;  // B stages of tiles kt, kt+1, kt+2
         for (int kt = 0; kt < nkf; ++kt) {
             const int a_cur = kt & 1;
@@ -1168,13 +1172,13 @@ __device__ __forceinline__ void gemm_bf16_dma_tile(const GemmBf16Args &a, unsign
             // barrier keeps the MFMAs behind the wait)
             __builtin_amdgcn_s_waitcnt(0xc07f);
             if (BMAJ) __builtin_amdgcn_sched_barrier(0);
-            group(0, true, a_cur, b_cur, KStep<1>(), next, true, kt + 1, a_cur ^ 1, 2);   // + second half of A(kt+1)
+            group(LO, 0, true, a_cur, b_cur, S0, next, true, kt + 1, a_cur ^ 1, 2);   // + second half of A(kt+1)
             __builtin_amdgcn_s_waitcnt(0xc07f);
             if (BMAJ) __builtin_amdgcn_sched_barrier(0);
-            group(1, true, a_cur, b_cur, KStep<2>(), next2, false, kt + 2, b_ld, 0);      // + B(kt+2): its stage held B(kt-1)
+            group(HI, 0, true, a_cur, b_cur, S1, next2, false, kt + 2, b_ld, 0);      // + B(kt+2): its stage held B(kt-1)
             __builtin_amdgcn_s_waitcnt(0xc07f);
             if (BMAJ) __builtin_amdgcn_sched_barrier(0);
-            group(0, true, a_cur, b_cur, KStep<3>(), next2, false, kt + 2, b_ld, 2);
+            group(LO, 1, true, a_cur, b_cur, S1, next2, false, kt + 2, b_ld, 2);
             // Tile kt+1 must have landed (this wavefront's share; the barrier covers the others');
             // the four loads of B(kt+2) just issued may stay in flight.  This wavefront's reads of
             // tile kt must be done before anyone overwrites its stages.
@@ -1182,9 +1186,9 @@ __device__ __forceinline__ void gemm_bf16_dma_tile(const GemmBf16Args &a, unsign
             else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
             __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0) again, this time visible to the compiler
             if (BMAJ) __builtin_amdgcn_sched_barrier(0);
-            // last k-step of tile kt; k-step 0 of tile kt+1 is requested from the stages that have
+            // last group of tile kt; the first fragments of tile kt+1 are requested from the stages that have
             // just been completed, and the first half of A(kt+2) goes into the stage just released
-            group(1, next, a_cur ^ 1, b_nxt, KStep<0>(), next2, true, kt + 2, a_cur, 0);
+            group(HI, 1, next, a_cur ^ 1, b_nxt, S0, next2, true, kt + 2, a_cur, 0);
             const int t = b_cur;
             b_cur = b_nxt;
             b_nxt = b_ld;
@@ -1204,7 +1208,7 @@ __device__ __forceinline__ void gemm_bf16_dma_tile(const GemmBf16Args &a, unsign
             const int q = isA ? idx : idx - BM * 8;
             if (BMAJ) {  // k-row q / 32, slot q % 32; k-rows past the end of the slice are zero
                 const int k = q >> 5, slot = q & 31;
-                const int chunk = slot ^ ((k & 3) << 2);
+                const int chunk = slot ^ swz_k(k);
                 uint4 x = {0u, 0u, 0u, 0u};
                 if (kbase + k < klen) {
                     const long long ld = isA ? a.lda : a.ldb;
@@ -1237,19 +1241,18 @@ __device__ __forceinline__ void gemm_bf16_dma_tile(const GemmBf16Args &a, unsign
                                        ((c ^ swz(R)) << 4)) = x;
         }
         __syncthreads();
-        read_frags(0, 0, 0, KStep<0>());
-        if (BMAJ) frags_landed();
-        mfma_step(0);
-        read_frags(1, 0, 0, KStep<1>());
-        if (BMAJ) frags_landed();
-        mfma_step(1);
-        read_frags(0, 0, 0, KStep<2>());
-        if (BMAJ) frags_landed();
-        mfma_step(0);
-        read_frags(1, 0, 0, KStep<3>());
-        if (BMAJ) frags_landed();
-        mfma_step(1);
+        read_first();
+        frags_landed();
+        group(LO, 0, true, 0, 0, S0, false, false, 0, 0, 0);
+        frags_landed();
+        group(HI, 0, true, 0, 0, S1, false, false, 0, 0, 0);
+        frags_landed();
+        group(LO, 1, true, 0, 0, S1, false, false, 0, 0, 0);
+        frags_landed();
+        group(HI, 1, false, 0, 0, S0, false, false, 0, 0, 0);
     }
+    v16f acc[TM][TN];
+    blocks_of_32<TM, TN>(acc, acc16);
 
     if (KIND == GEMM_DW && a.k_chunk > 0) {
         GemmBf16Args as = a;  // this slice's partial product

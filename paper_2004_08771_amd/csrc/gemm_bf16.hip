@@ -723,7 +723,7 @@ __global__ __launch_bounds__(NT *KG, KG == 1 ? 3 : 4) void gemm_bf16_mid_pair_ke
 
 // ---- 256 x 256 x 64 kernel with LDS-direct loads ------------------------------------------
 // Used when both operands allow 16-byte loads and the product is large enough for 256 x 256
-// tiles.  512 threads: eight wavefronts as 2 x 4, each 128 x 64 (4 x 2 MFMA blocks), two per
+// tiles.  512 threads: eight wavefronts as 2 x 4, each 128 x 64 (8 x 4 MFMA blocks), two per
 // SIMD.  Differences from the kernel above:
 //   * operand tiles go global -> LDS directly (global_load_lds_dwordx4: lane i of a wavefront
 //     writes its 16 bytes at LDS base + 16 i), no staging registers and no ds_write;

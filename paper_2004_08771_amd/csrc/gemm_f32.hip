@@ -407,9 +407,10 @@ int env_int(const char *name, int dflt)
 struct Shape {
     int bm, bn;
 };
-constexpr Shape SHAPES[] = {{64, 64}, {128, 64}, {128, 128}, {64, 64}};  // by the number launch_gemm_split takes
+constexpr Shape SHAPES[] = {{64, 64}, {128, 64}, {128, 128}, {64, 64}, {64, 32}};  // by the number launch_gemm_split takes
 constexpr int SHARED = 3;  // 64 x 64, the contraction shared by two groups of wavefronts ...
 constexpr int SHARED_K = 256;  // ... of at least this length (32-deep: 4.6 us alone, 4.8 shared)
+constexpr int HALF = 4;        // 64 x 32, the contraction shared by four groups (forward products only, long_fwd())
 constexpr int CUS = 256;
 constexpr int K_CHUNK_ALIGN = 32;  // slices of a split contraction are multiples of the k-tile
 
@@ -532,7 +533,7 @@ PairPlan plan_pair(const GemmArgs &da, const GemmArgs &dw, int max_splits)
 // of small products.  Small / split planes, us, forward products 512 wide: contraction of 128 4.4 / 5.0 with 64 tiles, 5.1 / 5.4
 // with 128, 5.9 / 5.6 with 152; of 256 4.7 / 6.4, 7.0 / 6.9, 8.2 / 7.0; of 512 7.5 / 9.2 with 64, 9.9 / 9.3 with 80, 9.8 / 9.4 with
 // 128, 11.7 / 9.4 with 152; of 1024 11.3 / 14.6, 15.8 / 14.7, 15.8 / 14.5, 19.8 / 14.8.  So the line of 160 tiles is that of
-// contractions up to 256; longer ones would be 0.5 to 5 us shorter as split planes from 80 tiles on.
+// contractions up to 256; longer ones: long_fwd().
 // Contractions below 64 stay with split planes, although the small kernels are quicker there (512 x 54 forward, 16 rows 5.3 us,
 // small 4.2; pair of 512 x 40, 48 rows 6.8, 4.2): over 300 drawn networks with inputs below 64 and 4 .. 63 rows their gradients
 // would be 1.035 times as far from 64 bits.
@@ -551,6 +552,19 @@ int small_k_max()
 bool small_out(int M, int N, int K)
 {
     return K >= 64 && (long long)((M + 63) / 64) * ((N + 63) / 64) < small_tiles_max();
+}
+// Forward products of 80 to 159 tiles (80 to 127 over contractions below 768, where the gain has come down to 3 %) over 512 and more go to the split planes, in tiles of 64 x 32 while each has a
+// compute unit of its own: four groups of two wavefronts share the contraction, a quarter of the k-tiles in a row each, where 64 x 64
+// tiles leave half of the device idle and fp32 MFMAs are a longer chain than the conversions.  Networks of w-w-w-w-w-w-4 (2048 and
+// more: w-w-w-4), forward and loss, us, small kernels / 64 x 64 / 64 x 32: w = 512 640 rows 55.5 / 54.0 / 47.1, 1021 rows 56.3 / 60.9 /
+// 54.6; 768 430 rows 72.7 / 76.7 / 64.1, 600 rows 74.3 / 71.6 / 61.9, 800 rows (312 tiles of 64 x 32) 90.0 / 77.3; 1024 320 rows 90.0 /
+// 82.6 / 66.9, 510 rows 93.4 / 89.8 / 80.8; 2048 130 rows 69.0 / 61.6 / 51.2, 250 rows 71.4 / 65.3 / 56.5; 4096 100 rows 130.7 / 116.6 /
+// 97.8.  Shorter contractions stay: 320 1021 rows 41.5 / 49.7 / 45.5; 256 2047 rows 38.9 / 45.3 / 43.0; fewer tiles too: 512 330 rows
+// 43.9 / - / 47.5, 768 300 rows 58.2 / - / 63.1.  Narrower outputs than the ones measured, and up to 64 rows (4096 wide 88.6 / 88.3 / -), stay too.
+bool long_fwd(int M, int N, int K)
+{
+    const long long tiles = (long long)((M + 63) / 64) * ((N + 63) / 64);
+    return K >= 512 && N >= 512 && M > 64 && tiles >= 80 && (K >= 768 || tiles < 128) && small_out(M, N, K);
 }
 // A weight gradient launched on its own (not paired with a backward-data product) whose output
 // is only a few tiles -- the first layer of a narrow input, 512 x 54 -- stays with the small
@@ -628,10 +642,12 @@ struct F32Plan {
 };
 F32Plan plan_f32(GemmKind kind, int M, int N, int K, int max_splits)
 {
-    if (kind == GEMM_DW ? small_dw_alone(M, N, K) : small_out(M, N, K)) {
+    if (kind == GEMM_DW ? small_dw_alone(M, N, K) : small_out(M, N, K) && !(kind == GEMM_FWD && long_fwd(M, N, K))) {
         if (kind == GEMM_DW) return {-1, plan_small_splits(K, max_splits)};
         return {-1, {1, (K + SMALL_CHUNK - 1) / SMALL_CHUNK * SMALL_CHUNK}};
     }
+    if (kind == GEMM_FWD && long_fwd(M, N, K) && tiles_of(HALF, M, N) <= CUS)
+        return {HALF, {1, (K + K_CHUNK_ALIGN - 1) / K_CHUNK_ALIGN * K_CHUNK_ALIGN}};
     if (kind != GEMM_DW)
         return {pick_shape(M, N, K), {1, (K + K_CHUNK_ALIGN - 1) / K_CHUNK_ALIGN * K_CHUNK_ALIGN}};
     int sh = (M >= 128) ? (N >= 128 ? 2 : 1) : 0;

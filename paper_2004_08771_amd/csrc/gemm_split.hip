@@ -644,7 +644,7 @@ hipError_t launch_kind(GemmKind kind, const GemmArgs &a, dim3 grid, hipStream_t 
 
 }  // namespace
 
-// shape: 0 64 x 64, 1 128 x 64, 2 128 x 128, 3 64 x 64 with two groups
+// shape: 0 64 x 64, 1 128 x 64, 2 128 x 128, 3 64 x 64 with two groups, 4 64 x 32 with four
 hipError_t launch_gemm_split(GemmKind kind, const GemmArgs &a, int shape, dim3 grid, hipStream_t stream,
                              const LaunchEvents &ev)
 {
@@ -652,6 +652,9 @@ hipError_t launch_gemm_split(GemmKind kind, const GemmArgs &a, int shape, dim3 g
     case 0: return launch_kind<256, 1, 64, 64, 2, 2>(kind, a, grid, stream, ev);
     case 1: return launch_kind<512, 1, 128, 64, 4, 1>(kind, a, grid, stream, ev);
     case 2: return launch_kind<512, 1, 128, 128, 2, 1>(kind, a, grid, stream, ev);
+    case 4:  // the forward product only
+        if (kind != GEMM_FWD) return hipErrorInvalidValue;
+        return launch_kernel(gemm_split_kernel<128, 4, 64, 32, 2, 1, true, true, GEMM_FWD>, grid, dim3(512), stream, ev, a);
     default: return launch_kind<256, 2, 64, 64, 2, 1>(kind, a, grid, stream, ev);
     }
 }

@@ -1268,6 +1268,28 @@ F32_EDGES = [
 ]
 
 
+F32_LONG_FORWARD = [
+    # tiles of 64 x 32 by four groups: 17 k-tiles, the partial one first, and 9 more than a row of groups; rows and columns cut
+    ((515, 546, 513, 4), hi.ACT_SIGMOID, 577, [5, 5]),
+    # the other line: 128 tiles over less than 768
+    ((512, 512, 4), hi.ACT_SIGMOID, 961, [0]),
+    # whole k-tiles, one row in the second tile, a wide output
+    ((512, 2560, 4), hi.ACT_RELU, 65, [5]),
+    # the line: 79 tiles, fp32 MFMAs; 156, but 312 of 64 x 32: 64 x 64 by two groups
+    ((512, 5056, 4), hi.ACT_SIGMOID, 64, [0]),
+    ((800, 768, 4), hi.ACT_SIGMOID, 800, [4]),
+]
+
+
+@pytest.mark.parametrize("dims,act,B,kernels", F32_LONG_FORWARD)
+def test_long_forward_products_of_few_tiles(dims, act, B, kernels):
+    from paper_2004_08771_amd import lib
+    got = [lib().hb_plan_f32_kernel(0, dims[l], dims[l - 1], B, B, None) for l in range(1, len(dims) - 1)]
+    check_plan(str(got), str(kernels))
+    params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=60 + B)
+    check_case(dims, act, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=False)
+
+
 F32_FEW_ROWS = [
     # the backward-data product's workgroups first (contraction 1100 against 17 rows) ...
     ((20, 1100, 1100, 3), hi.ACT_SIGMOID, 17, "64 small small; small 128x64; 128x64"),

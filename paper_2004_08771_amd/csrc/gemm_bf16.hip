@@ -707,7 +707,7 @@ void gemm_bf16_mid_kernel(GemmBf16Args a)
 
 // A weight gradient and the next product of the backward pass in one launch (pair_shares() below: KG).  What bounds either alone
 // is latency -- of the launch, of its first loads and of the round trip to memory that a k-tile is -- so both together
-// take little longer than one: 1024 x 1024 over 2047 rows 12.8 us + 2047 x 1024 x 1024 11.9 us apart, 22.4 in one launch, and
+// take little longer than one: 1024 x 1024 over 2047 rows 12.8 us + 2047 x 1024 x 1024 11.9 us apart, 21.3 in one launch, and
 // the narrow products of the output layer or of a 300-wide input vanish behind their neighbour (300-1024x3-2, 2047 rows: 133.5 ->
 // 113.1 us per step).  With two groups the register sets are two (105 registers), so that two workgroups fit a compute
 // unit; with one they are four and three workgroups do.

@@ -949,7 +949,7 @@ __global__ __launch_bounds__(256) void colsum_kernel(const float *__restrict__ d
 // the longest workgroups).  A workgroup takes ONE_COLS columns; the ones of up to LIGHT_MAX entries together, four
 // entries of each in a round, so that sixteen gathers are in flight, and their weight rows with one another: what bounds a
 // small batch is the chain offsets - entries - rows of delta - weights, four dependent trips to memory, and one column per
-// workgroup filled the device three times over with it.  Longer columns go one by one as in sparse_dw_kernel, the parts of
+// workgroup filled the device three times over with it (8003-320-64-2, 701 rows: 17.3 us with the bias gradient, 16.4 + 4.8 apart).  Longer columns go one by one as in sparse_dw_kernel, the parts of
 // those above CHUNK to the last ONE_EXTRA workgroups of each range.
 constexpr int ONE_COLS = 4, ONE_EXTRA = 4;
 

@@ -616,8 +616,8 @@ int run_step(hb_model *m, const Input &in, const int32_t *y, int64_t B, float lr
             if (csc_beside) {
                 HB_HIP(hipStreamWaitEvent(sw_stream, m->csc_join, 0));
             } else if (csc_one) {
-                HB_HIP(launch_csc_one(in.row_ptr, in.col_idx, in.vals, in.nnz, B, m->dims[0], m->d_col_start, m->d_chunk_start,
-                                      m->d_chunk_desc, m->d_csc_ent, sw_stream,
+                HB_HIP(launch_csc_one(in.row_ptr, in.col_idx, in.vals, in.nnz, B, m->dims[0], m->d_col_start, m->d_col_cnt,
+                                      m->d_chunk_start, m->d_chunk_desc, m->d_csc_ent, sw_stream,
                                       prof_begin(m, HB_K_OTHER, 2, 0, 0, 0, 0.0, 24.0 * in.nnz)));
             } else {
                 const int rc_b = csc_build(sw_stream);
@@ -637,6 +637,7 @@ int run_step(hb_model *m, const Input &in, const int32_t *y, int64_t B, float lr
             sd.lr = lr;
             sd.vec = (m->dims[1] % 4 == 0);
             if (csc_one) {
+                sd.col_cnt = m->d_col_cnt;
                 sd.colsum = m->partial_b[1];
                 sd.colsum_splits = m->b1_splits;
                 sd.B = B;

@@ -359,17 +359,19 @@ struct SparseDwArgs {
     int d0, d1;
     float lr;
     int vec;
-    // not null: the CSC comes from launch_csc_one, and the launch also adds up db_1's colsum_splits slices of the rows
+    // not null: the CSC comes from launch_csc_one, and the launch also adds up db_1's colsum_splits slices of the rows.  Then
+    // column c has col_cnt[c] entries from col_start[c], and chunk_start / chunk_desc hold the lists of long columns
     float *colsum;
+    const int32_t *col_cnt;
     int colsum_splits;
     long long B;
     int rows_per_split;          // filled in by launch_sparse_dw
 };
-// The CSC of a small batch in one launch (leaves col_start and per-range lists of long columns in chunk_start / chunk_desc)
+// The CSC of a small batch in one launch (leaves col_start, col_cnt and per-range lists of long columns in chunk_start / chunk_desc)
 bool csc_one_launch(long long nnz, long long B);
 hipError_t launch_csc_one(const int32_t *row_ptr, const int32_t *col_idx, const float *vals, long long nnz, long long B, int d0,
-                          int32_t *col_start, int32_t *chunk_start, int4 *chunk_desc, int2 *csc_ent, hipStream_t stream,
-                          const LaunchEvents &ev = LaunchEvents());
+                          int32_t *col_start, int32_t *col_cnt, int32_t *chunk_start, int4 *chunk_desc, int2 *csc_ent,
+                          hipStream_t stream, const LaunchEvents &ev = LaunchEvents());
 // Per-batch CSC (column-segmented copy of the batch's non-zeros) by a multi-block counting
 // sort; hist is scratch of csc_hist_elems(max_B, d0) int32, cnt of csc_cnt_elems(d0) int32.
 // Needs csc_supported(d0, max_B):

@@ -409,89 +409,114 @@ __global__ __launch_bounds__(CSC_NT) void csc_place_kernel(const int32_t *__rest
     }
 }
 
-// The CSC of a small batch in one launch: a workgroup owns a range of columns and looks at all of the batch's column
-// indices once (up to ONE_U to a thread, in registers), counts the ones below its range, which give the place of its first column,
-// and lists its own in LDS; then it counts and places these, a thread to each.  (Counted and placed where they were
-// found, by whichever lanes of a wavefront had one, the launch took 30 us longer per 17,000 entries.)  It
-// leaves col_start only and, per range, the list of its columns of more than CHUNK entries (chunk_desc[first column ..],
-// chunk_start[range] of them), for sparse_dw_columns_kernel.
+// The CSC of a small batch in one launch.  A workgroup owns a range of columns.  Each of its wavefronts looks at a contiguous
+// piece of the batch's column indices once (up to ONE_U to a lane), counts the ones below the range, which give the place of
+// its first column, and lists the workgroup's own in LDS; then it counts and places these, a lane to each.  (Counted and placed
+// where they were found, by whichever lanes had one, the launch took 30 us longer per 17,000 entries.)  Every column's
+// entries keep their order in the batch: wavefronts in turn (a prefix over their counts), lanes in turn (each compares its column
+// with the others' of a window of 64).  Placed by atomic counters instead, the sums of the weight gradient differed in the last
+// bits from run to run, and a few steps on a ReLU decision turned over.
+// It leaves, by column, the first entry and their number, and per range the list of its columns of more than ONE_LIST entries
+// (chunk_desc[first column ..], chunk_start[range] of them), for sparse_dw_columns_kernel.
 constexpr int ONE_RANGES = 128;  // at most
+constexpr int ONE_WAVES = CSC_NT / 64;
 constexpr int ONE_U = 20;      // 20,480 entries
 constexpr int ONE_BITS = 15;   // of an entry's number in a list
+constexpr int ONE_LIST = 32;
 static_assert(ONE_U * CSC_NT <= 1 << ONE_BITS, "entry numbers");
 __host__ __device__ inline int one_width(int d0) { return (d0 + ONE_RANGES - 1) / ONE_RANGES; }  // columns of a range
-inline int one_ranges(int d0) { return (d0 + one_width(d0) - 1) / one_width(d0); }
+__host__ __device__ inline int one_ranges(int d0) { return (d0 + one_width(d0) - 1) / one_width(d0); }
+// entries of a wavefront at most
+__host__ __device__ inline int one_piece(int nnz) { return ((nnz + ONE_WAVES - 1) / ONE_WAVES + 63) & ~63; }
 
 __global__ __launch_bounds__(CSC_NT) void csc_one_kernel(const int32_t *__restrict__ row_ptr,
                                                          const int32_t *__restrict__ col_idx,
                                                          const float *__restrict__ vals, int B, int d0, int cap,
                                                          int32_t *__restrict__ col_start,
+                                                         int32_t *__restrict__ col_cnt,
                                                          int32_t *__restrict__ chunk_start,
                                                          int4 *__restrict__ chunk_desc, int2 *__restrict__ csc_ent)
 {
-    extern __shared__ int32_t s_one[];  // cursors of the range's columns, row_ptr, the range's entries {column in the range, entry}
-    __shared__ int red[CSC_NT / 64], red2[CSC_NT / 64], n_heavy;
+    // cursors of the range's columns per wavefront, row_ptr, lists of entries {column in the range, entry} per wavefront
+    extern __shared__ int32_t s_one[];
+    __shared__ int red[ONE_WAVES], red2[ONE_WAVES], n_list;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int width = one_width(d0), lo = blockIdx.x * width, n = min(width, d0 - lo);  // n <= CSC_NT
-    int32_t *s_cnt = s_one, *s_rp = s_one + width;
-    unsigned *s_ent = reinterpret_cast<unsigned *>(s_rp + B + 1);
-    for (int c = t; c < n; c += CSC_NT) s_cnt[c] = 0;
+    const int range = blockIdx.x, width = one_width(d0), piece = one_piece(cap);
+    const int lo = range * width, n = min(width, d0 - lo);
+    int32_t *s_cur = s_one, *s_rp = s_one + ONE_WAVES * width;
+    unsigned *s_ent = reinterpret_cast<unsigned *>(s_rp + B + 1) + wave * piece;
+    for (int i = t; i < ONE_WAVES * width; i += CSC_NT) s_cur[i] = 0;
     for (int i = t; i <= B; i += CSC_NT) s_rp[i] = row_ptr[i];
-    if (t == 0) n_heavy = 0;
+    if (t == 0) n_list = 0;
     const int beg = row_ptr[0], entries = min(row_ptr[B] - beg, cap);
+    const int p0 = wave * piece, p1 = min(entries, p0 + piece);
     int c[ONE_U];
 #pragma unroll
-    for (int u = 0; u < ONE_U; ++u) c[u] = (t + u * CSC_NT < entries) ? col_idx[beg + t + u * CSC_NT] - lo : 0x7fffffff;
-    int below = 0, mine = 0;
+    for (int u = 0; u < ONE_U; ++u) {
+        const int p = p0 + u * 64 + lane;
+        c[u] = p < p1 ? col_idx[beg + p] - lo : 0x7fffffff;
+    }
+    int below = 0, mine = 0;  // mine: of the wavefront
 #pragma unroll
     for (int u = 0; u < ONE_U; ++u) {
+        const unsigned at = (unsigned)c[u];
         below += c[u] < 0 ? 1 : 0;
-        mine += (unsigned)c[u] < (unsigned)n ? 1 : 0;
+        const bool own = at < (unsigned)n;
+        const unsigned long long who = __ballot(own);
+        if (own) s_ent[mine + __popcll(who & ((1ull << lane) - 1))] = at << ONE_BITS | (unsigned)(p0 + u * 64 + lane);
+        mine += __popcll(who);
     }
-    const int incl_m = wave_incl_scan(mine, lane);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) below += __shfl_xor(below, o, 64);
-    if (lane == 63) {
-        red[wave] = below;
-        red2[wave] = incl_m;
-    }
+    if (lane == 0) red[wave] = below;
+    __syncthreads();  // cursors cleared, rows there
+    for (int i = lane; i < mine; i += 64) atomicAdd(&s_cur[wave * width + (s_ent[i] >> ONE_BITS)], 1);
     __syncthreads();
-    int first = 0, at = incl_m - mine, total = 0;
-#pragma unroll
-    for (int w = 0; w < CSC_NT / 64; ++w) {
-        first += red[w];
-        at += w < wave ? red2[w] : 0;
-        total += red2[w];
-    }
-#pragma unroll
-    for (int u = 0; u < ONE_U; ++u)
-        if ((unsigned)c[u] < (unsigned)n) s_ent[at++] = (unsigned)c[u] << ONE_BITS | (unsigned)(t + u * CSC_NT);
+    int cnt = 0;  // of column t of the range: a prefix over the wavefronts, and the whole
+    if (t < n)
+        for (int w = 0; w < ONE_WAVES; ++w) {
+            const int k = s_cur[w * width + t];
+            s_cur[w * width + t] = cnt;
+            cnt += k;
+        }
+    const int incl = wave_incl_scan(cnt, lane);
+    if (lane == 63) red2[wave] = incl;
     __syncthreads();
-    for (int i = t; i < total; i += CSC_NT) atomicAdd(&s_cnt[s_ent[i] >> ONE_BITS], 1);
-    __syncthreads();
-    const int cnt = t < n ? s_cnt[t] : 0, incl = wave_incl_scan(cnt, lane);
-    if (lane == 63) red[wave] = incl;
-    __syncthreads();
-    for (int w = 0; w < wave; ++w) first += red[w];
-    first += incl - cnt;
+    int first = incl - cnt;
+    for (int w = 0; w < ONE_WAVES; ++w) first += red[w] + (w < wave ? red2[w] : 0);
     if (t < n) {
-        s_cnt[t] = first;
-        col_start[lo + t] = first;
-        if (lo + t == d0 - 1) col_start[d0] = first + cnt;
-        if (cnt > CHUNK) chunk_desc[lo + atomicAdd(&n_heavy, 1)] = make_int4(lo + t, first, first + cnt, 1);
+        const int col = lo + t;
+        for (int w = 0; w < ONE_WAVES; ++w) s_cur[w * width + t] += first;
+        col_start[col] = first;
+        col_cnt[col] = cnt;
+        if (cnt > ONE_LIST) chunk_desc[lo + atomicAdd(&n_list, 1)] = make_int4(col, first, first + cnt, 1);
     }
     __syncthreads();
-    if (t == 0) chunk_start[blockIdx.x] = n_heavy;
-    for (int i = t; i < total; i += CSC_NT) {
-        const unsigned en = s_ent[i];
-        const int p = beg + (int)(en & ((1u << ONE_BITS) - 1));
-        const float v = vals[p];
+    if (t == 0) chunk_start[range] = n_list;
+    for (int i0 = 0; i0 < mine; i0 += 64) {
+        const bool live = i0 + lane < mine;
+        const unsigned en = live ? s_ent[i0 + lane] : ~0u;
+        const int at = (int)(en >> ONE_BITS), p = beg + (int)(en & ((1u << ONE_BITS) - 1));
+        const float v = live ? vals[p] : 0.f;
         int a = 0, b = B;  // s_rp[a] <= p < s_rp[b]
-        while (b - a > 1) {
+        while (live && b - a > 1) {
             const int mid = (a + b) >> 1;
             if (s_rp[mid] <= p) a = mid; else b = mid;
         }
-        csc_ent[atomicAdd(&s_cnt[en >> ONE_BITS], 1)] = make_int2(a, __float_as_int(v));
+        int rank = 0;  // entries of this column in the lanes before
+        bool last = true;
+        const int m = min(64, mine - i0);
+        for (int j = 0; j < m; ++j) {
+            const bool same = __builtin_amdgcn_readlane(at, j) == at;
+            rank += same && j < lane ? 1 : 0;
+            last = last && !(same && j > lane);
+        }
+        if (live) {
+            const int pos = s_cur[wave * width + at] + rank;
+            csc_ent[pos] = make_int2(a, __float_as_int(v));
+            if (last) s_cur[wave * width + at] = pos + 1;  // after every lane of the wavefront has read it
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
 }
 
@@ -674,7 +699,8 @@ struct CscEntries {
     }
 };
 
-template <bool AHEAD = false, class Entries>
+// EXACT: nothing is added past the end (with a row of infinities a zero value is not enough).
+template <bool AHEAD = false, bool EXACT = false, class Entries>
 __device__ __forceinline__ float4 group_gather_sum(float4 acc, const Entries en, int beg, int end,
                                                    const float *__restrict__ src, size_t ld, int l)
 {
@@ -710,6 +736,7 @@ __device__ __forceinline__ float4 group_gather_sum(float4 acc, const Entries en,
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const float v = __shfl(my_v, u0 + u, 16);
+                    if (EXACT && p + u0 + u >= end) continue;
                     acc.x += v * w[u].x; acc.y += v * w[u].y; acc.z += v * w[u].z; acc.w += v * w[u].w;
                 }
             }
@@ -946,44 +973,94 @@ __global__ __launch_bounds__(256) void colsum_kernel(const float *__restrict__ d
 }
 
 // Weight gradient of layer 1 from the CSC of csc_one_kernel, with the bias gradient's slices in the same launch (first: they are
-// the longest workgroups).  A workgroup takes ONE_COLS columns; the ones of up to LIGHT_MAX entries together, four
-// entries of each in a round, so that sixteen gathers are in flight, and their weight rows with one another: what bounds a
-// small batch is the chain offsets - entries - rows of delta - weights, four dependent trips to memory, and one column per
-// workgroup filled the device three times over with it (8003-320-64-2, 701 rows: 17.3 us with the bias gradient, 16.4 + 4.8 apart).  Longer columns go one by one as in sparse_dw_kernel, the parts of
-// those above CHUNK to the last ONE_EXTRA workgroups of each range.
-constexpr int ONE_COLS = 4, ONE_EXTRA = 4;
+// the longest workgroups).  What bounds a small batch is the chain offsets - entries - rows of delta - weights, four dependent
+// trips to memory, and one column per workgroup filled the device three times over with it.
+// Columns of up to ONE_LIST entries: a workgroup takes ONE_COLS, the ones of up to LIGHT_MAX entries together, four entries of
+// each in a round, so that sixteen gathers are in flight, and their weight rows with one another.  Longer columns come from
+// the lists: a workgroup takes 64 values of one, its eight groups of sixteen lanes a contiguous run of the entries each, and
+// adds their sums in order, so that a weight is rounded once and the same way in every run.
+constexpr int ONE_COLS = 4, ONE_ITEMS = 2048;
 
-__global__ __launch_bounds__(SP_NT) void sparse_dw_columns_kernel(SparseDwArgs a, int n_colsum, int ranges)
+__device__ __forceinline__ void sparse_dw_listed(const SparseDwArgs &a, int item, int items, float4 (&part)[SP_NT / 16][16])
 {
-    __shared__ float red[4][64];
+    const int lane = threadIdx.x & 63, g16 = threadIdx.x >> 4, l = threadIdx.x & 15;
+    const int ranges = one_ranges(a.d0), n_sl = (a.d1 + SL - 1) / SL, last4 = (a.d1 - 1) / 4 * 4;
+    // lane i has the columns of ranges 2 i and 2 i + 1
+    const int n0 = 2 * lane < ranges ? a.chunk_start[2 * lane] : 0, n1 = 2 * lane + 1 < ranges ? a.chunk_start[2 * lane + 1] : 0;
+    const int incl = wave_incl_scan(n0 + n1, lane), need = __shfl(incl, 63, 64) * n_sl;
+    for (; item < need; item += items) {
+        const int k = item / n_sl, col0 = (item - k * n_sl) * SL + 4 * l;
+        const int at = __popcll(__ballot(incl <= k));
+        int j = k - __shfl(incl - n0 - n1, at, 64), r = 2 * at;
+        const int n_first = __shfl(n0, at, 64);
+        if (j >= n_first) {
+            j -= n_first;
+            ++r;
+        }
+        const int4 desc = a.chunk_desc[r * one_width(a.d0) + j];
+        const int per = (((desc.z - desc.y + SP_NT / 16 - 1) / (SP_NT / 16)) + 15) & ~15;  // entries per group: whole windows
+        const int beg = min(desc.z, desc.y + g16 * per);
+        float4 g = {0.f, 0.f, 0.f, 0.f};
+        // lanes past d_1 repeat the last four values of the row (rows of delta are padded to four)
+        part[g16][l] = group_gather_sum<true, true>(g, CscEntries{a.csc_ent}, beg, min(desc.z, beg + per),
+                                                    a.delta + min(col0, last4), (size_t)a.ldd, l);
+        __syncthreads();
+        if (g16 == 0 && col0 < a.d1) {
+            float4 sum = part[0][l];
+#pragma unroll
+            for (int q = 1; q < SP_NT / 16; ++q) {
+                const float4 p = part[q][l];
+                sum.x += p.x; sum.y += p.y; sum.z += p.z; sum.w += p.w;
+            }
+            if (a.vec) {
+                apply_column_sum(a, desc.x, col0, sum);
+            } else {
+                const float s[4] = {sum.x, sum.y, sum.z, sum.w};
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (col0 + u < a.d1) {
+                        if (a.grad_out) a.grad_out[(size_t)(col0 + u) * a.d0 + desc.x] = s[u];
+                        else a.W1t[(size_t)desc.x * a.ldw + col0 + u] -= a.lr * s[u];
+                    }
+            }
+        }
+        __syncthreads();  // part is reused
+    }
+}
+
+__global__ __launch_bounds__(SP_NT, 4) void sparse_dw_columns_kernel(SparseDwArgs a, int n_colsum, int n_items)
+{
+    __shared__ union {
+        float red[4][64];
+        float4 part[SP_NT / 16][16];
+    } s;
     int b = (int)blockIdx.x;
     if (b < n_colsum) {
         const int cols = (a.d1 + 63) / 64;
-        colsum_slice<SP_NT>(a.delta, a.ldd, a.B, a.d1, a.rows_per_split, a.colsum, b % cols, b / cols, red);
+        colsum_slice<SP_NT>(a.delta, a.ldd, a.B, a.d1, a.rows_per_split, a.colsum, b % cols, b / cols, s.red);
         return;
     }
     b -= n_colsum;
-    const int n_light = (a.d0 + ONE_COLS - 1) / ONE_COLS;
-    if (b >= n_light) {
-        const int range = (b - n_light) % ranges, first = 1 + (b - n_light) / ranges, n = a.chunk_start[range];
-        for (int k = 0; k < n; ++k) {
-            const int4 desc = a.chunk_desc[range * one_width(a.d0) + k];
-            const int per = fb_part_len(desc.z - desc.y);
-            for (int part = first; desc.y + part * per < desc.z; part += ONE_EXTRA)
-                sparse_dw_part(a, desc.x, desc.y + part * per, min(desc.z, desc.y + (part + 1) * per), false);
-        }
+    if (b < n_items) {
+        sparse_dw_listed(a, b, n_items, s.part);
         return;
     }
-    const int c0 = b * ONE_COLS;
-    int at[ONE_COLS + 1], n[ONE_COLS], most = 0;
-#pragma unroll
-    for (int k = 0; k <= ONE_COLS; ++k) at[k] = a.col_start[min(c0 + k, a.d0)];
+    b -= n_items;
+    const int joint = a.vec ? LIGHT_MAX : 0;  // columns of up to this many entries are taken together
+    int c[ONE_COLS], at[ONE_COLS], n[ONE_COLS], most = 0;
 #pragma unroll
     for (int k = 0; k < ONE_COLS; ++k) {
-        n[k] = at[k + 1] - at[k];
-        if (n[k] <= LIGHT_MAX && a.vec) most = max(most, n[k]);
+        c[k] = b * ONE_COLS + k;
+        at[k] = a.col_start[min(c[k], a.d0 - 1)];
+        n[k] = a.col_cnt[min(c[k], a.d0 - 1)];
+    }
+#pragma unroll
+    for (int k = 0; k < ONE_COLS; ++k) {
+        if (c[k] >= a.d0) n[k] = 0;
+        if (n[k] <= joint) most = max(most, n[k]);
     }
     if (most > 0) {
+        auto mine = [&](int k) { return n[k] > 0 && n[k] <= joint; };
         const int n4 = a.d1 >> 2;
         for (int q = threadIdx.x; q < n4; q += SP_NT) {
             float4 g[ONE_COLS];
@@ -996,7 +1073,7 @@ __global__ __launch_bounds__(SP_NT) void sparse_dw_columns_kernel(SparseDwArgs a
                 for (int k = 0; k < ONE_COLS; ++k)
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
-                        const bool ok = n[k] <= LIGHT_MAX && e + u < n[k];
+                        const bool ok = n[k] <= joint && e + u < n[k];
                         const int2 en = ok ? a.csc_ent[at[k] + e + u] : make_int2(0, 0);
                         v[k][u] = __int_as_float(en.y);
                         d[k][u] = ok ? reinterpret_cast<const float4 *>(a.delta + (size_t)en.x * a.ldd)[q]
@@ -1010,34 +1087,30 @@ __global__ __launch_bounds__(SP_NT) void sparse_dw_columns_kernel(SparseDwArgs a
                         g[k].z += v[k][u] * d[k][u].z; g[k].w += v[k][u] * d[k][u].w;
                     }
             }
-            auto mine = [&](int k) { return n[k] > 0 && n[k] <= LIGHT_MAX; };
             if (a.grad_out) {
 #pragma unroll
-                for (int k = 0; k < ONE_COLS; ++k) {
-                    if (!mine(k)) continue;
-                    float *o = a.grad_out + (size_t)(4 * q) * a.d0 + c0 + k;
-                    o[0] = g[k].x; o[a.d0] = g[k].y; o[2 * (size_t)a.d0] = g[k].z; o[3 * (size_t)a.d0] = g[k].w;
-                }
+                for (int k = 0; k < ONE_COLS; ++k)
+                    if (mine(k)) apply_column_sum(a, c[k], 4 * q, g[k]);
             } else {
                 float4 x[ONE_COLS];
 #pragma unroll
                 for (int k = 0; k < ONE_COLS; ++k)
-                    if (mine(k)) x[k] = reinterpret_cast<const float4 *>(a.W1t + (size_t)(c0 + k) * a.ldw)[q];
+                    if (mine(k)) x[k] = reinterpret_cast<const float4 *>(a.W1t + (size_t)c[k] * a.ldw)[q];
 #pragma unroll
                 for (int k = 0; k < ONE_COLS; ++k) {
                     if (!mine(k)) continue;
                     x[k].x -= a.lr * g[k].x; x[k].y -= a.lr * g[k].y; x[k].z -= a.lr * g[k].z; x[k].w -= a.lr * g[k].w;
-                    reinterpret_cast<float4 *>(a.W1t + (size_t)(c0 + k) * a.ldw)[q] = x[k];
+                    reinterpret_cast<float4 *>(a.W1t + (size_t)c[k] * a.ldw)[q] = x[k];
                 }
             }
         }
     }
 #pragma unroll 1
-    for (int k = 0; k < ONE_COLS; ++k) {
-        const int beg = a.col_start[min(c0 + k, a.d0)], end = a.col_start[min(c0 + k + 1, a.d0)];
-        if (end - beg <= (a.vec ? LIGHT_MAX : 0)) continue;
-        const int per = fb_part_len(end - beg);
-        sparse_dw_part(a, c0 + k, beg, min(end, beg + per), end - beg <= per);
+    for (int k = 0; k < ONE_COLS; ++k) {  // one by one
+        const int col = b * ONE_COLS + k;
+        if (col >= a.d0) break;
+        const int beg = a.col_start[col], cnt = a.col_cnt[col];
+        if (cnt > joint && cnt <= ONE_LIST) sparse_dw_part(a, col, beg, beg + cnt, true);
     }
 }
 
@@ -1174,23 +1247,25 @@ bool csc_one_launch(long long nnz, long long B)
 }
 
 hipError_t launch_csc_one(const int32_t *row_ptr, const int32_t *col_idx, const float *vals, long long nnz, long long B, int d0,
-                          int32_t *col_start, int32_t *chunk_start, int4 *chunk_desc, int2 *csc_ent, hipStream_t stream,
-                          const LaunchEvents &ev)
+                          int32_t *col_start, int32_t *col_cnt, int32_t *chunk_start, int4 *chunk_desc, int2 *csc_ent,
+                          hipStream_t stream, const LaunchEvents &ev)
 {
     if (one_width(d0) > CSC_NT || B > CSC_ONE_ROWS || nnz > CSC_ONE_NNZ) return hipErrorInvalidValue;
     const int cap = (int)nnz;
-    const size_t lds = ((size_t)one_width(d0) + (size_t)B + 1 + (size_t)nnz) * sizeof(int32_t);  // 87 KB at most
+    const size_t lds = ((size_t)ONE_WAVES * one_width(d0) + (size_t)B + 1 + (size_t)ONE_WAVES * one_piece(cap)) *
+                       sizeof(int32_t);  // 106 KB at most: csc_supported() bounds d_0
     if (lds > 32 * 1024) {
         static LdsGrant granted;
         const hipError_t ea = grant_lds(granted, lds, csc_one_kernel);
         if (ea != hipSuccess) return ea;
     }
     if (ev.start)
-        hipExtLaunchKernelGGL(csc_one_kernel, dim3((unsigned)one_ranges(d0)), dim3(CSC_NT), (unsigned)lds, stream, ev.start, ev.stop,
-                              0, row_ptr, col_idx, vals, (int)B, d0, cap, col_start, chunk_start, chunk_desc, csc_ent);
+        hipExtLaunchKernelGGL(csc_one_kernel, dim3((unsigned)one_ranges(d0)), dim3(CSC_NT), (unsigned)lds, stream,
+                              ev.start, ev.stop, 0, row_ptr, col_idx, vals, (int)B, d0, cap, col_start, col_cnt,
+                              chunk_start, chunk_desc, csc_ent);
     else
-        hipLaunchKernelGGL(csc_one_kernel, dim3((unsigned)one_ranges(d0)), dim3(CSC_NT), lds, stream, row_ptr, col_idx, vals, (int)B,
-                           d0, cap, col_start, chunk_start, chunk_desc, csc_ent);
+        hipLaunchKernelGGL(csc_one_kernel, dim3((unsigned)one_ranges(d0)), dim3(CSC_NT), lds, stream, row_ptr, col_idx,
+                           vals, (int)B, d0, cap, col_start, col_cnt, chunk_start, chunk_desc, csc_ent);
     return hipGetLastError();
 }
 
@@ -1199,9 +1274,13 @@ hipError_t launch_sparse_dw(const SparseDwArgs &a_in, long long nnz, hipStream_t
     SparseDwArgs a = a_in;
     if (a.colsum) {
         a.rows_per_split = (int)((a.B + a.colsum_splits - 1) / a.colsum_splits);
-        const int n_colsum = (a.d1 + 63) / 64 * a.colsum_splits, ranges = one_ranges(a.d0);
-        const int blocks = n_colsum + (a.d0 + ONE_COLS - 1) / ONE_COLS + ONE_EXTRA * ranges;
-        return launch_kernel(sparse_dw_columns_kernel, dim3((unsigned)blocks), dim3(SP_NT), stream, ev, a, n_colsum, ranges);
+        const int n_colsum = (a.d1 + 63) / 64 * a.colsum_splits;
+        const long long listed = nnz / (ONE_LIST + 1) < a.d0 ? nnz / (ONE_LIST + 1) : a.d0;
+        long long items = listed * ((a.d1 + SL - 1) / SL);  // at most; a workgroup that finds none ends at once
+        if (items > ONE_ITEMS) items = ONE_ITEMS;
+        const long long blocks = n_colsum + items + (a.d0 + ONE_COLS - 1) / ONE_COLS;
+        return launch_kernel(sparse_dw_columns_kernel, dim3((unsigned)blocks), dim3(SP_NT), stream, ev, a, n_colsum,
+                             (int)items);
     }
     // descriptors: one per distinct column of the batch + the extra parts of the very long ones
     const long long max_cols = (nnz < a.d0 ? nnz : a.d0) + nnz / SPLIT;

@@ -669,7 +669,7 @@ def _csr_problem(dims, n_rows, seed, mean_nnz, max_nnz=256, bias_scale=0.2):
     return params, rp, ci, va, y
 
 
-def check_csr_case(dims, act, loss, params, rp, ci, va, y, lr, tol=TOL_F32):
+def check_csr_case(dims, act, loss, params, rp, ci, va, y, lr, tol=TOL_F32, helpers=None):
     import paper_2004_08771_amd as hb
     torch = _torch()
     B = y.size
@@ -696,6 +696,9 @@ def check_csr_case(dims, act, loss, params, rp, ci, va, y, lr, tol=TOL_F32):
     ls = m.batch_step_csr(d_rp, d_ci, d_va, ci.size, d_y, B, lr)
     after = np.empty_like(params)
     m.get_params(after)
+    if helpers is not None:
+        ran = csr_helper_launches(m, lambda: m.batch_step_csr(d_rp, d_ci, d_va, ci.size, d_y, B, lr))
+        assert ran == helpers, ran
     m.destroy()
 
     for name, v in (("batch_grad_csr", lg), ("batch_loss_csr", ll), ("batch_step_csr", ls)):
@@ -802,7 +805,116 @@ def test_csr_batches_with_the_columns_built_in_one_launch_and_in_four(monkeypatc
     params, rp, ci, va, y = _csr_problem(dims, B, seed=900 + B, mean_nnz=mean_nnz)
     assert B <= 1024 and ci.size <= 20480, ci.size
     rp, ci, va = hi.scramble_csr_rows(rp, ci, va, np.random.default_rng(B), dup_prob=0.0)
-    check_csr_case(dims, hi.ACT_SIGMOID, hi.LOSS_LOGISTIC, params, rp, ci, va, y, lr=0.1)
+    check_csr_case(dims, hi.ACT_SIGMOID, hi.LOSS_LOGISTIC, params, rp, ci, va, y, lr=0.1,
+                   helpers={2} if one == "" else {1, 2, 3, 4, 5})
+
+
+def csr_helper_launches(m, step):
+    """The helper kernels of a CSR step, by the number the profile gives them: {2} the columns in one launch, {1, 2, 3, 4, 5} in four."""
+    m.profile_enable(True)
+    step()
+    stats = m.profile_read()
+    m.profile_enable(False)
+    return {s["layer"] for s in stats if s["kind"] == 7}
+
+
+def csr_batch_on_gpu(rp, ci, va, y):
+    torch = _torch()
+    return [torch.from_numpy(rp).cuda(), torch.from_numpy(ci).cuda(), torch.from_numpy(va).cuda(), ci.size,
+            torch.from_numpy(y).cuda(), y.size]
+
+
+CSR_REPEATED = [
+    # columns of one entry up to nearly one per row; values of delta_1 that are a float4 and that are none
+    ((2003, 320, 64, 2), 701, 25),
+    ((1000, 50, 10, 2), 400, 40),
+    # entries named twice by a row, also those of the longest columns
+    ((300, 128, 2), 500, 20),
+]
+
+
+@pytest.mark.parametrize("dims,B,mean_nnz", CSR_REPEATED)
+def test_small_csr_steps_repeat_bit_for_bit(dims, B, mean_nnz):
+    """A column's entries are added in the order of the batch and a weight is rounded once, so that the same steps give the
+    same bits: a ReLU unit within rounding of zero is decided alike every time."""
+    import paper_2004_08771_amd as hb
+    torch = _torch()
+    params, rp, ci, va, y = _csr_problem(dims, B, seed=500 + B, mean_nnz=mean_nnz)
+    if dims[0] == 300:
+        rp, ci, va = hi.scramble_csr_rows(rp, ci, va, np.random.default_rng(B), dup_prob=0.5)
+    assert B <= 1024 and ci.size <= 20480 and np.bincount(ci).max() > 256
+    batch, runs = csr_batch_on_gpu(rp, ci, va, y), []
+    for _ in range(4):
+        m = hb.Model(dims, hi.ACT_RELU, hi.LOSS_LOGISTIC).configure(hb.HB_F32, B, sparse_first_layer=True)
+        m.set_params(params)
+        assert csr_helper_launches(m, lambda: m.batch_step_csr(*batch, 0.05)) == {2}
+        g = torch.full((params.size,), float("nan"), device="cuda")
+        losses = [m.batch_step_csr(*batch, 0.05) for _ in range(5)] + [m.batch_grad_csr(*batch, g)]
+        after = np.empty_like(params)
+        m.get_params(after)
+        m.destroy()
+        runs.append((np.array(losses), after, g.cpu().numpy()))
+    for losses, after, g in runs[1:]:
+        np.testing.assert_array_equal(losses, runs[0][0])
+        np.testing.assert_array_equal(after, runs[0][1])
+        np.testing.assert_array_equal(g, runs[0][2])
+
+
+@pytest.mark.parametrize("d1", [320, 50])
+def test_small_csr_batches_with_infinite_deltas(d1):
+    """Rows of the wrong class have a delta_1 of +inf (weights of 1e7 and 1e34), the others 0: a column of positive values sums to
+    inf or to 0, and no entry past its end makes a NaN of it."""
+    import paper_2004_08771_amd as hb
+    torch = _torch()
+    dims = (300, d1, 4, 2)
+    _, rp, ci, va, _ = _csr_problem(dims, 400, seed=61, mean_nnz=30)
+    rng = np.random.default_rng(62)
+    y = np.where(rng.random(400) < 0.5, 1, -1).astype(np.int32)
+    params = np.zeros(hi.num_params(dims), np.float32)
+    for (w, b), fill in zip(hi.param_offsets(dims), (1e-7, 1e7, 1e34)):
+        params[w:b] = fill
+    w3 = hi.param_offsets(dims)[2][0]
+    params[w3 + 4:w3 + 8] = -1e34  # the class of y = +1 (Section 7.1: labels -1, +1 are classes 0, 1) is never taken
+    m = hb.Model(dims, hi.ACT_RELU, hi.LOSS_LOGISTIC).configure(hb.HB_F32, 400, sparse_first_layer=True)
+    m.set_params(params)
+    g = torch.full((params.size,), float("nan"), device="cuda")
+    m.batch_grad_csr(*csr_batch_on_gpu(rp, ci, va, y), g)
+    m.destroy()
+    rows = np.repeat(np.arange(400), np.diff(rp))
+    wrong = np.bincount(ci, weights=(y[rows] > 0).astype(float), minlength=300)
+    assert wrong.max() > 128 and ((wrong > 0) & (wrong < 16)).any() and (wrong == 0).any()
+    expect = np.tile(np.where(wrong > 0, np.inf, 0.0).astype(np.float32), (d1, 1))
+    np.testing.assert_array_equal(g.cpu().numpy()[:300 * d1].reshape(d1, 300), expect)
+
+
+def test_csr_steps_of_changing_size_on_one_handle():
+    """Batches whose columns are built in one launch and in four, in turn: the arrays they leave differ in layout, and each step
+    has to use its own.  After every step the parameters, and before it the ReLU decisions, are compared with the oracle's from
+    the same parameters."""
+    import paper_2004_08771_amd as hb
+    dims, lr = (1500, 36, 24, 2), 0.1
+    rng = np.random.default_rng(31)
+    m = hb.Model(dims, hi.ACT_RELU, hi.LOSS_LOGISTIC).configure(hb.HB_F32, 1500, sparse_first_layer=True)
+    params = hi.xavier_uniform_params(dims, rng, bias_scale=0.2)
+    m.set_params(params)
+    for B, mean_nnz in ((300, 30), (1500, 20), (17, 60), (1024, 15), (1025, 15), (700, 40), (600, 30)):
+        rp, ci, va = hi.zipf_csr(B, dims[0], rng, mean_nnz=mean_nnz)
+        y = hi.csr_pm1_labels(rp, ci, va, dims[0], rng)
+        batch = csr_batch_on_gpu(rp, ci, va, y)
+        m.batch_loss_csr(*batch)
+        relu_on, _, _ = relu_decisions(dims, params, (rp, ci, va), gpu_hidden_activations(m, dims, B), EPS_Z_F32)
+        l_ref, g_ref, scale = mf.batch_grad(dims, hi.ACT_RELU, hi.LOSS_LOGISTIC, params, (rp, ci, va), y, with_error_scale=True,
+                                            relu_on=relu_on)
+        loss = []
+        helpers = csr_helper_launches(m, lambda: loss.append(m.batch_step_csr(*batch, lr)))
+        assert helpers == ({2} if B <= 1024 and ci.size <= 20480 else {1, 2, 3, 4, 5})
+        after = np.empty_like(params)
+        m.get_params(after)
+        assert abs(loss[0] - l_ref) <= TOL_F32 * abs(l_ref)
+        assert_close(dims, after, oracle.sgd_update(params, g_ref, lr), TOL_F32, f"parameters after {B} rows", scale=scale,
+                     tol_scale=TOL_F32_TERMS, scale_factor=lr, ref_rounding=2.0 ** -20)
+        params = after
+    m.destroy()
 
 
 @pytest.mark.parametrize("seed", [11, 12])

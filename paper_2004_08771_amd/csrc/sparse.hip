@@ -409,23 +409,26 @@ __global__ __launch_bounds__(CSC_NT) void csc_place_kernel(const int32_t *__rest
     }
 }
 
-// The CSC of a small batch in one launch.  A workgroup owns a range of columns.  Each of its wavefronts looks at a contiguous
-// piece of the batch's column indices once (up to ONE_U to a lane), counts the ones below the range, which give the place of
-// its first column, and lists the workgroup's own in LDS; then it counts and places these, a lane to each.  (Counted and placed
+// The CSC of a small batch in one launch.  A workgroup owns the columns of one residue modulo ONE_RANGES, so that neighbours,
+// which a vocabulary sorted by frequency makes the long ones, go to different workgroups.  Each of its wavefronts looks at a
+// contiguous piece of the batch's column indices once (up to ONE_U to a lane), counts the ones of smaller residues, which give
+// the place of the first column, and lists the workgroup's own in LDS; then it counts and places these, a lane to each.  (Counted and placed
 // where they were found, by whichever lanes had one, the launch took 30 us longer per 17,000 entries.)  Every column's
 // entries keep their order in the batch: wavefronts in turn (a prefix over their counts), lanes in turn (each compares its column
 // with the others' of a window of 64).  Placed by atomic counters instead, the sums of the weight gradient differed in the last
 // bits from run to run, and a few steps on a ReLU decision turned over.
 // It leaves, by column, the first entry and their number, and per range the list of its columns of more than ONE_LIST entries
-// (chunk_desc[first column ..], chunk_start[range] of them), for sparse_dw_columns_kernel.
-constexpr int ONE_RANGES = 128;  // at most
+// (chunk_desc[one_base ..], chunk_start[range] of them), for sparse_dw_columns_kernel.
+constexpr int ONE_RANGES = 128;
 constexpr int ONE_WAVES = CSC_NT / 64;
 constexpr int ONE_U = 20;      // 20,480 entries
 constexpr int ONE_BITS = 15;   // of an entry's number in a list
 constexpr int ONE_LIST = 32;
 static_assert(ONE_U * CSC_NT <= 1 << ONE_BITS, "entry numbers");
-__host__ __device__ inline int one_width(int d0) { return (d0 + ONE_RANGES - 1) / ONE_RANGES; }  // columns of a range
-__host__ __device__ inline int one_ranges(int d0) { return (d0 + one_width(d0) - 1) / one_width(d0); }
+__host__ __device__ inline int one_width(int d0) { return (d0 + ONE_RANGES - 1) / ONE_RANGES; }  // columns of a range at most
+__host__ __device__ inline int one_ranges(int d0) { return d0 < ONE_RANGES ? d0 : ONE_RANGES; }
+// columns of the ranges before r
+__device__ __forceinline__ int one_base(int d0, int r) { return r * (d0 / ONE_RANGES) + min(r, d0 % ONE_RANGES); }
 // entries of a wavefront at most
 __host__ __device__ inline int one_piece(int nnz) { return ((nnz + ONE_WAVES - 1) / ONE_WAVES + 63) & ~63; }
 
@@ -442,7 +445,7 @@ __global__ __launch_bounds__(CSC_NT) void csc_one_kernel(const int32_t *__restri
     __shared__ int red[ONE_WAVES], red2[ONE_WAVES], n_list;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int range = blockIdx.x, width = one_width(d0), piece = one_piece(cap);
-    const int lo = range * width, n = min(width, d0 - lo);
+    const int n = (d0 - range + ONE_RANGES - 1) / ONE_RANGES;  // columns range + i ONE_RANGES, i < n <= width
     int32_t *s_cur = s_one, *s_rp = s_one + ONE_WAVES * width;
     unsigned *s_ent = reinterpret_cast<unsigned *>(s_rp + B + 1) + wave * piece;
     for (int i = t; i < ONE_WAVES * width; i += CSC_NT) s_cur[i] = 0;
@@ -454,14 +457,14 @@ __global__ __launch_bounds__(CSC_NT) void csc_one_kernel(const int32_t *__restri
 #pragma unroll
     for (int u = 0; u < ONE_U; ++u) {
         const int p = p0 + u * 64 + lane;
-        c[u] = p < p1 ? col_idx[beg + p] - lo : 0x7fffffff;
+        c[u] = p < p1 ? col_idx[beg + p] : -1;  // past the end: the largest residue, beyond any range
     }
     int below = 0, mine = 0;  // mine: of the wavefront
 #pragma unroll
     for (int u = 0; u < ONE_U; ++u) {
-        const unsigned at = (unsigned)c[u];
-        below += c[u] < 0 ? 1 : 0;
-        const bool own = at < (unsigned)n;
+        const unsigned res = (unsigned)c[u] % ONE_RANGES, at = (unsigned)c[u] / ONE_RANGES;
+        below += res < (unsigned)range ? 1 : 0;
+        const bool own = res == (unsigned)range && at < (unsigned)n;
         const unsigned long long who = __ballot(own);
         if (own) s_ent[mine + __popcll(who & ((1ull << lane) - 1))] = at << ONE_BITS | (unsigned)(p0 + u * 64 + lane);
         mine += __popcll(who);
@@ -485,11 +488,11 @@ __global__ __launch_bounds__(CSC_NT) void csc_one_kernel(const int32_t *__restri
     int first = incl - cnt;
     for (int w = 0; w < ONE_WAVES; ++w) first += red[w] + (w < wave ? red2[w] : 0);
     if (t < n) {
-        const int col = lo + t;
+        const int col = range + t * ONE_RANGES;
         for (int w = 0; w < ONE_WAVES; ++w) s_cur[w * width + t] += first;
         col_start[col] = first;
         col_cnt[col] = cnt;
-        if (cnt > ONE_LIST) chunk_desc[lo + atomicAdd(&n_list, 1)] = make_int4(col, first, first + cnt, 1);
+        if (cnt > ONE_LIST) chunk_desc[one_base(d0, range) + atomicAdd(&n_list, 1)] = make_int4(col, first, first + cnt, 1);
     }
     __syncthreads();
     if (t == 0) chunk_start[range] = n_list;
@@ -533,12 +536,14 @@ __device__ __forceinline__ int fb_part_len(int cnt)
     return per > CHUNK ? per : CHUNK;
 }
 
-// entries [e_beg, e_end) of column c: their sum, then the update (plain if `single`)
-__device__ __forceinline__ void sparse_dw_part(const SparseDwArgs &a, int c, int e_beg, int e_end, bool single)
+// entries [e_beg, e_end) of column c: their sum, then the update (plain if `single`); piece / pieces: of the row, which
+// workgroups share
+__device__ __forceinline__ void sparse_dw_part(const SparseDwArgs &a, int c, int e_beg, int e_end, bool single, int piece = 0,
+                                               int pieces = 1)
 {
     if (a.vec) {
         const int n4 = a.d1 >> 2;
-        for (int q = threadIdx.x; q < n4; q += SP_NT) {
+        for (int q = threadIdx.x + piece * SP_NT; q < n4; q += pieces * SP_NT) {
             float4 g = {0.f, 0.f, 0.f, 0.f};
             int e = e_beg;
             for (; e + 16 <= e_end; e += 16) {  // sixteen row gathers in flight; added in index order
@@ -592,7 +597,7 @@ __device__ __forceinline__ void sparse_dw_part(const SparseDwArgs &a, int c, int
             }
         }
     } else {
-        for (int j = threadIdx.x; j < a.d1; j += SP_NT) {
+        for (int j = threadIdx.x + piece * SP_NT; j < a.d1; j += pieces * SP_NT) {
             float g = 0.f;
             for (int e = e_beg; e < e_end; ++e)
             {
@@ -975,11 +980,19 @@ __global__ __launch_bounds__(256) void colsum_kernel(const float *__restrict__ d
 // Weight gradient of layer 1 from the CSC of csc_one_kernel, with the bias gradient's slices in the same launch (first: they are
 // the longest workgroups).  What bounds a small batch is the chain offsets - entries - rows of delta - weights, four dependent
 // trips to memory, and one column per workgroup filled the device three times over with it.
-// Columns of up to ONE_LIST entries: a workgroup takes ONE_COLS, the ones of up to LIGHT_MAX entries together, four entries of
-// each in a round, so that sixteen gathers are in flight, and their weight rows with one another.  Longer columns come from
-// the lists: a workgroup takes 64 values of one, its eight groups of sixteen lanes a contiguous run of the entries each, and
-// adds their sums in order, so that a weight is rounded once and the same way in every run.
-constexpr int ONE_COLS = 4, ONE_ITEMS = 2048;
+// Columns of up to ONE_LIST entries: a workgroup takes up to ONE_COLS (of wide rows a piece), a stride of n_light apart, so that
+// neighbours, which may all be long, do not meet; the ones of up to LIGHT_MAX entries together, four entries of each in a round,
+// so that sixteen gathers are in flight, and their weight rows with one another.  Longer columns come from the lists: a workgroup takes 64 values of
+// one, its eight groups of sixteen lanes a contiguous run of the entries each, and adds their sums in order, so that a weight
+// is rounded once and the same way in every run.
+constexpr int ONE_COLS = 4, ONE_FULL = 4096, ONE_ITEMS = 2048;
+// workgroups for the columns when each takes 1 / pieces of a row: fewer than ONE_COLS columns to each while all of them are no
+// more than ONE_FULL (with 1024 in its place 8003-320-64-2 takes 54.9 instead of 52.6 us per step of 701 rows)
+inline int one_light(int d0, int pieces)
+{
+    const int least = (d0 + ONE_COLS - 1) / ONE_COLS, full = ONE_FULL / pieces;
+    return least > full ? least : d0 < full ? d0 : full;
+}
 
 __device__ __forceinline__ void sparse_dw_listed(const SparseDwArgs &a, int item, int items, float4 (&part)[SP_NT / 16][16])
 {
@@ -997,7 +1010,7 @@ __device__ __forceinline__ void sparse_dw_listed(const SparseDwArgs &a, int item
             j -= n_first;
             ++r;
         }
-        const int4 desc = a.chunk_desc[r * one_width(a.d0) + j];
+        const int4 desc = a.chunk_desc[one_base(a.d0, r) + j];
         const int per = (((desc.z - desc.y + SP_NT / 16 - 1) / (SP_NT / 16)) + 15) & ~15;  // entries per group: whole windows
         const int beg = min(desc.z, desc.y + g16 * per);
         float4 g = {0.f, 0.f, 0.f, 0.f};
@@ -1028,7 +1041,8 @@ __device__ __forceinline__ void sparse_dw_listed(const SparseDwArgs &a, int item
     }
 }
 
-__global__ __launch_bounds__(SP_NT, 4) void sparse_dw_columns_kernel(SparseDwArgs a, int n_colsum, int n_items)
+__global__ __launch_bounds__(SP_NT, 4) void sparse_dw_columns_kernel(SparseDwArgs a, int n_colsum, int n_items, int n_light,
+                                                                    int pieces)
 {
     __shared__ union {
         float red[4][64];
@@ -1046,11 +1060,13 @@ __global__ __launch_bounds__(SP_NT, 4) void sparse_dw_columns_kernel(SparseDwArg
         return;
     }
     b -= n_items;
-    const int joint = a.vec ? LIGHT_MAX : 0;  // columns of up to this many entries are taken together
+    const int piece = b % pieces;
+    b /= pieces;
+    const int joint = a.vec && n_light < a.d0 ? LIGHT_MAX : 0;  // columns of up to this many entries are taken together
     int c[ONE_COLS], at[ONE_COLS], n[ONE_COLS], most = 0;
 #pragma unroll
     for (int k = 0; k < ONE_COLS; ++k) {
-        c[k] = b * ONE_COLS + k;
+        c[k] = b + k * n_light;
         at[k] = a.col_start[min(c[k], a.d0 - 1)];
         n[k] = a.col_cnt[min(c[k], a.d0 - 1)];
     }
@@ -1062,7 +1078,7 @@ __global__ __launch_bounds__(SP_NT, 4) void sparse_dw_columns_kernel(SparseDwArg
     if (most > 0) {
         auto mine = [&](int k) { return n[k] > 0 && n[k] <= joint; };
         const int n4 = a.d1 >> 2;
-        for (int q = threadIdx.x; q < n4; q += SP_NT) {
+        for (int q = threadIdx.x + piece * SP_NT; q < n4; q += pieces * SP_NT) {
             float4 g[ONE_COLS];
 #pragma unroll
             for (int k = 0; k < ONE_COLS; ++k) g[k] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1107,10 +1123,10 @@ __global__ __launch_bounds__(SP_NT, 4) void sparse_dw_columns_kernel(SparseDwArg
     }
 #pragma unroll 1
     for (int k = 0; k < ONE_COLS; ++k) {  // one by one
-        const int col = b * ONE_COLS + k;
+        const int col = b + k * n_light;
         if (col >= a.d0) break;
         const int beg = a.col_start[col], cnt = a.col_cnt[col];
-        if (cnt > joint && cnt <= ONE_LIST) sparse_dw_part(a, col, beg, beg + cnt, true);
+        if (cnt > joint && cnt <= ONE_LIST) sparse_dw_part(a, col, beg, beg + cnt, true, piece, pieces);
     }
 }
 
@@ -1182,11 +1198,14 @@ bool csc_supported(int d0, long long max_B)
 // cnt[d0 + 1] followed by the per-group totals of the column scan
 size_t csc_cnt_elems(int d0) { return (size_t)d0 + 1 + (1 + N_CLASS) * (size_t)((d0 + COLG - 1) / COLG); }
 
-// The line of the one-launch build and of the weight gradient that goes with it.  Against four launches on a stream of their
-// own beside the forward pass, us per step (rows, entries: four launches / one): 8003-320-64-2 16 rows, 461: 67.6 / 33.0, 300, 7559:
-// 65.0 / 44.1, 701, 17744: 71.6 / 54.0, 1100, 27769: 72.1 / 67.3; 20958-512-512-2 300, 12421: 76.8 / 62.8, 701, 28975: 81.0 / 83.2;
-// with 8 entries a row 900, 6805: 71.8 / 66.1, 1500, 11409: 71.2 / 80.5; 30000-1000-2 900, 16203: 86.4 / 82.4, 1500, 26792: 96.9 / 108.5;
-// 2003-50-10 701, 16934: 78.7 / 76.8, 900, 21652: 79.7 / 88.5; 4001-128-2 701, 31769: 65.8 / 46.9.
+// The lines of the one-launch build and of the weight gradient that goes with it.  Against four launches on a stream of their
+// own beside the forward pass, us per step (rows, entries: four launches / one; columns in random order, as sorted by frequency one
+// launch takes up to 10 us less): 8003-320-64-2 16 rows, 461: 64.7 / 34.3, 300, 7559: 65.5 / 43.9, 701, 17744: 70.2 / 52.6;
+// 20958-512-512-2 300, 12421: 77.6 / 63.5, 1000, 7556: 73.6 / 67.9; 30000-1000-2 1000, 18027: 89.1 / 79.0; 2003-50-10 701,
+// 16934: 78.6 / 57.2; 4001-128-2 300, 13706: 63.1 / 36.1; 301-1024-2 701, 14943: 62.3 / 43.8; 50-320-64-2 1000, 12331: 58.9 / 52.5.
+// Built with room for 32,768 entries and 2048 rows: 20958-512-512-2 600, 24835: 79.1 / 77.9, 1500, 11409: 71.8 / 79.2, 30000-1000-2
+// 1500, 26792: 96.7 / 96.1, 50-320-64-2 1500, 14358: 62.6 / 65.9, 4001-128-2 700, 31719: 64.9 / 44.3: beyond 1024 rows it loses,
+// and room for more entries, which narrow layers alone would gain by, does not fit LDS beside the widest inputs.
 constexpr long long CSC_ONE_NNZ = ONE_U * CSC_NT;
 constexpr long long CSC_ONE_ROWS = 1024;  // the batch's row_ptr lies in LDS
 
@@ -1278,9 +1297,12 @@ hipError_t launch_sparse_dw(const SparseDwArgs &a_in, long long nnz, hipStream_t
         const long long listed = nnz / (ONE_LIST + 1) < a.d0 ? nnz / (ONE_LIST + 1) : a.d0;
         long long items = listed * ((a.d1 + SL - 1) / SL);  // at most; a workgroup that finds none ends at once
         if (items > ONE_ITEMS) items = ONE_ITEMS;
-        const long long blocks = n_colsum + items + (a.d0 + ONE_COLS - 1) / ONE_COLS;
+        const int pieces = a.vec ? (a.d1 / 4 + SP_NT - 1) / SP_NT : (a.d1 + SP_NT - 1) / SP_NT;  // of a row
+        const int n_light = one_light(a.d0, pieces);
+        const long long blocks = n_colsum + items + (long long)n_light * pieces;
+        if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
         return launch_kernel(sparse_dw_columns_kernel, dim3((unsigned)blocks), dim3(SP_NT), stream, ev, a, n_colsum,
-                             (int)items);
+                             (int)items, n_light, pieces);
     }
     // descriptors: one per distinct column of the batch + the extra parts of the very long ones
     const long long max_cols = (nnz < a.d0 ? nnz : a.d0) + nnz / SPLIT;

@@ -887,6 +887,40 @@ def test_small_csr_batches_with_infinite_deltas(d1):
     np.testing.assert_array_equal(g.cpu().numpy()[:300 * d1].reshape(d1, 300), expect)
 
 
+def hottest_columns_first(ci, d0):
+    """The columns renamed in the order of their number of entries, as in a vocabulary sorted by frequency."""
+    name = np.empty(d0, np.int32)
+    name[np.argsort(-np.bincount(ci, minlength=d0), kind="stable")] = np.arange(d0, dtype=np.int32)
+    return name[ci]
+
+
+@pytest.mark.parametrize("dims,B,mean_nnz", [((2003, 50, 10, 2), 701, 25), ((5003, 320, 2), 701, 25), ((5003, 701, 2), 300, 50)])
+def test_small_csr_batches_with_the_hot_columns_side_by_side(dims, B, mean_nnz):
+    """The column copy and the weight gradient take no longer where the long columns are neighbours: the same batch with its
+    columns in random order and sorted by frequency, kernel times.  (By ranges of neighbouring columns: 2.0 to 5.6 times.)"""
+    import paper_2004_08771_amd as hb
+    params, rp, ci, va, y = _csr_problem(dims, B, seed=40 + B, mean_nnz=mean_nnz)
+    by_rank = hottest_columns_first(ci, dims[0])
+    assert B <= 1024 and ci.size <= 20480 and np.bincount(by_rank)[:8].min() > 128
+    check_csr_case(dims, hi.ACT_SIGMOID, hi.LOSS_LOGISTIC, params, rp, by_rank, va, y, lr=0.1, helpers={2})
+    m = hb.Model(dims, hi.ACT_SIGMOID, hi.LOSS_LOGISTIC).configure(hb.HB_F32, B, sparse_first_layer=True)
+    m.set_params(params)
+
+    def kernel_ms(columns):
+        batch, times = csr_batch_on_gpu(rp, columns, va, y), []
+        m.profile_enable(True)
+        for _ in range(15):
+            m.batch_step_csr(*batch, 0.01)
+            times.append(sum(s["total_ms"] for s in m.profile_read()
+                             if s["kind"] == 6 or (s["kind"] == 7 and s["layer"] == 2)))
+        m.profile_enable(False)
+        return float(np.median(times))
+
+    apart, side_by_side = kernel_ms(ci), kernel_ms(by_rank)
+    m.destroy()
+    assert side_by_side <= 1.4 * apart, (side_by_side, apart)
+
+
 def test_csr_steps_of_changing_size_on_one_handle():
     """Batches whose columns are built in one launch and in four, in turn: the arrays they leave differ in layout, and each step
     has to use its own.  After every step the parameters, and before it the ReLU decisions, are compared with the oracle's from

@@ -411,7 +411,7 @@ int run_step(hb_model *m, const Input &in, const int32_t *y, int64_t B, float lr
     };
     // A small batch has it in one launch, on the handle's own stream: what four launches and the two records and waits of the
     // other stream cost the host is more than what runs beside the forward pass saves.
-    const bool csc_one = m->sparse && mode != MODE_LOSS && csc_one_launch(in.nnz, B);
+    const bool csc_one = m->sparse && mode != MODE_LOSS && csc_one_launch(in.nnz, B, m->dims[1]);
     const bool csc_beside = m->sparse && mode != MODE_LOSS && !csc_one && m->csc_stream != nullptr;
     if (csc_beside) {
         // forked at the start of the step: later fork points (behind the first or second forward

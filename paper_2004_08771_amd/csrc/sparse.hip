@@ -411,14 +411,14 @@ __global__ __launch_bounds__(CSC_NT) void csc_place_kernel(const int32_t *__rest
 
 // The CSC of a small batch in one launch.  A workgroup owns the columns of one residue modulo ONE_RANGES, so that neighbours,
 // which a vocabulary sorted by frequency makes the long ones, go to different workgroups.  Each of its wavefronts looks at a
-// contiguous piece of the batch's column indices once (up to ONE_U to a lane), counts the ones of smaller residues, which give
-// the place of the first column, and lists the workgroup's own in LDS; then it counts and places these, a lane to each.  (Counted and placed
-// where they were found, by whichever lanes had one, the launch took 30 us longer per 17,000 entries.)  Every column's
-// entries keep their order in the batch: wavefronts in turn (a prefix over their counts), lanes in turn (each compares its column
-// with the others' of a window of 64).  Placed by atomic counters instead, the sums of the weight gradient differed in the last
-// bits from run to run, and a few steps on a ReLU decision turned over.
-// It leaves, by column, the first entry and their number, and per range the list of its columns of more than ONE_LIST entries
-// (chunk_desc[one_base ..], chunk_start[range] of them), for sparse_dw_columns_kernel.
+// contiguous piece of the batch's column indices once (up to ONE_U to a lane), counts the ones of smaller residues, which
+// give the place of the first column, and lists the workgroup's own in LDS; then it counts and places these, a lane to each.
+// (Counted and placed where they were found, by whichever lanes had one, the launch took 30 us longer per 17,000 entries.)
+// Every column's entries keep their order in the batch: wavefronts in turn (a prefix over their counts), lanes in turn (each
+// compares its column with the others' of a window of 64).  Placed by atomic counters instead, the sums of the weight
+// gradient differed in the last bits from run to run, and a few steps on a ReLU decision turned over. It leaves, by column,
+// the first entry and their number, and per range the list of its columns of more than ONE_LIST entries (chunk_desc[one_base
+// ..], chunk_start[range] of them), for sparse_dw_columns_kernel.
 constexpr int ONE_RANGES = 128;
 constexpr int ONE_WAVES = CSC_NT / 64;
 constexpr int ONE_U = 20;      // 20,480 entries
@@ -977,14 +977,14 @@ __global__ __launch_bounds__(256) void colsum_kernel(const float *__restrict__ d
     colsum_slice<256>(delta, ldd, B, d, rows_per_split, partial, blockIdx.x, blockIdx.y, red);
 }
 
-// Weight gradient of layer 1 from the CSC of csc_one_kernel, with the bias gradient's slices in the same launch (first: they are
-// the longest workgroups).  What bounds a small batch is the chain offsets - entries - rows of delta - weights, four dependent
-// trips to memory, and one column per workgroup filled the device three times over with it.
-// Columns of up to ONE_LIST entries: a workgroup takes up to ONE_COLS (of wide rows a piece), a stride of n_light apart, so that
-// neighbours, which may all be long, do not meet; the ones of up to LIGHT_MAX entries together, four entries of each in a round,
-// so that sixteen gathers are in flight, and their weight rows with one another.  Longer columns come from the lists: a workgroup takes 64 values of
-// one, its eight groups of sixteen lanes a contiguous run of the entries each, and adds their sums in order, so that a weight
-// is rounded once and the same way in every run.
+// Weight gradient of layer 1 from the CSC of csc_one_kernel, with the bias gradient's slices in the same launch (first: they
+// are the longest workgroups).  What bounds a small batch is the chain offsets - entries - rows of delta - weights, four
+// dependent trips to memory, and one column per workgroup filled the device three times over with it. Columns of up to
+// ONE_LIST entries: a workgroup takes up to ONE_COLS (of wide rows a piece), a stride of n_light apart, so that neighbours,
+// which may all be long, do not meet; the ones of up to LIGHT_MAX entries together, four entries of each in a round, so that
+// sixteen gathers are in flight, and their weight rows with one another.  Longer columns come from the lists: a workgroup
+// takes 64 values of one, its eight groups of sixteen lanes a contiguous run of the entries each, and adds their sums in
+// order, so that a weight is rounded once and the same way in every run.
 constexpr int ONE_COLS = 4, ONE_FULL = 4096, ONE_ITEMS = 2048;
 // workgroups for the columns when each takes 1 / pieces of a row: fewer than ONE_COLS columns to each while all of them are no
 // more than ONE_FULL (with 1024 in its place 8003-320-64-2 takes 54.9 instead of 52.6 us per step of 701 rows)
@@ -1199,15 +1199,21 @@ bool csc_supported(int d0, long long max_B)
 size_t csc_cnt_elems(int d0) { return (size_t)d0 + 1 + (1 + N_CLASS) * (size_t)((d0 + COLG - 1) / COLG); }
 
 // The lines of the one-launch build and of the weight gradient that goes with it.  Against four launches on a stream of their
-// own beside the forward pass, us per step (rows, entries: four launches / one; columns in random order, as sorted by frequency one
-// launch takes up to 10 us less): 8003-320-64-2 16 rows, 461: 64.7 / 34.3, 300, 7559: 65.5 / 43.9, 701, 17744: 70.2 / 52.6;
-// 20958-512-512-2 300, 12421: 77.6 / 63.5, 1000, 7556: 73.6 / 67.9; 30000-1000-2 1000, 18027: 89.1 / 79.0; 2003-50-10 701,
-// 16934: 78.6 / 57.2; 4001-128-2 300, 13706: 63.1 / 36.1; 301-1024-2 701, 14943: 62.3 / 43.8; 50-320-64-2 1000, 12331: 58.9 / 52.5.
-// Built with room for 32,768 entries and 2048 rows: 20958-512-512-2 600, 24835: 79.1 / 77.9, 1500, 11409: 71.8 / 79.2, 30000-1000-2
-// 1500, 26792: 96.7 / 96.1, 50-320-64-2 1500, 14358: 62.6 / 65.9, 4001-128-2 700, 31719: 64.9 / 44.3: beyond 1024 rows it loses,
-// and room for more entries, which narrow layers alone would gain by, does not fit LDS beside the widest inputs.
+// own beside the forward pass, us per step (rows, entries: four launches / one; columns in random order, as sorted by
+// frequency one launch takes up to 10 us less): 8003-320-64-2 16 rows, 461: 64.7 / 34.3, 300, 7559: 65.5 / 43.9, 701, 17744:
+// 70.2 / 52.6; 20958-512-512-2 300, 12421: 77.6 / 63.5, 1000, 7556: 73.6 / 67.9; 30000-1000-2 1000, 18027: 89.1 / 79.0;
+// 2003-50-10 701, 16934: 78.6 / 57.2; 4001-128-2 300, 13706: 63.1 / 36.1; 301-1024-2 701, 14943: 62.3 / 43.8; 50-320-64-2
+// 1000, 12331: 58.9 / 52.5. Built with room for 32,768 entries and 2048 rows: 20958-512-512-2 600, 24835: 79.1 / 77.9, 1500,
+// 11409: 71.8 / 79.2, 30000-1000-2 1500, 26792: 96.7 / 96.1, 50-320-64-2 1500, 14358: 62.6 / 65.9, 4001-128-2 700, 31719:
+// 64.9 / 44.3: beyond 1024 rows it loses, and room for more entries, which narrow layers alone would gain by, does not fit
+// LDS beside the widest inputs.
 constexpr long long CSC_ONE_NNZ = ONE_U * CSC_NT;
 constexpr long long CSC_ONE_ROWS = 1024;  // the batch's row_ptr lies in LDS
+// Rows of more than 2048 values that the sliced kernels take stay with them, which spend nothing on columns that do not
+// occur: 16001-4096-2 16 rows 74.4 / 65.2, 64 rows 76.0 / 77.6, 300 rows 85.0 / 106.2, 701 rows 128 / 152; 2003-4096-2 16
+// rows 63.7 / 46.2, 300 rows 66.4 / 73.3, 701 rows 94 / 106; 8003-2048-2 300 rows 68.8 / 60.3, 701 rows 78.5 / 80.9 (sorted
+// 76.5 / 73.1).  Against the general kernel one launch is the shorter: 8003-3000-2 64 rows 79.4 / 67.4, 701 rows 135 / 116.
+constexpr int CSC_ONE_SLICED = 2048;
 
 size_t csc_hist_elems(long long max_B, int d0) { return (size_t)csc_blocks(max_B) * (size_t)d0; }
 
@@ -1258,8 +1264,10 @@ hipError_t launch_csc_build(const int32_t *row_ptr, const int32_t *col_idx, cons
 }
 
 // HB_CSC_ONE (tuning and test aid; read per call): a lower limit of non-zeros for the one-launch build, 0: never.
-bool csc_one_launch(long long nnz, long long B)
+bool csc_one_launch(long long nnz, long long B, int d1)
 {
+    SliceMap m;
+    if (d1 > CSC_ONE_SLICED && slice_map(d1, d1 % 4 == 0, &m)) return false;
     const char *env = getenv("HB_CSC_ONE");
     const long long most = env && *env && atoll(env) < CSC_ONE_NNZ ? atoll(env) : CSC_ONE_NNZ;
     return nnz > 0 && nnz <= most && B <= CSC_ONE_ROWS;

@@ -887,6 +887,15 @@ def test_small_csr_batches_with_infinite_deltas(d1):
     np.testing.assert_array_equal(g.cpu().numpy()[:300 * d1].reshape(d1, 300), expect)
 
 
+@pytest.mark.parametrize("d1,helpers", [(2048, {2}), (2052, {2}), (2560, {1, 2, 3, 4, 5})])
+def test_small_csr_batches_of_wide_rows(d1, helpers):
+    """Rows of 2048 values and ones that no XCD gets whole slices of: in one launch, a row shared by several workgroups; wider
+    rows in slices: in four."""
+    dims = (150, d1, 2)
+    params, rp, ci, va, y = _csr_problem(dims, 90, seed=d1, mean_nnz=12)
+    check_csr_case(dims, hi.ACT_SIGMOID, hi.LOSS_LOGISTIC, params, rp, ci, va, y, lr=0.1, helpers=helpers)
+
+
 def hottest_columns_first(ci, d0):
     """The columns renamed in the order of their number of entries, as in a vocabulary sorted by frequency."""
     name = np.empty(d0, np.int32)

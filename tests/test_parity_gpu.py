@@ -725,7 +725,8 @@ def check_csr_case(dims, act, loss, params, rp, ci, va, y, lr, tol=TOL_F32, help
     ((500, 1), hi.ACT_SIGMOID, 300, 10),             # sparse logistic regression
     ((2000, 64, 64, 1), hi.ACT_RELU, 1, 12),         # B = 1
     # d_1 a multiple of 64: the kernels that give each XCD a 64-float slice of d_1 -- one slice shared
-    # by all 8 XCDs (64), by 4 (128), by 2 (256), two slices per XCD (1024); ragged row / chunk groups
+    # by all 8 XCDs (64), by 4 (128), by 2 (256), two slices per XCD (1024); ragged row / chunk groups.
+    # (The forward kernel; the weight gradient's in the test of the four launches.)
     ((700, 64, 2), hi.ACT_SIGMOID, 333, 9),
     ((400, 128, 8, 2), hi.ACT_RELU, 100, 10),
     ((900, 256, 2), hi.ACT_RELU, 1001, 40),
@@ -734,6 +735,23 @@ def check_csr_case(dims, act, loss, params, rp, ci, va, y, lr, tol=TOL_F32, help
 def test_csr_small_shapes_match_oracle(dims, act, B, mean_nnz):
     params, rp, ci, va, y = _csr_problem(dims, B, seed=300 + B, mean_nnz=mean_nnz)
     check_csr_case(dims, act, hi.LOSS_LOGISTIC, params, rp, ci, va, y, lr=0.1)
+
+
+@pytest.mark.parametrize("dims,act,B,mean_nnz", [
+    ((700, 64, 2), hi.ACT_SIGMOID, 333, 9),
+    ((400, 128, 8, 2), hi.ACT_RELU, 100, 10),
+    ((900, 256, 2), hi.ACT_RELU, 700, 25),
+    ((600, 1024, 2), hi.ACT_SIGMOID, 70, 12),
+    ((1000, 130, 2), hi.ACT_RELU, 700, 25),
+    ((1000, 132, 2), hi.ACT_SIGMOID, 700, 25),
+])
+def test_csr_small_shapes_in_four_launches(monkeypatch, dims, act, B, mean_nnz):
+    """The kernels of larger batches at sizes that one launch would take: the sliced weight gradient with 8, 4 and 2 XCDs to a
+    slice and with two slices to an XCD, and the general one."""
+    monkeypatch.setenv("HB_CSC_ONE", "0")
+    params, rp, ci, va, y = _csr_problem(dims, B, seed=350 + B, mean_nnz=mean_nnz)
+    assert B <= 1024 and ci.size <= 20480
+    check_csr_case(dims, act, hi.LOSS_LOGISTIC, params, rp, ci, va, y, lr=0.1, helpers={1, 2, 3, 4, 5})
 
 
 def test_csr_rows_with_unsorted_and_duplicate_columns():

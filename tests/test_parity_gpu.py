@@ -162,7 +162,7 @@ def _problem(dims, loss, B, seed, bias_scale=0.3):
     return params, X, y
 
 
-F32_KERNELS = ["small", "64", "128x64", "128", "64s"]        # hb_plan_f32_kernel
+F32_KERNELS = ["small", "64", "128x64", "128", "64s", "64x32"]  # hb_plan_f32_kernel
 BF16_KERNELS = ["refused", "dma", "128", "128s", "64", "64s"]  # hb_plan_bf16_kernel; S: shifted rows of X, B: batch-major
 
 
@@ -1443,22 +1443,24 @@ F32_EDGES = [
 
 F32_LONG_FORWARD = [
     # tiles of 64 x 32 by four groups: 17 k-tiles, the partial one first, and 9 more than a row of groups; rows and columns cut
-    ((515, 546, 513, 4), hi.ACT_SIGMOID, 577, [5, 5]),
+    ((515, 546, 513, 4), hi.ACT_SIGMOID, 577, ["64x32", "64x32"]),
     # the other line: 128 tiles over less than 768
-    ((512, 512, 4), hi.ACT_SIGMOID, 961, [0]),
+    ((512, 512, 4), hi.ACT_SIGMOID, 961, ["small"]),
     # whole k-tiles, one row in the second tile, a wide output
-    ((512, 2560, 4), hi.ACT_RELU, 65, [5]),
-    # the line: 79 tiles, fp32 MFMAs; 156, but 312 of 64 x 32: 64 x 64 by two groups
-    ((512, 5056, 4), hi.ACT_SIGMOID, 64, [0]),
-    ((800, 768, 4), hi.ACT_SIGMOID, 800, [4]),
+    ((512, 2560, 4), hi.ACT_RELU, 65, ["64x32"]),
+    # the lines: 80 and 72 tiles, fp32 MFMAs; one row of tiles, however many; 156, but 312 of 64 x 32: 64 x 64 by two groups
+    ((512, 512, 4), hi.ACT_SIGMOID, 577, ["64x32"]),
+    ((512, 512, 4), hi.ACT_SIGMOID, 576, ["small"]),
+    ((512, 5120, 4), hi.ACT_SIGMOID, 64, ["small"]),
+    ((800, 768, 4), hi.ACT_SIGMOID, 800, ["64s"]),
 ]
 
 
 @pytest.mark.parametrize("dims,act,B,kernels", F32_LONG_FORWARD)
 def test_long_forward_products_of_few_tiles(dims, act, B, kernels):
     from paper_2004_08771_amd import lib
-    got = [lib().hb_plan_f32_kernel(0, dims[l], dims[l - 1], B, B, None) for l in range(1, len(dims) - 1)]
-    check_plan(str(got), str(kernels))
+    got = [F32_KERNELS[lib().hb_plan_f32_kernel(0, dims[l], dims[l - 1], B, B, None)] for l in range(1, len(dims) - 1)]
+    check_plan(got, kernels)
     params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=60 + B)
     check_case(dims, act, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=False)
 

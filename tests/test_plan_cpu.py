@@ -14,6 +14,11 @@ def test_bf16_cases_run_the_kernels_they_name(dims, B, plan):
     assert t.bf16_plan(dims, B) == plan
 
 
+@pytest.mark.parametrize("dims,B,kernels", [(r[0], r[2], r[3]) for r in t.F32_LONG_FORWARD])
+def test_f32_long_forward_cases_run_the_kernels_they_name(dims, B, kernels):
+    assert t.f32_plan(dims, B).split("; ")[0].split()[:-1] == kernels
+
+
 def test_the_cases_reach_every_form_of_the_small_products():
     for r in t.F32_SMALL:
         assert t.f32_small_forms(r[0], r[2]) == r[3]
@@ -28,7 +33,8 @@ def test_the_cases_reach_every_form_of_the_small_products():
 
 def test_the_cases_reach_every_kernel():
     forward, pairs, alone = ({k for r in t.F32_EDGES for k in r[-1].split("; ")[q].split()} for q in range(3))
-    assert forward == set(t.F32_KERNELS) and pairs == set(t.F32_KERNELS) and alone == set(t.F32_KERNELS)
+    forward |= {k for r in t.F32_LONG_FORWARD for k in r[-1]}
+    assert forward == set(t.F32_KERNELS) and pairs == alone == set(t.F32_KERNELS) - {"64x32"}
     bf16 = [r[-1].split("; ") for r in t.BF16_WIDE + t.BF16_SMALL_TILES + t.BF16_SHORT]
     forward, da, dw = ({k.split("/")[0] for r in bf16 for k in r[q].split()} for q in range(3))
     assert forward | {r[-1] for r in t.BF16_SHIFTED} == {"dma", "128", "128s", "64", "64s", "64S", "64sS", "128S", "128sS"}

@@ -235,8 +235,10 @@ enum {
     HB_K_SPARSE_DW = 6,  /* CSR first layer, gradient + update of the touched columns */
     HB_K_OTHER = 7,      /* helpers, numbered in `layer`; 6: a network that fits a workgroup, whole (M = rows) */
     HB_K_OUT_LAYER = 8,  /* narrow output layer: forward + loss + delta + its gradients, fused */
-    HB_K_BWD_PAIR = 9    /* backward-data and weight-gradient product of one layer in one launch;
-                            M, N, K are the backward-data shape, flops / bytes cover both */
+    HB_K_BWD_PAIR = 9    /* two backward products in one launch, flops / bytes cover both.  fp32: backward-data and
+                            weight gradient of `layer`, M, N, K those of the backward-data product.  bf16: the
+                            weight gradient of `layer`, M, N, K its own, and the next product, backward-data
+                            of layer - 1 or (layer 2) the weight gradient of layer 1 */
 };
 typedef struct hb_kernel_stat {
     int32_t kind;            /* HB_K_* */
@@ -271,7 +273,11 @@ int32_t hb_plan_bf16_dw_slices(int32_t d_out, int32_t d_in, int64_t B, int32_t c
  * 4 64 x 64 with two groups of wavefronts, 5 64 x 32 with four (forward only); *slices (may be NULL): slices of the weight gradient's batch.
  * bf16 mode: 1 256 x 256 (LDS-direct), 2 128 x 128, 3 128 x 128 with two workgroups per compute unit, 4 64 x 64,
  * 5 64 x 64 with two groups; + 16: rows of X that are not 4-byte aligned (16-byte aligned dX assumed), + 32: weight
- * gradient from the batch-major tensors.  layer: 1 for the first layer, 2 for the last, 3 for both, else 0.
+ * gradient from the batch-major tensors.  layer: 1 for the first layer, 2 for the last, 3 for both, else 0.  This is the
+ * kernel of a launch of its own; backward products of kernels 4 and 5 may share one:
+ * hb_plan_bf16_pair: whether the weight gradient of layer `layer` (1 .. n_dims - 1) shares a launch with the next product
+ * of the backward pass (backward-data of layer - 1, for layer 2 the weight gradient of layer 1).  0 no; 1 or 2: yes, tiles
+ * of 64 x 64 with that many groups of wavefronts, whatever each would take alone.
  * Products of the fused output layer, of a CSR first layer and of a dense fp32 network that fits a workgroup run other
  * kernels.  -1 on invalid arguments.
  * hb_plan_f32_small_form: how a small product (hb_plan_f32_kernel: 0) runs, 0 if it is none.  The block, 16 or 32; + 64: operands
@@ -282,6 +288,7 @@ int32_t hb_plan_bf16_dw_slices(int32_t d_out, int32_t d_in, int64_t B, int32_t c
  */
 int32_t hb_plan_f32_kernel(int32_t product, int32_t d_out, int32_t d_in, int64_t B, int64_t max_B, int32_t *slices);
 int32_t hb_plan_bf16_kernel(int32_t product, int32_t d_out, int32_t d_in, int64_t B, int32_t layer);
+int32_t hb_plan_bf16_pair(const int32_t *layer_dims, int32_t n_dims, int64_t B, int32_t layer);
 int32_t hb_plan_f32_small_form(int32_t product, int32_t d_out, int32_t d_in, int64_t B, int64_t max_B);
 int32_t hb_plan_small_net(const int32_t *layer_dims, int32_t n_dims, int64_t B);
 

@@ -40,6 +40,7 @@ SIGNATURES = {
     "hb_plan_bf16_dw_slices": (_i32, [_i32, _i32, _i64, _i32]),
     "hb_plan_f32_kernel": (_i32, [_i32, _i32, _i32, _i64, _i64, _i32p]),
     "hb_plan_bf16_kernel": (_i32, [_i32, _i32, _i32, _i64, _i32]),
+    "hb_plan_bf16_pair": (_i32, [_i32p, _i32, _i64, _i32]),
     "hb_plan_f32_small_form": (_i32, [_i32, _i32, _i32, _i64, _i64]),
     "hb_plan_small_net": (_i32, [_i32p, _i32, _i64]),
 }

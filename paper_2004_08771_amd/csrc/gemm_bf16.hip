@@ -1674,26 +1674,30 @@ static bool pair_shares(long long tiles, int K) { return K >= 8 * MID_BK && (til
 
 // Products that the kernels of 64 x 64 tiles take (apart / in one launch, us per step: 64-128-7 64 rows 25.7 / 21.5, 7001 80.1 / 50.4;
 // 512x4-100 500 rows 83.7 / 62.9; 2048-700x3-1000 2047 rows 172 / 137, 7001 rows, which has hardly any such product, 395 / 394;
-// 1024-2048-2048-10 4000 rows 309 / 309).  HB_BF16_NO_PAIR=1 (tuning aid): apart.
-bool gemm_bf16_pair_ok(const GemmBf16Args &dw, GemmKind kind, const GemmBf16Args &next)
+// 1024-2048-2048-10 4000 rows 309 / 309).  HB_BF16_NO_PAIR=1 (tuning and test aid; read per call): apart.
+int gemm_bf16_pair_groups(const GemmBf16Args &dw, GemmKind kind, const GemmBf16Args &next)
 {
-    static const int off = env_int_bf16("HB_BF16_NO_PAIR", 0);
-    if (off || dw.bmaj != BF16_DW_BMAJ_MID || kind == GEMM_FWD || (kind == GEMM_DW && next.bmaj != BF16_DW_BMAJ_MID)) return false;
+    if (env_int_bf16("HB_BF16_NO_PAIR", 0)) return 0;
+    if (dw.bmaj != BF16_DW_BMAJ_MID || kind == GEMM_FWD || (kind == GEMM_DW && next.bmaj != BF16_DW_BMAJ_MID)) return 0;
+    long long blocks = 0;
     for (const GemmBf16Args *a : {&dw, &next}) {
         const int k = gemm_bf16_kernel(a == &dw ? GEMM_DW : kind, *a);
-        if (k != BF16_K_64 && k != BF16_K_64_SHARED) return false;
+        if (k != BF16_K_64 && k != BF16_K_64_SHARED) return 0;
+        blocks += (long long)((a->M + 63) / 64) * ((a->N + 63) / 64) + (a->bmaj && a->fin.n > 0 ? 1 : 0);
     }
-    return next.bmaj || aligned4(next.A, next.lda);
+    if (!next.bmaj && !aligned4(next.A, next.lda)) return 0;
+    return pair_shares(blocks, dw.K) ? 2 : 1;
 }
 
 hipError_t launch_gemm_bf16_pair(GemmBf16Args dw, GemmKind kind, GemmBf16Args next, hipStream_t stream, const LaunchEvents &ev)
 {
-    if (!gemm_bf16_pair_ok(dw, kind, next)) return hipErrorInvalidValue;
+    const int groups = gemm_bf16_pair_groups(dw, kind, next);
+    if (groups == 0) return hipErrorInvalidValue;
     next.colsum_partial = nullptr;
     const long long n_dw = mid_tiles(dw, 64) + (dw.fin.n > 0 ? 1 : 0);
     const long long blocks = n_dw + mid_tiles(next, 64) + (kind == GEMM_DW && next.fin.n > 0 ? 1 : 0);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    const bool two = pair_shares(blocks, dw.K);
+    const bool two = groups == 2;
     const auto kernel = kind == GEMM_DA ? (two ? gemm_bf16_mid_pair_kernel<2, GEMM_DA> : gemm_bf16_mid_pair_kernel<1, GEMM_DA>)
                                         : (two ? gemm_bf16_mid_pair_kernel<2, GEMM_DW> : gemm_bf16_mid_pair_kernel<1, GEMM_DW>);
     return launch_kernel(kernel, dim3((unsigned)blocks), dim3(two ? 2 * NT : NT), stream, ev, dw, next, (int)n_dw);

@@ -869,7 +869,7 @@ int run_step_bf16(hb_model *m, const void *X, const int32_t *y, int64_t B, float
         if (l > 1) {  // with what comes next, which does not need it: D_{l-2}, or dW_1
             const GemmKind kind = l > 2 ? GEMM_DA : GEMM_DW;
             const GemmBf16Args next = l > 2 ? da_args(l - 1) : dw_args(1);
-            if ((three || kind == GEMM_DW) && gemm_bf16_pair_ok(g, kind, next)) {
+            if ((three || kind == GEMM_DW) && gemm_bf16_pair_groups(g, kind, next) > 0) {
                 HB_HIP(launch_gemm_bf16_pair(
                     g, kind, next, st,
                     prof_begin(m, HB_K_BWD_PAIR, l, g.M, g.N, g.K,
@@ -1145,25 +1145,24 @@ int32_t hb_plan_small_net(const int32_t *layer_dims, int32_t n_dims, int64_t B)
     return small_net_rows(layer_dims, n_dims - 1, B);
 }
 
-int32_t hb_plan_bf16_kernel(int32_t product, int32_t d_out, int32_t d_in, int64_t B, int32_t layer)
+// What the choice of a bf16 product's kernel looks at, X and the gradient buffers 16-byte aligned (layer: hb_plan_bf16_kernel)
+static GemmBf16Args plan_args_bf16(GemmKind kind, int d_out, int d_in, int Bi, int layer)
 {
-    if (product < 0 || product > 2 || d_out < 1 || d_in < 1 || d_out > MAX_DIM || d_in > MAX_DIM || B < 1 || B > MAX_BATCH)
-        return -1;
     const bool first = (layer & 1) != 0, last = (layer & 2) != 0;
-    const int Bi = (int)B, pitch_in = first ? d_in : round_up(d_in, 8), pitch_out = bf16_pitch(d_out, last);
+    const int pitch_in = first ? d_in : round_up(d_in, 8), pitch_out = bf16_pitch(d_out, last);
     GemmBf16Args g = {};
     g.b_vec = 1;
-    if (product == 0) {
+    if (kind == GEMM_FWD) {
         g.M = Bi, g.N = d_out, g.K = d_in;
         g.lda = pitch_in, g.ldb = round_up(d_in, 8);
         g.a_vec = (g.lda % 8 == 0);
-        return gemm_bf16_kernel(GEMM_FWD, g) + ((g.lda & 1) ? 16 : 0);
+        return g;
     }
     g.a_vec = 1;
-    if (product == 1) {
+    if (kind == GEMM_DA) {
         g.M = Bi, g.N = d_in, g.K = last ? pitch_out : d_out;
         g.lda = g.ldb = pitch_out;
-        return gemm_bf16_kernel(GEMM_DA, g);
+        return g;
     }
     g.M = d_out, g.N = d_in, g.K = Bi;
     g.bmaj = gemm_bf16_dw_form(d_out, d_in, Bi, pitch_out, pitch_in, nullptr, nullptr);
@@ -1176,7 +1175,33 @@ int32_t hb_plan_bf16_kernel(int32_t product, int32_t d_out, int32_t d_in, int64_
         g.write_grad = 1;
         g.k_chunk = (int)round_up((Bi + sp - 1) / sp, 64);
     }
-    return gemm_bf16_kernel(GEMM_DW, g) + (g.bmaj ? 32 : 0);
+    g.fin.n = (last && g.bmaj == BF16_DW_BMAJ_MID) ? 1 : 0;  // this product finishes the mean loss
+    return g;
+}
+
+int32_t hb_plan_bf16_kernel(int32_t product, int32_t d_out, int32_t d_in, int64_t B, int32_t layer)
+{
+    if (product < 0 || product > 2 || d_out < 1 || d_in < 1 || d_out > MAX_DIM || d_in > MAX_DIM || B < 1 || B > MAX_BATCH)
+        return -1;
+    const GemmKind kind = product == 0 ? GEMM_FWD : product == 1 ? GEMM_DA : GEMM_DW;
+    const GemmBf16Args g = plan_args_bf16(kind, d_out, d_in, (int)B, layer);
+    return gemm_bf16_kernel(kind, g) + (kind == GEMM_FWD && (g.lda & 1) ? 16 : 0) + (g.bmaj ? 32 : 0);
+}
+
+int32_t hb_plan_bf16_pair(const int32_t *layer_dims, int32_t n_dims, int64_t B, int32_t layer)
+{
+    if (!layer_dims || n_dims < 2 || n_dims > MAX_LAYERS + 1 || B < 1 || B > MAX_BATCH || layer < 1 || layer >= n_dims) return -1;
+    for (int i = 0; i < n_dims; ++i)
+        if (layer_dims[i] < 1 || layer_dims[i] > MAX_DIM) return -1;
+    if (layer == 1) return 0;  // nothing follows it
+    const int L = n_dims - 1;
+    auto args = [&](GemmKind kind, int l) {
+        return plan_args_bf16(kind, layer_dims[l], layer_dims[l - 1], (int)B, (l == 1) + 2 * (l == L));
+    };
+    if (layer == 2) return gemm_bf16_pair_groups(args(GEMM_DW, 2), GEMM_DW, args(GEMM_DW, 1));
+    for (int l = 2; l <= L; l += 2)  // their transposed copies take the buffer of the third delta
+        if (!args(GEMM_DW, l).bmaj) return 0;
+    return gemm_bf16_pair_groups(args(GEMM_DW, layer), GEMM_DA, args(GEMM_DA, layer - 1));
 }
 
 hb_model *hb_mlp_create(const int32_t *layer_dims, int32_t n_dims, int activation, int loss)

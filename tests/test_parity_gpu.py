@@ -168,7 +168,7 @@ BF16_KERNELS = ["refused", "dma", "128", "128s", "64", "64s"]  # hb_plan_bf16_ke
 
 def check_plan(got, want):
     """The sizes of a case reach the kernels it names -- unless a tuning aid of the environment sends them elsewhere."""
-    aids = ("HB_BF16_TILE", "HB_BF16_BMAJ", "HB_GEMM_SMALL_TILES", "HB_GEMM_SMALL_K", "HB_NO_PAIR")
+    aids = ("HB_BF16_TILE", "HB_BF16_BMAJ", "HB_BF16_NO_PAIR", "HB_GEMM_SMALL_TILES", "HB_GEMM_SMALL_K", "HB_NO_PAIR")
     assert got == want or any(a in os.environ for a in aids), (got, want)
     return got == want
 
@@ -201,6 +201,14 @@ def bf16_plan(dims, B):
                 (f"/{slices}" if slices > 1 else ""))
 
     return "; ".join(" ".join(name(q, l) for l in range(2 if q == 1 else 1, L + 1)) for q in range(3))
+
+
+def bf16_pairs(dims, B):
+    """{layer: groups of wavefronts} of the weight gradients that share a launch with the next backward product."""
+    import ctypes
+    from paper_2004_08771_amd import lib
+    arr = (ctypes.c_int32 * len(dims))(*dims)
+    return {l: n for l in range(1, len(dims)) if (n := lib().hb_plan_bf16_pair(arr, len(dims), B, l))}
 
 
 # ---------------------------------------------------------------- small shapes, every mode
@@ -1846,25 +1854,58 @@ def test_bf16_weight_gradient_of_rows_without_padding(d0, B):
     check_bf16_case(dims, hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=False)
 
 
+@pytest.mark.parametrize("dims,act,B,plan", BF16_SMALL_TILES + [
+    ((66, 129, 65, 70, 3), hi.ACT_SIGMOID, 200, "64 64 64 64; 64 64 64; 64B 64B 64B 64B"),
+    ((34, 1700, 1700, 2), hi.ACT_RELU, 600, "64 64s 64s; 64s 64; 64sB 64B 64sB"),
+])
+def test_bf16_small_tile_products_each_in_a_launch_of_its_own(monkeypatch, dims, act, B, plan):
+    """The backward products as they run where none can share a launch, in the kernels that hb_plan_bf16_kernel names."""
+    monkeypatch.setenv("HB_BF16_NO_PAIR", "1")
+    assert bf16_pairs(dims, B) == {}
+    check_plan(bf16_plan(dims, B), plan)
+    params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=310 + B, bias_scale=0.1)
+    assert bf16_pair_launches(dims, act, X, y) == set()
+    check_bf16_case(dims, act, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=False)
+
+
 BF16_PAIRS = [
     # two layers: the two weight gradients share a launch, with the mean loss; a batch cut inside its second k-tile
-    ((66, 129, 5), hi.ACT_RELU, 65),
+    ((66, 129, 5), hi.ACT_RELU, 65, {2: 1}),
     # each weight gradient with the next backward-data product, one group of wavefronts; three deltas at once
-    ((66, 129, 65, 70, 3), hi.ACT_SIGMOID, 200),
+    ((66, 129, 65, 70, 3), hi.ACT_SIGMOID, 200, {4: 1, 3: 1, 2: 1}),
     # two groups: nine k-tiles over the batch and one row
-    ((66, 129, 65, 70, 3), hi.ACT_RELU, 577),
-    # 758 tiles over ten k-tiles: one group; the launch before it 298 tiles: two
-    ((34, 1700, 1700, 2), hi.ACT_RELU, 600),
+    ((66, 129, 65, 70, 3), hi.ACT_RELU, 577, {4: 2, 3: 2, 2: 2}),
+    # 756 tiles over ten k-tiles: one group; the launch before it 298 tiles, the mean loss one of them: two
+    ((34, 1700, 1700, 2), hi.ACT_RELU, 600, {3: 2, 2: 1}),
     # 550 tiles over 49 k-tiles: two groups
-    ((34, 700, 700, 3), hi.ACT_SIGMOID, 3100),
+    ((34, 700, 700, 3), hi.ACT_SIGMOID, 3100, {3: 2, 2: 2}),
     # odd rows of X: dW_1 from transposed copies, in a launch of its own
-    ((65, 70, 90, 5), hi.ACT_SIGMOID, 130),
+    ((65, 70, 90, 5), hi.ACT_SIGMOID, 130, {3: 1}),
+    # 16 x 16 tiles over eight k-tiles and 16 x 16 of the next product: the most for two groups; with a row more, one group
+    ((34, 1024, 1024, 1024, 2), hi.ACT_SIGMOID, 1024, {4: 2, 3: 2, 2: 2}),
+    ((34, 1024, 1024, 1024, 2), hi.ACT_SIGMOID, 1025, {4: 2, 3: 1, 2: 2}),
 ]
 
 
-@pytest.mark.parametrize("dims,act,B", BF16_PAIRS)
-def test_bf16_backward_products_that_share_a_launch(dims, act, B):
+def bf16_pair_launches(dims, act, X, y):
+    """The layers whose weight gradient shared a launch in one step."""
+    import paper_2004_08771_amd as hb
+    torch = _torch()
+    m = hb.Model(dims, act, hi.LOSS_SOFTMAX_CE).configure(hb.HB_BF16_F32MASTER, y.size)
+    m.set_params(np.zeros(hi.num_params(dims), np.float32))
+    dX, dy = torch.from_numpy(X).cuda().to(torch.bfloat16), torch.from_numpy(y).cuda()
+    m.profile_enable(True)
+    m.batch_step(dX, dy, y.size, 0.1)
+    ran = {s["layer"] for s in m.profile_read() if s["kind"] == 9}
+    m.destroy()
+    return ran
+
+
+@pytest.mark.parametrize("dims,act,B,pairs", BF16_PAIRS)
+def test_bf16_backward_products_that_share_a_launch(dims, act, B, pairs):
     params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=700 + B, bias_scale=0.1)
+    check_plan(bf16_pairs(dims, B), pairs)
+    check_plan(bf16_pair_launches(dims, act, X, y), set(pairs))
     check_bf16_case(dims, act, hi.LOSS_SOFTMAX_CE, params, X, y, lr=0.1, condition_relu=False)
 
 

@@ -19,6 +19,11 @@ def test_f32_long_forward_cases_run_the_kernels_they_name(dims, B, kernels):
     assert t.f32_plan(dims, B).split("; ")[0].split()[:-1] == kernels
 
 
+@pytest.mark.parametrize("dims,B,pairs", [(r[0], r[2], r[3]) for r in t.BF16_PAIRS])
+def test_bf16_cases_share_the_launches_they_name(dims, B, pairs):
+    assert t.bf16_pairs(dims, B) == pairs
+
+
 def test_the_cases_reach_every_form_of_the_small_products():
     for r in t.F32_SMALL:
         assert t.f32_small_forms(r[0], r[2]) == r[3]
@@ -85,5 +90,9 @@ def test_plans_refuse_invalid_arguments():
     assert f(0, 0, 5, 5, 5, None) == -1 and f(3, 5, 5, 5, 5, None) == -1 and f(0, 5, 5, 6, 5, None) == -1
     s = lib().hb_plan_f32_small_form
     assert s(0, 0, 5, 5, 5) == -1 and s(3, 5, 5, 5, 5) == -1 and s(0, 5, 5, 6, 5) == -1 and s(0, 512, 512, 4096, 4096) == 0
+    import ctypes
+    p, dims = lib().hb_plan_bf16_pair, (ctypes.c_int32 * 3)(6, 5, 5)
+    assert p(dims, 3, 5, 0) == -1 and p(dims, 3, 5, 3) == -1 and p(dims, 3, 0, 1) == -1 and p(None, 3, 5, 1) == -1
+    assert p((ctypes.c_int32 * 3)(5, 0, 5), 3, 5, 1) == -1 and p(dims, 3, 5, 1) == 0 and p(dims, 3, 5, 2) == 1
     assert t.small_net_rows((5,), 5) == -1 and t.small_net_rows((5, 0, 5), 5) == -1 and t.small_net_rows((5, 5, 5), 0) == -1
     assert b(0, 5, 0, 5, 0) == -1 and b(-1, 5, 5, 5, 0) == -1 and b(0, 5, (1 << 24) + 1, 5, 0) == -1

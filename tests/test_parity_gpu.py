@@ -1650,19 +1650,21 @@ def _relu_gradient_in_64_bits(dims, params, X, y, on):
     return np.concatenate(grads[::-1]), acts
 
 
-def test_split_plane_products_of_tiny_operands():
+@pytest.mark.parametrize("dims,B,plan", [
+    ((300, 300, 290, 40), 2560, "64s 64s small; 128x64 64s; 128"),
+    ((546, 515, 530, 40), 577, "64x32 64x32 small; 64s 64s; small"),
+])
+def test_split_plane_products_of_tiny_operands(dims, B, plan):
     """Operands down to 2^-126 keep all their bits in the three planes: weights of 2^-116 against inputs of 2^100
     (forward), activations of 2^-116 (forward and weight gradient), deltas of 2^-117 (weight gradient of layer 1, read
     M-major).  Without a scale the planes of 2^-116 hold about 18 bits (relative error 2e-6)."""
-    dims, B = (300, 300, 290, 40), 2560
-    check_plan(f32_plan(dims, B), "64s 64s small; 128x64 64s; 128")
+    check_plan(f32_plan(dims, B), plan)
     rng = np.random.default_rng(11)
-    W = [rng.standard_normal((300, 300)) * 2.0 ** -116, rng.standard_normal((290, 300)) * 2.0 ** -108,
-         rng.standard_normal((40, 290)) * 0.1]
+    W = [rng.standard_normal((b, a)) * s for a, b, s in zip(dims[:-1], dims[1:], (2.0 ** -116, 2.0 ** -108, 0.1))]
     params = np.concatenate([np.concatenate([w.ravel(), np.zeros(w.shape[0])]) for w in W])
     params[-40:] = rng.standard_normal(40)
     params = params.astype(np.float32)
-    X = (rng.standard_normal((B, 300)) * 2.0 ** 100).astype(np.float32)
+    X = (rng.standard_normal((B, dims[0])) * 2.0 ** 100).astype(np.float32)
     y = rng.integers(0, 40, size=B).astype(np.int32)
     _, g, _, _, _, acts = gpu_grad_and_step(dims, hi.ACT_RELU, hi.LOSS_SOFTMAX_CE, params, X, y, 0.0, want_acts=True)
     ref, ref_acts = _relu_gradient_in_64_bits(dims, params, X, y, {l: acts[l] > 0 for l in (1, 2)})
@@ -1707,6 +1709,7 @@ SPLIT_SIZES = [
     ((130, 257, 250, 40), 4099, "128x64 128x64 small; 128 128x64; small"),
     ((97, 257, 129, 33), 4099, "128x64 64s small; 64 64s; small"),
     ((100, 500, 500, 40), 8150, "128 128 small; 128 128x64; small"),
+    ((546, 515, 530, 40), 577, "64x32 64x32 small; 64s 64s; small"),  # 64 x 32, four groups of wavefronts (forward)
 ]
 
 
@@ -1775,6 +1778,24 @@ def test_split_plane_products_of_values_without_finite_planes(dims, B, plan):
     assert np.isfinite(ref) and abs(got - ref) <= TOL_F32 * abs(ref)
     for row in (3, B - 1, B - 2):
         assert set(np.unique(acts[1][row])) <= {0.0, 1.0}
+
+
+@pytest.mark.parametrize("dims,B,plan", SPLIT_SIZES)
+def test_split_plane_products_keep_a_nan_in_its_row(dims, B, plan):
+    check_plan(f32_plan(dims, B), plan)
+    torch = _torch()
+    params, X, y = _problem(dims, hi.LOSS_SOFTMAX_CE, B, seed=7)
+    m, acts = make_model(dims, hi.ACT_SIGMOID, hi.LOSS_SOFTMAX_CE, B, params), []
+    dy = torch.from_numpy(y).cuda()
+    for value in (X[B - 1, dims[0] - 1], np.nan):
+        X[B - 1, dims[0] - 1] = value
+        m.batch_loss_async(torch.from_numpy(X).cuda(), dy, B)
+        acts.append(gpu_hidden_activations(m, dims, B))
+    m.destroy()
+    for l in (1, 2):
+        assert np.isnan(acts[1][l][B - 1]).all()
+        # the blocks with the NaN are the same planes or fp32 products of the same values: sums of up to 546 terms
+        assert np.allclose(acts[1][l][:B - 1], acts[0][l][:B - 1], rtol=1e-5, atol=0)
 
 
 def test_nan_operands_stay_nan_and_cost_no_second_product():

@@ -270,7 +270,8 @@ int32_t hb_plan_bf16_dw_slices(int32_t d_out, int32_t d_in, int64_t B, int32_t c
  * batches under 64 of a layer of more than 2^24 weights),
  * 2 weight gradient (fp32 mode: on its own, as the first layer's).
  * fp32 mode, model configured for max_B: 0 small products (blocks of 16 x 16 or 32 x 32), 1 64 x 64, 2 128 x 64, 3 128 x 128,
- * 4 64 x 64 with two groups of wavefronts, 5 64 x 32 with four (forward only); *slices (may be NULL): slices of the weight gradient's batch.
+ * 4 64 x 64 with two groups of wavefronts, 5 64 x 32 with four (forward only); *slices (may be NULL): slices of the weight
+ * gradient's batch.
  * bf16 mode: 1 256 x 256 (LDS-direct), 2 128 x 128, 3 128 x 128 with two workgroups per compute unit, 4 64 x 64,
  * 5 64 x 64 with two groups; + 16: rows of X that are not 4-byte aligned (16-byte aligned dX assumed), + 32: weight
  * gradient from the batch-major tensors.  layer: 1 for the first layer, 2 for the last, 3 for both, else 0.  This is the

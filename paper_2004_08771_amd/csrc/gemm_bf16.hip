@@ -291,12 +291,13 @@ __device__ __forceinline__ void epilogue_bf16(const GemmBf16Args &a, v16f (&acc)
     });
 }
 
-// The 256 x 256 kernel multiplies in 16 x 16 blocks (v_mfma_f32_16x16x32_bf16): a block has rows 4 g + e and column c in lane 16 g + c, register e.
-// Two wavefronts of a SIMD that issue v_mfma_f32_32x32x16_bf16 in turn reach only two thirds of what the 16 x 16 form gives
-// (registers only, normal values: 1290-1340 against 2030 TFLOP/s, zeros 1604 against 2468; one wavefront alone 1807 against 2041);
-// here, where both also read and load, four steps of 2048-4096x3-1000 over 16384 rows went from 18.53 to 18.06 ms with it.
-// The epilogues want 32 x 32 blocks (rows 8 q + 4 h + e, column r in lane 32 h + r, register 4 q + e): of a pair of blocks side by
-// side, lane bit 5 (rows 8 ..) becomes a register and the column block lane bit 4, two lane exchanges for two registers.
+// The 256 x 256 kernel multiplies in 16 x 16 blocks (v_mfma_f32_16x16x32_bf16): a block has rows 4 g + e and column c in lane
+// 16 g + c, register e.  Two wavefronts of a SIMD that issue v_mfma_f32_32x32x16_bf16 in turn reach only two thirds of what
+// the 16 x 16 form gives (registers only, normal values: 1290-1340 against 2030 TFLOP/s, zeros 1604 against 2468; one
+// wavefront alone 1807 against 2041); here, where both also read and load, four steps of 2048-4096x3-1000 over 16384 rows
+// went from 18.53 to 18.06 ms with it.  The epilogues want 32 x 32 blocks (rows 8 q + 4 h + e, column r in lane 32 h + r,
+// register 4 q + e): of a pair of blocks side by side, lane bit 5 (rows 8 ..) becomes a register and the column block lane
+// bit 4, two lane exchanges for two registers.
 typedef float v4f __attribute__((ext_vector_type(4)));
 template <int TM, int TN>
 __device__ __forceinline__ void blocks_of_32(v16f (&out)[TM][TN], const v4f (&in)[2 * TM][2 * TN])
@@ -307,7 +308,8 @@ __device__ __forceinline__ void blocks_of_32(v16f (&out)[TM][TN], const v4f (&in
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const auto y = __builtin_amdgcn_permlane16_swap(__float_as_uint(in[i][2 * j][e]), __float_as_uint(in[i][2 * j + 1][e]), false, false);
+                const auto y = __builtin_amdgcn_permlane16_swap(__float_as_uint(in[i][2 * j][e]),
+                                                                __float_as_uint(in[i][2 * j + 1][e]), false, false);
                 const auto z = __builtin_amdgcn_permlane32_swap(y[0], y[1], false, false);
                 out[i / 2][j][8 * (i & 1) + e] = __uint_as_float(z[0]);
                 out[i / 2][j][8 * (i & 1) + 4 + e] = __uint_as_float(z[1]);
@@ -1103,15 +1105,14 @@ __device__ __forceinline__ void gemm_bf16_dma_tile(const GemmBf16Args &a, unsign
             for (int j = 0; j < TN; ++j) mword[i][j] = mi[((size_t)i * a.mask_nb + j) * 64];
     }
 
-    // One MFMA group: the sixteen MFMAs of one half of the wavefront's rows at one k-step (A fragments in fa[half], B fragments in
-    // fb[bs]), and in their shadow (a wavefront can issue other instructions while its MFMA executes) the
-    // requests for the next group's fragments -- the other half of the rows, or (second half) the first one of the next k-step
-    // and that step's B --, one after each of the first MFMAs, and
-    // two direct loads after the sixth and eleventh (eleventh and fifteenth).  Clumped, these
-    // requests are issued by both wavefronts of a SIMD at the same time (the barrier keeps
-    // them in step) and the MFMA pipe idles meanwhile: with two fragments to an MFMA and the two loads together four steps of
-    // 2048-4096x3-1000 over 16384 rows, their readback included, take 18.06 ms, so 17.53.  Only the requests are conditional,
-    // so that there is one MFMA stream.
+    // One MFMA group: the sixteen MFMAs of one half of the wavefront's rows at one k-step (A fragments in fa[half], B
+    // fragments in fb[bs]), and in their shadow (a wavefront can issue other instructions while its MFMA executes) the
+    // requests for the next group's fragments -- the other half of the rows, or (second half) the first one of the next
+    // k-step and that step's B --, one after each of the first MFMAs, and two direct loads after the sixth and eleventh
+    // (eleventh and fifteenth).  Clumped, these requests are issued by both wavefronts of a SIMD at the same time (the
+    // barrier keeps them in step) and the MFMA pipe idles meanwhile: with two fragments to an MFMA and the two loads together
+    // four steps of 2048-4096x3-1000 over 16384 rows, their readback included, take 18.06 ms, so 17.53.  Only the requests
+    // are conditional, so that there is one MFMA stream.
     auto group = [&](auto half_c, int bs, bool rd, int sa, int sb, auto kk, bool ld, bool is_a, int t, int stage, int first) {
         constexpr int half = decltype(half_c)::value;
         const unsigned char *pa = smem_raw + sa * DMA_A_BYTES;
@@ -1672,9 +1673,9 @@ hipError_t launch_gemm_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream, c
 // (1536 tiles) 103.9 / 107.8, 2047 157.2 / 159.3, 4000 309 / 309, 7001 400 / 392.
 static bool pair_shares(long long tiles, int K) { return K >= 8 * MID_BK && (tiles <= 512 || K >= 48 * MID_BK); }
 
-// Products that the kernels of 64 x 64 tiles take (apart / in one launch, us per step: 64-128-7 64 rows 25.7 / 21.5, 7001 80.1 / 50.4;
-// 512x4-100 500 rows 83.7 / 62.9; 2048-700x3-1000 2047 rows 172 / 137, 7001 rows, which has hardly any such product, 395 / 394;
-// 1024-2048-2048-10 4000 rows 309 / 309).  HB_BF16_NO_PAIR=1 (tuning and test aid; read per call): apart.
+// Products that the kernels of 64 x 64 tiles take (apart / in one launch, us per step: 64-128-7 64 rows 25.7 / 21.5, 7001
+// 80.1 / 50.4; 512x4-100 500 rows 83.7 / 62.9; 2048-700x3-1000 2047 rows 172 / 137, 7001 rows, which has hardly any such
+// product, 395 / 394; 1024-2048-2048-10 4000 rows 309 / 309).  HB_BF16_NO_PAIR=1 (tuning and test aid; read per call): apart.
 int gemm_bf16_pair_groups(const GemmBf16Args &dw, GemmKind kind, const GemmBf16Args &next)
 {
     if (env_int_bf16("HB_BF16_NO_PAIR", 0)) return 0;

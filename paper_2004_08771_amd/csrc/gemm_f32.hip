@@ -553,14 +553,17 @@ bool small_out(int M, int N, int K)
 {
     return K >= 64 && (long long)((M + 63) / 64) * ((N + 63) / 64) < small_tiles_max();
 }
-// Forward products of 80 to 159 tiles (80 to 127 over contractions below 768, where the gain has come down to 3 %) over 512 and more go to the split planes, in tiles of 64 x 32 while each has a
-// compute unit of its own: four groups of two wavefronts share the contraction, a quarter of the k-tiles in a row each, where 64 x 64
-// tiles leave half of the device idle and fp32 MFMAs are a longer chain than the conversions.  Networks of w-w-w-w-w-w-4 (2048 and
-// more: w-w-w-4), forward and loss, us, small kernels / 64 x 64 / 64 x 32: w = 512 640 rows 55.5 / 54.0 / 47.1, 1021 rows 56.3 / 60.9 /
-// 54.6; 768 430 rows 72.7 / 76.7 / 64.1, 600 rows 74.3 / 71.6 / 61.9, 800 rows (312 tiles of 64 x 32) 90.0 / 77.3; 1024 320 rows 90.0 /
-// 82.6 / 66.9, 510 rows 93.4 / 89.8 / 80.8; 2048 130 rows 69.0 / 61.6 / 51.2, 250 rows 71.4 / 65.3 / 56.5; 4096 100 rows 130.7 / 116.6 /
-// 97.8.  Shorter contractions stay: 320 1021 rows 41.5 / 49.7 / 45.5; 256 2047 rows 38.9 / 45.3 / 43.0; fewer tiles too: 512 330 rows
-// 43.9 / - / 47.5, 768 300 rows 58.2 / - / 63.1.  Narrower outputs than the ones measured, and up to 64 rows (4096 wide 88.6 / 88.3 / -), stay too.
+// Forward products of 80 to 159 tiles over 768 and more, and of 80 to 127 over 512 to 767, go to the split planes, in tiles
+// of 64 x 32 while each has a compute unit of its own (else 64 x 64): four groups of two wavefronts share the contraction, a
+// quarter of the k-tiles in a row each, where 64 x 64 tiles leave half of the device idle and fp32 MFMAs are a longer chain
+// than the conversions.  Networks of w-w-w-w-w-w-4 (2048 and more: w-w-w-4), forward and loss, us, small kernels / 64 x 64 /
+// 64 x 32: w = 512 640 rows 55.5 / 54.0 / 47.1, 1021 rows 56.3 / 60.9 / 54.6; 768 430 rows 72.7 / 76.7 / 64.1, 600 rows 74.3
+// / 71.6 / 61.9, 800 rows (312 tiles of 64 x 32) 90.0 / 77.3; 1024 320 rows 90.0 / 82.6 / 66.9, 510 rows 93.4 / 89.8 / 80.8;
+// 2048 130 rows 69.0 / 61.6 / 51.2, 250 rows 71.4 / 65.3 / 56.5; 4096 100 rows 130.7 / 116.6 / 97.8.  Shorter contractions
+// stay: 320 1021 rows 41.5 / 49.7 / 45.5; 256 2047 rows 38.9 / 45.3 / 43.0; fewer tiles too: 512 330 rows 43.9 / - / 47.5,
+// 768 300 rows 58.2 / - / 63.1.  Narrower outputs than the ones measured, and up to 64 rows (4096 wide 88.6 / 88.3 / -), stay
+// too.  So do 128 tiles and more over less than 768: 3 % (512 1021 rows) is little to give up the sums that all small forms
+// share for, by which a row comes out the same, bit for bit, in batches of any size up to there.
 bool long_fwd(int M, int N, int K)
 {
     const long long tiles = (long long)((M + 63) / 64) * ((N + 63) / 64);

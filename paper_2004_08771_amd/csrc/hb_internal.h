@@ -367,7 +367,8 @@ struct SparseDwArgs {
     long long B;
     int rows_per_split;          // filled in by launch_sparse_dw
 };
-// The CSC of a small batch in one launch (leaves col_start, col_cnt and per-range lists of long columns in chunk_start / chunk_desc)
+// The CSC of a small batch in one launch (leaves col_start, col_cnt and per-range lists of long columns in chunk_start /
+// chunk_desc)
 bool csc_one_launch(long long nnz, long long B, int d1);
 hipError_t launch_csc_one(const int32_t *row_ptr, const int32_t *col_idx, const float *vals, long long nnz, long long B, int d0,
                           int32_t *col_start, int32_t *col_cnt, int32_t *chunk_start, int4 *chunk_desc, int2 *csc_ent,

@@ -416,7 +416,7 @@ __global__ __launch_bounds__(CSC_NT) void csc_place_kernel(const int32_t *__rest
 // (Counted and placed where they were found, by whichever lanes had one, the launch took 30 us longer per 17,000 entries.)
 // Every column's entries keep their order in the batch: wavefronts in turn (a prefix over their counts), lanes in turn (each
 // compares its column with the others' of a window of 64).  Placed by atomic counters instead, the sums of the weight
-// gradient differed in the last bits from run to run, and a few steps on a ReLU decision turned over. It leaves, by column,
+// gradient differed in the last bits from run to run, and a few steps on a ReLU decision turned over.  It leaves, by column,
 // the first entry and their number, and per range the list of its columns of more than ONE_LIST entries (chunk_desc[one_base
 // ..], chunk_start[range] of them), for sparse_dw_columns_kernel.
 constexpr int ONE_RANGES = 128;
@@ -979,7 +979,7 @@ __global__ __launch_bounds__(256) void colsum_kernel(const float *__restrict__ d
 
 // Weight gradient of layer 1 from the CSC of csc_one_kernel, with the bias gradient's slices in the same launch (first: they
 // are the longest workgroups).  What bounds a small batch is the chain offsets - entries - rows of delta - weights, four
-// dependent trips to memory, and one column per workgroup filled the device three times over with it. Columns of up to
+// dependent trips to memory, and one column per workgroup filled the device three times over with it.  Columns of up to
 // ONE_LIST entries: a workgroup takes up to ONE_COLS (of wide rows a piece), a stride of n_light apart, so that neighbours,
 // which may all be long, do not meet; the ones of up to LIGHT_MAX entries together, four entries of each in a round, so that
 // sixteen gathers are in flight, and their weight rows with one another.  Longer columns come from the lists: a workgroup

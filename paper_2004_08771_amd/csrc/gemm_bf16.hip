@@ -1675,10 +1675,10 @@ static bool pair_shares(long long tiles, int K) { return K >= 8 * MID_BK && (til
 
 // Products that the kernels of 64 x 64 tiles take (apart / in one launch, us per step: 64-128-7 64 rows 25.7 / 21.5, 7001
 // 80.1 / 50.4; 512x4-100 500 rows 83.7 / 62.9; 2048-700x3-1000 2047 rows 172 / 137, 7001 rows, which has hardly any such
-// product, 395 / 394; 1024-2048-2048-10 4000 rows 309 / 309).  HB_BF16_NO_PAIR=1 (tuning and test aid; read per call): apart.
+// product, 395 / 394; 1024-2048-2048-10 4000 rows 309 / 309).  HB_BF16_NO_PAIR=1 (tuning and test aid; read per step): apart.
+bool gemm_bf16_pairs_on() { return env_int_bf16("HB_BF16_NO_PAIR", 0) == 0; }
 int gemm_bf16_pair_groups(const GemmBf16Args &dw, GemmKind kind, const GemmBf16Args &next)
 {
-    if (env_int_bf16("HB_BF16_NO_PAIR", 0)) return 0;
     if (dw.bmaj != BF16_DW_BMAJ_MID || kind == GEMM_FWD || (kind == GEMM_DW && next.bmaj != BF16_DW_BMAJ_MID)) return 0;
     long long blocks = 0;
     for (const GemmBf16Args *a : {&dw, &next}) {

@@ -858,6 +858,7 @@ int run_step_bf16(hb_model *m, const void *X, const int32_t *y, int64_t B, float
     auto dw_bytes = [&](const GemmBf16Args &g) {
         return 2.0 * ((double)g.M * g.K + (double)g.N * g.K) + (grad_mode ? 4.0 : 12.0) * g.M * g.N;
     };
+    const bool pairs_on = gemm_bf16_pairs_on();
     std::vector<char> done_da((size_t)L + 2, 0), done_dw((size_t)L + 2, 0);
     for (int l = L; l >= 1; --l) {
         if (l > 1 && !done_da[l])
@@ -866,7 +867,7 @@ int run_step_bf16(hb_model *m, const void *X, const int32_t *y, int64_t B, float
                                     &colsum_slices[l - 1]));
         if (done_dw[l]) continue;
         const GemmBf16Args g = dw_args(l);
-        if (l > 1) {  // with what comes next, which does not need it: D_{l-2}, or dW_1
+        if (l > 1 && pairs_on) {  // with what comes next, which does not need it: D_{l-2}, or dW_1
             const GemmKind kind = l > 2 ? GEMM_DA : GEMM_DW;
             const GemmBf16Args next = l > 2 ? da_args(l - 1) : dw_args(1);
             if ((three || kind == GEMM_DW) && gemm_bf16_pair_groups(g, kind, next) > 0) {
@@ -1193,7 +1194,7 @@ int32_t hb_plan_bf16_pair(const int32_t *layer_dims, int32_t n_dims, int64_t B, 
     if (!layer_dims || n_dims < 2 || n_dims > MAX_LAYERS + 1 || B < 1 || B > MAX_BATCH || layer < 1 || layer >= n_dims) return -1;
     for (int i = 0; i < n_dims; ++i)
         if (layer_dims[i] < 1 || layer_dims[i] > MAX_DIM) return -1;
-    if (layer == 1) return 0;  // nothing follows it
+    if (layer == 1 || !gemm_bf16_pairs_on()) return 0;  // nothing follows the first layer's
     const int L = n_dims - 1;
     auto args = [&](GemmKind kind, int l) {
         return plan_args_bf16(kind, layer_dims[l], layer_dims[l - 1], (int)B, (l == 1) + 2 * (l == L));

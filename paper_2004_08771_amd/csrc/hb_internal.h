@@ -166,6 +166,7 @@ hipError_t launch_gemm_bf16(GemmKind kind, GemmBf16Args a, hipStream_t stream,
                             const LaunchEvents &ev = LaunchEvents(), int *colsum_slices_out = nullptr);
 // A weight gradient (BF16_DW_BMAJ_MID) and the next product of the backward pass (backward-data, or the weight gradient of layer
 // 1) in one launch, which neither may depend on the other's results for: the groups of wavefronts per tile, 0 if they run apart.
+bool gemm_bf16_pairs_on();
 int gemm_bf16_pair_groups(const GemmBf16Args &dw, GemmKind kind, const GemmBf16Args &next);
 hipError_t launch_gemm_bf16_pair(GemmBf16Args dw, GemmKind kind, GemmBf16Args next, hipStream_t stream,
                                  const LaunchEvents &ev = LaunchEvents());

@@ -296,9 +296,12 @@ __device__ __forceinline__ void epilogue_bf16(const GemmBf16Args &a, v16f (&acc)
 // the 16 x 16 form gives (registers only, normal values: 1290-1340 against 2030 TFLOP/s, zeros 1604 against 2468; one
 // wavefront alone 1807 against 2041); here, where both also read and load, four steps of 2048-4096x3-1000 over 16384 rows
 // went from 18.53 to 18.06 ms with it.  The epilogues want 32 x 32 blocks (rows 8 q + 4 h + e, column r in lane 32 h + r,
-// register 4 q + e): of a pair of blocks side by side, lane bit 5 (rows 8 ..) becomes a register and the column block lane
-// bit 4, two lane exchanges for two registers.
+// register 4 q + e): of a pair of blocks side by side, lane bit 4 (which of two groups of four rows) becomes a register and
+// the column block lane bit 4, one lane exchange for two registers.  For that row c of an A fragment is row a_row(c) of the
+// tile, groups 1 and 2 of four rows in each other's place; with the rows in order a second exchange was needed (8192 x 1024,
+// K = 784, backward-data over 1024 and 10: 22.5 us, so 21.9).
 typedef float v4f __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ int a_row(int c) { return (c & 3) | (c & 4) << 1 | (c & 8) >> 1; }
 template <int TM, int TN>
 __device__ __forceinline__ void blocks_of_32(v16f (&out)[TM][TN], const v4f (&in)[2 * TM][2 * TN])
 {
@@ -310,9 +313,8 @@ __device__ __forceinline__ void blocks_of_32(v16f (&out)[TM][TN], const v4f (&in
             for (int e = 0; e < 4; ++e) {
                 const auto y = __builtin_amdgcn_permlane16_swap(__float_as_uint(in[i][2 * j][e]),
                                                                 __float_as_uint(in[i][2 * j + 1][e]), false, false);
-                const auto z = __builtin_amdgcn_permlane32_swap(y[0], y[1], false, false);
-                out[i / 2][j][8 * (i & 1) + e] = __uint_as_float(z[0]);
-                out[i / 2][j][8 * (i & 1) + 4 + e] = __uint_as_float(z[1]);
+                out[i / 2][j][8 * (i & 1) + e] = __uint_as_float(y[0]);
+                out[i / 2][j][8 * (i & 1) + 4 + e] = __uint_as_float(y[1]);
             }
 }
 
@@ -1038,18 +1040,18 @@ __device__ __forceinline__ void gemm_bf16_dma_tile(const GemmBf16Args &a, unsign
                                          (lptr_t)(smem_raw + DMA_B_BASE + stage * DMA_B_BYTES + (wave + 8 * v) * 1024), 16, 0, 0);
     };
 
-    // ---- LDS side of the fragment reads: lane 16 g + c reads chunk 4 kk + g of row c of its block (k-step kk: 32 deep).  The
-    // block offsets i * 16 rows leave (R >> 1) & 7 unchanged, so the swizzle depends on c only.
+    // ---- LDS side of the fragment reads: lane 16 g + c reads chunk 4 kk + g of row c (A: a_row(c)) of its block (k-step kk:
+    // 32 deep).  The block offsets i * 16 rows leave (R >> 1) & 7 unchanged, so the swizzle depends on c only.
     // BMAJ: lane 16 g + 4 j + q addresses k-row 32 kk + 8 g + 4 t + j (t = 0, 1: the two reads of a fragment), bytes 8 q ..
-    // of the block's 32, which are the (block % 2)-th half of segment block / 2; both indices are exchanged as swz_k
-    // says, and the block index enters as one more XOR.
+    // (A: 2 a_row(4 q) ..) of the block's 32, which are the (block % 2)-th half of segment block / 2; both
+    // indices are exchanged as swz_k says, and the block index enters as one more XOR.
     const int c16 = lane & 15, g4 = lane >> 4;
-    const int fr = swz(c16);
     const int tj = c16 >> 2;
-    const int a_off = BMAJ ? (8 * g4 + tj) * 512 + (((wm * 4) ^ tj) << 6) + 32 * (g4 & 1) + 8 * (lane & 3)
-                         : (wm * 128 + c16) * DMA_ROW_BYTES + ((g4 ^ fr) << 4);  // k-step kk: a_off ^ (kk << 6)
+    const int arow = a_row(c16);
+    const int a_off = BMAJ ? (8 * g4 + tj) * 512 + (((wm * 4) ^ tj) << 6) + 32 * (g4 & 1) + 2 * a_row(4 * (lane & 3))
+                         : (wm * 128 + arow) * DMA_ROW_BYTES + ((g4 ^ swz(arow)) << 4);  // k-step kk: a_off ^ (kk << 6)
     const int b_off = DMA_B_BASE + (BMAJ ? (8 * g4 + tj) * 512 + (((wn * 2) ^ tj) << 6) + 32 * (g4 & 1) + 8 * (lane & 3)
-                                       : (wn * 64 + c16) * DMA_ROW_BYTES + ((g4 ^ fr) << 4));
+                                       : (wn * 64 + c16) * DMA_ROW_BYTES + ((g4 ^ swz(c16)) << 4));
     v8bf fa[2][TM], fb[2][2 * TN];  // half of the wavefront's rows (64) / all of its columns at one k-step
     const unsigned lds0 = (unsigned)(size_t)(lptr_t)smem_raw;  // LDS byte address of the stages
     // one operand fragment (block q of the A or B tile at p, k-step kk; kk is a KStep<> so

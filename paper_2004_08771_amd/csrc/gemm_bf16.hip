@@ -185,6 +185,10 @@ __device__ __forceinline__ void epilogue_bf16_impl(const GemmBf16Args &a, v16f (
                 mword[i] = a.mask_in[((size_t)((mw + i * 32) >> 5) * a.mask_nb + (nb >> 5)) * 64 + 32 * h + r];
         }
         float csum = 0.f;  // backward-data: sum of the lane's stored results of this column
+        // The current row of the results, moved on by additions.  A wavefront runs through this code once, so what counts is
+        // its length, and 64-bit products for the addresses were a third of it: 8192 x 1000 x 784, whose last tiles come here,
+        // 48.4 us, so 45.5; 128 x 128 tiles of 8192 x 600 x 1000 31.2, so 30.0.
+        unsigned char *cf = cf0 + ((size_t)mw * a.ldc + nb) * 4, *cb = cb0 + ((size_t)mw * a.ldcb + nb) * 2;
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             unsigned mbits = 0u;
@@ -213,8 +217,7 @@ __device__ __forceinline__ void epilogue_bf16_impl(const GemmBf16Args &a, v16f (
                     if (FULL || (mq + e < a.M && n_ok)) {
                         if (KIND == GEMM_FWD) {
                             val = act_fwd<ACT>(val + bias);
-                            if (has_cf)
-                                *reinterpret_cast<float *>(cf0 + ((size_t)(mb + e) * a.ldc + nb) * 4 + lo_cf) = val;
+                            if (has_cf) *reinterpret_cast<float *>(cf + lo_cf) = val;
                             if (MASK) {
                                 const bf16_t b = f2bf(val);
                                 if ((b & 0x7fffu) != 0 && (b & 0x8000u) == 0) mbits |= 1u << relu_bit_pos(q, e);
@@ -233,15 +236,16 @@ __device__ __forceinline__ void epilogue_bf16_impl(const GemmBf16Args &a, v16f (
                             if (ACT == ACT_SIGMOID) val *= o * (1.f - o);
                             else if (ACT == ACT_RELU) val = (o > 0.f) ? val : 0.f;
                         } else {  // GEMM_DW
-                            float *cf = reinterpret_cast<float *>(cf0 + ((size_t)(mb + e) * a.ldc + nb) * 4 + lo_cf);
-                            if (!a.write_grad) val = (FULL ? w[4 * q + e] : *cf) - a.lr * val;  // Eq. (3), fp32 master
-                            *cf = val;
+                            float *p = reinterpret_cast<float *>(cf + lo_cf);
+                            if (!a.write_grad) val = (FULL ? w[4 * q + e] : *p) - a.lr * val;  // Eq. (3), fp32 master
+                            *p = val;
                         }
-                        if (has_cb)
-                            *reinterpret_cast<bf16_t *>(cb0 + ((size_t)(mb + e) * a.ldcb + nb) * 2 + lo_cb) = f2bf(val);
+                        if (has_cb) *reinterpret_cast<bf16_t *>(cb + lo_cb) = f2bf(val);
                         if (KIND == GEMM_DA && a.colsum_partial != nullptr) csum += bf2f(f2bf(val));
                     }
                     x[e] = val;
+                    cf += a.ldc * (e < 3 ? 4 : 20);  // the group's last row: past the four of the other half-wavefront
+                    cb += a.ldcb * (e < 3 ? 2 : 10);
                 }
                 if (has_ct && n_ok) {
                     unsigned char *ct = ct0 + ((size_t)nb * a.ldct + mb) * 2 + lo_ct;

@@ -1758,11 +1758,12 @@ int gemm_bf16_dw_splits_cap(int M, int N, int K)
     if (s > 8) s = 8;
     if (s > K / 1024) s = K / 1024;  // at least 16 k-tiles per slice
     // With fewer workgroups than half of the compute units, the kernel of small tiles is faster on the whole
-    // contraction until it gets long: its time grows with the contraction, that of the slices hardly does, but these are
-    // followed by the passes over their sums and the bias.  While every 64 x 64 tile has a compute unit the two meet at 7500
-    // to 8000 rows (steps of 64-w-w-10, small tiles / slices: w = 256 181 / 192 us at 7001 rows, 198 / 192 at 8001; 768 239 / 245
-    // at 7501, 248 / 250 at 8001; 1024 237 / 260 at 7001, 287 / 282 at 8001).  With more tiles they share compute units and
-    // the line is where a fifth slice comes (steps of 1280 x 4-10: 376 / 389 at 4096 rows, 434 / 424 at 5121, 483 / 458 at 5999).
+    // contraction: its time grows with the contraction, that of the slices hardly does, but these are
+    // followed by the passes over their sums and the bias.  The lines are where the two met while every product had a launch
+    // of its own; now that a weight gradient of small tiles shares its launch with the next product, they meet beyond.
+    // Steps, small tiles / slices, us: 64-w-w-10, w = 256 93 / 184 at 7001 rows, 100 / 184 at 8001, 292 / 370 at 30000; 768
+    // 144 / 227 at 7501; 1024 174 / 249 at 7001, 181 / 247 at 7501; 64-1280x4-10 335 / 453 at 4096 rows, 382 / 492 at 5121,
+    // 419 / 530 at 5999, 730 / 742 at 12001; 54-512x4-7 233 / 336 at 8192.
     const long long small = (long long)((M + 63) / 64) * ((N + 63) / 64);
     return (s < 2 || (tiles * s < 128 && K < (small <= 256 ? 7500 : 5120))) ? 1 : (int)s;
 }
